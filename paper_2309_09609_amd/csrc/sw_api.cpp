@@ -29,10 +29,10 @@
 #include "sw_internal.h"
 
 namespace sw {
-hipError_t launch_sweep(bool i16, int R, const SweepArgs& a, int grid, hipStream_t st);
-hipError_t sweep_occupancy(bool i16, int R, int* blocks_per_cu);
-hipError_t launch_sweep_q2(int R, const SweepArgs& a, int grid, hipStream_t st);
-hipError_t sweep_occupancy_q2(int R, int* blocks_per_cu);
+hipError_t launch_sweep(int form, int R, const SweepArgs& a, int grid, hipStream_t st);
+hipError_t sweep_occupancy(int form, int R, int* blocks_per_cu);
+hipError_t launch_sweep_q2(int form, int R, const SweepArgs& a, int grid, hipStream_t st);
+hipError_t sweep_occupancy_q2(int form, int R, int* blocks_per_cu);
 hipError_t launch_sweep_mode(int mode, int R, const SweepArgs& a, int grid, hipStream_t st);
 hipError_t launch_sweep_mode16(int mode, int R, const SweepArgs& a, int grid, hipStream_t st);
 hipError_t sweep_occupancy_mode16(int mode, int R, int* blocks_per_cu);
@@ -147,12 +147,24 @@ struct Staged {
     const int8_t* sm_q = nullptr;
     int nq = 0;
     int max_mp = 0;
-    int bias = 0;                 // 16-bit cell bias: minus the lowest substitution score, at least 0
+};
+
+// The 16-bit cells of one local search: their form and what the kernels are told about it.
+struct CellForm {
+    int cell = kCellI16;          // kCellI16 or kCellOff
+    int32_t bias = 0;             // plain cells: minus the lowest substitution score, at least 0
+    int32_t off_k = 0;            // offset cells: steps between renormalisations
+    int32_t add = 0;              // offset cells: the profile holds SM + add
+    int32_t sat = kSat16;         // scores (as the cells hold them) from here on are recomputed
+    bool operator==(const CellForm& o) const {
+        return cell == o.cell && bias == o.bias && off_k == o.off_k && add == o.add && sat == o.sat;
+    }
 };
 
 struct GraphEntry {
     std::vector<int> qlens;
-    int32_t go = 0, ge = 0, k = 0, bias = 0;
+    int32_t go = 0, ge = 0, k = 0;
+    CellForm form;
     const void* scores = nullptr;
     const void* top_s = nullptr;
     const void* top_i = nullptr;
@@ -178,7 +190,8 @@ struct GraphEntry {
 // it comes in a row (one-off shapes, e.g. served batches, are enqueued directly and never wait).
 struct BatchKey {
     std::vector<int> qlens;
-    int32_t go = 0, ge = 0, k = 0, bias = 0;
+    int32_t go = 0, ge = 0, k = 0;
+    CellForm form;
     const void* scores = nullptr;
     const void* top_s = nullptr;
     const void* top_i = nullptr;
@@ -186,7 +199,7 @@ struct BatchKey {
     uint64_t gen = 0;
     const void* ws = nullptr;
     bool operator==(const BatchKey& o) const {
-        return qlens == o.qlens && go == o.go && ge == o.ge && k == o.k && bias == o.bias && scores == o.scores &&
+        return qlens == o.qlens && go == o.go && ge == o.ge && k == o.k && form == o.form && scores == o.scores &&
                top_s == o.top_s && top_i == o.top_i && stream == o.stream && gen == o.gen && ws == o.ws;
     }
 };
@@ -616,20 +629,22 @@ sw_status ensure_geometry(sw_db* db) {
         int b32 = 0;
         db->wg16 = 0;
         for (int R : kRowChoices) {
-            int b = 0;
-            HIP_TRY(sweep_occupancy(true, R, &b));
-            if (b < 1) return fail(SW_E_HIP, "16-bit sweep (R=%d) cannot be resident", R);
-            db->wgR[R] = db->cus * std::min(b, kMaxWgPerCu);
+            int b = 0, bo = 0;
+            HIP_TRY(sweep_occupancy(kCellI16, R, &b));
+            HIP_TRY(sweep_occupancy(kCellOff, R, &bo));
+            if (b < 1 || bo < 1) return fail(SW_E_HIP, "16-bit sweep (R=%d) cannot be resident", R);
+            db->wgR[R] = db->cus * std::min(std::max(b, bo), kMaxWgPerCu);
             db->wg16 = std::max(db->wg16, db->wgR[R]);
         }
         for (int R : {8, 16}) {
-            int b = 0;
-            HIP_TRY(sweep_occupancy_q2(R, &b));
-            if (b < 1) return fail(SW_E_HIP, "query-pair sweep (R=%d) cannot be resident", R);
-            db->wgQ[R] = db->cus * std::min(b, kMaxWgPerCu);
+            int b = 0, bo = 0;
+            HIP_TRY(sweep_occupancy_q2(kCellI16, R, &b));
+            HIP_TRY(sweep_occupancy_q2(kCellOff, R, &bo));
+            if (b < 1 || bo < 1) return fail(SW_E_HIP, "query-pair sweep (R=%d) cannot be resident", R);
+            db->wgQ[R] = db->cus * std::min(std::max(b, bo), kMaxWgPerCu);
             db->wg16 = std::max(db->wg16, db->wgQ[R]);
         }
-        HIP_TRY(sweep_occupancy(false, kRerunRows, &b32));
+        HIP_TRY(sweep_occupancy(kCellI32, kRerunRows, &b32));
         if (b32 < 1) return fail(SW_E_HIP, "32-bit sweep cannot be resident");
         db->wg32 = kRerunGrid;
         // a unit's boundary row is (columns x subjects-or-pairs per wave); the widest
@@ -848,9 +863,6 @@ sw_status stage_queries(sw_db* db, const Work& W, const int8_t* h_queries, const
         qo[q] = h_qoffsets[q] - h_qoffsets[0];
     }
     memcpy(h + L.off_sm, subst, (size_t)db->alphabet * db->alphabet);
-    int lowest = 0;
-    for (int e = 0; e < db->alphabet * db->alphabet; ++e) lowest = std::min<int>(lowest, subst[e]);
-    out->bias = -lowest;
     const int64_t qbytes = h_qoffsets[nq] - h_qoffsets[0];
     if (qbytes) memcpy(h + L.off_sm + kMaxAlphabet * kMaxAlphabet, h_queries + h_qoffsets[0], qbytes);
     if (with_plan) {
@@ -869,6 +881,44 @@ sw_status stage_queries(sw_db* db, const Work& W, const int8_t* h_queries, const
     out->nq = nq;
     out->max_mp = L.max_mp;
     return SW_OK;
+}
+
+// The cells of a local search of these queries.  Offset cells (sw_offset.h) need Ge <= Go (a gap opens at
+// Go - Ge more), substitution bytes SM + Go + Ge in 0..255 and offsets that leave nearly the whole 16-bit
+// range: they are lowered every K steps, with Ge K <= 128 (more would let a NaN pattern in S pass 0x7FFF),
+// so Ge <= 32.  The usual protein scorings (10/2, 11/1, 14/2 with BLOSUM, PAM) all qualify.  Their exact
+// range ends Go + Ge (K + 17) below the plain cells' 0x7C00, so a query whose best possible score lies
+// between the two limits keeps plain cells, which hold every one of its scores without a recompute; from
+// the plain limit on both forms recompute, and the offset cells are the faster ones.
+CellForm choose_form(const sw_db* db, const int8_t* subst, int32_t go, int32_t ge, const int8_t* h_queries,
+                     const int64_t* h_qoffsets, int nq) {
+    const int A = db->alphabet;
+    int lo = 0, hi = 0, best[kMaxAlphabet];
+    for (int q = 0; q < A; ++q) {
+        best[q] = 0;
+        for (int d = 0; d < A; ++d) {
+            lo = std::min<int>(lo, subst[q * A + d]);
+            best[q] = std::max<int>(best[q], subst[q * A + d]);
+        }
+        hi = std::max(hi, best[q]);
+    }
+    CellForm f;
+    f.bias = -lo;
+    f.sat = std::min<int32_t>(db->sat + f.bias, kSat16);
+    if (ge > go || ge > 32 || go > 255 || go + ge + lo < 0 || go + ge + hi > 255) return f;
+    const int K = ge > 0 ? std::min(64, 4 * (32 / ge)) : 64;
+    const int32_t limit = kSat16 - go - ge * (K + 17);
+    for (int q = 0; q < nq; ++q) {
+        int64_t top = 0;
+        for (int64_t i = h_qoffsets[q]; i < h_qoffsets[q + 1]; ++i) top += best[h_queries[i]];
+        if (top >= limit && top < kSat16 - f.bias) return f;
+    }
+    f.cell = kCellOff;
+    f.bias = 0;
+    f.off_k = K;
+    f.add = go + ge;
+    f.sat = std::min<int32_t>(db->sat, limit);
+    return f;
 }
 
 // Timing events of the dominant launches (sw_profile_kernels): a ring of
@@ -891,12 +941,12 @@ int record_timer_start(sw_db* db, hipStream_t st) {
 // The launch sequence of a search: profile (zeroes the counters), the side and
 // bulk 16-bit sweeps, the 32-bit recompute, top-k.  Allocates nothing and never
 // waits on the host, so it can be captured into a graph.
-sw_status enqueue(sw_db* db, const Staged& S, const Plan& plan, const Work& W, int32_t go, int32_t ge,
-                  int32_t* d_scores, int64_t n, int k, int32_t* top_s, int64_t* top_i, hipStream_t st,
+sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& plan, const Work& W, int32_t go,
+                  int32_t ge, int32_t* d_scores, int64_t n, int k, int32_t* top_s, int64_t* top_i, hipStream_t st,
                   bool time_sweep) {
     int32_t* ctr = W.counters;
     HIP_TRY(launch_profile(S.sm_q, db->alphabet, S.qd, S.nq, S.qoff, W.prof, ctr, kCounters, W.bits, W.L.bits_words,
-                           S.max_mp, st));
+                           S.max_mp, st, form.add));
     SweepArgs a = sweep_args(db, S, W, go, ge, d_scores);
     a.items = W.items;
     a.n_items_dev = nullptr;
@@ -904,8 +954,10 @@ sw_status enqueue(sw_db* db, const Staged& S, const Plan& plan, const Work& W, i
     a.counter = ctr + 0;
     set_rerun_args(db, a, W, ctr);
     a.unit_list = 0;
-    a.bias = S.bias;
-    a.sat = std::min<int32_t>(db->sat + S.bias, kSat16);
+    a.bias = form.bias;
+    a.sat = form.sat;
+    a.off_k = form.off_k;
+    a.sm_shift = form.add;
     a.qpairs = plan.qpack ? W.qpairs : nullptr;
     // the side launch takes the first slots; the bulk launch fills the rest of the GPU
     const int wg_main = plan.qpack ? db->wgQ[plan.R_main] : db->wgR[plan.R_main];
@@ -919,15 +971,15 @@ sw_status enqueue(sw_db* db, const Staged& S, const Plan& plan, const Work& W, i
         b.slot_base = grid_main;
         HIP_TRY(hipEventRecord(db->ev_fork, st));
         HIP_TRY(hipStreamWaitEvent(db->side, db->ev_fork, 0));
-        HIP_TRY(launch_sweep(true, plan.R_side, b, grid_side, db->side));
+        HIP_TRY(launch_sweep(form.cell, plan.R_side, b, grid_side, db->side));
         HIP_TRY(hipEventRecord(db->ev_join, db->side));
     }
     const int ev = time_sweep && db->timing ? record_timer_start(db, st) : -1;
     if (plan.n_main > 0) {
         if (plan.qpack)
-            HIP_TRY(launch_sweep_q2(plan.R_main, a, grid_main, st));
+            HIP_TRY(launch_sweep_q2(form.cell, plan.R_main, a, grid_main, st));
         else
-            HIP_TRY(launch_sweep(true, plan.R_main, a, grid_main, st));
+            HIP_TRY(launch_sweep(form.cell, plan.R_main, a, grid_main, st));
     }
     if (plan.n_side > 0) HIP_TRY(hipStreamWaitEvent(st, db->ev_join, 0));
     if (ev >= 0) {
@@ -936,7 +988,7 @@ sw_status enqueue(sw_db* db, const Staged& S, const Plan& plan, const Work& W, i
     }
     // exact 32-bit recompute of saturated pairs; the count is read on the device
     const SweepArgs r = recompute_args(db, a, W, ctr);
-    HIP_TRY(launch_sweep(false, kRerunRows, r, db->wg32, st));
+    HIP_TRY(launch_sweep(kCellI32, kRerunRows, r, db->wg32, st));
     if (k > 0)
         HIP_TRY(launch_topk_ws(d_scores, n, n, S.nq, k, top_s, top_i, topk_ws_bytes(n, S.nq, k) > 0 ? W.topk : nullptr,
                                st));
@@ -1148,7 +1200,8 @@ sw_status search_one(const int8_t* h_query, int32_t qlen, sw_db* db, const int64
     Staged S;
     if ((s = stage_queries(db, W, h_query, qo, 1, h_subst, 0, st, &S, nullptr, d_ws ? plan : nullptr)) != SW_OK)
         return s;
-    return enqueue(db, S, *plan, W, gap_open, gap_extend, d_scores_out, n, 0, nullptr, nullptr, st, true);
+    const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_query, qo, 1);
+    return enqueue(db, S, form, *plan, W, gap_open, gap_extend, d_scores_out, n, 0, nullptr, nullptr, st, true);
 }
 
 }  // namespace
@@ -1214,13 +1267,14 @@ sw_status search_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int32
     Staged S;
     if ((s = stage_queries(db, W, h_queries, h_qoffsets, nq, h_subst, n, st, &S, nullptr, d_ws ? plan : nullptr)) != SW_OK)
         return s;
+    const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_queries, h_qoffsets, nq);
     GraphEntry& G = db->graph;
     BatchKey key;
     key.qlens = qlens;
     key.go = gap_open;
     key.ge = gap_extend;
     key.k = k;
-    key.bias = S.bias;
+    key.form = form;
     key.scores = scores;
     key.top_s = d_top_scores;
     key.top_i = d_top_index;
@@ -1228,12 +1282,12 @@ sw_status search_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int32
     key.gen = db->gen;
     key.ws = W.scratch16;
     const bool hit = G.exec && G.gen == db->gen && G.ws == W.scratch16 && G.qlens == qlens && G.go == gap_open &&
-                     G.ge == gap_extend && G.bias == S.bias && G.k == k && G.scores == scores &&
+                     G.ge == gap_extend && G.form == form && G.k == k && G.scores == scores &&
                      G.top_s == d_top_scores && G.top_i == d_top_index && G.stream == st;
     if (!hit && !(key == db->last_eager)) {
         db->last_eager = key;
         const int ev = db->timing ? record_timer_start(db, st) : -1;
-        s = enqueue(db, S, *plan, W, gap_open, gap_extend, scores, n, k, d_top_scores, d_top_index, st, false);
+        s = enqueue(db, S, form, *plan, W, gap_open, gap_extend, scores, n, k, d_top_scores, d_top_index, st, false);
         if (s != SW_OK) return s;
         if (ev >= 0) {
             HIP_TRY(hipEventRecord(db->ev_pool[ev].second, st));
@@ -1246,7 +1300,7 @@ sw_status search_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int32
         // default stream, which cannot be captured); launched on the caller's
         G.clear();
         HIP_TRY(hipStreamBeginCapture(db->cap, hipStreamCaptureModeThreadLocal));
-        s = enqueue(db, S, *plan, W, gap_open, gap_extend, scores, n, k, d_top_scores, d_top_index, db->cap, false);
+        s = enqueue(db, S, form, *plan, W, gap_open, gap_extend, scores, n, k, d_top_scores, d_top_index, db->cap, false);
         hipGraph_t graph = nullptr;
         hipError_t e = hipStreamEndCapture(db->cap, &graph);
         if (s != SW_OK) { if (graph) hipGraphDestroy(graph); return s; }
@@ -1259,7 +1313,7 @@ sw_status search_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int32
         G.qlens = qlens;
         G.go = gap_open;
         G.ge = gap_extend;
-        G.bias = S.bias;
+        G.form = form;
         G.k = k;
         G.scores = scores;
         G.top_s = d_top_scores;
@@ -1507,7 +1561,8 @@ sw_status sw_search_multi(const int8_t* h_queries, const int64_t* h_qoffsets, in
     if ((s = get_work(db, h_qoffsets, nq, 0, false, &db->multi_plan, nullptr, 0, &W)) != SW_OK) return s;
     Staged S;
     if ((s = stage_queries(db, W, h_queries, h_qoffsets, nq, h_subst, 0, st, &S, h_d_scores)) != SW_OK) return s;
-    return enqueue(db, S, db->multi_plan, W, gap_open, gap_extend, nullptr, db->n, 0, nullptr, nullptr, st, true);
+    const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_queries, h_qoffsets, nq);
+    return enqueue(db, S, form, db->multi_plan, W, gap_open, gap_extend, nullptr, db->n, 0, nullptr, nullptr, st, true);
 }
 
 sw_status sw_profile_kernels(sw_db* db, int32_t enable) {

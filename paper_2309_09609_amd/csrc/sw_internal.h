@@ -29,6 +29,9 @@ constexpr int32_t kModeTop = 0x7C00 - 128;
 // Test hook: what a flagged pair's 16-bit scores read until its 32-bit recompute overwrites them.
 constexpr int32_t kPoison = -0x3B9ACA07;
 
+// Cell forms of the local sweep: plain biased 16-bit cells, 16-bit cells on anti-diagonal offsets, 32-bit cells.
+constexpr int kCellI16 = 0, kCellOff = 1, kCellI32 = 2;
+
 // Packed database image, one record per group of 128 length-sorted subjects.
 // Residues of group g live at image + base, as chunk rows of kChunkBytes bytes:
 // byte (chunk c, pair p, half h, k) = 1 + residue (4c + k) of subject 2p + h of the group,
@@ -95,8 +98,10 @@ struct SweepArgs {
                                   // end-to-end modes: the middle of the 16-bit range)
     const int2* qpairs;           // query-pair sweep: item.q indexes these (query a, query b or -1)
     const int32_t* slen;          // end-to-end modes: subject length per sorted slot (0 for padding slots)
-    int32_t sm_shift;             // global mode on column-offset cells: the profile holds SM + sm_shift on
-                                  // real residues; 32-bit cells subtract it again
+    int32_t sm_shift;             // the profile holds SM + sm_shift on real residues (global mode on
+                                  // column-offset cells: Ge; local offset cells: Go + Ge); 32-bit cells
+                                  // subtract it again
+    int32_t off_k;                // local offset cells: steps between two renormalisations
 };
 
 // One (query, subject) pair of an alignment launch.

@@ -41,6 +41,9 @@
 // cells start from the floor).  So S < kSat16 (0x7C00) is exact (no H reached
 // it, so no sum was clamped) and the score is S - c; S >= kSat16 sends the
 // pair to the 32-bit sweep.
+//
+// That form serves any penalties and matrices; scorings that the host's rule
+// admits (choose_form) run the faster cells of sw_offset.h instead.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -717,11 +720,14 @@ __device__ __forceinline__ void sweep_pass_mode16(const PassIO& io, int ncols, i
     }
 }
 
+#include "sw_offset.h"
+
 // Load rows [row0, row0 + B*R) of a query profile into LDS as [b][residue][R],
-// in 16-byte units (8-byte units when R = 4).
+// in 16-byte units (8-byte units when R = 4), lowered by the constant the
+// profile carries beside the scores (local 32-bit recompute of offset cells).
 template <int R>
 __device__ __forceinline__ void load_slice(int16_t* dst, const int16_t* prof, int mp, int row0, int lgB,
-                                           int tid, int nthreads) {
+                                           int tid, int nthreads, int shift = 0) {
     constexpr int U = (R % 8 == 0) ? 8 : 4;            // int16 elements per copy unit
     using V = typename std::conditional<U == 8, uint4, uint2>::type;
     const int rows = R << lgB;
@@ -732,7 +738,14 @@ __device__ __forceinline__ void load_slice(int16_t* dst, const int16_t* prof, in
         const int rem = e - d * per_res;               // = b * (R/U) + ru
         const int bb = rem / (R / U);
         const int ru = rem - bb * (R / U);
-        const V v = *reinterpret_cast<const V*>(prof + (int64_t)d * mp + row0 + rem * U);
+        V v = *reinterpret_cast<const V*>(prof + (int64_t)d * mp + row0 + rem * U);
+        if (shift) {                                   // padding goes below every score: it raises no cell
+            uint32_t w[U / 2];
+            __builtin_memcpy(w, &v, sizeof v);
+#pragma unroll
+            for (int i = 0; i < U / 2; ++i) w[i] = bits<uint32_t>(bits<s2>(w[i]) - s2{(short)shift, (short)shift});
+            __builtin_memcpy(&v, w, sizeof v);
+        }
         *reinterpret_cast<V*>(dst + (bb * kNRes + d) * R + ru * U) = v;
     }
 }
@@ -812,9 +825,13 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
     io.cstride = (uint32_t)(P * 16 * C::kWords);
     io.bnd = make_rsrc(slot, (uint32_t)(ncols >> 2) * io.cstride);
     const uint32_t lane_words = (uint32_t)(s * 16 * C::kWords);
-    uint32_t* region32 = reinterpret_cast<uint32_t*>(shared_slice ? lds : lds + wave * (kNRes * 16 * R));
+    constexpr bool kOffset = std::is_same<C, CellOff>::value;
+    constexpr int kWaveSlice = kNRes * 16 * R * (kOffset && !PACKED ? 1 : 2);   // bytes of one wave's own slice
+    uint32_t* region32 = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(lds) + (shared_slice ? 0 : wave * kWaveSlice));
     const int16_t* lrow = PACKED ? reinterpret_cast<const int16_t*>(region32 + b * kNRes * R)
                                  : reinterpret_cast<const int16_t*>(region32) + b * kNRes * R;
+    const uint8_t* lrow8 = PACKED ? reinterpret_cast<const uint8_t*>(lrow)
+                                  : reinterpret_cast<const uint8_t*>(region32) + b * kNRes * R;
     const typename C::G go = C::gapv(a.go), ge = C::gapv(a.ge);
     T bias = C::zero();
     int ub = 0;                                 // subtracted from every score on the way out
@@ -823,6 +840,8 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
         ub = a.bias;
     }
     T S = bias;
+    u2 So = {0, 0};                             // offset cells: true scores
+    const OffCtx oc{(uint32_t)a.ge * 0x10001u, (uint32_t)(a.go - a.ge) * 0x10001u, (uint32_t)a.go * 0x10001u, a.off_k};
     constexpr bool kMode16 = MODE != 0 && std::is_same<C, CellI16>::value;
     T lmin = C::zero(), lmax = C::zero();       // 16-bit end-to-end modes: range of every H
     EndCtx ec{};
@@ -856,23 +875,25 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
     const bool chain = lgB >= 5;
     if (chain) __builtin_amdgcn_s_setprio(2);
     for (int p = 0; p < passes; ++p) {
+        auto load = [&](int tid, int nthreads) {
+            const int16_t *pa = a.prof + Qa.prof_off, *pb = a.prof + Qb.prof_off;
+            if constexpr (PACKED && kOffset)
+                load_slice_off_q2<R>(region32, pa, Qa.mp, pb, Qb.mp, p * rows_pp, lgB, tid, nthreads);
+            else if constexpr (PACKED)
+                load_slice_q2<R>(region32, pa, Qa.mp, pb, Qb.mp, p * rows_pp, lgB, tid, nthreads);
+            else if constexpr (kOffset)
+                load_slice_off<R>(reinterpret_cast<uint8_t*>(region32), pa, Qa.mp, p * rows_pp, lgB, tid, nthreads);
+            else
+                load_slice<R>(reinterpret_cast<int16_t*>(region32), pa, Qa.mp, p * rows_pp, lgB, tid, nthreads,
+                              MODE == 0 && std::is_same<C, CellI32>::value ? a.sm_shift : 0);
+        };
         if (shared_slice) {
             __syncthreads();
-            if constexpr (PACKED)
-                load_slice_q2<R>(region32, a.prof + Qa.prof_off, Qa.mp, a.prof + Qb.prof_off, Qb.mp, p * rows_pp, lgB,
-                                 threadIdx.x, blockDim.x);
-            else
-                load_slice<R>(reinterpret_cast<int16_t*>(region32), a.prof + Qa.prof_off, Qa.mp, p * rows_pp, lgB,
-                              threadIdx.x, blockDim.x);
+            load(threadIdx.x, blockDim.x);
             __syncthreads();
         } else {
             __builtin_amdgcn_wave_barrier();
-            if constexpr (PACKED)
-                load_slice_q2<R>(region32, a.prof + Qa.prof_off, Qa.mp, a.prof + Qb.prof_off, Qb.mp, p * rows_pp, lgB,
-                                 lane, 64);
-            else
-                load_slice<R>(reinterpret_cast<int16_t*>(region32), a.prof + Qa.prof_off, Qa.mp, p * rows_pp, lgB,
-                              lane, 64);
+            load(lane, 64);
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
             __builtin_amdgcn_wave_barrier();
         }
@@ -882,7 +903,10 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
             ec.row0 = p * rows_pp + b * R;
             ec.top = p == 0;
             ec.last = p == passes - 1;
-            if constexpr (kMode16) {
+            if constexpr (kOffset) {
+                if (lgB == 0) sweep_pass_off<R, false, PACKED>(io, ncols, B, b, lrow8, oc, So);
+                else sweep_pass_off<R, true, PACKED>(io, ncols, B, b, lrow8, oc, So);
+            } else if constexpr (kMode16) {
                 if (lgB == 0)
                     sweep_pass_mode16<R, false, MODE>(io, ncols, B, b, lrow, go, ge, S, lmin, lmax, ec);
                 else
@@ -898,6 +922,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
     }
     if (chain) __builtin_amdgcn_s_setprio(0);
     if (!valid) return;
+    if constexpr (kOffset) S = bits<T>(So);
     for (int o = 1; o < B; o <<= 1) S = C::xmax(S, o);
     int out_of_range = 0;                       // 16-bit end-to-end: some value left the exact range
     if constexpr (kMode16) {
@@ -950,7 +975,8 @@ constexpr int kBitsBlock = 64;
 template <class C, int R, int MODE = 0>
 __global__ __launch_bounds__(64 * kWaves) void k_sweep(SweepArgs a) {
     // one shared slice of up to 64*R rows, or four per-wave slices of up to 16*R rows
-    __shared__ __attribute__((aligned(16))) int16_t lds[kNRes * 64 * R];
+    // (offset cells hold one byte a row)
+    __shared__ __attribute__((aligned(16))) int16_t lds[kNRes * 64 * R / (std::is_same<C, CellOff>::value ? 2 : 1)];
     __shared__ int s_item;
     __shared__ uint32_t s_bits[kBitsBlock];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: buffer resources stay scalar
@@ -1033,7 +1059,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_sweep(SweepArgs a) {
 // dword of a pre-interleaved profile slice and needs no permute.  A wave owns
 // P = 64/B subjects of a group (B lanes each, anti-diagonal as above); a group
 // has 2B such units.
-template <int R>
+template <class C, int R>
 __global__ __launch_bounds__(64 * kWaves) void k_sweep_q2(SweepArgs a) {
     __shared__ __attribute__((aligned(16))) int16_t lds[kNRes * 64 * R];
     __shared__ int s_item;
@@ -1052,7 +1078,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_sweep_q2(SweepArgs a) {
         const int g = I.g0 + (k / units) * I.gstep;
         k %= units;
         const bool shared_slice = I.lgB > 3;            // more than 8 lanes per subject
-        run_unit<CellI16, R, true>(a, g, k, I.lgB, I.q, wave < I.count, shared_slice, lds, wave, lane, slot);
+        run_unit<C, R, true>(a, g, k, I.lgB, I.q, wave < I.count, shared_slice, lds, wave, lane, slot);
     }
 }
 
@@ -1253,40 +1279,41 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
 }
 
 // ------------------------------------------------------------ host-side launchers
-// Kernel instances: 16-bit cells with R = 4, 8, 16 rows per lane; 32-bit cells with R = 8.
-static const void* sweep_kernel_q2(int R) {
-    if (R == 8) return (const void*)k_sweep_q2<8>;
-    if (R == 16) return (const void*)k_sweep_q2<16>;
-    return nullptr;
+// Kernel instances: 16-bit cells (plain or on offsets) with R = 4, 8, 16 rows per lane; 32-bit cells with R = 8.
+static const void* sweep_kernel_q2(int form, int R) {
+    if (form == kCellOff)
+        return R == 8 ? (const void*)k_sweep_q2<CellOff, 8> : R == 16 ? (const void*)k_sweep_q2<CellOff, 16> : nullptr;
+    return R == 8 ? (const void*)k_sweep_q2<CellI16, 8> : R == 16 ? (const void*)k_sweep_q2<CellI16, 16> : nullptr;
 }
 
-hipError_t launch_sweep_q2(int R, const SweepArgs& a, int grid, hipStream_t st) {
-    const void* k = sweep_kernel_q2(R);
+hipError_t launch_sweep_q2(int form, int R, const SweepArgs& a, int grid, hipStream_t st) {
+    const void* k = sweep_kernel_q2(form, R);
     if (!k) return hipErrorInvalidValue;
     SweepArgs copy = a;
     void* args[] = {&copy};
     return hipLaunchKernel(k, dim3(grid), dim3(64 * kWaves), args, 0, st);
 }
 
-hipError_t sweep_occupancy_q2(int R, int* blocks_per_cu) {
-    const void* k = sweep_kernel_q2(R);
+hipError_t sweep_occupancy_q2(int form, int R, int* blocks_per_cu) {
+    const void* k = sweep_kernel_q2(form, R);
     if (!k) return hipErrorInvalidValue;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, 64 * kWaves, 0);
 }
 
-static const void* sweep_kernel(bool i16, int R) {
-    if (i16) {
-        if (R == 4) return (const void*)k_sweep<CellI16, 4>;
-        if (R == 8) return (const void*)k_sweep<CellI16, 8>;
-        if (R == 16) return (const void*)k_sweep<CellI16, 16>;
-        return nullptr;
-    }
-    if (R == 8) return (const void*)k_sweep<CellI32, 8>;
-    return nullptr;
+static const void* sweep_kernel(int form, int R) {
+    if (form == kCellOff)
+        return R == 4    ? (const void*)k_sweep<CellOff, 4>
+               : R == 8  ? (const void*)k_sweep<CellOff, 8>
+               : R == 16 ? (const void*)k_sweep<CellOff, 16> : nullptr;
+    if (form == kCellI16)
+        return R == 4    ? (const void*)k_sweep<CellI16, 4>
+               : R == 8  ? (const void*)k_sweep<CellI16, 8>
+               : R == 16 ? (const void*)k_sweep<CellI16, 16> : nullptr;
+    return R == 8 ? (const void*)k_sweep<CellI32, 8> : nullptr;
 }
 
-hipError_t launch_sweep(bool i16, int R, const SweepArgs& a, int grid, hipStream_t st) {
-    const void* k = sweep_kernel(i16, R);
+hipError_t launch_sweep(int form, int R, const SweepArgs& a, int grid, hipStream_t st) {
+    const void* k = sweep_kernel(form, R);
     if (!k) return hipErrorInvalidValue;
     SweepArgs copy = a;
     void* args[] = {&copy};
@@ -1342,8 +1369,8 @@ hipError_t launch_sweep_mode(int mode, int R, const SweepArgs& a, int grid, hipS
 }
 
 
-hipError_t sweep_occupancy(bool i16, int R, int* blocks_per_cu) {
-    const void* k = sweep_kernel(i16, R);
+hipError_t sweep_occupancy(int form, int R, int* blocks_per_cu) {
+    const void* k = sweep_kernel(form, R);
     if (!k) return hipErrorInvalidValue;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, k, 64 * kWaves, 0);
 }

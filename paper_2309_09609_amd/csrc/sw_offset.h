@@ -1,0 +1,449 @@
+// 16-bit cells on anti-diagonal offsets: the local sweep's fast form.
+//
+// Included by sw_kernels.hip inside namespace sw, after the buffer access
+// helpers, PassIO and Res.
+//
+// Cells store H, E and F plus an offset that grows by Ge from row to row of a
+// lane and from step to step, phi(r, tau) = Go + Ge (r + tau) (tau counts steps
+// from 1 and falls back by K every K steps, when everything held is lowered by
+// Ge K).  On such cells a gap extends for free in both directions, and E and F
+// open from the same value G = H - (Go - Ge):
+//   hd = G(r-1, j-1) + (SM + Go + Ge)   the profile holds SM + Go + Ge, a byte
+//   H  = maximum3(hd, E, F)
+//   G  = H - (Go - Ge)                  kept instead of H
+//   E' = maximum3(E, G, floor)          floor = phi of the next step: true 0
+//   F' = max(F, G)
+//   S  = maximum3(S, G(r, j), G(r+1, j-1))   two cells of one anti-diagonal
+//                                       carry one offset; one S per two rows
+// With Go >= Go - Ge every value stays non-negative without saturating
+// arithmetic, so plain integer additions serve: one v_lshl_add_u64 forms the
+// diagonal sums of two rows (four cells), and another raises two S words to
+// the next step's offset.  Per row of two cells that is 5.25 instructions and,
+// with two subjects per lane, one permute, against 7.5 and one for the plain
+// biased form; the substitution bytes of 16 rows are one 16-byte LDS read per
+// subject instead of two (and the 16-byte slots of 25 residues spread over all
+// banks).
+//
+// What bounds it: VALU issue, 7.3 instructions per row of two cells over a whole
+// 16-row step with two subjects per lane (9.5 in the plain form).  Measured
+// against the plain form: 570,000 subjects, a query of 1,003 residues 27.3 ->
+// 22.6 ms, of 5,478 149.4 -> 122.6 ms; 16 queries x 40,000 subjects, two queries
+// per lane, 105.3 -> 82.2 ms; two queries of 330 - 361 x 200,000 10.8 -> 8.4 ms.
+// (v_lshl_add_u64 issues at the rate of a 32-bit addition: 1.85 ns per wave and
+// SIMD, as the packed maxima do.)
+//
+// Range: H <= 0x7BFF - phi is exact, as in the plain form (values below 0x7C00
+// order like half floats; 0x7C00 and above are infinity or NaN and stay in S,
+// whose own NaN v_pk_maximum3_f16 keeps, as the first operand).  The offsets
+// cost Go + Ge (K + 17) of the range; the host recomputes pairs from there on
+// (SweepArgs::sat).
+//
+// The rows' G live in fixed registers v64.. (row r's in v65 + r, the value
+// above the block in v64) because v_lshl_add_u64 reads them in pairs and the
+// rest one by one, which asm operands cannot express; so do S (v82..) and the
+// block's temporaries (v90..v96).
+//
+// Schedule: no instruction reads the result of the packed (VOP3P) instruction
+// just before it (a wait state the compiler cannot insert inside the block),
+// and no DPP reads a register written by the two instructions before it.
+
+struct CellOff : CellI16 {};
+
+// What a launch's offset cells need, all packed twice into 32 bits.
+struct OffCtx {
+    uint32_t ge, goe;      // Ge, Go - Ge
+    uint32_t go;           // Go
+    int K;                 // steps between two renormalisations, a multiple of 4
+};
+
+#define SWO_P0 "v64"
+#define SWO_P1 "v65"
+#define SWO_P2 "v66"
+#define SWO_P3 "v67"
+#define SWO_P4 "v68"
+#define SWO_P5 "v69"
+#define SWO_P6 "v70"
+#define SWO_P7 "v71"
+#define SWO_P8 "v72"
+#define SWO_P9 "v73"
+#define SWO_P10 "v74"
+#define SWO_P11 "v75"
+#define SWO_P12 "v76"
+#define SWO_P13 "v77"
+#define SWO_P14 "v78"
+#define SWO_P15 "v79"
+#define SWO_P16 "v80"
+#define SWO_PP0 "v[64:65]"
+#define SWO_PP2 "v[66:67]"
+#define SWO_PP4 "v[68:69]"
+#define SWO_PP6 "v[70:71]"
+#define SWO_PP8 "v[72:73]"
+#define SWO_PP10 "v[74:75]"
+#define SWO_PP12 "v[76:77]"
+#define SWO_PP14 "v[78:79]"
+#define SWO_S0 "v82"
+#define SWO_S1 "v83"
+#define SWO_S2 "v84"
+#define SWO_S3 "v85"
+#define SWO_S4 "v86"
+#define SWO_S5 "v87"
+#define SWO_S6 "v88"
+#define SWO_S7 "v89"
+#define SWO_SS0 "v[82:83]"
+#define SWO_SS1 "v[84:85]"
+#define SWO_SS2 "v[86:87]"
+#define SWO_SS3 "v[88:89]"
+// diagonal sums of a row pair, alternating between two register pairs
+#define SWO_DA "v[92:93]"
+#define SWO_DA0 "v92"
+#define SWO_DA1 "v93"
+#define SWO_DB "v[94:95]"
+#define SWO_DB0 "v94"
+#define SWO_DB1 "v95"
+
+#define SWO_M(d, r) "v_pk_maximum3_f16 v96, " d ", %[e" #r "], %[f]\n"
+#define SWO_G(p) "v_subrev_u32 " p ", %[goe], v96\n"
+#define SWO_F(p) "v_pk_max_i16 %[f], %[f], " p "\n"
+#define SWO_E(r, p) "v_pk_maximum3_f16 %[e" #r "], %[e" #r "], " p ", %[k" #r "]\n"
+#define SWO_S(s, p, q) "v_pk_maximum3_f16 " s ", " s ", " p ", " q "\n"
+#define SWO_SA(ss) "v_lshl_add_u64 " ss ", %[ge64], 0, " ss "\n"
+// subject pairs: bytes q of a[w] and b[w], zero extended into the two halves
+#define SWO_PERM(t, w, q) "v_perm_b32 " t ", %[b" #w "], %[a" #w "], %[q" #q "]\n"
+#define SWO_HD(d, pp) "v_lshl_add_u64 " d ", " pp ", 0, v[90:91]\n"
+// query pairs: w<k> holds the substitution pairs of rows 2k and 2k + 1
+#define SWO_HDW(d, pp, k) "v_lshl_add_u64 " d ", " pp ", 0, %[w" #k "]\n"
+
+// Rows r0, r1 (= r0 + 1) with their diagonal sums in d0, d1: G to p1, p2, where p2 and p3 hold the rows
+// r1 and r1 + 1 of the previous column until then; the next pair's sums go to nd.  rp = the row before r0
+// (its E update was left over; pp = its G).
+#define SWO_BLK(d0, d1, nd, r0, r1, p1, p2, npp, s, w, qa, qb, EPREV)                                         \
+    SWO_M(d0, r0) SWO_PERM("v90", w, qa) EPREV SWO_G(p1) SWO_F(p1) SWO_PERM("v91", w, qb) SWO_M(d1, r1)       \
+    SWO_HD(nd, npp) SWO_S(s, p1, p2) SWO_G(p2) SWO_F(p2) SWO_E(r0, p1)
+#define SWO_BLKW(d0, d1, nd, r0, r1, p1, p2, npp, s, w, EPREV)                                                \
+    SWO_M(d0, r0) EPREV SWO_G(p1) SWO_F(p1) SWO_HDW(nd, npp, w) SWO_M(d1, r1)                                 \
+    SWO_S(s, p1, p2) SWO_G(p2) SWO_F(p2) SWO_E(r0, p1)
+// the last two rows: nothing to prepare, and F is followed by an instruction that leaves it alone
+#define SWO_LAST(d0, d1, r0, r1, p1, p2, s, EPREV)                                                            \
+    SWO_M(d0, r0) EPREV SWO_G(p1) SWO_F(p1) SWO_E(r0, p1) SWO_M(d1, r1) SWO_S(s, p1, p2) SWO_G(p2) SWO_F(p2)  \
+    SWO_E(r1, p2)
+
+// What comes from above: a cooperating lane takes lane b-1's bottom row (its G and F of one step ago) and
+// drops the rows' offset Ge (R - 1); the first lane of a group takes the boundary words, raised by as much.
+#define SWO_TOP_COOP(pr)                                                                                      \
+    "v_cndmask_b32_dpp %[f], %[f], %[bf], vcc wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n"           \
+    "v_cndmask_b32_dpp v64, " pr ", %[bg], vcc wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n"          \
+    "v_subrev_u32 %[f], %[cr], %[f]\n" "v_subrev_u32 v64, %[cr], v64\n"
+#define SWO_TOP_ALONE "v_mov_b32 %[f], %[bf]\n" "v_mov_b32 v64, %[bg]\n"
+
+#define SWO_PRE "s_mov_b64 vcc, %[first]\n" SWO_PERM("v90", 0, 0) SWO_PERM("v91", 0, 1)
+#define SWO_ROWS4(TOP)                                                                                        \
+    SWO_PRE SWO_SA(SWO_SS0) SWO_HD(SWO_DA, SWO_PP0) TOP                                                       \
+    SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 0, 1, SWO_P1, SWO_P2, SWO_PP2, SWO_S0, 0, 2, 3, "")                     \
+    SWO_LAST(SWO_DB0, SWO_DB1, 2, 3, SWO_P3, SWO_P4, SWO_S1, SWO_E(1, SWO_P2))
+#define SWO_ROWS8(TOP)                                                                                        \
+    SWO_PRE SWO_SA(SWO_SS0) SWO_SA(SWO_SS1) SWO_HD(SWO_DA, SWO_PP0) TOP                                       \
+    SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 0, 1, SWO_P1, SWO_P2, SWO_PP2, SWO_S0, 0, 2, 3, "")                     \
+    SWO_BLK(SWO_DB0, SWO_DB1, SWO_DA, 2, 3, SWO_P3, SWO_P4, SWO_PP4, SWO_S1, 1, 0, 1, SWO_E(1, SWO_P2))       \
+    SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 4, 5, SWO_P5, SWO_P6, SWO_PP6, SWO_S2, 1, 2, 3, SWO_E(3, SWO_P4))       \
+    SWO_LAST(SWO_DB0, SWO_DB1, 6, 7, SWO_P7, SWO_P8, SWO_S3, SWO_E(5, SWO_P6))
+#define SWO_ROWS16(TOP)                                                                                       \
+    SWO_PRE SWO_SA(SWO_SS0) SWO_SA(SWO_SS1) SWO_HD(SWO_DA, SWO_PP0) TOP SWO_SA(SWO_SS2) SWO_SA(SWO_SS3)       \
+    SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 0, 1, SWO_P1, SWO_P2, SWO_PP2, SWO_S0, 0, 2, 3, "")                     \
+    SWO_BLK(SWO_DB0, SWO_DB1, SWO_DA, 2, 3, SWO_P3, SWO_P4, SWO_PP4, SWO_S1, 1, 0, 1, SWO_E(1, SWO_P2))       \
+    SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 4, 5, SWO_P5, SWO_P6, SWO_PP6, SWO_S2, 1, 2, 3, SWO_E(3, SWO_P4))       \
+    SWO_BLK(SWO_DB0, SWO_DB1, SWO_DA, 6, 7, SWO_P7, SWO_P8, SWO_PP8, SWO_S3, 2, 0, 1, SWO_E(5, SWO_P6))       \
+    SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 8, 9, SWO_P9, SWO_P10, SWO_PP10, SWO_S4, 2, 2, 3, SWO_E(7, SWO_P8))     \
+    SWO_BLK(SWO_DB0, SWO_DB1, SWO_DA, 10, 11, SWO_P11, SWO_P12, SWO_PP12, SWO_S5, 3, 0, 1, SWO_E(9, SWO_P10)) \
+    SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 12, 13, SWO_P13, SWO_P14, SWO_PP14, SWO_S6, 3, 2, 3, SWO_E(11, SWO_P12)) \
+    SWO_LAST(SWO_DB0, SWO_DB1, 14, 15, SWO_P15, SWO_P16, SWO_S7, SWO_E(13, SWO_P14))
+#define SWO_PREW "s_mov_b64 vcc, %[first]\n"
+#define SWO_ROWS8W(TOP)                                                                                       \
+    SWO_PREW SWO_SA(SWO_SS0) SWO_HDW(SWO_DA, SWO_PP0, 0) TOP                                                  \
+    SWO_BLKW(SWO_DA0, SWO_DA1, SWO_DB, 0, 1, SWO_P1, SWO_P2, SWO_PP2, SWO_S0, 1, SWO_SA(SWO_SS1))             \
+    SWO_BLKW(SWO_DB0, SWO_DB1, SWO_DA, 2, 3, SWO_P3, SWO_P4, SWO_PP4, SWO_S1, 2, SWO_E(1, SWO_P2))            \
+    SWO_BLKW(SWO_DA0, SWO_DA1, SWO_DB, 4, 5, SWO_P5, SWO_P6, SWO_PP6, SWO_S2, 3, SWO_E(3, SWO_P4))            \
+    SWO_LAST(SWO_DB0, SWO_DB1, 6, 7, SWO_P7, SWO_P8, SWO_S3, SWO_E(5, SWO_P6))
+#define SWO_ROWS16W(TOP)                                                                                      \
+    SWO_PREW SWO_SA(SWO_SS0) SWO_SA(SWO_SS1) SWO_HDW(SWO_DA, SWO_PP0, 0) TOP SWO_SA(SWO_SS2)                  \
+    SWO_BLKW(SWO_DA0, SWO_DA1, SWO_DB, 0, 1, SWO_P1, SWO_P2, SWO_PP2, SWO_S0, 1, SWO_SA(SWO_SS3))             \
+    SWO_BLKW(SWO_DB0, SWO_DB1, SWO_DA, 2, 3, SWO_P3, SWO_P4, SWO_PP4, SWO_S1, 2, SWO_E(1, SWO_P2))            \
+    SWO_BLKW(SWO_DA0, SWO_DA1, SWO_DB, 4, 5, SWO_P5, SWO_P6, SWO_PP6, SWO_S2, 3, SWO_E(3, SWO_P4))            \
+    SWO_BLKW(SWO_DB0, SWO_DB1, SWO_DA, 6, 7, SWO_P7, SWO_P8, SWO_PP8, SWO_S3, 4, SWO_E(5, SWO_P6))            \
+    SWO_BLKW(SWO_DA0, SWO_DA1, SWO_DB, 8, 9, SWO_P9, SWO_P10, SWO_PP10, SWO_S4, 5, SWO_E(7, SWO_P8))          \
+    SWO_BLKW(SWO_DB0, SWO_DB1, SWO_DA, 10, 11, SWO_P11, SWO_P12, SWO_PP12, SWO_S5, 6, SWO_E(9, SWO_P10))      \
+    SWO_BLKW(SWO_DA0, SWO_DA1, SWO_DB, 12, 13, SWO_P13, SWO_P14, SWO_PP14, SWO_S6, 7, SWO_E(11, SWO_P12))     \
+    SWO_LAST(SWO_DB0, SWO_DB1, 14, 15, SWO_P15, SWO_P16, SWO_S7, SWO_E(13, SWO_P14))
+
+#define SWO_OE(i) [e##i] "+v"(E[i])
+#define SWO_E4 SWO_OE(0), SWO_OE(1), SWO_OE(2), SWO_OE(3)
+#define SWO_E8 SWO_E4, SWO_OE(4), SWO_OE(5), SWO_OE(6), SWO_OE(7)
+#define SWO_E16 SWO_E8, SWO_OE(8), SWO_OE(9), SWO_OE(10), SWO_OE(11), SWO_OE(12), SWO_OE(13), SWO_OE(14), SWO_OE(15)
+#define SWO_OP4 "+{v64}"(P[0]), "+{v65}"(P[1]), "+{v66}"(P[2]), "+{v67}"(P[3]), "+{v68}"(P[4])
+#define SWO_OP8 SWO_OP4, "+{v69}"(P[5]), "+{v70}"(P[6]), "+{v71}"(P[7]), "+{v72}"(P[8])
+#define SWO_OP16 SWO_OP8, "+{v73}"(P[9]), "+{v74}"(P[10]), "+{v75}"(P[11]), "+{v76}"(P[12]), "+{v77}"(P[13]), \
+                 "+{v78}"(P[14]), "+{v79}"(P[15]), "+{v80}"(P[16])
+#define SWO_OS4 "+{v82}"(S[0]), "+{v83}"(S[1])
+#define SWO_OS8 SWO_OS4, "+{v84}"(S[2]), "+{v85}"(S[3])
+#define SWO_OS16 SWO_OS8, "+{v86}"(S[4]), "+{v87}"(S[5]), "+{v88}"(S[6]), "+{v89}"(S[7])
+#define SWO_K(i) [k##i] "s"(k[i])
+#define SWO_K4 SWO_K(0), SWO_K(1), SWO_K(2), SWO_K(3)
+#define SWO_K8 SWO_K4, SWO_K(4), SWO_K(5), SWO_K(6), SWO_K(7)
+#define SWO_K16 SWO_K8, SWO_K(8), SWO_K(9), SWO_K(10), SWO_K(11), SWO_K(12), SWO_K(13), SWO_K(14), SWO_K(15)
+#define SWO_ABI(i) [a##i] "v"(w[i]), [b##i] "v"(w[R / 4 + i])
+#define SWO_WI(i) [w##i] "v"(w64[i])
+#define SWO_IN [bf] "v"(bf), [bg] "v"(bg), [goe] "s"(goe), [cr] "s"(cr), [ge64] "s"(ge64), [first] "s"(first)
+#define SWO_INQ [q0] "s"(0x0c040c00u), [q1] "s"(0x0c050c01u), [q2] "s"(0x0c060c02u), [q3] "s"(0x0c070c03u)
+#define SWO_CLOB "v90", "v91", "v92", "v93", "v94", "v95", "v96", "vcc"
+
+// One column step of R rows, subject pairs: w holds R bytes of subject a's substitution scores, then of b's.
+// P[0] = G above the block at the previous column, P[r + 1] = G of row r; F enters as lane b's F of the step
+// before (handed to lane b + 1 here) and leaves as this step's.
+template <int R, bool COOP>
+__device__ __forceinline__ void rows_off_pair(uint32_t* P, uint32_t* E, uint32_t* S, uint32_t& F, uint32_t bg,
+                                              uint32_t bf, const uint32_t* w, const uint32_t* k, uint32_t goe,
+                                              uint32_t cr, uint64_t ge64, uint64_t first) {
+    if constexpr (R == 16) {
+        if constexpr (COOP)
+            asm(SWO_ROWS16(SWO_TOP_COOP(SWO_P16)) : SWO_E16, [f] "+v"(F), SWO_OP16, SWO_OS16
+                : SWO_IN, SWO_INQ, SWO_K16, SWO_ABI(0), SWO_ABI(1), SWO_ABI(2), SWO_ABI(3) : SWO_CLOB);
+        else
+            asm(SWO_ROWS16(SWO_TOP_ALONE) : SWO_E16, [f] "+v"(F), SWO_OP16, SWO_OS16
+                : SWO_IN, SWO_INQ, SWO_K16, SWO_ABI(0), SWO_ABI(1), SWO_ABI(2), SWO_ABI(3) : SWO_CLOB);
+    } else if constexpr (R == 8) {
+        if constexpr (COOP)
+            asm(SWO_ROWS8(SWO_TOP_COOP(SWO_P8)) : SWO_E8, [f] "+v"(F), SWO_OP8, SWO_OS8
+                : SWO_IN, SWO_INQ, SWO_K8, SWO_ABI(0), SWO_ABI(1) : SWO_CLOB);
+        else
+            asm(SWO_ROWS8(SWO_TOP_ALONE) : SWO_E8, [f] "+v"(F), SWO_OP8, SWO_OS8
+                : SWO_IN, SWO_INQ, SWO_K8, SWO_ABI(0), SWO_ABI(1) : SWO_CLOB);
+    } else {
+        static_assert(R == 4, "rows per lane must be 4, 8 or 16");
+        if constexpr (COOP)
+            asm(SWO_ROWS4(SWO_TOP_COOP(SWO_P4)) : SWO_E4, [f] "+v"(F), SWO_OP4, SWO_OS4
+                : SWO_IN, SWO_INQ, SWO_K4, SWO_ABI(0) : SWO_CLOB);
+        else
+            asm(SWO_ROWS4(SWO_TOP_ALONE) : SWO_E4, [f] "+v"(F), SWO_OP4, SWO_OS4
+                : SWO_IN, SWO_INQ, SWO_K4, SWO_ABI(0) : SWO_CLOB);
+    }
+}
+
+// Query pairs: w[r] = row r's substitution pair (both halves non-negative).
+template <int R, bool COOP>
+__device__ __forceinline__ void rows_off_packed(uint32_t* P, uint32_t* E, uint32_t* S, uint32_t& F, uint32_t bg,
+                                                uint32_t bf, const uint32_t* w, const uint32_t* k, uint32_t goe,
+                                                uint32_t cr, uint64_t ge64, uint64_t first) {
+    uint64_t w64[R / 2];
+#pragma unroll
+    for (int i = 0; i < R / 2; ++i) w64[i] = ((uint64_t)w[2 * i + 1] << 32) | w[2 * i];
+    if constexpr (R == 16) {
+        if constexpr (COOP)
+            asm(SWO_ROWS16W(SWO_TOP_COOP(SWO_P16)) : SWO_E16, [f] "+v"(F), SWO_OP16, SWO_OS16
+                : SWO_IN, SWO_K16, SWO_WI(0), SWO_WI(1), SWO_WI(2), SWO_WI(3), SWO_WI(4), SWO_WI(5), SWO_WI(6),
+                  SWO_WI(7) : SWO_CLOB);
+        else
+            asm(SWO_ROWS16W(SWO_TOP_ALONE) : SWO_E16, [f] "+v"(F), SWO_OP16, SWO_OS16
+                : SWO_IN, SWO_K16, SWO_WI(0), SWO_WI(1), SWO_WI(2), SWO_WI(3), SWO_WI(4), SWO_WI(5), SWO_WI(6),
+                  SWO_WI(7) : SWO_CLOB);
+    } else {
+        static_assert(R == 8, "query pairs run 8 or 16 rows per lane");
+        if constexpr (COOP)
+            asm(SWO_ROWS8W(SWO_TOP_COOP(SWO_P8)) : SWO_E8, [f] "+v"(F), SWO_OP8, SWO_OS8
+                : SWO_IN, SWO_K8, SWO_WI(0), SWO_WI(1), SWO_WI(2), SWO_WI(3) : SWO_CLOB);
+        else
+            asm(SWO_ROWS8W(SWO_TOP_ALONE) : SWO_E8, [f] "+v"(F), SWO_OP8, SWO_OS8
+                : SWO_IN, SWO_K8, SWO_WI(0), SWO_WI(1), SWO_WI(2), SWO_WI(3) : SWO_CLOB);
+    }
+}
+
+// Substitution values of one step: subject pairs read R bytes of each subject (slice [residue][R bytes]),
+// query pairs R dwords of their residue, four rows at a time (slice [row / 4][residue][4 dwords]: the
+// 16-byte slots of one read's residues spread over all banks).
+template <int R, bool PACKED>
+__device__ __forceinline__ void fetch_off(const uint8_t* lrow, typename Res<PACKED>::V rr, int u, uint32_t* out) {
+    if constexpr (PACKED) {
+        const int d = (rr >> (8 * u)) & 0xff;
+        const uint8_t* q = lrow + d * 16;
+#pragma unroll
+        for (int v = 0; v < R / 4; ++v) {
+            const uint4 x = *reinterpret_cast<const uint4*>(q + v * kNRes * 16);
+            out[4 * v] = x.x; out[4 * v + 1] = x.y; out[4 * v + 2] = x.z; out[4 * v + 3] = x.w;
+        }
+    } else {
+        const uint8_t* qa = lrow + ((rr.x >> (8 * u)) & 0xff) * R;
+        const uint8_t* qb = lrow + ((rr.y >> (8 * u)) & 0xff) * R;
+        if constexpr (R == 16) {
+            const uint4 x = *reinterpret_cast<const uint4*>(qa), y = *reinterpret_cast<const uint4*>(qb);
+            out[0] = x.x; out[1] = x.y; out[2] = x.z; out[3] = x.w;
+            out[4] = y.x; out[5] = y.y; out[6] = y.z; out[7] = y.w;
+        } else if constexpr (R == 8) {
+            const uint2 x = *reinterpret_cast<const uint2*>(qa), y = *reinterpret_cast<const uint2*>(qb);
+            out[0] = x.x; out[1] = x.y; out[2] = y.x; out[3] = y.y;
+        } else {
+            out[0] = *reinterpret_cast<const uint32_t*>(qa);
+            out[1] = *reinterpret_cast<const uint32_t*>(qb);
+        }
+    }
+}
+
+__device__ __forceinline__ uint32_t sgpr(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// One pass on offset cells: as sweep_pass, with the boundary words G and F free of offsets (the zero border
+// of a first pass reads as zeros).  S receives the true scores of the lane's two matrices.
+template <int R, bool COOP, bool PACKED>
+__device__ __forceinline__ void sweep_pass_off(const PassIO& io, int ncols, int B, int b, const uint8_t* lrow,
+                                               const OffCtx& o, u2& S) {
+    using RV = typename Res<PACKED>::V;
+    constexpr int NW = PACKED ? R : R / 2;                 // dwords of substitution values per step
+    const int nsteps = ncols + B - 1;
+    const int nloop = (nsteps + 3) >> 2;
+    const uint32_t ge = sgpr(o.ge), goe = sgpr(o.goe), go = sgpr(o.go);
+    const uint64_t ge64 = ((uint64_t)ge << 32) | ge;
+    const uint64_t first = __ballot(b == 0);
+    const uint32_t cr = ge * (R - 1);                      // no half of a product leaves 16 bits (host check)
+    uint32_t P[R + 1], E[R], Sx[R / 2];
+    // tau = 1 at the first step: G of column 0 carries Ge r, E of column 1 the floor Go + Ge (r + 1)
+#pragma unroll
+    for (int r = 0; r <= R; ++r) P[r] = ge * r;
+#pragma unroll
+    for (int r = 0; r < R; ++r) E[r] = go + ge * (r + 1);
+#pragma unroll
+    for (int i = 0; i < R / 2; ++i) Sx[i] = ge * (2 * i + 1);
+    uint32_t F = ge * R;                                   // what lane b-1 hands over before its first column
+    int tau = 1;                                           // of the chunk's first step
+    const int coff = COOP ? ((-b) >> 2) : 0;
+    const int csh = COOP ? ((-b) & 3) : 0;
+    auto res_at = [&](int c) { return Res<PACKED>::load(io.img, io.img_lane + (uint32_t)(c * kChunkBytes)); };
+    auto resid = [&](RV lo, RV hi) { return COOP ? Res<PACKED>::align(hi, lo, csh) : lo; };
+    RV c0 = res_at(coff), c1 = res_at(coff + 1), c2 = res_at(coff + 2);
+    uint4 bw[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) bw[i] = ld128(io.bnd, io.rd_lane + 16u * i);
+    RV rr = resid(c0, c1);
+    // subject pairs read their substitution bytes two steps ahead, query pairs (four times the words) one
+    constexpr bool kLead2 = !PACKED;
+    uint32_t cur[NW], nxt[NW];
+    fetch_off<R, PACKED>(lrow, rr, 0, cur);
+    if constexpr (kLead2) fetch_off<R, PACKED>(lrow, rr, 1, nxt);
+    for (int c = 0; c < nloop; ++c) {
+        const RV c3 = res_at(coff + c + 3);
+        uint4 nw[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) nw[i] = ld128(io.bnd, io.rd_lane + (uint32_t)(c + 1) * io.cstride + 16u * i);
+        const RV rn = resid(c1, c2);
+        const uint32_t get = ge * (uint32_t)tau;           // Ge tau of the chunk's first step
+        uint32_t kk[R + 3];                                // floors of the next step, row r at step u: kk[r + u]
+#pragma unroll
+        for (int i = 0; i < R + 3; ++i) kk[i] = go + get + ge * (uint32_t)(i + 1);
+        // boundary words of the four columns at their steps' offsets
+        uint32_t bg[4], bf[4];
+        const uint32_t b0 = get + (COOP ? cr : 0u);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint4 v = bw[u >> 1];
+            bg[u] = ((u & 1) ? v.z : v.x) + (b0 + ge * u);
+            bf[u] = ((u & 1) ? v.w : v.y) + (b0 + ge * u);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            uint32_t nx2[NW];
+            if constexpr (kLead2) {
+                if (u < 2) fetch_off<R, PACKED>(lrow, rr, u + 2, nx2);
+                else fetch_off<R, PACKED>(lrow, rn, u - 2, nx2);
+            } else {
+                if (u < 3) fetch_off<R, PACKED>(lrow, rr, u + 1, nxt);
+                else fetch_off<R, PACKED>(lrow, rn, 0, nxt);
+            }
+            if constexpr (PACKED) rows_off_packed<R, COOP>(P, E, Sx, F, bg[u], bf[u], cur, kk + u, goe, cr, ge64, first);
+            else rows_off_pair<R, COOP>(P, E, Sx, F, bg[u], bf[u], cur, kk + u, goe, cr, ge64, first);
+            // the last lane of a lane group hands column j = t - (B - 1) to the next pass, without offset
+            const int j = 4 * c + u - (B - 1);
+            const uint32_t off = get + ge * (uint32_t)(R + u);
+            st64(io.bnd, io.wr_lane + (uint32_t)((j >> 2) * (int)io.cstride + (j & 3) * 8), P[R] - off, F - off);
+#pragma unroll
+            for (int r = 0; r < NW; ++r) {
+                cur[r] = nxt[r];
+                if constexpr (kLead2) nxt[r] = nx2[r];
+            }
+        }
+        tau += 4;
+        if (tau > o.K) {                                   // lower everything by Ge K
+            const uint32_t down = ge * (uint32_t)o.K;
+#pragma unroll
+            for (int r = 0; r <= R; ++r) P[r] -= down;
+#pragma unroll
+            for (int r = 0; r < R; ++r) E[r] -= down;
+#pragma unroll
+            for (int i = 0; i < R / 2; ++i) Sx[i] -= down;
+            F -= down;
+            tau -= o.K;
+        }
+        c0 = c1;
+        c1 = c2;
+        c2 = c3;
+        rr = rn;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) bw[i] = nw[i];
+    }
+    // S[i] stands at offset Ge (2i + 1 + tau) of the last step (tau - 1 now); the odd rows of the last column
+    // were not folded yet (their own offset is Ge more).  Infinity and NaN patterns stay above every score.
+    const uint32_t last = ge * (uint32_t)(tau - 1);
+#pragma unroll
+    for (int i = 0; i < R / 2; ++i) {
+        const u2 x = __builtin_elementwise_sub_sat(bits<u2>(Sx[i]), bits<u2>(last + ge * (uint32_t)(2 * i + 1)));
+        const u2 y = __builtin_elementwise_sub_sat(bits<u2>(P[2 * i + 2]), bits<u2>(last + ge * (uint32_t)(2 * i + 2)));
+        S = __builtin_elementwise_max(S, __builtin_elementwise_max(x, y));
+    }
+}
+
+// Rows [row0, row0 + B*R) of a query profile (int16, SM + Go + Ge on real residues) into LDS as bytes
+// [b][residue][R].
+template <int R>
+__device__ __forceinline__ void load_slice_off(uint8_t* dst, const int16_t* prof, int mp, int row0, int lgB, int tid,
+                                               int nthreads) {
+    constexpr int U = (R % 8 == 0) ? 8 : 4;
+    const int per_res = (R << lgB) / U;
+    const int total = kNRes * per_res;
+    for (int e = tid; e < total; e += nthreads) {
+        const int d = e / per_res;
+        const int rem = e - d * per_res;
+        const int bb = rem / (R / U);
+        const int ru = rem - bb * (R / U);
+        const int16_t* src = prof + (int64_t)d * mp + row0 + rem * U;
+        uint8_t* out = dst + (bb * kNRes + d) * R + ru * U;
+        if constexpr (U == 8) {
+            const uint4 v = *reinterpret_cast<const uint4*>(src);
+            *reinterpret_cast<uint2*>(out) = make_uint2(__builtin_amdgcn_perm(v.y, v.x, 0x06040200u),
+                                                        __builtin_amdgcn_perm(v.w, v.z, 0x06040200u));
+        } else {
+            const uint2 v = *reinterpret_cast<const uint2*>(src);
+            *reinterpret_cast<uint32_t*>(out) = __builtin_amdgcn_perm(v.y, v.x, 0x06040200u);
+        }
+    }
+}
+
+// Rows [row0, row0 + B*R) of two query profiles interleaved into LDS as [b][row / 4][residue][4 dwords] (low
+// half query a, high half query b).  Rows past a profile's stride read as padding (0).
+template <int R>
+__device__ __forceinline__ void load_slice_off_q2(uint32_t* dst, const int16_t* pa, int mpa, const int16_t* pb, int mpb,
+                                                  int row0, int lgB, int tid, int nthreads) {
+    const int per_res = (R << lgB) / 8;                 // 8-row units per residue
+    const int total = kNRes * per_res;
+    for (int e = tid; e < total; e += nthreads) {
+        const int d = e / per_res;
+        const int rem = e - d * per_res;
+        const int row = row0 + rem * 8;
+        const int bb = (rem * 8) / R;
+        const int v0 = (rem * 8 - bb * R) / 4;
+        uint4 va = make_uint4(0, 0, 0, 0), vb = va;
+        if (row < mpa) va = *reinterpret_cast<const uint4*>(pa + (int64_t)d * mpa + row);
+        if (row < mpb) vb = *reinterpret_cast<const uint4*>(pb + (int64_t)d * mpb + row);
+        uint4 o0, o1;
+        o0.x = __builtin_amdgcn_perm(vb.x, va.x, 0x05040100u); o0.y = __builtin_amdgcn_perm(vb.x, va.x, 0x07060302u);
+        o0.z = __builtin_amdgcn_perm(vb.y, va.y, 0x05040100u); o0.w = __builtin_amdgcn_perm(vb.y, va.y, 0x07060302u);
+        o1.x = __builtin_amdgcn_perm(vb.z, va.z, 0x05040100u); o1.y = __builtin_amdgcn_perm(vb.z, va.z, 0x07060302u);
+        o1.z = __builtin_amdgcn_perm(vb.w, va.w, 0x05040100u); o1.w = __builtin_amdgcn_perm(vb.w, va.w, 0x07060302u);
+        uint4* out = reinterpret_cast<uint4*>(dst) + ((bb * (R / 4) + v0) * kNRes + d);
+        out[0] = o0;
+        out[kNRes] = o1;
+    }
+}

@@ -125,14 +125,17 @@ struct HostPinned {
     }
 };
 
-// Work items of one search: the bulk at R_main rows per lane and, on a side
-// stream, the long pairs of a short query at a smaller R_side.  Searches on
+// Work items of one search.  On offset cells one launch runs the head (the long
+// pairs: chained ones on a workgroup each, those of a short query on a wave each
+// at 4 rows per lane) and the bulk at R_main rows per lane behind it.  On plain
+// cells the bulk is one launch and the side list, the same long pairs on a wave
+// each at R_side rows per lane, another on a side stream.  Searches on
 // the handle's own workspace read the items from device copies made once;
 // searches on a caller's workspace upload them with the queries.
 struct Plan {
-    std::vector<WgItem> h_items;  // [main items..., side items...]
+    std::vector<WgItem> h_items;  // [head..., bulk..., side...]
     std::vector<int2> h_pairs;    // query pairs (query a, query b or -1) when qpack
-    int32_t n_main = 0, n_side = 0;
+    int32_t n_head = 0, n_main = 0, n_side = 0;
     int R_main = 16, R_side = 16;
     bool qpack = false;           // items index query pairs (two queries per lane)
     DevBuf items, qpairs;         // device copies (handle workspace only)
@@ -334,14 +337,66 @@ sw_status apply_opts(sw_db* db, const sw_pack_opts* opts) {
 
 // ------------------------------------------------------------------ planning
 // Issue slots of one unit (in half instructions): passes x steps x the step's
-// instruction count, 9.5 per row of R plus loads, addressing and, with
-// cooperating lanes, the shift of the bottom row.
+// instruction count on offset cells, 6.25 per row of R plus loads, addressing and, with
+// cooperating lanes, the hand-over of the bottom row.
 int64_t unit_cost(int m, int ncols, int lgB, int R) {
     const int B = 1 << lgB;
     const int64_t passes = (m + (R << lgB) - 1) / (R << lgB);
     const int64_t steps = round_up(ncols + B - 1, 4);
-    const int64_t per_step = 19 * R + 30 + (lgB ? 8 : 0);
+    const int64_t per_step = 25 * R / 2 + 32 + (lgB ? 8 : 0);
     return passes * steps * per_step;
+}
+
+// A step of a wave that nothing may hold up (long units run at raised priority) takes about 50 ns more than its
+// instructions: in the same units, per step.
+constexpr int64_t kLoneStep = 54;
+
+// Elapsed cost of one pair on a wave at R rows per lane.
+int64_t lone_cost(int m, int ncols, int lgB, int R) {
+    const int64_t passes = (m + (R << lgB) - 1) / (R << lgB);
+    return unit_cost(m, ncols, lgB, R) + passes * round_up(ncols + (1 << lgB) - 1, 4) * kLoneStep;
+}
+
+// The same for one pair on a workgroup (a chain item): its four waves at 4 rows per lane run side by side, 96
+// steps apart, or on windows of the subject (whose overlap depends on the query; 4 m is typical).
+int64_t chain_cost(int m, int ncols) {
+    const int64_t passes = (m + 1023) / 1024;
+    const int waves = passes > 1 ? 4 : (m + 255) / 256;
+    int64_t cols = ncols;
+    for (int windows = 4 / waves; windows > 1; --windows)
+        if (4 * m + ncols / windows <= ncols - ncols / 4) { cols = ncols / windows + 4 * m; break; }
+    return passes * (cols + 100 * waves) * (25 * 4 / 2 + 52 + kLoneStep);
+}
+
+// A unit of one wave (the widest lane cooperation) that costs more than a unit should: pair k of group g against
+// query (or query pair) q.
+struct LongUnit {
+    int g, k, q;
+    int64_t cost;                 // elapsed as a unit of one wave, at the rows per lane it would run with
+    int64_t chain;                // elapsed as chain items: the longest one, and
+    int64_t chain_sum;            // all of them (a query pair makes two)
+};
+
+// How many of the long units (sorted, longest first) to run as chain items.  A workgroup finishes a pair sooner
+// than a wave but spends four waves' time on it, much of it waiting, so only the units that would outlast the
+// search go: the cut with the smallest estimated end of the search, which is the issue time of all work, the
+// longest chain item, or the longest unit left to one wave.  (Of a chain item's elapsed time its four waves issue
+// for about half.)
+size_t chain_cut(const sw_db* db, const std::vector<LongUnit>& units, double bulk, double* end) {
+    const double nsimd = 4.0 * std::max(db->cus, 1);
+    double all = bulk, longest = 0, best = 0;
+    size_t cut = 0;
+    for (const LongUnit& u : units) all += (double)u.cost;
+    for (size_t k = 0;; ++k) {
+        const double rest = k < units.size() ? (double)units[k].cost : 0.0;
+        const double t = std::max({all / nsimd, longest, rest});
+        if (k == 0 || t < best) { best = t; cut = k; }
+        if (k == units.size()) break;
+        all += 2.0 * (double)units[k].chain_sum - (double)units[k].cost;
+        longest = std::max(longest, (double)units[k].chain);
+    }
+    *end = std::max(*end, best);
+    return cut;
 }
 
 // Work items for queries of lengths qlens (query index = position) against all
@@ -350,25 +405,54 @@ int64_t unit_cost(int m, int ncols, int lgB, int R) {
 // default: smaller units force wide lane cooperation whose pass height exceeds
 // short queries, larger ones lengthen the longest-first tail) and whose
 // boundary row fits a scratch slot.  Units still above that share at B = 64
-// are pairs that a single wave sweeps column by column; for a single short
-// query a smaller R makes them cheaper (most of a 64 x 16-row pass would be
-// padding) and they go to the side list.  Items are ordered longest first.
+// are long pairs that a single wave sweeps column by column.  Those that would
+// outlast the search are chained (chain_cut); for a single short query the
+// others run at fewer rows per lane (most of a 64 x 16-row pass would be
+// padding).  Items are ordered longest first.
 // Overrides for sweeps other than the 16-bit ones: fixed R, their slot capacity and wave count, and
 // whether the long pairs of a single short query may still go to the side list at a smaller R.
 struct PlanLimits { int R; int64_t slot_cap; int64_t nwaves; bool side = false; };
 
 // Groups [g_lo, g_hi) only (g_hi < 0: to the end).
+// head_out is null where only plain cells or 32-bit cells run the plan.
 void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std::vector<WgItem>& main_out,
-                std::vector<WgItem>& side_out, const std::vector<int>* chunk = nullptr, int nchunks = 1,
-                const PlanLimits* lim = nullptr, int g_lo = 0, int g_hi = -1) {
+                std::vector<WgItem>& side_out, std::vector<WgItem>* head_out, const std::vector<int>* chunk = nullptr,
+                int nchunks = 1, const PlanLimits* lim = nullptr, int g_lo = 0, int g_hi = -1) {
     if (g_hi < 0) g_hi = db->ngroups;
     const int64_t slot_cap = lim ? lim->slot_cap : db->slot_cap;
     const bool force_R = lim ? true : db->force_R != 0;
     // query qi covers groups chunk[qi], chunk[qi] + nchunks, ... (all groups when nchunks == 1)
     auto first_group = [&](size_t qi) { return chunk ? (*chunk)[qi] : 0; };
     struct Tmp { WgItem it; int64_t cost; };
+    // Bundles units of one query and lane count into items of up to kWaves, in the order they are added.
+    struct Bundle {
+        std::vector<Tmp>& out;
+        int g_first, nchunks;
+        WgItem cur;
+        int64_t cost = 0;
+        Bundle(std::vector<Tmp>& o, int q, int gf, int nc) : out(o), g_first(gf), nchunks(nc), cur{0, q, 0, -1, 0, nc} {}
+        void flush() {
+            if (cur.count > 0) out.push_back({cur, cost});
+            cur.count = 0;
+            cost = 0;
+        }
+        void add(int g, int k, int lgB, int64_t c) {
+            // position of (group, sub-unit) in this query's unit sequence
+            const int64_t seq_g = (g - g_first) / nchunks, seq_c = (cur.g0 - g_first) / nchunks;
+            const bool contiguous = cur.count > 0 && cur.lgB == lgB && (seq_c << lgB) + cur.k0 + cur.count == (seq_g << lgB) + k;
+            if (cur.count == kWaves || !contiguous) {
+                flush();
+                cur.g0 = g;
+                cur.k0 = (int16_t)k;
+                cur.lgB = (int8_t)lgB;
+            }
+            cur.count++;
+            cost = std::max(cost, c);
+        }
+    };
+    struct Lists { std::vector<Tmp> main, side, head; int R_side = 0; };
     // The plan at R rows per lane; returns its estimated makespan in cost units per wave.
-    auto plan_at = [&](int R_main, std::vector<Tmp>& items, std::vector<Tmp>& sitems, int& R_side) -> double {
+    auto plan_at = [&](int R_main, Lists& L) -> double {
         const int64_t nwaves = std::max<int64_t>(lim ? lim->nwaves : (int64_t)db->wgR[R_main] * kWaves, 1);
         int64_t total = 0;
         for (size_t qi = 0; qi < qlens.size(); ++qi)
@@ -376,37 +460,22 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
                 for (int g = first_group(qi); g < db->ngroups; g += nchunks)
                     if (g >= g_lo && g < g_hi) total += unit_cost(qlens[qi], db->ncols[g], 0, R_main);
         const double cap = db->unit_share * (double)total / (double)nwaves;
-        R_side = R_main;
-        int64_t sum = 0, biggest = 0, sbiggest = 0;
+        L.R_side = R_main;
+        int64_t sum = 0, biggest = 0;
+        std::vector<LongUnit> longs;
+        auto side_rows = [&](int m) {
+            int r = R_main;
+            if (qlens.size() == 1 && (!force_R || (lim && lim->side)))
+                for (int R : kRowChoices)
+                    if (unit_cost(m, db->ncols_max, 6, R) < unit_cost(m, db->ncols_max, 6, r)) r = R;
+            return r;
+        };
         for (size_t qi = 0; qi < qlens.size(); ++qi) {
             const int m = qlens[qi];
             if (m <= 0) continue;
-            int r_long = R_main;
-            if (qlens.size() == 1 && (!force_R || (lim && lim->side)))
-                for (int R : kRowChoices)
-                    if (unit_cost(m, db->ncols_max, 6, R) < unit_cost(m, db->ncols_max, 6, r_long)) r_long = R;
-            const int g_first = first_group(qi);
-            WgItem cur{0, (int32_t)qi, 0, -1, 0, nchunks}, scur{0, (int32_t)qi, 0, -1, 0, nchunks};
-            int64_t cur_cost = 0, scur_cost = 0;
-            auto flush = [](std::vector<Tmp>& v, WgItem& c, int64_t& cc) {
-                if (c.count > 0) v.push_back({c, cc});
-                c.count = 0;
-                cc = 0;
-            };
-            auto add = [&](std::vector<Tmp>& v, WgItem& c, int64_t& cc, int g, int k, int lgB, int64_t cost) {
-                // position of (group, sub-unit) in this query's unit sequence
-                const int64_t seq_g = (g - g_first) / nchunks, seq_c = (c.g0 - g_first) / nchunks;
-                const bool contiguous = c.count > 0 && c.lgB == lgB && (seq_c << lgB) + c.k0 + c.count == (seq_g << lgB) + k;
-                if (c.count == kWaves || !contiguous) {
-                    flush(v, c, cc);
-                    c.g0 = g;
-                    c.k0 = (int16_t)k;
-                    c.lgB = (int8_t)lgB;
-                }
-                c.count++;
-                cc = std::max(cc, cost);
-            };
-            for (int g = g_first; g < db->ngroups; g += nchunks) {
+            const int r_long = side_rows(m);
+            Bundle bulk(L.main, (int)qi, first_group(qi), nchunks);
+            for (int g = first_group(qi); g < db->ngroups; g += nchunks) {
                 if (g < g_lo || g >= g_hi) continue;
                 const int nc = db->ncols[g];
                 int lgB = 0;
@@ -421,56 +490,85 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
                 for (int k = 0; k < (1 << lgB); ++k) {
                     const int uc = db->pcols[(size_t)g * kGroupPairs + (k << (6 - lgB))];
                     const int64_t c = unit_cost(m, uc, lgB, R_main);
-                    if (lgB == 6 && db->force_lgB < 0 && r_long != R_main && (double)c > cap &&
-                        unit_cost(m, uc, 6, r_long) < c) {
-                        const int64_t sc = unit_cost(m, uc, 6, r_long);
-                        add(sitems, scur, scur_cost, g, k, 6, sc);
-                        sbiggest = std::max(sbiggest, sc);
-                        R_side = r_long;
+                    if (lgB == 6 && db->force_lgB < 0 && (double)c > cap) {
+                        const int64_t cc = head_out ? chain_cost(m, uc) : 0;
+                        longs.push_back({g, k, (int)qi, std::min(lone_cost(m, uc, 6, R_main), lone_cost(m, uc, 6, r_long)), cc, cc});
                     } else {
-                        add(items, cur, cur_cost, g, k, lgB, c);
+                        bulk.add(g, k, lgB, c);
                         sum += c;
                         biggest = std::max(biggest, c);
                     }
                 }
             }
-            flush(items, cur, cur_cost);
-            flush(sitems, scur, scur_cost);
+            bulk.flush();
         }
         // issue time: the SIMDs share the total; a unit shares its SIMD with the other resident waves
         const double nsimd = 4.0 * db->cus, per_simd = (double)nwaves / nsimd;
-        return std::max({(double)sum / nsimd, (double)biggest * per_simd, (double)sbiggest * per_simd});
+        double end = std::max((double)sum / nsimd, (double)biggest * per_simd);
+        size_t cut = 0;
+        if (head_out) {
+            std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
+            cut = chain_cut(db, longs, (double)sum, &end);
+        } else
+            for (const LongUnit& u : longs) end = std::max(end, (double)u.cost * per_simd);
+        for (size_t i = 0; i < cut; ++i) {
+            const LongUnit& u = longs[i];
+            L.head.push_back({WgItem{u.g, u.q, (int16_t)u.k, kItemChain, 1, nchunks}, u.chain});
+        }
+        // units of one wave: for one query whose long pairs do better at fewer rows per lane all of them go to the
+        // side list at those rows, and those not chained to the head at 4; otherwise those not chained are bulk
+        const bool small = qlens.size() == 1 && side_rows(qlens[0]) != R_main;
+        if (small) L.R_side = side_rows(qlens[0]);
+        auto wave_units = [&](std::vector<Tmp>& out, size_t i0, size_t i1, int lgB, int R) {
+            std::sort(longs.begin() + i0, longs.begin() + i1, [](const LongUnit& a, const LongUnit& b) {
+                return a.q != b.q ? a.q < b.q : a.g != b.g ? a.g < b.g : a.k < b.k;
+            });
+            for (size_t i = i0; i < i1;) {
+                const int q = longs[i].q;
+                Bundle b(out, q, first_group(q), nchunks);
+                const size_t at = out.size();
+                for (; i < i1 && longs[i].q == q; ++i)
+                    b.add(longs[i].g, longs[i].k, 6,
+                          unit_cost(qlens[q], db->pcols[(size_t)longs[i].g * kGroupPairs + longs[i].k], 6, R));
+                b.flush();
+                for (size_t x = at; x < out.size(); ++x) out[x].it.lgB = (int8_t)lgB;
+            }
+        };
+        if (small && head_out) wave_units(L.head, cut, longs.size(), kItemSmall, 4);
+        if (!small) wave_units(L.main, cut, longs.size(), 6, R_main);
+        wave_units(L.side, 0, small ? longs.size() : cut, 6, L.R_side);
+        return end;
     };
-    std::vector<Tmp> items, sitems;
-    int R_main = lim ? lim->R : db->force_R ? db->force_R : 16, R_side = R_main;
-    const double t_main = plan_at(R_main, items, sitems, R_side);
+    Lists L;
+    int R_main = lim ? lim->R : db->force_R ? db->force_R : 16;
+    const double t_main = plan_at(R_main, L);
     if (!force_R) {
         // fewer rows per lane pay more per cell but pad less when lanes cooperate on a short query
-        std::vector<Tmp> items8, sitems8;
-        int side8 = 8;
-        const double t8 = plan_at(8, items8, sitems8, side8);
-        if (t8 < t_main) {
-            items.swap(items8);
-            sitems.swap(sitems8);
+        Lists L8;
+        if (plan_at(8, L8) < t_main) {
+            std::swap(L, L8);
             R_main = 8;
-            R_side = side8;
         }
     }
-    auto by_cost = [](const Tmp& a, const Tmp& b) { return a.cost > b.cost; };
-    std::stable_sort(items.begin(), items.end(), by_cost);
-    std::stable_sort(sitems.begin(), sitems.end(), by_cost);
-    for (auto& t : items) main_out.push_back(t.it);
-    for (auto& t : sitems) side_out.push_back(t.it);
+    auto emit = [](std::vector<Tmp>& v, std::vector<WgItem>& out) {
+        std::stable_sort(v.begin(), v.end(), [](const Tmp& a, const Tmp& b) { return a.cost > b.cost; });
+        for (auto& t : v) out.push_back(t.it);
+    };
+    emit(L.main, main_out);
+    emit(L.side, side_out);
+    if (head_out) emit(L.head, *head_out);
     plan->R_main = R_main;
-    plan->R_side = R_side;
+    plan->R_side = L.R_side;
 }
 
 // Query-pair plan: queries on the same chunk are sorted by length and paired
 // neighbour with neighbour (a leftover query runs alone in its half-empty lanes);
 // each pair sweeps max(m_a, m_b) rows.  A unit holds P = 64/B subjects and a
 // group 2B units; B is capped at 32 (the interleaved slice is twice as large).
+// Long subject pairs are chained as in plan_units (a chain item takes one query
+// against the two subjects).
 void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std::vector<WgItem>& out,
-                   std::vector<int2>& pairs, const std::vector<int>* chunk, int nchunks) {
+                   std::vector<WgItem>& side_out, std::vector<WgItem>& head_out, std::vector<int2>& pairs, const std::vector<int>* chunk, int nchunks) {
     const int R = db->force_R == 8 ? 8 : 16;
     std::vector<int> order;
     for (int q = 0; q < (int)qlens.size(); ++q)
@@ -491,7 +589,7 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
     auto cost = [&](int m, int nc, int lgB) {
         const int B = 1 << lgB;
         const int64_t passes = (m + (R << lgB) - 1) / (R << lgB);
-        return passes * round_up(nc + B - 1, 4) * (int64_t)(17 * R + 30 + (lgB ? 8 : 0));
+        return passes * round_up(nc + B - 1, 4) * (int64_t)(21 * R / 2 + 32 + (lgB ? 8 : 0));
     };
     const int64_t nwaves = (int64_t)db->wgQ[R] * kWaves;
     int64_t total = 0;
@@ -501,7 +599,9 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
     }
     const double cap = db->unit_share * (double)total / (double)std::max<int64_t>(nwaves, 1);
     struct Tmp { WgItem it; int64_t cost; };
-    std::vector<Tmp> items;
+    std::vector<Tmp> items, uitems, citems;
+    std::vector<LongUnit> longs;
+    int64_t sum = 0;
     for (size_t pi = 0; pi < pairs.size(); ++pi) {
         const int2 pr = pairs[pi];
         const int m = std::max(qlens[pr.x], pr.y >= 0 ? qlens[pr.y] : 0);
@@ -519,7 +619,20 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
             const int P = kGroupPairs >> lgB;
             const int64_t seq_g = (g - g_first) / nchunks;
             for (int k = 0; k < units; ++k) {
-                const int64_t c = cost(m, db->pcols[(size_t)g * kGroupPairs + ((k * P) >> 1)], lgB);
+                const int uc = db->pcols[(size_t)g * kGroupPairs + ((k * P) >> 1)];
+                const int64_t c = cost(m, uc, lgB);
+                if (lgB == 5 && db->force_lgB < 0 && (double)c > cap) {       // P = 2: unit k is pair k
+                    LongUnit u{g, k, (int)pi, c + (int64_t)((m + 32 * R - 1) / (32 * R)) * uc * kLoneStep, 0, 0};
+                    for (int q : {pr.x, pr.y})
+                        if (q >= 0) {
+                            const int64_t x = chain_cost(qlens[q], uc);
+                            u.chain = std::max(u.chain, x);
+                            u.chain_sum += x;
+                        }
+                    longs.push_back(u);
+                    continue;
+                }
+                sum += c;
                 const int64_t seq_c = (cur.g0 - g_first) / nchunks;
                 const bool contiguous = cur.count > 0 && cur.lgB == lgB &&
                                         seq_c * units + cur.k0 + cur.count == seq_g * units + k;
@@ -537,25 +650,44 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
         }
         if (cur.count > 0) items.push_back({cur, cc});
     }
-    std::stable_sort(items.begin(), items.end(), [](const Tmp& a, const Tmp& b) { return a.cost > b.cost; });
-    for (auto& t : items) out.push_back(t.it);
+    std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
+    double end = 0;
+    const size_t cut = chain_cut(db, longs, (double)sum, &end);
+    for (size_t i = 0; i < longs.size(); ++i) {
+        const LongUnit& u = longs[i];
+        (i < cut ? uitems : items).push_back({WgItem{u.g, u.q, (int16_t)u.k, 5, 1, nchunks}, u.cost});
+        if (i >= cut) continue;
+        for (int q : {pairs[u.q].x, pairs[u.q].y})
+            if (q >= 0)
+                citems.push_back({WgItem{u.g, q, (int16_t)u.k, kItemChain, 1, nchunks},
+                                  chain_cost(qlens[q], db->pcols[(size_t)u.g * kGroupPairs + u.k])});
+    }
+    auto emit = [](std::vector<Tmp>& v, std::vector<WgItem>& to) {
+        std::stable_sort(v.begin(), v.end(), [](const Tmp& a, const Tmp& b) { return a.cost > b.cost; });
+        for (auto& t : v) to.push_back(t.it);
+    };
+    emit(items, out);
+    emit(uitems, side_out);
+    emit(citems, head_out);
     plan->R_main = R;
     plan->R_side = R;
 }
 
 sw_status build_plan(sw_db* db, const std::vector<int>& qlens, Plan* p, const std::vector<int>* chunk = nullptr,
                      int nchunks = 1) {
-    std::vector<WgItem> mi, si;
+    std::vector<WgItem> mi, si, hi;
     std::vector<int2> pairs;
     int nonempty = 0;
     for (int m : qlens) nonempty += m > 0;
     p->qpack = db->lane_pack == 2 && nonempty >= 2;
     if (p->qpack)
-        plan_units_q2(db, qlens, p, mi, pairs, chunk, nchunks);
+        plan_units_q2(db, qlens, p, mi, si, hi, pairs, chunk, nchunks);
     else
-        plan_units(db, qlens, p, mi, si, chunk, nchunks);
+        plan_units(db, qlens, p, mi, si, &hi, chunk, nchunks);
+    p->n_head = (int32_t)hi.size();
     p->n_main = (int32_t)mi.size();
     p->n_side = (int32_t)si.size();
+    mi.insert(mi.begin(), hi.begin(), hi.end());
     mi.insert(mi.end(), si.begin(), si.end());
     p->h_items.swap(mi);
     p->h_pairs.swap(pairs);
@@ -597,10 +729,10 @@ void clear_caches(sw_db* db) {
     db->plans.clear();
     db->batch_plan.release();
     db->batch_plan.h_items.clear();
-    db->batch_plan.n_main = db->batch_plan.n_side = 0;
+    db->batch_plan.n_head = db->batch_plan.n_main = db->batch_plan.n_side = 0;
     db->multi_plan.release();
     db->multi_plan.h_items.clear();
-    db->multi_plan.n_main = db->multi_plan.n_side = 0;
+    db->multi_plan.n_head = db->multi_plan.n_main = db->multi_plan.n_side = 0;
     db->batch_qlens.clear();
     db->graph.clear();
     db->last_eager = BatchKey();
@@ -846,19 +978,37 @@ SweepArgs sweep_args(const sw_db* db, const Staged& S, const Work& W, int32_t go
     return a;
 }
 
+// Most subject residues that a local alignment of a positive score covers, for a query of m residues whose best
+// substitution scores add up to top: at most m are aligned, and d more in gaps cost at least Go + (d - 1) Ge
+// (Ge <= Go), which must stay below top.
+int32_t alignment_span(int64_t m, int64_t top, int32_t go, int32_t ge) {
+    constexpr int64_t kWhole = (int64_t)1 << 28;              // beyond every subject
+    if (top <= go) return (int32_t)std::min(m + 1, kWhole);
+    if (ge <= 0 || ge > go) return (int32_t)kWhole;
+    return (int32_t)std::min(m + (top - go) / ge + 1, kWhole);
+}
+
 // Copies the queries (host) into the staging buffer on the device.  No launch.
 sw_status stage_queries(sw_db* db, const Work& W, const int8_t* h_queries, const int64_t* h_qoffsets, int nq,
-                        const int8_t* subst, int64_t score_row_stride, hipStream_t st, Staged* out,
+                        const int8_t* subst, int32_t go, int32_t ge, int64_t score_row_stride, hipStream_t st, Staged* out,
                         int32_t* const* per_query_out = nullptr, const Plan* with_plan = nullptr) {
     const StageLayout& L = W.L.st;
     char* h = static_cast<char*>(W.host->p);
     int64_t prof_off = 0;
+    int best[kMaxAlphabet];
+    for (int q = 0; q < db->alphabet; ++q) {
+        best[q] = 0;
+        for (int d = 0; d < db->alphabet; ++d) best[q] = std::max<int>(best[q], subst[q * db->alphabet + d]);
+    }
     QDesc* qd = reinterpret_cast<QDesc*>(h);
     int64_t* qo = reinterpret_cast<int64_t*>(h + L.off_qoff);
     for (int q = 0; q < nq; ++q) {
         const int m = (int)(h_qoffsets[q + 1] - h_qoffsets[q]);
         const int mp = (int)round_up(std::max(m, 1), kProfRowAlign);
-        qd[q] = QDesc{prof_off, (int64_t)q * score_row_stride, per_query_out ? per_query_out[q] : nullptr, m, mp};
+        int64_t top = 0;
+        for (int64_t i = h_qoffsets[q]; i < h_qoffsets[q + 1]; ++i) top += best[h_queries[i]];
+        qd[q] = QDesc{prof_off, (int64_t)q * score_row_stride, per_query_out ? per_query_out[q] : nullptr, m, mp,
+                      alignment_span(m, top, go, ge), 0};
         prof_off += (int64_t)kNRes * mp;
         qo[q] = h_qoffsets[q] - h_qoffsets[0];
     }
@@ -948,9 +1098,10 @@ sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& 
     HIP_TRY(launch_profile(S.sm_q, db->alphabet, S.qd, S.nq, S.qoff, W.prof, ctr, kCounters, W.bits, W.L.bits_words,
                            S.max_mp, st, form.add));
     SweepArgs a = sweep_args(db, S, W, go, ge, d_scores);
-    a.items = W.items;
+    const bool off = form.cell == kCellOff;
+    a.items = W.items + (off ? 0 : plan.n_head);
     a.n_items_dev = nullptr;
-    a.n_items = plan.n_main;
+    a.n_items = plan.n_main + (off ? plan.n_head : 0);
     a.counter = ctr + 0;
     set_rerun_args(db, a, W, ctr);
     a.unit_list = 0;
@@ -959,29 +1110,33 @@ sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& 
     a.off_k = form.off_k;
     a.sm_shift = form.add;
     a.qpairs = plan.qpack ? W.qpairs : nullptr;
-    // the side launch takes the first slots; the bulk launch fills the rest of the GPU
+    // on plain cells the side launch takes the first slots; the bulk launch fills the rest of the GPU
     const int wg_main = plan.qpack ? db->wgQ[plan.R_main] : db->wgR[plan.R_main];
-    const int grid_side = std::min(plan.n_side, std::max(1, wg_main / 8));
-    const int grid_main = std::max(1, std::min(wg_main - grid_side, std::max(plan.n_main, 1)));
-    if (plan.n_side > 0) {
+    const int n_side = off ? 0 : plan.n_side;
+    const int grid_side = std::min(n_side, a.n_items > 0 ? std::max(1, wg_main / 8) : wg_main);
+    const int grid_main = std::max(1, std::min(wg_main - grid_side, std::max(a.n_items, 1)));
+    if (n_side > 0) {
         SweepArgs b = a;
-        b.items = W.items + plan.n_main;
-        b.n_items = plan.n_side;
+        b.items = W.items + plan.n_head + plan.n_main;
+        b.n_items = n_side;
         b.counter = ctr + 3;
         b.slot_base = grid_main;
         HIP_TRY(hipEventRecord(db->ev_fork, st));
         HIP_TRY(hipStreamWaitEvent(db->side, db->ev_fork, 0));
-        HIP_TRY(launch_sweep(form.cell, plan.R_side, b, grid_side, db->side));
+        if (plan.qpack)
+            HIP_TRY(launch_sweep_q2(form.cell, plan.R_side, b, grid_side, db->side));
+        else
+            HIP_TRY(launch_sweep(form.cell, plan.R_side, b, grid_side, db->side));
         HIP_TRY(hipEventRecord(db->ev_join, db->side));
     }
     const int ev = time_sweep && db->timing ? record_timer_start(db, st) : -1;
-    if (plan.n_main > 0) {
+    if (a.n_items > 0) {
         if (plan.qpack)
             HIP_TRY(launch_sweep_q2(form.cell, plan.R_main, a, grid_main, st));
         else
             HIP_TRY(launch_sweep(form.cell, plan.R_main, a, grid_main, st));
     }
-    if (plan.n_side > 0) HIP_TRY(hipStreamWaitEvent(st, db->ev_join, 0));
+    if (n_side > 0) HIP_TRY(hipStreamWaitEvent(st, db->ev_join, 0));
     if (ev >= 0) {
         HIP_TRY(hipEventRecord(db->ev_pool[ev].second, st));
         db->ev_used.push_back(ev);
@@ -992,11 +1147,11 @@ sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& 
     if (k > 0)
         HIP_TRY(launch_topk_ws(d_scores, n, n, S.nq, k, top_s, top_i, topk_ws_bytes(n, S.nq, k) > 0 ? W.topk : nullptr,
                                st));
-    db->last_items = plan.n_main;
+    db->last_items = off ? plan.n_main : a.n_items;
     db->last_rows = plan.R_main;
-    db->last_side_items = plan.n_side;
-    db->last_side_rows = plan.n_side ? plan.R_side : 0;
-    db->last_grid = grid_main + (plan.n_side > 0 ? grid_side : 0);
+    db->last_side_items = off ? plan.n_head : n_side;
+    db->last_side_rows = db->last_side_items == 0 ? 0 : off ? 4 : plan.R_side;
+    db->last_grid = grid_main + (n_side > 0 ? grid_side : 0);
     db->last_counters = ctr;
     return SW_OK;
 }
@@ -1198,7 +1353,7 @@ sw_status search_one(const int8_t* h_query, int32_t qlen, sw_db* db, const int64
     Work W;
     if ((s = get_work(db, qo, 1, 0, false, plan, d_ws, ws_bytes, &W)) != SW_OK) return s;
     Staged S;
-    if ((s = stage_queries(db, W, h_query, qo, 1, h_subst, 0, st, &S, nullptr, d_ws ? plan : nullptr)) != SW_OK)
+    if ((s = stage_queries(db, W, h_query, qo, 1, h_subst, gap_open, gap_extend, 0, st, &S, nullptr, d_ws ? plan : nullptr)) != SW_OK)
         return s;
     const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_query, qo, 1);
     return enqueue(db, S, form, *plan, W, gap_open, gap_extend, d_scores_out, n, 0, nullptr, nullptr, st, true);
@@ -1265,7 +1420,7 @@ sw_status search_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int32
     for (int q = 0; q < nq; ++q)
         if (qlens[q] == 0) HIP_TRY(launch_fill(scores + (int64_t)q * n, n, 0, st));
     Staged S;
-    if ((s = stage_queries(db, W, h_queries, h_qoffsets, nq, h_subst, n, st, &S, nullptr, d_ws ? plan : nullptr)) != SW_OK)
+    if ((s = stage_queries(db, W, h_queries, h_qoffsets, nq, h_subst, gap_open, gap_extend, n, st, &S, nullptr, d_ws ? plan : nullptr)) != SW_OK)
         return s;
     const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_queries, h_qoffsets, nq);
     GraphEntry& G = db->graph;
@@ -1556,11 +1711,11 @@ sw_status sw_search_multi(const int8_t* h_queries, const int64_t* h_qoffsets, in
         if (qlens[q] == 0) HIP_TRY(launch_fill(h_d_scores[q], db->n, 0, st));
     HIP_TRY(hipStreamSynchronize(st));              // the previous call may still read the plan buffer
     if ((s = build_plan(db, qlens, &db->multi_plan, &chunk, nchunks)) != SW_OK) return s;
-    if (db->multi_plan.n_main + db->multi_plan.n_side == 0) return SW_OK;
+    if (db->multi_plan.h_items.empty()) return SW_OK;
     Work W;
     if ((s = get_work(db, h_qoffsets, nq, 0, false, &db->multi_plan, nullptr, 0, &W)) != SW_OK) return s;
     Staged S;
-    if ((s = stage_queries(db, W, h_queries, h_qoffsets, nq, h_subst, 0, st, &S, h_d_scores)) != SW_OK) return s;
+    if ((s = stage_queries(db, W, h_queries, h_qoffsets, nq, h_subst, gap_open, gap_extend, 0, st, &S, h_d_scores)) != SW_OK) return s;
     const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_queries, h_qoffsets, nq);
     return enqueue(db, S, form, db->multi_plan, W, gap_open, gap_extend, nullptr, db->n, 0, nullptr, nullptr, st, true);
 }
@@ -1902,7 +2057,7 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
     if (g_split < db->ngroups) {
         PlanLimits lim{16, db->slot_cap, (int64_t)db->wg_mode * kWaves};
         lim.side = true;
-        plan_units(db, std::vector<int>{qlen}, &db->mode_plan, mi, si, nullptr, 1, &lim, g_split, -1);
+        plan_units(db, std::vector<int>{qlen}, &db->mode_plan, mi, si, nullptr, nullptr, 1, &lim, g_split, -1);
     }
     // (4 rows per lane measured no faster for the 32-bit chain of a short query, and slower for longer ones)
     constexpr int R32 = 8;
@@ -1910,7 +2065,7 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
         // 32-bit units in the 32-bit boundary slots: one wave slot holds the widest subject's columns
         const PlanLimits lim32{R32, std::max<int64_t>(db->ncols_max, 4), (int64_t)db->wg32 * kWaves};
         Plan tmp;
-        plan_units(db, std::vector<int>{qlen}, &tmp, m32, s32, nullptr, 1, &lim32, 0, g_split);
+        plan_units(db, std::vector<int>{qlen}, &tmp, m32, s32, nullptr, nullptr, 1, &lim32, 0, g_split);
     }
     HIP_TRY(hipStreamSynchronize(st));            // the plan buffer may still be read by an earlier launch
     // device item list: [16-bit main..., 16-bit side..., 32-bit...]
@@ -1923,7 +2078,7 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
     Work W;
     if ((s = get_work(db, qo, 1, 0, false, nullptr, nullptr, 0, &W)) != SW_OK) return s;
     Staged S;
-    if ((s = stage_queries(db, W, h_query, qo, 1, h_subst, 0, st, &S)) != SW_OK) return s;
+    if ((s = stage_queries(db, W, h_query, qo, 1, h_subst, gap_open, gap_extend, 0, st, &S)) != SW_OK) return s;
     int32_t* ctr = W.counters;
     HIP_TRY(launch_profile(S.sm_q, db->alphabet, S.qd, S.nq, S.qoff, W.prof, ctr, kCounters, W.bits, W.L.bits_words,
                            S.max_mp, st, sm_shift));

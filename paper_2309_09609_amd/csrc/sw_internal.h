@@ -50,10 +50,14 @@ struct WgItem {
     int32_t g0;       // group of the first unit
     int32_t q;        // query index within the launch
     int16_t k0;       // sub-group index of the first unit within g0
-    int8_t lgB;       // log2 of lanes per pair (0..6)
+    int8_t lgB;       // log2 of lanes per pair (0..6), or one of the kinds below
     int8_t count;     // number of valid units (1..kWaves)
     int32_t gstep;    // distance between consecutive groups of the item
 };
+
+// Kinds of items that only launches on offset cells hold: up to kWaves pairs of a wave each at 4 rows per lane,
+// and one pair on the whole workgroup.
+constexpr int kItemSmall = 7, kItemChain = 8;
 
 // Per-query descriptor.
 struct QDesc {
@@ -62,6 +66,8 @@ struct QDesc {
     int32_t* out;         // if non-null: this query's own score vector (out_off is then ignored)
     int32_t m;            // query length (>= 1)
     int32_t mp;           // profile row stride (multiple of kProfRowAlign, >= m)
+    int32_t span;         // local search: most subject residues an alignment with a positive score can cover
+    int32_t unused;
 };
 
 // Form of the 16-bit end-to-end sweep beside SW_GLOBAL (1) and SW_SEMIGLOBAL (2): global scores on

@@ -971,14 +971,89 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
     }
 }
 
+// One long subject pair (pair k of group g) against query q on a whole workgroup (sw_offset.h, "long subjects").
+__device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int q, uint8_t* lds, int wave, int lane,
+                                          uint32_t* slot) {
+    constexpr int R = kChainRows;
+    const QDesc Q = a.qd[q];
+    const GroupRec G = a.groups[g];
+    const int cols = a.pair_cols[g * kGroupPairs + k];
+    constexpr int kWaveRows = 64 * R;
+    const int passes = (Q.m + kChainWaves * kWaveRows - 1) / (kChainWaves * kWaveRows);
+    // waves per window, and windows: as many as the waves allow while a window stays well below the subject
+    int waves = passes > 1 ? kChainWaves : (Q.m + kWaveRows - 1) / kWaveRows;
+    int windows = kChainWaves / waves;
+    while (windows > 1 && Q.span + cols / windows > cols - cols / 4) --windows;
+    const int core = ((cols / 4 + windows - 1) / windows) * 4;            // columns a window answers for
+    const int win = wave / waves;
+    const int w = wave - win * waves;
+    const bool mine = win < windows && win * core < cols;
+    int start = 0, end = cols;
+    if (windows > 1 && mine) {
+        start = max(0, win * core - Q.span) & ~3;
+        end = min(cols, (win + 1) * core);
+    }
+    const int ncols = mine ? end - start : 0;
+    // the longest window sets the stages of every wave (the first one has no overlap in front)
+    const int longest = windows > 1 ? min(cols, core + Q.span + 3) : cols;
+    const int stages = (((longest + 66) >> 2) + kChainStage / 4 - 1) / (kChainStage / 4) +
+                       (waves - 1) * (kChainLag / kChainStage);
+    PassIO io;
+    io.img = make_rsrc(a.image + G.base + (int64_t)(start >> 2) * kChunkBytes, (uint32_t)(ncols >> 2) * kChunkBytes);
+    io.img_lane = (uint32_t)(k * 8);
+    io.cstride = 32;
+    io.bnd = make_rsrc(slot, (uint32_t)(cols >> 2) * 32u);
+    uint8_t* slice = lds + wave * (kWaveRows * kNRes);
+    uint8_t* rings = lds + kChainWaves * (kWaveRows * kNRes);
+    const uint8_t* ring_in = rings + (wave > 0 ? wave - 1 : 0) * kChainRingBytes;
+    uint8_t* out_lane = lane == 63 ? rings + wave * kChainRingBytes : rings + kChainWaves * kChainRingBytes + lane * 8;
+    const OffCtx oc{(uint32_t)a.ge * 0x10001u, (uint32_t)(a.go - a.ge) * 0x10001u, (uint32_t)a.go * 0x10001u, a.off_k};
+    u2 S = {0, 0};
+    __builtin_amdgcn_s_setprio(3);                  // its steps are the search's longest chain
+    for (int p = 0; p < passes; ++p) {
+        const int row0 = (p * kChainWaves + w) * kWaveRows;
+        const bool active = mine && row0 < Q.m;
+        // a wave reads only its own slice; the barriers of the last pass's stages are behind it
+        if (active) load_slice_off<R>(slice, a.prof + Q.prof_off, Q.mp, row0, 6, lane, 64);
+        io.rd_lane = (lane == 0 && p > 0) ? 0u : kNoAccess;
+        io.wr_lane = lane == 63 ? 0u : kNoAccess;
+        __syncthreads();
+        chain_pass<R>(io, ncols, w, waves, stages, active, lane, slice + lane * (kNRes * R), ring_in, out_lane,
+                      p + 1 < passes, oc, S);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");   // boundary stores visible to the next pass
+        __syncthreads();
+    }
+    __builtin_amdgcn_s_setprio(0);
+    for (int o = 1; o < 64; o <<= 1) S = bits<u2>(CellI16::xmax(bits<s2>(S), o));
+    u2* best = reinterpret_cast<u2*>(rings);
+    if (lane == 0) best[wave] = S;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int x = 1; x < kChainWaves; ++x) S = __builtin_elementwise_max(S, best[x]);
+        const bool flag = a.rerun != nullptr && ((int)S.x >= a.sat || (int)S.y >= a.sat);
+        const bool poisoned = flag && a.poison;
+        const int slot0 = g * kGroupSubjects + 2 * k;
+        const int o0 = a.perm[slot0], o1 = a.perm[slot0 + 1];
+        int32_t* out = Q.out ? Q.out : a.scores + Q.out_off;
+        if (o0 >= 0) out[o0] = poisoned ? kPoison : (int)S.x;
+        if (o1 >= 0) out[o1] = poisoned ? kPoison : (int)S.y;
+        if (flag) append_rerun(a, g, q, k);
+    }
+    // Thread 0 goes on to pull the next item: without a barrier between, the compiler joins the two and lets the
+    // other lanes run ahead to the pull's barrier (and to a stale item).
+    __syncthreads();
+}
+
 // Recompute items past the list: blocks of kBitsBlock words of the flag bits.
 constexpr int kBitsBlock = 64;
 
 template <class C, int R, int MODE = 0>
 __global__ __launch_bounds__(64 * kWaves) void k_sweep(SweepArgs a) {
     // one shared slice of up to 64*R rows, or four per-wave slices of up to 16*R rows
-    // (offset cells hold one byte a row)
-    __shared__ __attribute__((aligned(16))) int16_t lds[kNRes * 64 * R / (std::is_same<C, CellOff>::value ? 2 : 1)];
+    // (offset cells hold one byte a row, and need room for a chain item)
+    constexpr bool kOffset = std::is_same<C, CellOff>::value;
+    constexpr int kLdsBytes = kOffset ? (kNRes * 64 * R > kChainLds ? kNRes * 64 * R : kChainLds) : kNRes * 64 * R * 2;
+    __shared__ __attribute__((aligned(16))) int16_t lds[kLdsBytes / 2];
     __shared__ int s_item;
     __shared__ uint32_t s_bits[kBitsBlock];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: buffer resources stay scalar
@@ -1044,6 +1119,20 @@ __global__ __launch_bounds__(64 * kWaves) void k_sweep(SweepArgs a) {
             }
         }
         const WgItem I = a.items[it];
+        if constexpr (kOffset) {
+            if (I.lgB == kItemChain) {
+                run_chain(a, I.g0, I.k0, I.q, reinterpret_cast<uint8_t*>(lds), wave, lane,
+                          a.scratch + (int64_t)(a.slot_base + blockIdx.x) * kWaves * a.slot_words);
+                continue;
+            }
+            if (R != kChainRows && I.lgB == kItemSmall) {
+                // long pairs of a short query: a wave each at fewer rows per lane
+                const int k = I.k0 + wave;
+                run_unit<C, kChainRows, false, MODE>(a, I.g0 + (k >> 6) * I.gstep, k & 63, 6, I.q, wave < I.count, true,
+                                                     lds, wave, lane, slot);
+                continue;
+            }
+        }
         {
             const int B = 1 << I.lgB;
             int k = I.k0 + wave;
@@ -1063,7 +1152,9 @@ __global__ __launch_bounds__(64 * kWaves) void k_sweep(SweepArgs a) {
 // has 2B such units.
 template <class C, int R>
 __global__ __launch_bounds__(64 * kWaves) void k_sweep_q2(SweepArgs a) {
-    __shared__ __attribute__((aligned(16))) int16_t lds[kNRes * 64 * R];
+    static_assert(kNRes * 64 * 8 * 2 < kChainLds && kChainLds <= kNRes * 64 * 16 * 2, "R = 8 takes a chain item's room");
+    constexpr int kLdsBytes = kNRes * 64 * R * 2 > kChainLds ? kNRes * 64 * R * 2 : kChainLds;
+    __shared__ __attribute__((aligned(16))) int16_t lds[kLdsBytes / 2];
     __shared__ int s_item;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: buffer resources stay scalar
     const int lane = threadIdx.x & 63;
@@ -1075,6 +1166,13 @@ __global__ __launch_bounds__(64 * kWaves) void k_sweep_q2(SweepArgs a) {
         __syncthreads();
         if (it >= a.n_items) break;
         const WgItem I = a.items[it];
+        if constexpr (std::is_same<C, CellOff>::value) {
+            if (I.lgB == kItemChain) {              // one query of the pair; I.q is the query itself
+                run_chain(a, I.g0, I.k0, I.q, reinterpret_cast<uint8_t*>(lds), wave, lane,
+                          a.scratch + (int64_t)(a.slot_base + blockIdx.x) * kWaves * a.slot_words);
+                continue;
+            }
+        }
         const int units = 2 << I.lgB;                   // units per group
         int k = I.k0 + wave;
         const int g = I.g0 + (k / units) * I.gstep;

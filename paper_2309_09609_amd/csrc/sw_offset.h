@@ -447,3 +447,156 @@ __device__ __forceinline__ void load_slice_off_q2(uint32_t* dst, const int16_t* 
         out[kNRes] = o1;
     }
 }
+
+// ------------------------------------------------------------ long subjects
+// One subject pair on the four waves of a workgroup.  A subject much longer
+// than a wave's share of the search is one serial chain of steps; here the
+// chain is cut both ways:
+//   * rows: wave w owns rows [64 R w, 64 R (w + 1)) of a pass and runs kChainLag
+//     steps behind wave w - 1, whose bottom row reaches it through a ring of
+//     columns in LDS (a workgroup barrier every kChainStage steps; a column is
+//     written more than one stage before it is read, one chunk of read-ahead
+//     included);
+//   * columns: a query whose rows need one or two of the four waves lets the
+//     others sweep further windows of the subject.  A window starts `span`
+//     columns before its own ones: no local alignment with a positive score
+//     covers more subject residues (QDesc::span), so each lies wholly in the
+//     window that holds its end, and the score is the largest window's.
+// Every wave of a workgroup runs the same number of stages, and so of barriers,
+// computed from the item before the first.
+//
+// Bound by the latency of a wave's step (about 60 instructions at 4 rows per
+// lane, the fewest; more rows would need more LDS than the bulk units beside
+// it leave).  The items run in the bulk launch itself, ahead of its units: a
+// launch of their own on another stream shares a hardware queue with the bulk
+// launch as soon as a process holds a few handles, and then runs before it
+// instead of beside it.  CHAIN_FIGURES
+constexpr int kChainWaves = kWaves;
+constexpr int kChainRows = 4;
+constexpr int kChainStage = 16;              // steps between barriers (4 chunks)
+constexpr int kChainLag = 96;                // steps between neighbouring waves: 64 lanes + 2 stages
+constexpr int kChainRing = 256;              // columns of a ring
+static_assert(kChainLag - 63 > kChainStage + 2 * kChunkCols, "a column is read after the barrier that follows its write");
+static_assert(kChainLag % kChainStage == 0 && kChainRing > 2 * kChainLag, "ring and stages");
+constexpr int kChainRingBytes = kChainRing * 8;
+constexpr int kChainIdle = kChainRingBytes + 64 * 8;       // where the 63 lanes that hand on nothing write
+// LDS of a workgroup: the waves' slices, their rings, the idle lanes' place
+constexpr int kChainLds = kChainWaves * (64 * kNRes * kChainRows + kChainRingBytes) + kChainIdle;
+
+// Wave w (of `waves` on one window) for all its chunks of one pass; `stages` barriers pass whatever it does.
+template <int R>
+__device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, int waves, int stages, bool active, int b,
+                                           const uint8_t* lrow, const uint8_t* ring_in, uint8_t* out_lane, bool more,
+                                           const OffCtx& o, u2& S) {
+    using RV = uint2;
+    constexpr int NW = R / 2;
+    const int nloop = (ncols + 63 + 3) >> 2;
+    const int first_stage = w * (kChainLag / kChainStage);
+    const uint32_t ge = sgpr(o.ge), goe = sgpr(o.goe), go = sgpr(o.go);
+    const uint64_t ge64 = ((uint64_t)ge << 32) | ge;
+    const uint64_t first = 1;
+    const uint32_t cr = ge * (R - 1);
+    uint32_t P[R + 1], E[R], Sx[R / 2];
+#pragma unroll
+    for (int r = 0; r <= R; ++r) P[r] = ge * r;
+#pragma unroll
+    for (int r = 0; r < R; ++r) E[r] = go + ge * (r + 1);
+#pragma unroll
+    for (int i = 0; i < R / 2; ++i) Sx[i] = ge * (2 * i + 1);
+    uint32_t F = ge * R;
+    int tau = 1;
+    const int coff = (-b) >> 2, csh = (-b) & 3;
+    auto res_at = [&](int c) { return Res<false>::load(io.img, io.img_lane + (uint32_t)(c * kChunkBytes)); };
+    // the boundary words of chunk c: the wave above, the pass above, or the zero border
+    auto bound = [&](int c, uint4* v) {
+        if (w > 0) {
+            const uint4* q = reinterpret_cast<const uint4*>(ring_in + ((4 * c) & (kChainRing - 1)) * 8);
+            const uint4 x = q[0], y = q[1];
+            const uint32_t in = 4 * c < ncols ? ~0u : 0u;       // past the subject the ring holds old columns
+            v[0] = make_uint4(x.x & in, x.y & in, x.z & in, x.w & in);
+            v[1] = make_uint4(y.x & in, y.y & in, y.z & in, y.w & in);
+        } else {
+            v[0] = ld128(io.bnd, io.rd_lane + (uint32_t)c * io.cstride);
+            v[1] = ld128(io.bnd, io.rd_lane + (uint32_t)c * io.cstride + 16u);
+        }
+    };
+    RV c0 = {}, c1 = {}, c2 = {}, rr = {};
+    uint4 bw[2] = {};
+    uint32_t cur[NW], nxt[NW];
+    for (int i = 0; i < NW; ++i) cur[i] = nxt[i] = 0;
+    for (int s = 0; s < stages; ++s) {
+        const int ls = s - first_stage;
+        if (active && ls >= 0 && ls * (kChainStage / 4) < nloop) {
+            if (ls == 0) {
+                c0 = res_at(coff);
+                c1 = res_at(coff + 1);
+                c2 = res_at(coff + 2);
+                bound(0, bw);
+                rr = Res<false>::align(c1, c0, csh);
+                fetch_off<R, false>(lrow, rr, 0, cur);
+                fetch_off<R, false>(lrow, rr, 1, nxt);
+            }
+            const int c_end = min(nloop, (ls + 1) * (kChainStage / 4));
+            for (int c = ls * (kChainStage / 4); c < c_end; ++c) {
+                const RV c3 = res_at(coff + c + 3);
+                uint4 nw[2];
+                bound(c + 1, nw);
+                const RV rn = Res<false>::align(c2, c1, csh);
+                const uint32_t get = ge * (uint32_t)tau;
+                uint32_t kk[R + 3];
+#pragma unroll
+                for (int i = 0; i < R + 3; ++i) kk[i] = go + get + ge * (uint32_t)(i + 1);
+                uint32_t bg[4], bf[4];
+                const uint32_t b0 = get + cr;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint4 v = bw[u >> 1];
+                    bg[u] = ((u & 1) ? v.z : v.x) + (b0 + ge * u);
+                    bf[u] = ((u & 1) ? v.w : v.y) + (b0 + ge * u);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    uint32_t nx2[NW];
+                    if (u < 2) fetch_off<R, false>(lrow, rr, u + 2, nx2);
+                    else fetch_off<R, false>(lrow, rn, u - 2, nx2);
+                    rows_off_pair<R, true>(P, E, Sx, F, bg[u], bf[u], cur, kk + u, goe, cr, ge64, first);
+                    const int j = 4 * c + u - 63;
+                    const uint32_t off = get + ge * (uint32_t)(R + u);
+                    if (w + 1 < waves)
+                        *reinterpret_cast<uint2*>(out_lane + (j & (kChainRing - 1)) * 8) = make_uint2(P[R] - off, F - off);
+                    else if (more)
+                        st64(io.bnd, io.wr_lane + (uint32_t)((j >> 2) * (int)io.cstride + (j & 3) * 8), P[R] - off, F - off);
+#pragma unroll
+                    for (int r = 0; r < NW; ++r) { cur[r] = nxt[r]; nxt[r] = nx2[r]; }
+                }
+                tau += 4;
+                if (tau > o.K) {
+                    const uint32_t down = ge * (uint32_t)o.K;
+#pragma unroll
+                    for (int r = 0; r <= R; ++r) P[r] -= down;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) E[r] -= down;
+#pragma unroll
+                    for (int i = 0; i < R / 2; ++i) Sx[i] -= down;
+                    F -= down;
+                    tau -= o.K;
+                }
+                c0 = c1;
+                c1 = c2;
+                c2 = c3;
+                rr = rn;
+                bw[0] = nw[0];
+                bw[1] = nw[1];
+            }
+        }
+        __syncthreads();
+    }
+    if (!active) return;
+    const uint32_t last = ge * (uint32_t)(tau - 1);
+#pragma unroll
+    for (int i = 0; i < R / 2; ++i) {
+        const u2 x = __builtin_elementwise_sub_sat(bits<u2>(Sx[i]), bits<u2>(last + ge * (uint32_t)(2 * i + 1)));
+        const u2 y = __builtin_elementwise_sub_sat(bits<u2>(P[2 * i + 2]), bits<u2>(last + ge * (uint32_t)(2 * i + 2)));
+        S = __builtin_elementwise_max(S, __builtin_elementwise_max(x, y));
+    }
+}

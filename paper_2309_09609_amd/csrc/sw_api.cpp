@@ -125,18 +125,17 @@ struct HostPinned {
     }
 };
 
-// Work items of one search.  On offset cells one launch runs the head (the long
-// pairs: chained ones on a workgroup each, those of a short query on a wave each
-// at 4 rows per lane) and the bulk at R_main rows per lane behind it.  On plain
-// cells the bulk is one launch and the side list, the same long pairs on a wave
-// each at R_side rows per lane, another on a side stream.  Searches on
+// Work items of one search, run by one launch: the chained pairs (a workgroup
+// each) and the bulk on offset cells; on plain cells the bulk and, ahead of it,
+// the same pairs on a wave each (unchained).  Searches on
 // the handle's own workspace read the items from device copies made once;
 // searches on a caller's workspace upload them with the queries.
 struct Plan {
-    std::vector<WgItem> h_items;  // [head..., bulk..., side...]
+    std::vector<WgItem> h_items;  // [chained..., bulk..., unchained...]
     std::vector<int2> h_pairs;    // query pairs (query a, query b or -1) when qpack
-    int32_t n_head = 0, n_main = 0, n_side = 0;
-    int R_main = 16, R_side = 16;
+    int32_t n_chain = 0, n_main = 0, n_unchained = 0;
+    int32_t n_small = 0;          // bulk items at 4 rows per lane
+    int R_main = 16;
     bool qpack = false;           // items index query pairs (two queries per lane)
     DevBuf items, qpairs;         // device copies (handle workspace only)
     bool on_device = false;
@@ -251,6 +250,7 @@ struct sw_db {
     int align_tiles = 0;              // tiled traceback fill: 0 = long pairs, 1 = never, 2 = every pair
     int wg_mode = 0;                  // persistent workgroups of an end-to-end sweep
     Plan mode_plan;
+    int mode_side_rows = 16;          // end-to-end modes: rows per lane of the long pairs' launch
     // launch geometry
     int cus = 0, wg16 = 0, wg32 = 0;  // scratch slots (workgroups) of the 16-bit sweeps; 32-bit grid
     int wgR[17] = {0};                // persistent workgroups per 16-bit instance, by R
@@ -347,14 +347,14 @@ int64_t unit_cost(int m, int ncols, int lgB, int R) {
     return passes * steps * per_step;
 }
 
-// A step of a wave that nothing may hold up (long units run at raised priority) takes about 50 ns more than its
-// instructions: in the same units, per step.
-constexpr int64_t kLoneStep = 54;
+// Elapsed cost of a unit whose wave issues ahead of the others of its SIMD (long units run at raised priority), in
+// the same units: a lone wave's step takes 70 + 11 R ns (measured at 4, 8 and 16 rows per lane), about 35 units more
+// than it issues for, and other waves' instructions in flight hold up every one of its own (x 1.4).
+int64_t elapsed(int64_t step_cost, int64_t steps) { return (step_cost + 35) * steps * 7 / 5; }
 
-// Elapsed cost of one pair on a wave at R rows per lane.
 int64_t lone_cost(int m, int ncols, int lgB, int R) {
     const int64_t passes = (m + (R << lgB) - 1) / (R << lgB);
-    return unit_cost(m, ncols, lgB, R) + passes * round_up(ncols + (1 << lgB) - 1, 4) * kLoneStep;
+    return elapsed(25 * R / 2 + 32 + (lgB ? 8 : 0), passes * round_up(ncols + (1 << lgB) - 1, 4));
 }
 
 // The same for one pair on a workgroup (a chain item): its four waves at 4 rows per lane run side by side, 96
@@ -365,7 +365,7 @@ int64_t chain_cost(int m, int ncols) {
     int64_t cols = ncols;
     for (int windows = 4 / waves; windows > 1; --windows)
         if (4 * m + ncols / windows <= ncols - ncols / 4) { cols = ncols / windows + 4 * m; break; }
-    return passes * (cols + 100 * waves) * (25 * 4 / 2 + 52 + kLoneStep);
+    return elapsed(25 * 4 / 2 + 55, passes * (cols + 100 * waves));
 }
 
 // A unit of one wave (the widest lane cooperation) that costs more than a unit should: pair k of group g against
@@ -375,24 +375,25 @@ struct LongUnit {
     int64_t cost;                 // elapsed as a unit of one wave, at the rows per lane it would run with
     int64_t chain;                // elapsed as chain items: the longest one, and
     int64_t chain_sum;            // all of them (a query pair makes two)
+    int R;                        // rows per lane of the unit of one wave
 };
 
 // How many of the long units (sorted, longest first) to run as chain items.  A workgroup finishes a pair sooner
 // than a wave but spends four waves' time on it, much of it waiting, so only the units that would outlast the
 // search go: the cut with the smallest estimated end of the search, which is the issue time of all work, the
-// longest chain item, or the longest unit left to one wave.  (Of a chain item's elapsed time its four waves issue
-// for about half.)
+// longest chain item, or the longest unit left to one wave.  (A chain item's four waves issue for about half of its
+// elapsed time, a unit's wave for two thirds.)
 size_t chain_cut(const sw_db* db, const std::vector<LongUnit>& units, double bulk, double* end) {
     const double nsimd = 4.0 * std::max(db->cus, 1);
     double all = bulk, longest = 0, best = 0;
     size_t cut = 0;
-    for (const LongUnit& u : units) all += (double)u.cost;
+    for (const LongUnit& u : units) all += 0.67 * (double)u.cost;
     for (size_t k = 0;; ++k) {
         const double rest = k < units.size() ? (double)units[k].cost : 0.0;
         const double t = std::max({all / nsimd, longest, rest});
         if (k == 0 || t < best) { best = t; cut = k; }
         if (k == units.size()) break;
-        all += 2.0 * (double)units[k].chain_sum - (double)units[k].cost;
+        all += 2.0 * (double)units[k].chain_sum - 0.67 * (double)units[k].cost;
         longest = std::max(longest, (double)units[k].chain);
     }
     *end = std::max(*end, best);
@@ -406,18 +407,21 @@ size_t chain_cut(const sw_db* db, const std::vector<LongUnit>& units, double bul
 // short queries, larger ones lengthen the longest-first tail) and whose
 // boundary row fits a scratch slot.  Units still above that share at B = 64
 // are long pairs that a single wave sweeps column by column.  Those that would
-// outlast the search are chained (chain_cut); for a single short query the
-// others run at fewer rows per lane (most of a 64 x 16-row pass would be
-// padding).  Items are ordered longest first.
+// outlast the search are chained (chain_cut).  Where a unit's lanes x rows pad
+// a short query, the group may run at 4 rows per lane instead of the launch's
+// R: among the choices that keep its units within the share, the cheaper one is
+// taken.  Items are ordered longest first.
 // Overrides for sweeps other than the 16-bit ones: fixed R, their slot capacity and wave count, and
 // whether the long pairs of a single short query may still go to the side list at a smaller R.
 struct PlanLimits { int R; int64_t slot_cap; int64_t nwaves; bool side = false; };
 
 // Groups [g_lo, g_hi) only (g_hi < 0: to the end).
-// head_out is null where only plain cells or 32-bit cells run the plan.
+// head_out takes the chained pairs and side_out the same as units of one wave; head_out is null for the end-to-end
+// modes, whose long pairs go to side_out alone.
 void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std::vector<WgItem>& main_out,
                 std::vector<WgItem>& side_out, std::vector<WgItem>* head_out, const std::vector<int>* chunk = nullptr,
-                int nchunks = 1, const PlanLimits* lim = nullptr, int g_lo = 0, int g_hi = -1) {
+                int nchunks = 1, const PlanLimits* lim = nullptr, int g_lo = 0, int g_hi = -1,
+                int* side_rows_out = nullptr) {
     if (g_hi < 0) g_hi = db->ngroups;
     const int64_t slot_cap = lim ? lim->slot_cap : db->slot_cap;
     const bool force_R = lim ? true : db->force_R != 0;
@@ -439,7 +443,8 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
         void add(int g, int k, int lgB, int64_t c) {
             // position of (group, sub-unit) in this query's unit sequence
             const int64_t seq_g = (g - g_first) / nchunks, seq_c = (cur.g0 - g_first) / nchunks;
-            const bool contiguous = cur.count > 0 && cur.lgB == lgB && (seq_c << lgB) + cur.k0 + cur.count == (seq_g << lgB) + k;
+            const int lg = lgB & (kItemSmall - 1);
+            const bool contiguous = cur.count > 0 && cur.lgB == lgB && (seq_c << lg) + cur.k0 + cur.count == (seq_g << lg) + k;
             if (cur.count == kWaves || !contiguous) {
                 flush();
                 cur.g0 = g;
@@ -475,13 +480,25 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
             if (m <= 0) continue;
             const int r_long = side_rows(m);
             Bundle bulk(L.main, (int)qi, first_group(qi), nchunks);
+            Bundle small(L.main, (int)qi, first_group(qi), nchunks);
             for (int g = first_group(qi); g < db->ngroups; g += nchunks) {
                 if (g < g_lo || g >= g_hi) continue;
                 const int nc = db->ncols[g];
-                int lgB = 0;
-                for (; lgB < 6; ++lgB) {
-                    const int64_t P = kGroupPairs >> lgB;
-                    if ((double)unit_cost(m, nc, lgB, R_main) <= cap && (int64_t)nc * P <= slot_cap) break;
+                // the fewest lanes per pair at R rows whose units stay within the share (6: perhaps none do)
+                auto lanes = [&](int R) {
+                    int l = 0;
+                    while (l < 6 && ((double)unit_cost(m, nc, l, R) > cap || (int64_t)nc * (kGroupPairs >> l) > slot_cap)) ++l;
+                    return l;
+                };
+                int lgB = lanes(R_main), R = R_main;
+                if (head_out && R_main != kSmallRows && db->force_lgB < 0 && db->force_R == 0) {
+                    const int l4 = lanes(kSmallRows);
+                    const int64_t c4 = unit_cost(m, nc, l4, kSmallRows), c = unit_cost(m, nc, lgB, R_main);
+                    // (units over the share are compared by what they take, the others by what the group takes)
+                    if ((double)std::min(c, c4) > cap ? c4 < c : (double)c4 <= cap && ((c4 << l4) < (c << lgB) || (double)c > cap)) {
+                        lgB = l4;
+                        R = kSmallRows;
+                    }
                 }
                 if (db->force_lgB >= 0) {
                     lgB = db->force_lgB;
@@ -489,18 +506,19 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
                 }
                 for (int k = 0; k < (1 << lgB); ++k) {
                     const int uc = db->pcols[(size_t)g * kGroupPairs + (k << (6 - lgB))];
-                    const int64_t c = unit_cost(m, uc, lgB, R_main);
+                    const int64_t c = unit_cost(m, uc, lgB, R);
                     if (lgB == 6 && db->force_lgB < 0 && (double)c > cap) {
                         const int64_t cc = head_out ? chain_cost(m, uc) : 0;
-                        longs.push_back({g, k, (int)qi, std::min(lone_cost(m, uc, 6, R_main), lone_cost(m, uc, 6, r_long)), cc, cc});
+                        longs.push_back({g, k, (int)qi, lone_cost(m, uc, 6, head_out ? R : r_long), cc, cc, R});
                     } else {
-                        bulk.add(g, k, lgB, c);
+                        (R == R_main ? bulk : small).add(g, k, R == R_main ? lgB : lgB + kItemSmall, c);
                         sum += c;
                         biggest = std::max(biggest, c);
                     }
                 }
             }
             bulk.flush();
+            small.flush();
         }
         // issue time: the SIMDs share the total; a unit shares its SIMD with the other resident waves
         const double nsimd = 4.0 * db->cus, per_simd = (double)nwaves / nsimd;
@@ -515,39 +533,44 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
             const LongUnit& u = longs[i];
             L.head.push_back({WgItem{u.g, u.q, (int16_t)u.k, kItemChain, 1, nchunks}, u.chain});
         }
-        // units of one wave: for one query whose long pairs do better at fewer rows per lane all of them go to the
-        // side list at those rows, and those not chained to the head at 4; otherwise those not chained are bulk
-        const bool small = qlens.size() == 1 && side_rows(qlens[0]) != R_main;
-        if (small) L.R_side = side_rows(qlens[0]);
-        auto wave_units = [&](std::vector<Tmp>& out, size_t i0, size_t i1, int lgB, int R) {
+        // units of one wave: those not chained are bulk, the chained ones the list for plain cells; without chains,
+        // a single query's go to the side list at fewer rows per lane where that is cheaper
+        auto wave_units = [&](std::vector<Tmp>& out, size_t i0, size_t i1, int R_side) {
             std::sort(longs.begin() + i0, longs.begin() + i1, [](const LongUnit& a, const LongUnit& b) {
-                return a.q != b.q ? a.q < b.q : a.g != b.g ? a.g < b.g : a.k < b.k;
+                return a.q != b.q ? a.q < b.q : a.R != b.R ? a.R < b.R : a.g != b.g ? a.g < b.g : a.k < b.k;
             });
             for (size_t i = i0; i < i1;) {
-                const int q = longs[i].q;
+                const int q = longs[i].q, R = longs[i].R;
                 Bundle b(out, q, first_group(q), nchunks);
-                const size_t at = out.size();
-                for (; i < i1 && longs[i].q == q; ++i)
-                    b.add(longs[i].g, longs[i].k, 6,
-                          unit_cost(qlens[q], db->pcols[(size_t)longs[i].g * kGroupPairs + longs[i].k], 6, R));
+                for (; i < i1 && longs[i].q == q && longs[i].R == R; ++i)
+                    b.add(longs[i].g, longs[i].k, R == R_main ? 6 : 6 + kItemSmall,
+                          unit_cost(qlens[q], db->pcols[(size_t)longs[i].g * kGroupPairs + longs[i].k], 6, R_side ? R_side : R));
                 b.flush();
-                for (size_t x = at; x < out.size(); ++x) out[x].it.lgB = (int8_t)lgB;
             }
         };
-        if (small && head_out) wave_units(L.head, cut, longs.size(), kItemSmall, 4);
-        if (!small) wave_units(L.main, cut, longs.size(), 6, R_main);
-        wave_units(L.side, 0, small ? longs.size() : cut, 6, L.R_side);
+        if (head_out) {
+            wave_units(L.main, cut, longs.size(), 0);
+            wave_units(L.side, 0, cut, 0);
+        } else {
+            const int r = qlens.size() == 1 ? side_rows(qlens[0]) : R_main;
+            L.R_side = r;
+            wave_units(r != R_main ? L.side : L.main, 0, longs.size(), r);
+        }
         return end;
     };
     Lists L;
     int R_main = lim ? lim->R : db->force_R ? db->force_R : 16;
-    const double t_main = plan_at(R_main, L);
+    double t_main = plan_at(R_main, L);
     if (!force_R) {
         // fewer rows per lane pay more per cell but pad less when lanes cooperate on a short query
-        Lists L8;
-        if (plan_at(8, L8) < t_main) {
-            std::swap(L, L8);
-            R_main = 8;
+        for (int R : {12, 8}) {
+            Lists other;
+            const double t = plan_at(R, other);
+            if (t < t_main) {
+                std::swap(L, other);
+                t_main = t;
+                R_main = R;
+            }
         }
     }
     auto emit = [](std::vector<Tmp>& v, std::vector<WgItem>& out) {
@@ -558,7 +581,7 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
     emit(L.side, side_out);
     if (head_out) emit(L.head, *head_out);
     plan->R_main = R_main;
-    plan->R_side = L.R_side;
+    if (side_rows_out) *side_rows_out = L.R_side;
 }
 
 // Query-pair plan: queries on the same chunk are sorted by length and paired
@@ -622,7 +645,7 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
                 const int uc = db->pcols[(size_t)g * kGroupPairs + ((k * P) >> 1)];
                 const int64_t c = cost(m, uc, lgB);
                 if (lgB == 5 && db->force_lgB < 0 && (double)c > cap) {       // P = 2: unit k is pair k
-                    LongUnit u{g, k, (int)pi, c + (int64_t)((m + 32 * R - 1) / (32 * R)) * uc * kLoneStep, 0, 0};
+                    LongUnit u{g, k, (int)pi, elapsed(21 * R / 2 + 40, (int64_t)((m + 32 * R - 1) / (32 * R)) * (uc + 31)), 0, 0, R};
                     for (int q : {pr.x, pr.y})
                         if (q >= 0) {
                             const int64_t x = chain_cost(qlens[q], uc);
@@ -670,7 +693,6 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
     emit(uitems, side_out);
     emit(citems, head_out);
     plan->R_main = R;
-    plan->R_side = R;
 }
 
 sw_status build_plan(sw_db* db, const std::vector<int>& qlens, Plan* p, const std::vector<int>* chunk = nullptr,
@@ -684,9 +706,11 @@ sw_status build_plan(sw_db* db, const std::vector<int>& qlens, Plan* p, const st
         plan_units_q2(db, qlens, p, mi, si, hi, pairs, chunk, nchunks);
     else
         plan_units(db, qlens, p, mi, si, &hi, chunk, nchunks);
-    p->n_head = (int32_t)hi.size();
+    p->n_chain = (int32_t)hi.size();
     p->n_main = (int32_t)mi.size();
-    p->n_side = (int32_t)si.size();
+    p->n_unchained = (int32_t)si.size();
+    p->n_small = 0;
+    for (const WgItem& it : mi) p->n_small += it.lgB >= kItemSmall;
     mi.insert(mi.begin(), hi.begin(), hi.end());
     mi.insert(mi.end(), si.begin(), si.end());
     p->h_items.swap(mi);
@@ -729,10 +753,10 @@ void clear_caches(sw_db* db) {
     db->plans.clear();
     db->batch_plan.release();
     db->batch_plan.h_items.clear();
-    db->batch_plan.n_head = db->batch_plan.n_main = db->batch_plan.n_side = 0;
+    db->batch_plan.n_chain = db->batch_plan.n_main = db->batch_plan.n_unchained = 0;
     db->multi_plan.release();
     db->multi_plan.h_items.clear();
-    db->multi_plan.n_head = db->multi_plan.n_main = db->multi_plan.n_side = 0;
+    db->multi_plan.n_chain = db->multi_plan.n_main = db->multi_plan.n_unchained = 0;
     db->batch_qlens.clear();
     db->graph.clear();
     db->last_eager = BatchKey();
@@ -768,6 +792,11 @@ sw_status ensure_geometry(sw_db* db) {
             db->wgR[R] = db->cus * std::min(std::max(b, bo), kMaxWgPerCu);
             db->wg16 = std::max(db->wg16, db->wgR[R]);
         }
+        int b12 = 0;
+        HIP_TRY(sweep_occupancy(kCellOff, 12, &b12));
+        if (b12 < 1) return fail(SW_E_HIP, "16-bit sweep (R=12) cannot be resident");
+        db->wgR[12] = db->cus * std::min(b12, kMaxWgPerCu);
+        db->wg16 = std::max(db->wg16, db->wgR[12]);
         for (int R : {8, 16}) {
             int b = 0, bo = 0;
             HIP_TRY(sweep_occupancy_q2(kCellI16, R, &b));
@@ -1098,10 +1127,12 @@ sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& 
     HIP_TRY(launch_profile(S.sm_q, db->alphabet, S.qd, S.nq, S.qoff, W.prof, ctr, kCounters, W.bits, W.L.bits_words,
                            S.max_mp, st, form.add));
     SweepArgs a = sweep_args(db, S, W, go, ge, d_scores);
+    // one launch: the chained pairs and then the bulk, or the unchained units and then the bulk
     const bool off = form.cell == kCellOff;
-    a.items = W.items + (off ? 0 : plan.n_head);
+    a.items = W.items + (off ? 0 : plan.n_chain);
     a.n_items_dev = nullptr;
-    a.n_items = plan.n_main + (off ? plan.n_head : 0);
+    a.n_items = plan.n_main + (off ? plan.n_chain : plan.n_unchained);
+    a.first_item = off || plan.n_unchained == 0 ? 0 : plan.n_main;
     a.counter = ctr + 0;
     set_rerun_args(db, a, W, ctr);
     a.unit_list = 0;
@@ -1110,33 +1141,17 @@ sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& 
     a.off_k = form.off_k;
     a.sm_shift = form.add;
     a.qpairs = plan.qpack ? W.qpairs : nullptr;
-    // on plain cells the side launch takes the first slots; the bulk launch fills the rest of the GPU
-    const int wg_main = plan.qpack ? db->wgQ[plan.R_main] : db->wgR[plan.R_main];
-    const int n_side = off ? 0 : plan.n_side;
-    const int grid_side = std::min(n_side, a.n_items > 0 ? std::max(1, wg_main / 8) : wg_main);
-    const int grid_main = std::max(1, std::min(wg_main - grid_side, std::max(a.n_items, 1)));
-    if (n_side > 0) {
-        SweepArgs b = a;
-        b.items = W.items + plan.n_head + plan.n_main;
-        b.n_items = n_side;
-        b.counter = ctr + 3;
-        b.slot_base = grid_main;
-        HIP_TRY(hipEventRecord(db->ev_fork, st));
-        HIP_TRY(hipStreamWaitEvent(db->side, db->ev_fork, 0));
-        if (plan.qpack)
-            HIP_TRY(launch_sweep_q2(form.cell, plan.R_side, b, grid_side, db->side));
-        else
-            HIP_TRY(launch_sweep(form.cell, plan.R_side, b, grid_side, db->side));
-        HIP_TRY(hipEventRecord(db->ev_join, db->side));
-    }
+    // (a bulk wholly at 4 rows per lane takes the kernel of 4, which is smaller; plain cells have no kernel of 12
+    // rows per lane: the units of such a plan run at 16)
+    const int R = plan.n_main > 0 && plan.n_small == plan.n_main ? kSmallRows : !off && plan.R_main == 12 ? 16 : plan.R_main;
+    const int grid = std::max(1, std::min(plan.qpack ? db->wgQ[R] : db->wgR[R], std::max(a.n_items, 1)));
     const int ev = time_sweep && db->timing ? record_timer_start(db, st) : -1;
     if (a.n_items > 0) {
         if (plan.qpack)
-            HIP_TRY(launch_sweep_q2(form.cell, plan.R_main, a, grid_main, st));
+            HIP_TRY(launch_sweep_q2(form.cell, R, a, grid, st));
         else
-            HIP_TRY(launch_sweep(form.cell, plan.R_main, a, grid_main, st));
+            HIP_TRY(launch_sweep(form.cell, R, a, grid, st));
     }
-    if (n_side > 0) HIP_TRY(hipStreamWaitEvent(st, db->ev_join, 0));
     if (ev >= 0) {
         HIP_TRY(hipEventRecord(db->ev_pool[ev].second, st));
         db->ev_used.push_back(ev);
@@ -1147,11 +1162,11 @@ sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& 
     if (k > 0)
         HIP_TRY(launch_topk_ws(d_scores, n, n, S.nq, k, top_s, top_i, topk_ws_bytes(n, S.nq, k) > 0 ? W.topk : nullptr,
                                st));
-    db->last_items = off ? plan.n_main : a.n_items;
-    db->last_rows = plan.R_main;
-    db->last_side_items = off ? plan.n_head : n_side;
-    db->last_side_rows = db->last_side_items == 0 ? 0 : off ? 4 : plan.R_side;
-    db->last_grid = grid_main + (n_side > 0 ? grid_side : 0);
+    db->last_items = plan.n_main - plan.n_small;
+    db->last_rows = R;
+    db->last_side_items = a.n_items - db->last_items;
+    db->last_side_rows = db->last_side_items > 0 ? kSmallRows : 0;
+    db->last_grid = grid;
     db->last_counters = ctr;
     return SW_OK;
 }
@@ -2057,7 +2072,8 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
     if (g_split < db->ngroups) {
         PlanLimits lim{16, db->slot_cap, (int64_t)db->wg_mode * kWaves};
         lim.side = true;
-        plan_units(db, std::vector<int>{qlen}, &db->mode_plan, mi, si, nullptr, nullptr, 1, &lim, g_split, -1);
+        plan_units(db, std::vector<int>{qlen}, &db->mode_plan, mi, si, nullptr, nullptr, 1, &lim, g_split, -1,
+                   &db->mode_side_rows);
     }
     // (4 rows per lane measured no faster for the 32-bit chain of a short query, and slower for longer ones)
     constexpr int R32 = 8;
@@ -2107,7 +2123,7 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
         b.n_items = (int32_t)n16s;
         b.counter = ctr + 3;
         b.slot_base = grid;
-        HIP_TRY(launch_sweep_mode16(mode16, db->mode_plan.R_side, b, grid_side, db->side));
+        HIP_TRY(launch_sweep_mode16(mode16, db->mode_side_rows, b, grid_side, db->side));
         HIP_TRY(hipEventRecord(db->ev_join, db->side));
     }
     if (!m32.empty()) {
@@ -2143,7 +2159,7 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
     db->last_items = (int)n16;
     db->last_rows = 16;
     db->last_side_items = (int)(n16s + m32.size());
-    db->last_side_rows = n16s ? db->mode_plan.R_side : m32.empty() ? 0 : R32;
+    db->last_side_rows = n16s ? db->mode_side_rows : m32.empty() ? 0 : R32;
     db->last_grid = grid + grid_side;
     db->last_counters = ctr;
     return SW_OK;

@@ -50,14 +50,14 @@ struct WgItem {
     int32_t g0;       // group of the first unit
     int32_t q;        // query index within the launch
     int16_t k0;       // sub-group index of the first unit within g0
-    int8_t lgB;       // log2 of lanes per pair (0..6), or one of the kinds below
+    int8_t lgB;       // log2 of lanes per pair (0..6), which kItemSmall may be added to, or kItemChain
     int8_t count;     // number of valid units (1..kWaves)
     int32_t gstep;    // distance between consecutive groups of the item
 };
 
-// Kinds of items that only launches on offset cells hold: up to kWaves pairs of a wave each at 4 rows per lane,
-// and one pair on the whole workgroup.
-constexpr int kItemSmall = 7, kItemChain = 8;
+// Items beside the units at the launch's rows per lane: units at 4 rows per lane (plain 16-bit local launches, not
+// query pairs), and one pair on the whole workgroup (offset cells).
+constexpr int kItemChain = 8, kItemSmall = 16, kSmallRows = 4;
 
 // Per-query descriptor.
 struct QDesc {
@@ -78,6 +78,7 @@ struct SweepArgs {
     const WgItem* items;
     const int32_t* n_items_dev;   // if non-null, the item count is read here (rerun launches)
     int32_t n_items;              // item count (or capacity when n_items_dev is used)
+    int32_t first_item;           // items are taken from here on, and from the first one on after the last
     int32_t* counter;             // work counter, zeroed before the launch
     const uint8_t* image;
     const GroupRec* groups;

@@ -907,6 +907,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
             ec.last = p == passes - 1;
             if constexpr (kOffset) {
                 if (lgB == 0) sweep_pass_off<R, false, PACKED>(io, ncols, B, b, lrow8, oc, So);
+                else if (R == kSmallRows && passes == 1) sweep_pass_off<R, true, PACKED, R != kSmallRows>(io, ncols, B, b, lrow8, oc, So);
                 else sweep_pass_off<R, true, PACKED>(io, ncols, B, b, lrow8, oc, So);
             } else if constexpr (kMode16) {
                 if (lgB == 0)
@@ -1005,8 +1006,12 @@ __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int 
     io.bnd = make_rsrc(slot, (uint32_t)(cols >> 2) * 32u);
     uint8_t* slice = lds + wave * (kWaveRows * kNRes);
     uint8_t* rings = lds + kChainWaves * (kWaveRows * kNRes);
-    const uint8_t* ring_in = rings + (wave > 0 ? wave - 1 : 0) * kChainRingBytes;
-    uint8_t* out_lane = lane == 63 ? rings + wave * kChainRingBytes : rings + kChainWaves * kChainRingBytes + lane * 8;
+    uint8_t* resq = rings + kChainWaves * kChainRingBytes + wave * kChainResBytes;
+    uint8_t* idle = rings + kChainWaves * (kChainRingBytes + kChainResBytes);
+    uint8_t* zeros = idle + kChainIdle;
+    if (threadIdx.x < 8) reinterpret_cast<uint32_t*>(zeros)[threadIdx.x] = 0;
+    uint8_t* ring_in = rings + wave * kChainRingBytes;
+    uint8_t* out_lane = lane == 63 && w + 1 < waves ? ring_in + kChainRingBytes : idle + lane * 8;
     const OffCtx oc{(uint32_t)a.ge * 0x10001u, (uint32_t)(a.go - a.ge) * 0x10001u, (uint32_t)a.go * 0x10001u, a.off_k};
     u2 S = {0, 0};
     __builtin_amdgcn_s_setprio(3);                  // its steps are the search's longest chain
@@ -1015,11 +1020,15 @@ __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int 
         const bool active = mine && row0 < Q.m;
         // a wave reads only its own slice; the barriers of the last pass's stages are behind it
         if (active) load_slice_off<R>(slice, a.prof + Q.prof_off, Q.mp, row0, 6, lane, 64);
-        io.rd_lane = (lane == 0 && p > 0) ? 0u : kNoAccess;
-        io.wr_lane = lane == 63 ? 0u : kNoAccess;
+        io.rd_lane = p > 0 ? 0u : kNoAccess;
+        io.wr_lane = (lane == 63 && w == waves - 1) ? 0u : kNoAccess;
         __syncthreads();
-        chain_pass<R>(io, ncols, w, waves, stages, active, lane, slice + lane * (kNRes * R), ring_in, out_lane,
-                      p + 1 < passes, oc, S);
+        if (p + 1 < passes)
+            chain_pass<R, true>(io, ncols, w, stages, active, lane, slice + lane * (kNRes * R), ring_in, out_lane, resq,
+                                zeros, oc, S);
+        else
+            chain_pass<R, false>(io, ncols, w, stages, active, lane, slice + lane * (kNRes * R), ring_in, out_lane, resq,
+                                zeros, oc, S);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");   // boundary stores visible to the next pass
         __syncthreads();
     }
@@ -1047,8 +1056,13 @@ __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int 
 // Recompute items past the list: blocks of kBitsBlock words of the flag bits.
 constexpr int kBitsBlock = 64;
 
+// Waves per SIMD the registers must allow: 3 at 12 or 16 rows per lane of 16-bit cells (168 VGPRs; without the bound
+// the allocator goes a few over and loses a third of the waves), 4 at fewer.
+template <class C, int R>
+constexpr int kMinWaves = std::is_same<C, CellI32>::value ? 1 : R >= 12 ? 3 : 4;
+
 template <class C, int R, int MODE = 0>
-__global__ __launch_bounds__(64 * kWaves) void k_sweep(SweepArgs a) {
+__global__ __launch_bounds__(64 * kWaves, (kMinWaves<C, R>)) void k_sweep(SweepArgs a) {
     // one shared slice of up to 64*R rows, or four per-wave slices of up to 16*R rows
     // (offset cells hold one byte a row, and need room for a chain item)
     constexpr bool kOffset = std::is_same<C, CellOff>::value;
@@ -1118,29 +1132,27 @@ __global__ __launch_bounds__(64 * kWaves) void k_sweep(SweepArgs a) {
                 continue;
             }
         }
-        const WgItem I = a.items[it];
+        const int at = it + a.first_item;
+        const WgItem I = a.items[at < a.n_items ? at : at - a.n_items];
         if constexpr (kOffset) {
             if (I.lgB == kItemChain) {
                 run_chain(a, I.g0, I.k0, I.q, reinterpret_cast<uint8_t*>(lds), wave, lane,
                           a.scratch + (int64_t)(a.slot_base + blockIdx.x) * kWaves * a.slot_words);
                 continue;
             }
-            if (R != kChainRows && I.lgB == kItemSmall) {
-                // long pairs of a short query: a wave each at fewer rows per lane
-                const int k = I.k0 + wave;
-                run_unit<C, kChainRows, false, MODE>(a, I.g0 + (k >> 6) * I.gstep, k & 63, 6, I.q, wave < I.count, true,
-                                                     lds, wave, lane, slot);
+        }
+        const int lgB = I.lgB & (kItemSmall - 1);
+        int k = I.k0 + wave;
+        const int g = I.g0 + (k >> lgB) * I.gstep;
+        k &= (1 << lgB) - 1;
+        const bool shared_slice = lgB > 4;              // more than 16 lanes per pair
+        if constexpr (MODE == 0 && !std::is_same<C, CellI32>::value && R != kSmallRows) {
+            if (I.lgB >= kItemSmall) {
+                run_unit<C, kSmallRows, false, MODE>(a, g, k, lgB, I.q, wave < I.count, shared_slice, lds, wave, lane, slot);
                 continue;
             }
         }
-        {
-            const int B = 1 << I.lgB;
-            int k = I.k0 + wave;
-            const int g = I.g0 + (k >> I.lgB) * I.gstep;
-            k &= B - 1;
-            const bool shared_slice = I.lgB > 4;        // more than 16 lanes per pair
-            run_unit<C, R, false, MODE>(a, g, k, I.lgB, I.q, wave < I.count, shared_slice, lds, wave, lane, slot);
-        }
+        run_unit<C, R, false, MODE>(a, g, k, lgB, I.q, wave < I.count, shared_slice, lds, wave, lane, slot);
     }
 }
 
@@ -1151,7 +1163,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_sweep(SweepArgs a) {
 // P = 64/B subjects of a group (B lanes each, anti-diagonal as above); a group
 // has 2B such units.
 template <class C, int R>
-__global__ __launch_bounds__(64 * kWaves) void k_sweep_q2(SweepArgs a) {
+__global__ __launch_bounds__(64 * kWaves, 3) void k_sweep_q2(SweepArgs a) {
     static_assert(kNRes * 64 * 8 * 2 < kChainLds && kChainLds <= kNRes * 64 * 16 * 2, "R = 8 takes a chain item's room");
     constexpr int kLdsBytes = kNRes * 64 * R * 2 > kChainLds ? kNRes * 64 * R * 2 : kChainLds;
     __shared__ __attribute__((aligned(16))) int16_t lds[kLdsBytes / 2];
@@ -1165,7 +1177,8 @@ __global__ __launch_bounds__(64 * kWaves) void k_sweep_q2(SweepArgs a) {
         const int it = __builtin_amdgcn_readfirstlane(s_item);
         __syncthreads();
         if (it >= a.n_items) break;
-        const WgItem I = a.items[it];
+        const int at = it + a.first_item;
+        const WgItem I = a.items[at < a.n_items ? at : at - a.n_items];
         if constexpr (std::is_same<C, CellOff>::value) {
             if (I.lgB == kItemChain) {              // one query of the pair; I.q is the query itself
                 run_chain(a, I.g0, I.k0, I.q, reinterpret_cast<uint8_t*>(lds), wave, lane,
@@ -1477,6 +1490,7 @@ static const void* sweep_kernel(int form, int R) {
     if (form == kCellOff)
         return R == 4    ? (const void*)k_sweep<CellOff, 4>
                : R == 8  ? (const void*)k_sweep<CellOff, 8>
+               : R == 12 ? (const void*)k_sweep<CellOff, 12>
                : R == 16 ? (const void*)k_sweep<CellOff, 16> : nullptr;
     if (form == kCellI16)
         return R == 4    ? (const void*)k_sweep<CellI16, 4>

@@ -146,6 +146,14 @@ struct OffCtx {
     SWO_BLK(SWO_DB0, SWO_DB1, SWO_DA, 2, 3, SWO_P3, SWO_P4, SWO_PP4, SWO_S1, 1, 0, 1, SWO_E(1, SWO_P2))       \
     SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 4, 5, SWO_P5, SWO_P6, SWO_PP6, SWO_S2, 1, 2, 3, SWO_E(3, SWO_P4))       \
     SWO_LAST(SWO_DB0, SWO_DB1, 6, 7, SWO_P7, SWO_P8, SWO_S3, SWO_E(5, SWO_P6))
+#define SWO_ROWS12(TOP)                                                                                       \
+    SWO_PRE SWO_SA(SWO_SS0) SWO_SA(SWO_SS1) SWO_HD(SWO_DA, SWO_PP0) TOP SWO_SA(SWO_SS2)                       \
+    SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 0, 1, SWO_P1, SWO_P2, SWO_PP2, SWO_S0, 0, 2, 3, "")                     \
+    SWO_BLK(SWO_DB0, SWO_DB1, SWO_DA, 2, 3, SWO_P3, SWO_P4, SWO_PP4, SWO_S1, 1, 0, 1, SWO_E(1, SWO_P2))       \
+    SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 4, 5, SWO_P5, SWO_P6, SWO_PP6, SWO_S2, 1, 2, 3, SWO_E(3, SWO_P4))       \
+    SWO_BLK(SWO_DB0, SWO_DB1, SWO_DA, 6, 7, SWO_P7, SWO_P8, SWO_PP8, SWO_S3, 2, 0, 1, SWO_E(5, SWO_P6))       \
+    SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 8, 9, SWO_P9, SWO_P10, SWO_PP10, SWO_S4, 2, 2, 3, SWO_E(7, SWO_P8))     \
+    SWO_LAST(SWO_DB0, SWO_DB1, 10, 11, SWO_P11, SWO_P12, SWO_S5, SWO_E(9, SWO_P10))
 #define SWO_ROWS16(TOP)                                                                                       \
     SWO_PRE SWO_SA(SWO_SS0) SWO_SA(SWO_SS1) SWO_HD(SWO_DA, SWO_PP0) TOP SWO_SA(SWO_SS2) SWO_SA(SWO_SS3)       \
     SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 0, 1, SWO_P1, SWO_P2, SWO_PP2, SWO_S0, 0, 2, 3, "")                     \
@@ -177,17 +185,20 @@ struct OffCtx {
 #define SWO_OE(i) [e##i] "+v"(E[i])
 #define SWO_E4 SWO_OE(0), SWO_OE(1), SWO_OE(2), SWO_OE(3)
 #define SWO_E8 SWO_E4, SWO_OE(4), SWO_OE(5), SWO_OE(6), SWO_OE(7)
+#define SWO_E12 SWO_E8, SWO_OE(8), SWO_OE(9), SWO_OE(10), SWO_OE(11)
 #define SWO_E16 SWO_E8, SWO_OE(8), SWO_OE(9), SWO_OE(10), SWO_OE(11), SWO_OE(12), SWO_OE(13), SWO_OE(14), SWO_OE(15)
 #define SWO_OP4 "+{v64}"(P[0]), "+{v65}"(P[1]), "+{v66}"(P[2]), "+{v67}"(P[3]), "+{v68}"(P[4])
 #define SWO_OP8 SWO_OP4, "+{v69}"(P[5]), "+{v70}"(P[6]), "+{v71}"(P[7]), "+{v72}"(P[8])
-#define SWO_OP16 SWO_OP8, "+{v73}"(P[9]), "+{v74}"(P[10]), "+{v75}"(P[11]), "+{v76}"(P[12]), "+{v77}"(P[13]), \
-                 "+{v78}"(P[14]), "+{v79}"(P[15]), "+{v80}"(P[16])
+#define SWO_OP12 SWO_OP8, "+{v73}"(P[9]), "+{v74}"(P[10]), "+{v75}"(P[11]), "+{v76}"(P[12])
+#define SWO_OP16 SWO_OP12, "+{v77}"(P[13]), "+{v78}"(P[14]), "+{v79}"(P[15]), "+{v80}"(P[16])
 #define SWO_OS4 "+{v82}"(S[0]), "+{v83}"(S[1])
 #define SWO_OS8 SWO_OS4, "+{v84}"(S[2]), "+{v85}"(S[3])
+#define SWO_OS12 SWO_OS8, "+{v86}"(S[4]), "+{v87}"(S[5])
 #define SWO_OS16 SWO_OS8, "+{v86}"(S[4]), "+{v87}"(S[5]), "+{v88}"(S[6]), "+{v89}"(S[7])
 #define SWO_K(i) [k##i] "s"(k[i])
 #define SWO_K4 SWO_K(0), SWO_K(1), SWO_K(2), SWO_K(3)
 #define SWO_K8 SWO_K4, SWO_K(4), SWO_K(5), SWO_K(6), SWO_K(7)
+#define SWO_K12 SWO_K8, SWO_K(8), SWO_K(9), SWO_K(10), SWO_K(11)
 #define SWO_K16 SWO_K8, SWO_K(8), SWO_K(9), SWO_K(10), SWO_K(11), SWO_K(12), SWO_K(13), SWO_K(14), SWO_K(15)
 #define SWO_ABI(i) [a##i] "v"(w[i]), [b##i] "v"(w[R / 4 + i])
 #define SWO_WI(i) [w##i] "v"(w64[i])
@@ -209,6 +220,13 @@ __device__ __forceinline__ void rows_off_pair(uint32_t* P, uint32_t* E, uint32_t
         else
             asm(SWO_ROWS16(SWO_TOP_ALONE) : SWO_E16, [f] "+v"(F), SWO_OP16, SWO_OS16
                 : SWO_IN, SWO_INQ, SWO_K16, SWO_ABI(0), SWO_ABI(1), SWO_ABI(2), SWO_ABI(3) : SWO_CLOB);
+    } else if constexpr (R == 12) {
+        if constexpr (COOP)
+            asm(SWO_ROWS12(SWO_TOP_COOP(SWO_P12)) : SWO_E12, [f] "+v"(F), SWO_OP12, SWO_OS12
+                : SWO_IN, SWO_INQ, SWO_K12, SWO_ABI(0), SWO_ABI(1), SWO_ABI(2) : SWO_CLOB);
+        else
+            asm(SWO_ROWS12(SWO_TOP_ALONE) : SWO_E12, [f] "+v"(F), SWO_OP12, SWO_OS12
+                : SWO_IN, SWO_INQ, SWO_K12, SWO_ABI(0), SWO_ABI(1), SWO_ABI(2) : SWO_CLOB);
     } else if constexpr (R == 8) {
         if constexpr (COOP)
             asm(SWO_ROWS8(SWO_TOP_COOP(SWO_P8)) : SWO_E8, [f] "+v"(F), SWO_OP8, SWO_OS8
@@ -217,7 +235,7 @@ __device__ __forceinline__ void rows_off_pair(uint32_t* P, uint32_t* E, uint32_t
             asm(SWO_ROWS8(SWO_TOP_ALONE) : SWO_E8, [f] "+v"(F), SWO_OP8, SWO_OS8
                 : SWO_IN, SWO_INQ, SWO_K8, SWO_ABI(0), SWO_ABI(1) : SWO_CLOB);
     } else {
-        static_assert(R == 4, "rows per lane must be 4, 8 or 16");
+        static_assert(R == 4, "rows per lane must be 4, 8, 12 or 16");
         if constexpr (COOP)
             asm(SWO_ROWS4(SWO_TOP_COOP(SWO_P4)) : SWO_E4, [f] "+v"(F), SWO_OP4, SWO_OS4
                 : SWO_IN, SWO_INQ, SWO_K4, SWO_ABI(0) : SWO_CLOB);
@@ -275,6 +293,10 @@ __device__ __forceinline__ void fetch_off(const uint8_t* lrow, typename Res<PACK
             const uint4 x = *reinterpret_cast<const uint4*>(qa), y = *reinterpret_cast<const uint4*>(qb);
             out[0] = x.x; out[1] = x.y; out[2] = x.z; out[3] = x.w;
             out[4] = y.x; out[5] = y.y; out[6] = y.z; out[7] = y.w;
+        } else if constexpr (R == 12) {
+            const uint32_t *x = reinterpret_cast<const uint32_t*>(qa), *y = reinterpret_cast<const uint32_t*>(qb);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) { out[i] = x[i]; out[3 + i] = y[i]; }
         } else if constexpr (R == 8) {
             const uint2 x = *reinterpret_cast<const uint2*>(qa), y = *reinterpret_cast<const uint2*>(qb);
             out[0] = x.x; out[1] = x.y; out[2] = y.x; out[3] = y.y;
@@ -285,11 +307,21 @@ __device__ __forceinline__ void fetch_off(const uint8_t* lrow, typename Res<PACK
     }
 }
 
+__device__ __forceinline__ uint64_t pair64(uint32_t lo, uint32_t hi) { return ((uint64_t)hi << 32) | lo; }
+// Four 16-bit sums in one instruction: no half of a wraps; the uniform x counts for both words.  (From C++ the
+// compiler makes a 64-bit multiply-add of it.)
+__device__ __forceinline__ uint64_t add_pairs(uint64_t a, uint32_t x) {
+    uint64_t r;
+    asm("v_lshl_add_u64 %0, %1, 0, %2" : "=v"(r) : "v"(a), "s"(pair64(x, x)));
+    return r;
+}
 __device__ __forceinline__ uint32_t sgpr(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // One pass on offset cells: as sweep_pass, with the boundary words G and F free of offsets (the zero border
 // of a first pass reads as zeros).  S receives the true scores of the lane's two matrices.
-template <int R, bool COOP, bool PACKED>
+// IO = false: the query's only pass, with no boundary row to read or write (of a lone wave's step at 4 rows per lane
+// that is one instruction in six).
+template <int R, bool COOP, bool PACKED, bool IO = true>
 __device__ __forceinline__ void sweep_pass_off(const PassIO& io, int ncols, int B, int b, const uint8_t* lrow,
                                                const OffCtx& o, u2& S) {
     using RV = typename Res<PACKED>::V;
@@ -315,9 +347,10 @@ __device__ __forceinline__ void sweep_pass_off(const PassIO& io, int ncols, int 
     auto res_at = [&](int c) { return Res<PACKED>::load(io.img, io.img_lane + (uint32_t)(c * kChunkBytes)); };
     auto resid = [&](RV lo, RV hi) { return COOP ? Res<PACKED>::align(hi, lo, csh) : lo; };
     RV c0 = res_at(coff), c1 = res_at(coff + 1), c2 = res_at(coff + 2);
-    uint4 bw[2];
+    uint4 bw[2] = {};
+    if constexpr (IO)
 #pragma unroll
-    for (int i = 0; i < 2; ++i) bw[i] = ld128(io.bnd, io.rd_lane + 16u * i);
+        for (int i = 0; i < 2; ++i) bw[i] = ld128(io.bnd, io.rd_lane + 16u * i);
     RV rr = resid(c0, c1);
     // subject pairs read their substitution bytes two steps ahead, query pairs (four times the words) one
     constexpr bool kLead2 = !PACKED;
@@ -326,23 +359,16 @@ __device__ __forceinline__ void sweep_pass_off(const PassIO& io, int ncols, int 
     if constexpr (kLead2) fetch_off<R, PACKED>(lrow, rr, 1, nxt);
     for (int c = 0; c < nloop; ++c) {
         const RV c3 = res_at(coff + c + 3);
-        uint4 nw[2];
+        uint4 nw[2] = {};
+        if constexpr (IO)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) nw[i] = ld128(io.bnd, io.rd_lane + (uint32_t)(c + 1) * io.cstride + 16u * i);
+            for (int i = 0; i < 2; ++i) nw[i] = ld128(io.bnd, io.rd_lane + (uint32_t)(c + 1) * io.cstride + 16u * i);
         const RV rn = resid(c1, c2);
         const uint32_t get = ge * (uint32_t)tau;           // Ge tau of the chunk's first step
         uint32_t kk[R + 3];                                // floors of the next step, row r at step u: kk[r + u]
 #pragma unroll
         for (int i = 0; i < R + 3; ++i) kk[i] = go + get + ge * (uint32_t)(i + 1);
-        // boundary words of the four columns at their steps' offsets
-        uint32_t bg[4], bf[4];
         const uint32_t b0 = get + (COOP ? cr : 0u);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint4 v = bw[u >> 1];
-            bg[u] = ((u & 1) ? v.z : v.x) + (b0 + ge * u);
-            bf[u] = ((u & 1) ? v.w : v.y) + (b0 + ge * u);
-        }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             uint32_t nx2[NW];
@@ -353,12 +379,22 @@ __device__ __forceinline__ void sweep_pass_off(const PassIO& io, int ncols, int 
                 if (u < 3) fetch_off<R, PACKED>(lrow, rr, u + 1, nxt);
                 else fetch_off<R, PACKED>(lrow, rn, 0, nxt);
             }
-            if constexpr (PACKED) rows_off_packed<R, COOP>(P, E, Sx, F, bg[u], bf[u], cur, kk + u, goe, cr, ge64, first);
-            else rows_off_pair<R, COOP>(P, E, Sx, F, bg[u], bf[u], cur, kk + u, goe, cr, ge64, first);
+            // the column's boundary words at this step's offset (no half leaves 16 bits)
+            const uint4 v = bw[u >> 1];
+            uint32_t bg = b0 + ge * u, bf = bg;
+            if constexpr (IO) {
+                const uint64_t top = add_pairs((u & 1) ? pair64(v.z, v.w) : pair64(v.x, v.y), b0 + ge * u);
+                bg = (uint32_t)top;
+                bf = (uint32_t)(top >> 32);
+            }
+            if constexpr (PACKED) rows_off_packed<R, COOP>(P, E, Sx, F, bg, bf, cur, kk + u, goe, cr, ge64, first);
+            else rows_off_pair<R, COOP>(P, E, Sx, F, bg, bf, cur, kk + u, goe, cr, ge64, first);
             // the last lane of a lane group hands column j = t - (B - 1) to the next pass, without offset
-            const int j = 4 * c + u - (B - 1);
-            const uint32_t off = get + ge * (uint32_t)(R + u);
-            st64(io.bnd, io.wr_lane + (uint32_t)((j >> 2) * (int)io.cstride + (j & 3) * 8), P[R] - off, F - off);
+            if constexpr (IO) {
+                const int j = 4 * c + u - (B - 1);
+                const uint32_t off = get + ge * (uint32_t)(R + u);
+                st64(io.bnd, io.wr_lane + (uint32_t)((j >> 2) * (int)io.cstride + (j & 3) * 8), P[R] - off, F - off);
+            }
 #pragma unroll
             for (int r = 0; r < NW; ++r) {
                 cur[r] = nxt[r];
@@ -465,6 +501,10 @@ __device__ __forceinline__ void load_slice_off_q2(uint32_t* dst, const int16_t* 
 // Every wave of a workgroup runs the same number of stages, and so of barriers,
 // computed from the item before the first.
 //
+// A step of a lone wave takes less time than a load from memory is on its way for
+// four of them, so global memory is read 64 chunks of residues (and 64 boundary
+// columns) at a time, one of each lane, half a ring ahead, and passed on in LDS.
+//
 // Bound by the latency of a wave's step (about 60 instructions at 4 rows per
 // lane, the fewest; more rows would need more LDS than the bulk units beside
 // it leave).  The items run in the bulk launch itself, ahead of its units: a
@@ -479,15 +519,21 @@ constexpr int kChainRing = 256;              // columns of a ring
 static_assert(kChainLag - 63 > kChainStage + 2 * kChunkCols, "a column is read after the barrier that follows its write");
 static_assert(kChainLag % kChainStage == 0 && kChainRing > 2 * kChainLag, "ring and stages");
 constexpr int kChainRingBytes = kChainRing * 8;
-constexpr int kChainIdle = kChainRingBytes + 64 * 8;       // where the 63 lanes that hand on nothing write
-// LDS of a workgroup: the waves' slices, their rings, the idle lanes' place
-constexpr int kChainLds = kChainWaves * (64 * kNRes * kChainRows + kChainRingBytes) + kChainIdle;
+constexpr int kChainResBytes = 128 * 8;                    // residues of 128 chunks
+constexpr int kChainIdle = kChainRingBytes + 64 * 8;       // where lanes that hand on nothing write
+// LDS of a workgroup: the waves' slices, the ring that feeds each wave, their residues, the idle lanes' place, zeros
+constexpr int kChainLds = kChainWaves * (64 * kNRes * kChainRows + kChainRingBytes + kChainResBytes) + kChainIdle + 32;
 
-// Wave w (of `waves` on one window) for all its chunks of one pass; `stages` barriers pass whatever it does.
-template <int R>
-__device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, int waves, int stages, bool active, int b,
-                                           const uint8_t* lrow, const uint8_t* ring_in, uint8_t* out_lane, bool more,
-                                           const OffCtx& o, u2& S) {
+// The barrier between stages orders the rings in LDS only: what is on its way from or to global memory (residues
+// and boundary words of later chunks) stays in flight, which a workgroup fence would wait for.
+__device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// Wave w (of several on one window) for all its chunks of one pass; `stages` barriers pass whatever it does.
+// STORE: the last wave's bottom row goes to the next pass through global memory.
+template <int R, bool STORE>
+__device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, int stages, bool active, int b,
+                                           const uint8_t* lrow, uint8_t* ring_in, uint8_t* out_lane, uint8_t* resq,
+                                           const uint8_t* zeros, const OffCtx& o, u2& S) {
     using RV = uint2;
     constexpr int NW = R / 2;
     const int nloop = (ncols + 63 + 3) >> 2;
@@ -506,21 +552,26 @@ __device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, i
     uint32_t F = ge * R;
     int tau = 1;
     const int coff = (-b) >> 2, csh = (-b) & 3;
-    auto res_at = [&](int c) { return Res<false>::load(io.img, io.img_lane + (uint32_t)(c * kChunkBytes)); };
-    // the boundary words of chunk c: the wave above, the pass above, or the zero border
+    // chunk b + 64 x of the residues, column b + 64 x of the boundary row (wave 0; zeros in the first pass)
+    auto res_block = [&](int x) { return ld64(io.img, io.img_lane + (uint32_t)((64 * x + b) * kChunkBytes)); };
+    // a residue byte becomes its slot's offset in the slice (at most 24 x 4)
+    static_assert(R == 4, "residue x R fits a byte");
+    auto stage_res = [&](int x, RV v) { *reinterpret_cast<RV*>(resq + ((64 * x + b) & 127) * 8) = RV{v.x * R, v.y * R}; };
+    auto bnd_block = [&](int x) { return ld64(io.bnd, io.rd_lane + (uint32_t)(64 * x + b) * 8u); };
+    auto res_at = [&](int c) { return *reinterpret_cast<const RV*>(resq + ((c + coff) & 127) * 8); };
+    // the boundary words of chunk c
+    // (past the subject the ring holds old columns: zeros instead)
     auto bound = [&](int c, uint4* v) {
-        if (w > 0) {
-            const uint4* q = reinterpret_cast<const uint4*>(ring_in + ((4 * c) & (kChainRing - 1)) * 8);
-            const uint4 x = q[0], y = q[1];
-            const uint32_t in = 4 * c < ncols ? ~0u : 0u;       // past the subject the ring holds old columns
-            v[0] = make_uint4(x.x & in, x.y & in, x.z & in, x.w & in);
-            v[1] = make_uint4(y.x & in, y.y & in, y.z & in, y.w & in);
-        } else {
-            v[0] = ld128(io.bnd, io.rd_lane + (uint32_t)c * io.cstride);
-            v[1] = ld128(io.bnd, io.rd_lane + (uint32_t)c * io.cstride + 16u);
-        }
+        const uint4* q = reinterpret_cast<const uint4*>(4 * c < ncols ? ring_in + ((4 * c) & (kChainRing - 1)) * 8 : zeros);
+        v[0] = q[0];
+        v[1] = q[1];
     };
-    RV c0 = {}, c1 = {}, c2 = {}, rr = {};
+    // substitution bytes of column u of a chunk
+    auto bytes = [&](RV v, int u, uint32_t* out) {
+        out[0] = *reinterpret_cast<const uint32_t*>(lrow + ((v.x >> (8 * u)) & 0xff));
+        out[1] = *reinterpret_cast<const uint32_t*>(lrow + ((v.y >> (8 * u)) & 0xff));
+    };
+    RV c0 = {}, c1 = {}, c2 = {}, rr = {}, res_next = {}, bnd_next = {};
     uint4 bw[2] = {};
     uint32_t cur[NW], nxt[NW];
     for (int i = 0; i < NW; ++i) cur[i] = nxt[i] = 0;
@@ -528,17 +579,37 @@ __device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, i
         const int ls = s - first_stage;
         if (active && ls >= 0 && ls * (kChainStage / 4) < nloop) {
             if (ls == 0) {
-                c0 = res_at(coff);
-                c1 = res_at(coff + 1);
-                c2 = res_at(coff + 2);
+                const RV r0 = res_block(0);
+                res_next = res_block(1);
+                stage_res(1, RV{0, 0});                          // columns before the first
+                stage_res(0, r0);
+                if (w == 0) {
+                    const RV b0 = bnd_block(0);
+                    bnd_next = bnd_block(1);
+                    *reinterpret_cast<RV*>(ring_in + b * 8) = b0;
+                }
+                c0 = res_at(0);
+                c1 = res_at(1);
+                c2 = res_at(2);
                 bound(0, bw);
                 rr = Res<false>::align(c1, c0, csh);
-                fetch_off<R, false>(lrow, rr, 0, cur);
-                fetch_off<R, false>(lrow, rr, 1, nxt);
+                bytes(rr, 0, cur);
+                bytes(rr, 1, nxt);
             }
             const int c_end = min(nloop, (ls + 1) * (kChainStage / 4));
             for (int c = ls * (kChainStage / 4); c < c_end; ++c) {
-                const RV c3 = res_at(coff + c + 3);
+                // half way through a block its successor goes to LDS and the next one is asked for
+                if ((c & 63) == 32) {
+                    const int x = (c >> 6) + 1;
+                    stage_res(x, res_next);
+                    res_next = res_block(x + 1);
+                }
+                if (w == 0 && (c & 15) == 8) {
+                    const int x = (c >> 4) + 1;
+                    *reinterpret_cast<RV*>(ring_in + ((64 * x + b) & (kChainRing - 1)) * 8) = bnd_next;
+                    bnd_next = bnd_block(x + 1);
+                }
+                const RV c3 = res_at(c + 3);
                 uint4 nw[2];
                 bound(c + 1, nw);
                 const RV rn = Res<false>::align(c2, c1, csh);
@@ -546,26 +617,23 @@ __device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, i
                 uint32_t kk[R + 3];
 #pragma unroll
                 for (int i = 0; i < R + 3; ++i) kk[i] = go + get + ge * (uint32_t)(i + 1);
-                uint32_t bg[4], bf[4];
                 const uint32_t b0 = get + cr;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    const uint4 v = bw[u >> 1];
-                    bg[u] = ((u & 1) ? v.z : v.x) + (b0 + ge * u);
-                    bf[u] = ((u & 1) ? v.w : v.y) + (b0 + ge * u);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
                     uint32_t nx2[NW];
-                    if (u < 2) fetch_off<R, false>(lrow, rr, u + 2, nx2);
-                    else fetch_off<R, false>(lrow, rn, u - 2, nx2);
-                    rows_off_pair<R, true>(P, E, Sx, F, bg[u], bf[u], cur, kk + u, goe, cr, ge64, first);
+                    if (u < 2) bytes(rr, u + 2, nx2);
+                    else bytes(rn, u - 2, nx2);
+                    // G and F of the row above, raised to this step's offset (no half leaves 16 bits)
+                    const uint4 v = bw[u >> 1];
+                    const uint64_t top = add_pairs((u & 1) ? pair64(v.z, v.w) : pair64(v.x, v.y), b0 + ge * u);
+                    const uint32_t bg = (uint32_t)top, bf = (uint32_t)(top >> 32);
+                    rows_off_pair<R, true>(P, E, Sx, F, bg, bf, cur, kk + u, goe, cr, ge64, first);
                     const int j = 4 * c + u - 63;
                     const uint32_t off = get + ge * (uint32_t)(R + u);
-                    if (w + 1 < waves)
-                        *reinterpret_cast<uint2*>(out_lane + (j & (kChainRing - 1)) * 8) = make_uint2(P[R] - off, F - off);
-                    else if (more)
-                        st64(io.bnd, io.wr_lane + (uint32_t)((j >> 2) * (int)io.cstride + (j & 3) * 8), P[R] - off, F - off);
+                    const uint2 down = make_uint2(P[R] - off, F - off);
+                    *reinterpret_cast<uint2*>(out_lane + (j & (kChainRing - 1)) * 8) = down;
+                    if constexpr (STORE)
+                        st64(io.bnd, io.wr_lane + (uint32_t)((j >> 2) * (int)io.cstride + (j & 3) * 8), down.x, down.y);
 #pragma unroll
                     for (int r = 0; r < NW; ++r) { cur[r] = nxt[r]; nxt[r] = nx2[r]; }
                 }
@@ -589,7 +657,7 @@ __device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, i
                 bw[1] = nw[1];
             }
         }
-        __syncthreads();
+        stage_barrier();
     }
     if (!active) return;
     const uint32_t last = ge * (uint32_t)(tau - 1);

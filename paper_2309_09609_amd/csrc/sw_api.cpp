@@ -35,6 +35,7 @@ hipError_t launch_sweep_q2(int form, int R, const SweepArgs& a, int grid, hipStr
 hipError_t sweep_occupancy_q2(int form, int R, int* blocks_per_cu);
 hipError_t launch_sweep_mode(int mode, int R, const SweepArgs& a, int grid, hipStream_t st);
 hipError_t launch_sweep_mode16(int mode, int R, const SweepArgs& a, int grid, hipStream_t st);
+hipError_t launch_sweep_mode_off(int mode, int R, const SweepArgs& a, int grid, hipStream_t st);
 hipError_t sweep_occupancy_mode16(int mode, int R, int* blocks_per_cu);
 hipError_t launch_align_fill(const AlignPair* pairs, int npairs, int W, const int8_t* subst, int A, int go, int ge,
                              uint8_t* dirs, int32_t* bnd, int32_t* best, int lds_max, hipStream_t st);
@@ -48,7 +49,7 @@ int64_t align_dir_bytes(int m, int64_t n);
 int64_t align_bnd_words(int64_t n);
 hipError_t launch_profile(const int8_t* stage, int A, const QDesc* qd, int nq, const int64_t* qoff, int16_t* prof,
                           int32_t* counters, int ncounters, uint32_t* bits, int64_t nbits_words, int max_mp,
-                          hipStream_t st, int add = 0);
+                          hipStream_t st, int add, int pad);
 hipError_t launch_interleave(const int8_t* res, const int64_t* soff, const int32_t* slen, int64_t n, int A,
                              const GroupRec* groups, const int64_t* gdw, int ngroups, uint32_t* image,
                              int64_t total_dw, int32_t* err, hipStream_t st);
@@ -151,15 +152,18 @@ struct Staged {
     int max_mp = 0;
 };
 
-// The 16-bit cells of one local search: their form and what the kernels are told about it.
+// The 16-bit cells of one search: their form and what the kernels are told about it.
 struct CellForm {
     int cell = kCellI16;          // kCellI16 or kCellOff
-    int32_t bias = 0;             // plain cells: minus the lowest substitution score, at least 0
+    int32_t mode = SW_LOCAL;      // end-to-end modes: offset cells here, the others through their own launches
+    int32_t bias = 0;             // plain cells: minus the lowest substitution score, at least 0; end-to-end modes: what
+                                  // every value carries
+    int32_t pad = kPadScore;      // what the profile holds for padding
     int32_t off_k = 0;            // offset cells: steps between renormalisations
     int32_t add = 0;              // offset cells: the profile holds SM + add
     int32_t sat = kSat16;         // scores (as the cells hold them) from here on are recomputed
     bool operator==(const CellForm& o) const {
-        return cell == o.cell && bias == o.bias && off_k == o.off_k && add == o.add && sat == o.sat;
+        return cell == o.cell && mode == o.mode && bias == o.bias && pad == o.pad && off_k == o.off_k && add == o.add && sat == o.sat;
     }
 };
 
@@ -267,7 +271,7 @@ struct sw_db {
     // reuses a buffer only once the copy of the call kStageRing before it has run
     HostPinned hstage[kStageRing];
     int hstage_next = 0;
-    std::map<int, Plan> plans;        // plain searches: query length -> plan
+    std::map<int, Plan> plans;        // query length -> plan of a local or semi-global search, minus it -> global
     Plan batch_plan, multi_plan;
     std::vector<int> batch_qlens;
     GraphEntry graph;                 // batched form: last captured shape
@@ -358,12 +362,13 @@ int64_t lone_cost(int m, int ncols, int lgB, int R) {
 }
 
 // The same for one pair on a workgroup (a chain item): its four waves at 4 rows per lane run side by side, 96
-// steps apart, or on windows of the subject (whose overlap depends on the query; 4 m is typical).
-int64_t chain_cost(int m, int ncols) {
+// steps apart, or on windows of the subject (whose overlap depends on the query; 4 m is typical), which global scores
+// cannot be cut into.
+int64_t chain_cost(int m, int ncols, bool cut) {
     const int64_t passes = (m + 1023) / 1024;
     const int waves = passes > 1 ? 4 : (m + 255) / 256;
     int64_t cols = ncols;
-    for (int windows = 4 / waves; windows > 1; --windows)
+    for (int windows = cut ? 4 / waves : 1; windows > 1; --windows)
         if (4 * m + ncols / windows <= ncols - ncols / 4) { cols = ncols / windows + 4 * m; break; }
     return elapsed(25 * 4 / 2 + 55, passes * (cols + 100 * waves));
 }
@@ -416,12 +421,12 @@ size_t chain_cut(const sw_db* db, const std::vector<LongUnit>& units, double bul
 struct PlanLimits { int R; int64_t slot_cap; int64_t nwaves; bool side = false; };
 
 // Groups [g_lo, g_hi) only (g_hi < 0: to the end).
-// head_out takes the chained pairs and side_out the same as units of one wave; head_out is null for the end-to-end
-// modes, whose long pairs go to side_out alone.
+// head_out takes the chained pairs and side_out the same as units of one wave; head_out is null for end-to-end modes
+// on plain cells, whose long pairs go to side_out alone.  whole: a subject cannot be cut into windows (global scores).
 void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std::vector<WgItem>& main_out,
                 std::vector<WgItem>& side_out, std::vector<WgItem>* head_out, const std::vector<int>* chunk = nullptr,
                 int nchunks = 1, const PlanLimits* lim = nullptr, int g_lo = 0, int g_hi = -1,
-                int* side_rows_out = nullptr) {
+                int* side_rows_out = nullptr, bool whole = false) {
     if (g_hi < 0) g_hi = db->ngroups;
     const int64_t slot_cap = lim ? lim->slot_cap : db->slot_cap;
     const bool force_R = lim ? true : db->force_R != 0;
@@ -508,7 +513,7 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
                     const int uc = db->pcols[(size_t)g * kGroupPairs + (k << (6 - lgB))];
                     const int64_t c = unit_cost(m, uc, lgB, R);
                     if (lgB == 6 && db->force_lgB < 0 && (double)c > cap) {
-                        const int64_t cc = head_out ? chain_cost(m, uc) : 0;
+                        const int64_t cc = head_out ? chain_cost(m, uc, !whole) : 0;
                         longs.push_back({g, k, (int)qi, lone_cost(m, uc, 6, head_out ? R : r_long), cc, cc, R});
                     } else {
                         (R == R_main ? bulk : small).add(g, k, R == R_main ? lgB : lgB + kItemSmall, c);
@@ -648,7 +653,7 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
                     LongUnit u{g, k, (int)pi, elapsed(21 * R / 2 + 40, (int64_t)((m + 32 * R - 1) / (32 * R)) * (uc + 31)), 0, 0, R};
                     for (int q : {pr.x, pr.y})
                         if (q >= 0) {
-                            const int64_t x = chain_cost(qlens[q], uc);
+                            const int64_t x = chain_cost(qlens[q], uc, true);
                             u.chain = std::max(u.chain, x);
                             u.chain_sum += x;
                         }
@@ -683,7 +688,7 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
         for (int q : {pairs[u.q].x, pairs[u.q].y})
             if (q >= 0)
                 citems.push_back({WgItem{u.g, q, (int16_t)u.k, kItemChain, 1, nchunks},
-                                  chain_cost(qlens[q], db->pcols[(size_t)u.g * kGroupPairs + u.k])});
+                                  chain_cost(qlens[q], db->pcols[(size_t)u.g * kGroupPairs + u.k], true)});
     }
     auto emit = [](std::vector<Tmp>& v, std::vector<WgItem>& to) {
         std::stable_sort(v.begin(), v.end(), [](const Tmp& a, const Tmp& b) { return a.cost > b.cost; });
@@ -696,7 +701,7 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
 }
 
 sw_status build_plan(sw_db* db, const std::vector<int>& qlens, Plan* p, const std::vector<int>* chunk = nullptr,
-                     int nchunks = 1) {
+                     int nchunks = 1, bool whole = false) {
     std::vector<WgItem> mi, si, hi;
     std::vector<int2> pairs;
     int nonempty = 0;
@@ -705,7 +710,7 @@ sw_status build_plan(sw_db* db, const std::vector<int>& qlens, Plan* p, const st
     if (p->qpack)
         plan_units_q2(db, qlens, p, mi, si, hi, pairs, chunk, nchunks);
     else
-        plan_units(db, qlens, p, mi, si, &hi, chunk, nchunks);
+        plan_units(db, qlens, p, mi, si, &hi, chunk, nchunks, nullptr, 0, -1, nullptr, whole);
     p->n_chain = (int32_t)hi.size();
     p->n_main = (int32_t)mi.size();
     p->n_unchained = (int32_t)si.size();
@@ -734,16 +739,17 @@ sw_status upload_plan(sw_db* db, Plan* p) {
     return SW_OK;
 }
 
-sw_status get_plan(sw_db* db, int m, Plan** out) {
-    auto it = db->plans.find(m);
+sw_status get_plan(sw_db* db, int m, Plan** out, bool whole = false) {
+    const int key = whole ? -m : m;
+    auto it = db->plans.find(key);
     if (it != db->plans.end()) { *out = &it->second; return SW_OK; }
     if (db->plans.size() >= 64) {
         for (auto& kv : db->plans) kv.second.release();
         db->plans.clear();
     }
-    Plan& p = db->plans[m];
-    sw_status s = build_plan(db, std::vector<int>{m}, &p);
-    if (s != SW_OK) { p.release(); db->plans.erase(m); return s; }
+    Plan& p = db->plans[key];
+    sw_status s = build_plan(db, std::vector<int>{m}, &p, nullptr, 1, whole);
+    if (s != SW_OK) { p.release(); db->plans.erase(key); return s; }
     *out = &p;
     return SW_OK;
 }
@@ -1017,10 +1023,19 @@ int32_t alignment_span(int64_t m, int64_t top, int32_t go, int32_t ge) {
     return (int32_t)std::min(m + (top - go) / ge + 1, kWhole);
 }
 
+// The same for a semi-global alignment that scores more than the query's own gap run, -(Go + (m - 1) Ge), which
+// every subject's column 0 offers.
+int32_t semiglobal_span(int64_t m, int64_t top, int32_t go, int32_t ge) {
+    constexpr int64_t kWhole = (int64_t)1 << 28;
+    if (ge <= 0 || ge > go) return (int32_t)kWhole;
+    return (int32_t)std::min(m + (top + (m - 1) * ge) / ge + 1, kWhole);
+}
+
 // Copies the queries (host) into the staging buffer on the device.  No launch.
 sw_status stage_queries(sw_db* db, const Work& W, const int8_t* h_queries, const int64_t* h_qoffsets, int nq,
                         const int8_t* subst, int32_t go, int32_t ge, int64_t score_row_stride, hipStream_t st, Staged* out,
-                        int32_t* const* per_query_out = nullptr, const Plan* with_plan = nullptr) {
+                        int32_t* const* per_query_out = nullptr, const Plan* with_plan = nullptr,
+                        int32_t mode = SW_LOCAL) {
     const StageLayout& L = W.L.st;
     char* h = static_cast<char*>(W.host->p);
     int64_t prof_off = 0;
@@ -1037,7 +1052,7 @@ sw_status stage_queries(sw_db* db, const Work& W, const int8_t* h_queries, const
         int64_t top = 0;
         for (int64_t i = h_qoffsets[q]; i < h_qoffsets[q + 1]; ++i) top += best[h_queries[i]];
         qd[q] = QDesc{prof_off, (int64_t)q * score_row_stride, per_query_out ? per_query_out[q] : nullptr, m, mp,
-                      alignment_span(m, top, go, ge), 0};
+                      mode == SW_LOCAL ? alignment_span(m, top, go, ge) : semiglobal_span(m, top, go, ge), 0};
         prof_off += (int64_t)kNRes * mp;
         qo[q] = h_qoffsets[q] - h_qoffsets[0];
     }
@@ -1100,6 +1115,34 @@ CellForm choose_form(const sw_db* db, const int8_t* subst, int32_t go, int32_t g
     return f;
 }
 
+// The cells of an end-to-end search: offset cells under the local form's conditions on gaps and bytes, as long as the
+// lowest value a pair of this query can reach (the gap run down it, and what the cells themselves take off) leaves
+// room above: half the range for semi-global scores, and for global ones, whose long similar subjects are lifted
+// by their gap run as well, a fifth (queries up to about 3,100 residues at 10/2; beyond, plain cells run the longest
+// subjects in 32 bits beside the others instead of recomputing high scorers one by one).  Anything else stays with
+// the plain cells (cell = kCellI16 here).
+CellForm choose_mode_form(const sw_db* db, int32_t mode, const int8_t* subst, int32_t go, int32_t ge, int32_t m) {
+    int lo = 0, hi = 0;
+    for (int i = 0; i < db->alphabet * db->alphabet; ++i) {
+        lo = std::min<int>(lo, subst[i]);
+        hi = std::max<int>(hi, subst[i]);
+    }
+    CellForm f;
+    f.mode = mode;
+    if (ge > go || ge > 32 || go > 255 || go + ge + lo < 0 || go + ge + hi > 255) return f;
+    const int64_t run = (int64_t)go + (int64_t)(m - 1) * ge;          // the gap run down the query
+    if (mode == SW_GLOBAL ? 5 * (128 + run) > 2 * (int64_t)kModeBias : kOffLo + run + 3 * (go - ge) > kModeBias) return f;
+    f.cell = kCellOff;
+    f.off_k = ge > 0 ? std::min(64, 4 * (32 / ge)) : 64;
+    f.add = go + ge;
+    f.bias = (int32_t)(kOffLo + run) + 3 * (go - ge);
+    // padding neither gains nor loses: its diagonal step grows by what the offset does
+    f.pad = mode == SW_GLOBAL ? go : go + ge;
+    // (the range test reads G, Go - Ge below H)
+    f.sat = (db->sat < kSat16 ? std::min<int32_t>(f.bias + db->sat, kSat16) : kSat16) - (go - ge);
+    return f;
+}
+
 // Timing events of the dominant launches (sw_profile_kernels): a ring of
 // kTimerSlots start/stop pairs; the oldest is forgotten when it is full.
 constexpr int kTimerSlots = 4096;
@@ -1125,7 +1168,7 @@ sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& 
                   bool time_sweep) {
     int32_t* ctr = W.counters;
     HIP_TRY(launch_profile(S.sm_q, db->alphabet, S.qd, S.nq, S.qoff, W.prof, ctr, kCounters, W.bits, W.L.bits_words,
-                           S.max_mp, st, form.add));
+                           S.max_mp, st, form.add, form.pad));
     SweepArgs a = sweep_args(db, S, W, go, ge, d_scores);
     // one launch: the chained pairs and then the bulk, or the unchained units and then the bulk
     const bool off = form.cell == kCellOff;
@@ -1149,6 +1192,8 @@ sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& 
     if (a.n_items > 0) {
         if (plan.qpack)
             HIP_TRY(launch_sweep_q2(form.cell, R, a, grid, st));
+        else if (form.mode != SW_LOCAL)
+            HIP_TRY(launch_sweep_mode_off(form.mode, R, a, grid, st));
         else
             HIP_TRY(launch_sweep(form.cell, R, a, grid, st));
     }
@@ -1157,8 +1202,12 @@ sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& 
         db->ev_used.push_back(ev);
     }
     // exact 32-bit recompute of saturated pairs; the count is read on the device
-    const SweepArgs r = recompute_args(db, a, W, ctr);
-    HIP_TRY(launch_sweep(kCellI32, kRerunRows, r, db->wg32, st));
+    SweepArgs r = recompute_args(db, a, W, ctr);
+    if (form.mode != SW_LOCAL) {
+        r.bias = 0;
+        HIP_TRY(launch_sweep_mode(form.mode, kRerunRows, r, db->wg32, st));
+    } else
+        HIP_TRY(launch_sweep(kCellI32, kRerunRows, r, db->wg32, st));
     if (k > 0)
         HIP_TRY(launch_topk_ws(d_scores, n, n, S.nq, k, top_s, top_i, topk_ws_bytes(n, S.nq, k) > 0 ? W.topk : nullptr,
                                st));
@@ -2029,6 +2078,22 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
         return SW_OK;
     }
     if ((s = ensure_geometry(db)) != SW_OK) return s;
+    const int64_t qo[2] = {0, qlen};
+    const CellForm form = choose_mode_form(db, mode, h_subst, gap_open, gap_extend, qlen);
+    if (form.cell == kCellOff) {
+        // one launch, planned as a local search's; not for a stream under capture, as with the plain cells below
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        HIP_TRY(hipStreamIsCapturing(st, &cap));
+        if (cap != hipStreamCaptureStatusNone) return fail(SW_E_HIP, "end-to-end search on a stream under capture");
+        Plan* plan = nullptr;
+        if ((s = get_plan(db, qlen, &plan, mode == SW_GLOBAL)) != SW_OK) return s;
+        Work W;
+        if ((s = get_work(db, qo, 1, 0, false, plan, nullptr, 0, &W)) != SW_OK) return s;
+        Staged S;
+        if ((s = stage_queries(db, W, h_query, qo, 1, h_subst, gap_open, gap_extend, 0, st, &S, nullptr, nullptr, mode)) != SW_OK)
+            return s;
+        return enqueue(db, S, form, *plan, W, gap_open, gap_extend, d_scores_out, n, 0, nullptr, nullptr, st, true);
+    }
     if (db->wg_mode == 0) {
         int b1 = 0, b2 = 0;
         int b3 = 0;
@@ -2039,6 +2104,7 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
         if (b < 1) return fail(SW_E_HIP, "16-bit end-to-end sweep cannot be resident");
         db->wg_mode = std::min(db->cus * b, db->wg16);     // within the 16-bit boundary slots
     }
+    // Plain cells (gaps or substitution scores that offset cells cannot hold, or a query too long for them).
     // 16-bit cells hold values in [128 - bias, kModeTop - bias).  Semi-global H never falls below the
     // gap run down the query, g(m) = -(Go + (m - 1) Ge), so its bias is just large enough for that (at
     // most the middle of the range), which leaves the most room above for high scores.  Global mode with
@@ -2090,14 +2156,13 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
     mi.insert(mi.end(), si.begin(), si.end());
     mi.insert(mi.end(), m32.begin(), m32.end());
     if (n_items) HIP_TRY(hipMemcpy(db->mode_plan.items.p, mi.data(), sizeof(WgItem) * n_items, hipMemcpyHostToDevice));
-    const int64_t qo[2] = {0, qlen};
     Work W;
     if ((s = get_work(db, qo, 1, 0, false, nullptr, nullptr, 0, &W)) != SW_OK) return s;
     Staged S;
     if ((s = stage_queries(db, W, h_query, qo, 1, h_subst, gap_open, gap_extend, 0, st, &S)) != SW_OK) return s;
     int32_t* ctr = W.counters;
     HIP_TRY(launch_profile(S.sm_q, db->alphabet, S.qd, S.nq, S.qoff, W.prof, ctr, kCounters, W.bits, W.L.bits_words,
-                           S.max_mp, st, sm_shift));
+                           S.max_mp, st, sm_shift, kPadScore));
     SweepArgs a = sweep_args(db, S, W, gap_open, gap_extend, d_scores_out);
     a.sm_shift = sm_shift;
     a.items = db->mode_plan.items.as<WgItem>();

@@ -26,6 +26,9 @@ constexpr int16_t kSat16 = 0x7C00; // 16-bit scores at or above this are recompu
 // the exact range), and a pair whose H leaves [128, kModeTop) is recomputed in 32 bits.
 constexpr int32_t kModeBias = 0x3E00;
 constexpr int32_t kModeTop = 0x7C00 - 128;
+// End-to-end modes on offset cells: a pair whose G falls below kOffLo is recomputed (no sum of offsets that is taken off
+// a G -- Ge K <= 128 and Ge R <= 512 -- reaches it).
+constexpr int32_t kOffLo = 704;
 // Test hook: what a flagged pair's 16-bit scores read until its 32-bit recompute overwrites them.
 constexpr int32_t kPoison = -0x3B9ACA07;
 

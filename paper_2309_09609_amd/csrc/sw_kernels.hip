@@ -365,6 +365,7 @@ struct PassIO {
     uint32_t rd_lane;      // byte offset of this lane group's boundary words in a chunk, or kNoAccess
     uint32_t wr_lane;      // same for the writing lane, or kNoAccess
     uint32_t cstride;      // boundary bytes per chunk (all lane groups)
+    bool first;            // the query's first pass
 };
 
 // Residues of 4 columns: two subjects (x: a, y: b) or one.
@@ -845,6 +846,8 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
     u2 So = {0, 0};                             // offset cells: true scores
     const OffCtx oc{(uint32_t)a.ge * 0x10001u, (uint32_t)(a.go - a.ge) * 0x10001u, (uint32_t)a.go * 0x10001u, a.off_k};
     constexpr bool kMode16 = MODE != 0 && std::is_same<C, CellI16>::value;
+    constexpr bool kModeOff = MODE != 0 && kOffset;
+    EndOff eo{};
     T lmin = C::zero(), lmax = C::zero();       // 16-bit end-to-end modes: range of every H
     EndCtx ec{};
     if constexpr (MODE != 0) {
@@ -858,7 +861,23 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
         ec.nb = valid ? a.slen[slot0 + 1] : 0;
         // the lane holding the query's last row starts S at H[m][0] where that counts
         const bool cap = (m - 1 - (passes - 1) * rows_pp) / R == b;
-        if constexpr (kMode16) {
+        if constexpr (kModeOff) {
+            eo.m = m;
+            eo.go = a.go;
+            eo.ge = a.ge;
+            eo.bias = a.bias;
+            eo.na = ec.na;
+            eo.nb = ec.nb;
+            int least = min(ec.na, ec.nb), most = max(ec.na, ec.nb);
+            for (int o = B; o < 64; o <<= 1) {
+                least = min(least, __shfl_xor(least, o, 64));
+                most = max(most, __shfl_xor(most, o, 64));
+            }
+            eo.least = __builtin_amdgcn_readfirstlane(least);
+            eo.most = __builtin_amdgcn_readfirstlane(most);
+            eo.bcap = __builtin_amdgcn_readfirstlane((m - 1 - (passes - 1) * rows_pp) / R);
+            eo.S = end_start<MODE>(eo, (m - 1) % R);
+        } else if constexpr (kMode16) {
             ec.bias = a.bias;
             const short hm = ec.enc(ec.border(m));
             S = T{cap && (MODE == 2 || ec.na == 0) ? hm : (short)0, cap && (MODE == 2 || ec.nb == 0) ? hm : (short)0};
@@ -902,13 +921,19 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
         if (valid) {
             io.rd_lane = (b == 0 && p > 0) ? lane_words : kNoAccess;
             io.wr_lane = (b == B - 1 && p + 1 < passes) ? lane_words : kNoAccess;
+            io.first = p == 0;
+            eo.row0 = p * rows_pp + b * R;
+            eo.rcap = __builtin_amdgcn_readfirstlane(p == passes - 1 ? (m - 1) % R : -1);
             ec.row0 = p * rows_pp + b * R;
             ec.top = p == 0;
             ec.last = p == passes - 1;
             if constexpr (kOffset) {
-                if (lgB == 0) sweep_pass_off<R, false, PACKED>(io, ncols, B, b, lrow8, oc, So);
-                else if (R == kSmallRows && passes == 1) sweep_pass_off<R, true, PACKED, R != kSmallRows>(io, ncols, B, b, lrow8, oc, So);
-                else sweep_pass_off<R, true, PACKED>(io, ncols, B, b, lrow8, oc, So);
+                if (lgB == 0)
+                    sweep_pass_off<R, false, PACKED, true, MODE>(io, ncols, B, b, lrow8, oc, So, eo);
+                else if (R == kSmallRows && passes == 1)
+                    sweep_pass_off<R, true, PACKED, R != kSmallRows, MODE>(io, ncols, B, b, lrow8, oc, So, eo);
+                else
+                    sweep_pass_off<R, true, PACKED, true, MODE>(io, ncols, B, b, lrow8, oc, So, eo);
             } else if constexpr (kMode16) {
                 if (lgB == 0)
                     sweep_pass_mode16<R, false, MODE>(io, ncols, B, b, lrow, go, ge, S, lmin, lmax, ec);
@@ -925,9 +950,15 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
     }
     if (chain) __builtin_amdgcn_s_setprio(0);
     if (!valid) return;
-    if constexpr (kOffset) S = bits<T>(So);
-    for (int o = 1; o < B; o <<= 1) S = C::xmax(S, o);
+    if constexpr (kModeOff) S = bits<T>((uint32_t)__shfl((int)eo.S, (lane & ~(B - 1)) + eo.bcap, 64));
+    else if constexpr (kOffset) S = bits<T>(So);
+    if constexpr (!kModeOff)
+        for (int o = 1; o < B; o <<= 1) S = C::xmax(S, o);
     int out_of_range = 0;                       // 16-bit end-to-end: some value left the exact range
+    if constexpr (kModeOff) {
+        out_of_range = end_outside(eo, a.sat) ? 1 : 0;
+        for (int o = 1; o < B; o <<= 1) out_of_range |= __shfl_xor(out_of_range, o, 64);
+    }
     if constexpr (kMode16) {
         const bool ra = (unsigned short)lmin.x < kModeLo || (unsigned short)lmax.x >= (unsigned)a.sat;
         const bool rb = (unsigned short)lmin.y < kModeLo || (unsigned short)lmax.y >= (unsigned)a.sat;
@@ -958,7 +989,7 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
     } else {
         if (b != 0) return;
         bool flag = false;                      // the pair must be recomputed with 32-bit cells
-        if (a.rerun != nullptr) flag = kMode16 ? out_of_range != 0 : (C::lo(S) >= a.sat || C::hi(S) >= a.sat);
+        if (a.rerun != nullptr) flag = kMode16 || kModeOff ? out_of_range != 0 : (C::lo(S) >= a.sat || C::hi(S) >= a.sat);
         const bool poisoned = flag && a.poison;
         const int slot0 = g * kGroupSubjects + 2 * su;
         const int o0 = a.perm[slot0], o1 = a.perm[slot0 + 1];
@@ -966,13 +997,19 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
         // column-offset global cells hold H'[m][n] = H[m][n] - g(n)
         const int ra = MODE == kModeGlobalOffset ? ec.border(ec.na) : 0;
         const int rb = MODE == kModeGlobalOffset ? ec.border(ec.nb) : 0;
-        if (o0 >= 0) out[o0] = poisoned ? kPoison : C::lo(S) - ub + ra;
-        if (o1 >= 0) out[o1] = poisoned ? kPoison : C::hi(S) - ub + rb;
+        int sa = C::lo(S) - ub + ra, sb = C::hi(S) - ub + rb;
+        if constexpr (kModeOff) {
+            sa = end_score<MODE>(eo, C::lo(S), (m - 1) % R, ec.na);
+            sb = end_score<MODE>(eo, C::hi(S), (m - 1) % R, ec.nb);
+        }
+        if (o0 >= 0) out[o0] = poisoned ? kPoison : sa;
+        if (o1 >= 0) out[o1] = poisoned ? kPoison : sb;
         if (flag) append_rerun(a, g, qa, su);
     }
 }
 
 // One long subject pair (pair k of group g) against query q on a whole workgroup (sw_offset.h, "long subjects").
+template <int MODE>
 __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int q, uint8_t* lds, int wave, int lane,
                                           uint32_t* slot) {
     constexpr int R = kChainRows;
@@ -984,7 +1021,7 @@ __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int 
     // waves per window, and windows: as many as the waves allow while a window stays well below the subject
     int waves = passes > 1 ? kChainWaves : (Q.m + kWaveRows - 1) / kWaveRows;
     int windows = kChainWaves / waves;
-    while (windows > 1 && Q.span + cols / windows > cols - cols / 4) --windows;
+    while (windows > 1 && (MODE == 1 || Q.span + cols / windows > cols - cols / 4)) --windows;
     const int core = ((cols / 4 + windows - 1) / windows) * 4;            // columns a window answers for
     const int win = wave / waves;
     const int w = wave - win * waves;
@@ -1014,38 +1051,74 @@ __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int 
     uint8_t* out_lane = lane == 63 && w + 1 < waves ? ring_in + kChainRingBytes : idle + lane * 8;
     const OffCtx oc{(uint32_t)a.ge * 0x10001u, (uint32_t)(a.go - a.ge) * 0x10001u, (uint32_t)a.go * 0x10001u, a.off_k};
     u2 S = {0, 0};
+    const int slot0 = g * kGroupSubjects + 2 * k;
+    EndOff ec{};
+    if constexpr (MODE != 0) {
+        ec.m = Q.m;
+        ec.go = a.go;
+        ec.ge = a.ge;
+        ec.bias = a.bias;
+        ec.na = min(a.slen[slot0] - start, ncols);
+        ec.nb = min(a.slen[slot0 + 1] - start, ncols);
+        ec.least = __builtin_amdgcn_readfirstlane(max(0, min(ec.na, ec.nb)));
+        ec.most = __builtin_amdgcn_readfirstlane(max(ec.na, ec.nb));
+        ec.bcap = __builtin_amdgcn_readfirstlane(((Q.m - 1) / R) & 63);
+        ec.S = end_start<MODE>(ec, (Q.m - 1) % R);
+    }
     __builtin_amdgcn_s_setprio(3);                  // its steps are the search's longest chain
     for (int p = 0; p < passes; ++p) {
         const int row0 = (p * kChainWaves + w) * kWaveRows;
         const bool active = mine && row0 < Q.m;
         // a wave reads only its own slice; the barriers of the last pass's stages are behind it
         if (active) load_slice_off<R>(slice, a.prof + Q.prof_off, Q.mp, row0, 6, lane, 64);
+        ec.row0 = row0 + lane * R;
+        ec.rcap = __builtin_amdgcn_readfirstlane(active && row0 + kWaveRows >= Q.m ? (Q.m - 1) % R : -1);
+        io.first = p == 0;
         io.rd_lane = p > 0 ? 0u : kNoAccess;
         io.wr_lane = (lane == 63 && w == waves - 1) ? 0u : kNoAccess;
         __syncthreads();
         if (p + 1 < passes)
-            chain_pass<R, true>(io, ncols, w, stages, active, lane, slice + lane * (kNRes * R), ring_in, out_lane, resq,
-                                zeros, oc, S);
+            chain_pass<R, true, MODE>(io, ncols, w, stages, active, lane, slice + lane * (kNRes * R), ring_in, out_lane, resq,
+                                zeros, oc, S, ec);
         else
-            chain_pass<R, false>(io, ncols, w, stages, active, lane, slice + lane * (kNRes * R), ring_in, out_lane, resq,
-                                zeros, oc, S);
+            chain_pass<R, false, MODE>(io, ncols, w, stages, active, lane, slice + lane * (kNRes * R), ring_in, out_lane, resq,
+                                zeros, oc, S, ec);
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");   // boundary stores visible to the next pass
         __syncthreads();
     }
     __builtin_amdgcn_s_setprio(0);
-    for (int o = 1; o < 64; o <<= 1) S = bits<u2>(CellI16::xmax(bits<s2>(S), o));
+    bool bad = false;                               // a value left the exact range
+    if constexpr (MODE != 0) {
+        bad = end_outside(ec, a.sat);
+        const bool held = mine && w == ((Q.m - 1) / kWaveRows) % kChainWaves;
+        S = bits<u2>(held ? (uint32_t)__shfl((int)ec.S, ec.bcap, 64) : 0u);
+        bad = __ballot(mine && bad) != 0;
+    } else
+        for (int o = 1; o < 64; o <<= 1) S = bits<u2>(CellI16::xmax(bits<s2>(S), o));
     u2* best = reinterpret_cast<u2*>(rings);
-    if (lane == 0) best[wave] = S;
+    uint32_t* worst = reinterpret_cast<uint32_t*>(rings) + kChainWaves;
+    if (lane == 0) {
+        best[wave] = S;
+        worst[wave] = bad;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int x = 1; x < kChainWaves; ++x) S = __builtin_elementwise_max(S, best[x]);
-        const bool flag = a.rerun != nullptr && ((int)S.x >= a.sat || (int)S.y >= a.sat);
+        for (int x = 1; x < kChainWaves; ++x) {
+            S = __builtin_elementwise_max(S, best[x]);
+            bad = bad || worst[x] != 0;
+        }
+        int sa = (int)S.x, sb = (int)S.y;
+        bool flag = a.rerun != nullptr && (sa >= a.sat || sb >= a.sat);
+        if constexpr (MODE != 0) {
+            flag = a.rerun != nullptr && bad;
+            sa = end_score<MODE>(ec, sa, (Q.m - 1) % R, a.slen[slot0]);
+            sb = end_score<MODE>(ec, sb, (Q.m - 1) % R, a.slen[slot0 + 1]);
+        }
         const bool poisoned = flag && a.poison;
-        const int slot0 = g * kGroupSubjects + 2 * k;
         const int o0 = a.perm[slot0], o1 = a.perm[slot0 + 1];
         int32_t* out = Q.out ? Q.out : a.scores + Q.out_off;
-        if (o0 >= 0) out[o0] = poisoned ? kPoison : (int)S.x;
-        if (o1 >= 0) out[o1] = poisoned ? kPoison : (int)S.y;
+        if (o0 >= 0) out[o0] = poisoned ? kPoison : sa;
+        if (o1 >= 0) out[o1] = poisoned ? kPoison : sb;
         if (flag) append_rerun(a, g, q, k);
     }
     // Thread 0 goes on to pull the next item: without a barrier between, the compiler joins the two and lets the
@@ -1136,7 +1209,7 @@ __global__ __launch_bounds__(64 * kWaves, (kMinWaves<C, R>)) void k_sweep(SweepA
         const WgItem I = a.items[at < a.n_items ? at : at - a.n_items];
         if constexpr (kOffset) {
             if (I.lgB == kItemChain) {
-                run_chain(a, I.g0, I.k0, I.q, reinterpret_cast<uint8_t*>(lds), wave, lane,
+                run_chain<MODE>(a, I.g0, I.k0, I.q, reinterpret_cast<uint8_t*>(lds), wave, lane,
                           a.scratch + (int64_t)(a.slot_base + blockIdx.x) * kWaves * a.slot_words);
                 continue;
             }
@@ -1146,7 +1219,7 @@ __global__ __launch_bounds__(64 * kWaves, (kMinWaves<C, R>)) void k_sweep(SweepA
         const int g = I.g0 + (k >> lgB) * I.gstep;
         k &= (1 << lgB) - 1;
         const bool shared_slice = lgB > 4;              // more than 16 lanes per pair
-        if constexpr (MODE == 0 && !std::is_same<C, CellI32>::value && R != kSmallRows) {
+        if constexpr ((MODE == 0 || kOffset) && !std::is_same<C, CellI32>::value && R != kSmallRows) {
             if (I.lgB >= kItemSmall) {
                 run_unit<C, kSmallRows, false, MODE>(a, g, k, lgB, I.q, wave < I.count, shared_slice, lds, wave, lane, slot);
                 continue;
@@ -1181,7 +1254,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void k_sweep_q2(SweepArgs a) {
         const WgItem I = a.items[at < a.n_items ? at : at - a.n_items];
         if constexpr (std::is_same<C, CellOff>::value) {
             if (I.lgB == kItemChain) {              // one query of the pair; I.q is the query itself
-                run_chain(a, I.g0, I.k0, I.q, reinterpret_cast<uint8_t*>(lds), wave, lane,
+                run_chain<0>(a, I.g0, I.k0, I.q, reinterpret_cast<uint8_t*>(lds), wave, lane,
                           a.scratch + (int64_t)(a.slot_base + blockIdx.x) * kWaves * a.slot_words);
                 continue;
             }
@@ -1197,7 +1270,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void k_sweep_q2(SweepArgs a) {
 
 // ------------------------------------------------------------ query profile
 // prof[d][i] = SM(Q[i], d - 1) + add for image codes d = 1..A and i < m
-// (add = Ge for column-offset global cells, else 0); kPadScore for d = 0
+// (add: what the cells' offsets grow by along a diagonal); pad for d = 0
 // (padding), d > A and past m.  One staging buffer holds the A x A
 // matrix (in a kMaxAlphabet^2-byte region) followed by the query codes.
 // Thread 0 also zeroes the launch counters (they are consumed by later kernels
@@ -1205,7 +1278,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void k_sweep_q2(SweepArgs a) {
 // The blocks of query 0 also clear the recompute's flag bits.
 __global__ void k_profile(const int8_t* stage, int A, const QDesc* qd, int nq, const int64_t* qoff,
                           int16_t* prof, int32_t* counters, int ncounters, uint32_t* bits, int64_t nbits_words,
-                          int add) {
+                          int add, int pad) {
     const int q = blockIdx.y;
     if (q == 0 && blockIdx.x == 0 && threadIdx.x < ncounters) counters[threadIdx.x] = 0;
     if (q == 0)
@@ -1219,7 +1292,7 @@ __global__ void k_profile(const int8_t* stage, int A, const QDesc* qd, int nq, c
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
         const int d = (int)(e / Q.mp);
         const int i = (int)(e - (int64_t)d * Q.mp);
-        int16_t v = kPadScore;
+        int16_t v = (int16_t)pad;
         if (d >= 1 && d <= A && i < Q.m) v = (int16_t)(sm[query[i] * A + (d - 1)] + add);
         prof[Q.prof_off + e] = v;
     }
@@ -1515,6 +1588,27 @@ static const void* mode_kernel(int mode, int R) {
     return nullptr;
 }
 
+// End-to-end modes on offset cells.
+static const void* mode_off_kernel(int mode, int R) {
+    if (mode == 1)
+        return R == 16 ? (const void*)k_sweep<CellOff, 16, 1>
+             : R == 12 ? (const void*)k_sweep<CellOff, 12, 1>
+             : R == 8  ? (const void*)k_sweep<CellOff, 8, 1>
+             : R == 4  ? (const void*)k_sweep<CellOff, 4, 1> : nullptr;
+    return R == 16 ? (const void*)k_sweep<CellOff, 16, 2>
+         : R == 12 ? (const void*)k_sweep<CellOff, 12, 2>
+         : R == 8  ? (const void*)k_sweep<CellOff, 8, 2>
+         : R == 4  ? (const void*)k_sweep<CellOff, 4, 2> : nullptr;
+}
+
+hipError_t launch_sweep_mode_off(int mode, int R, const SweepArgs& a, int grid, hipStream_t st) {
+    const void* k = mode_off_kernel(mode, R);
+    if (!k) return hipErrorInvalidValue;
+    SweepArgs copy = a;
+    void* args[] = {&copy};
+    return hipLaunchKernel(k, dim3(grid), dim3(64 * kWaves), args, 0, st);
+}
+
 static const void* mode16_kernel(int mode, int R) {
     if (mode == 1)
         return R == 16 ? (const void*)k_sweep<CellI16, 16, 1>
@@ -1564,11 +1658,11 @@ hipError_t sweep_occupancy(int form, int R, int* blocks_per_cu) {
 
 hipError_t launch_profile(const int8_t* stage, int A, const QDesc* qd, int nq, const int64_t* qoff, int16_t* prof,
                           int32_t* counters, int ncounters, uint32_t* bits, int64_t nbits_words, int max_mp,
-                          hipStream_t st, int add) {
+                          hipStream_t st, int add, int pad) {
     const int64_t work = std::max<int64_t>((int64_t)kNRes * max_mp, nbits_words);
     const int bx = (int)std::min<int64_t>((work + 255) / 256, 1024);
     hipLaunchKernelGGL(k_profile, dim3(bx, std::max(nq, 1)), dim3(256), 0, st, stage, A, qd, nq, qoff, prof,
-                       counters, ncounters, bits, nbits_words, add);
+                       counters, ncounters, bits, nbits_words, add, pad);
     return hipGetLastError();
 }
 

@@ -38,6 +38,19 @@
 // cost Go + Ge (K + 17) of the range; the host recomputes pairs from there on
 // (SweepArgs::sat).
 //
+// End-to-end modes (global, semi-global; Ge <= Go) run on the same cells without
+// the floor: E' = max(E, G), and instead of S every G folds into a running
+// minimum and maximum that tell whether all values stayed in the exact range.
+// Values carry ec.bias instead of Go, just above the lowest value a pair can
+// reach.  Global cells hold H + Ge j and so on (gap runs along the subject cost
+// the offset's growth, and the border of row 0 is a constant), which is the
+// same recurrence with no term in tau and nothing to lower.  5.5 instructions
+// per row of two cells and a permute, against 8 and one for plain cells.  The
+// last row's cells are read off once per step, only by the wave that holds them
+// and in the columns that count.  Measured against the plain cells, with the
+// longest pairs on a workgroup each (below): global, 405 residues x 570,000
+// subjects, 17.5 -> 10.8 ms; semi-global, 331 x 100,000, 10.9 -> 3.5 ms.
+//
 // The rows' G live in fixed registers v64.. (row r's in v65 + r, the value
 // above the block in v64) because v_lshl_add_u64 reads them in pairs and the
 // rest one by one, which asm operands cannot express; so do S (v82..) and the
@@ -127,6 +140,17 @@ struct OffCtx {
     SWO_M(d0, r0) EPREV SWO_G(p1) SWO_F(p1) SWO_E(r0, p1) SWO_M(d1, r1) SWO_S(s, p1, p2) SWO_G(p2) SWO_F(p2)  \
     SWO_E(r1, p2)
 
+// End-to-end modes: no floor, the range folds of a row pair behind its second F.  (E and G are plain integers: a
+// half that fell below 0 reads 0xFF.., a NaN pattern, and stays in the folds.)
+#define SWO_E0(r, p) "v_pk_max_i16 %[e" #r "], %[e" #r "], " p "\n"
+#define SWO_FOLD(p, q) "v_pk_maximum3_f16 %[hi], %[hi], " p ", " q "\n" "v_pk_minimum3_f16 %[lo], %[lo], " p ", " q "\n"
+#define SWO_MBLK(d0, d1, nd, r0, r1, p1, p2, npp, w, qa, qb, EPREV)                                           \
+    SWO_M(d0, r0) SWO_PERM("v90", w, qa) EPREV SWO_G(p1) SWO_F(p1) SWO_PERM("v91", w, qb) SWO_M(d1, r1)       \
+    SWO_HD(nd, npp) SWO_G(p2) SWO_F(p2) SWO_FOLD(p1, p2) SWO_E0(r0, p1)
+#define SWO_MLAST(d0, d1, r0, r1, p1, p2, EPREV)                                                              \
+    SWO_M(d0, r0) EPREV SWO_G(p1) SWO_F(p1) SWO_E0(r0, p1) SWO_M(d1, r1) "s_nop 0\n" SWO_G(p2) SWO_F(p2)      \
+    SWO_FOLD(p1, p2) SWO_E0(r1, p2)
+
 // What comes from above: a cooperating lane takes lane b-1's bottom row (its G and F of one step ago) and
 // drops the rows' offset Ge (R - 1); the first lane of a group takes the boundary words, raised by as much.
 #define SWO_TOP_COOP(pr)                                                                                      \
@@ -164,6 +188,37 @@ struct OffCtx {
     SWO_BLK(SWO_DB0, SWO_DB1, SWO_DA, 10, 11, SWO_P11, SWO_P12, SWO_PP12, SWO_S5, 3, 0, 1, SWO_E(9, SWO_P10)) \
     SWO_BLK(SWO_DA0, SWO_DA1, SWO_DB, 12, 13, SWO_P13, SWO_P14, SWO_PP14, SWO_S6, 3, 2, 3, SWO_E(11, SWO_P12)) \
     SWO_LAST(SWO_DB0, SWO_DB1, 14, 15, SWO_P15, SWO_P16, SWO_S7, SWO_E(13, SWO_P14))
+// (end-to-end modes: a cooperating lane keeps its column-0 border until its first column)
+#define SWO_MON "s_mov_b64 exec, %[act]\n"
+#define SWO_MOFF "s_mov_b64 exec, -1\n"
+#define SWO_MROWS4(TOP)                                                                                       \
+    SWO_PRE SWO_HD(SWO_DA, SWO_PP0) TOP                                                                       \
+    SWO_MBLK(SWO_DA0, SWO_DA1, SWO_DB, 0, 1, SWO_P1, SWO_P2, SWO_PP2, 0, 2, 3, "")                            \
+    SWO_MLAST(SWO_DB0, SWO_DB1, 2, 3, SWO_P3, SWO_P4, SWO_E0(1, SWO_P2))
+#define SWO_MROWS8(TOP)                                                                                       \
+    SWO_PRE SWO_HD(SWO_DA, SWO_PP0) TOP                                                                       \
+    SWO_MBLK(SWO_DA0, SWO_DA1, SWO_DB, 0, 1, SWO_P1, SWO_P2, SWO_PP2, 0, 2, 3, "")                            \
+    SWO_MBLK(SWO_DB0, SWO_DB1, SWO_DA, 2, 3, SWO_P3, SWO_P4, SWO_PP4, 1, 0, 1, SWO_E0(1, SWO_P2))             \
+    SWO_MBLK(SWO_DA0, SWO_DA1, SWO_DB, 4, 5, SWO_P5, SWO_P6, SWO_PP6, 1, 2, 3, SWO_E0(3, SWO_P4))             \
+    SWO_MLAST(SWO_DB0, SWO_DB1, 6, 7, SWO_P7, SWO_P8, SWO_E0(5, SWO_P6))
+#define SWO_MROWS12(TOP)                                                                                      \
+    SWO_PRE SWO_HD(SWO_DA, SWO_PP0) TOP                                                                       \
+    SWO_MBLK(SWO_DA0, SWO_DA1, SWO_DB, 0, 1, SWO_P1, SWO_P2, SWO_PP2, 0, 2, 3, "")                            \
+    SWO_MBLK(SWO_DB0, SWO_DB1, SWO_DA, 2, 3, SWO_P3, SWO_P4, SWO_PP4, 1, 0, 1, SWO_E0(1, SWO_P2))             \
+    SWO_MBLK(SWO_DA0, SWO_DA1, SWO_DB, 4, 5, SWO_P5, SWO_P6, SWO_PP6, 1, 2, 3, SWO_E0(3, SWO_P4))             \
+    SWO_MBLK(SWO_DB0, SWO_DB1, SWO_DA, 6, 7, SWO_P7, SWO_P8, SWO_PP8, 2, 0, 1, SWO_E0(5, SWO_P6))             \
+    SWO_MBLK(SWO_DA0, SWO_DA1, SWO_DB, 8, 9, SWO_P9, SWO_P10, SWO_PP10, 2, 2, 3, SWO_E0(7, SWO_P8))           \
+    SWO_MLAST(SWO_DB0, SWO_DB1, 10, 11, SWO_P11, SWO_P12, SWO_E0(9, SWO_P10))
+#define SWO_MROWS16(TOP)                                                                                      \
+    SWO_PRE SWO_HD(SWO_DA, SWO_PP0) TOP                                                                       \
+    SWO_MBLK(SWO_DA0, SWO_DA1, SWO_DB, 0, 1, SWO_P1, SWO_P2, SWO_PP2, 0, 2, 3, "")                            \
+    SWO_MBLK(SWO_DB0, SWO_DB1, SWO_DA, 2, 3, SWO_P3, SWO_P4, SWO_PP4, 1, 0, 1, SWO_E0(1, SWO_P2))             \
+    SWO_MBLK(SWO_DA0, SWO_DA1, SWO_DB, 4, 5, SWO_P5, SWO_P6, SWO_PP6, 1, 2, 3, SWO_E0(3, SWO_P4))             \
+    SWO_MBLK(SWO_DB0, SWO_DB1, SWO_DA, 6, 7, SWO_P7, SWO_P8, SWO_PP8, 2, 0, 1, SWO_E0(5, SWO_P6))             \
+    SWO_MBLK(SWO_DA0, SWO_DA1, SWO_DB, 8, 9, SWO_P9, SWO_P10, SWO_PP10, 2, 2, 3, SWO_E0(7, SWO_P8))           \
+    SWO_MBLK(SWO_DB0, SWO_DB1, SWO_DA, 10, 11, SWO_P11, SWO_P12, SWO_PP12, 3, 0, 1, SWO_E0(9, SWO_P10))       \
+    SWO_MBLK(SWO_DA0, SWO_DA1, SWO_DB, 12, 13, SWO_P13, SWO_P14, SWO_PP14, 3, 2, 3, SWO_E0(11, SWO_P12))      \
+    SWO_MLAST(SWO_DB0, SWO_DB1, 14, 15, SWO_P15, SWO_P16, SWO_E0(13, SWO_P14))
 #define SWO_PREW "s_mov_b64 vcc, %[first]\n"
 #define SWO_ROWS8W(TOP)                                                                                       \
     SWO_PREW SWO_SA(SWO_SS0) SWO_HDW(SWO_DA, SWO_PP0, 0) TOP                                                  \
@@ -245,6 +300,120 @@ __device__ __forceinline__ void rows_off_pair(uint32_t* P, uint32_t* E, uint32_t
     }
 }
 
+// End-to-end modes, subject pairs: lo and hi fold every G; lanes outside act keep everything.
+template <int R, bool COOP>
+__device__ __forceinline__ void rows_off_mode(uint32_t* P, uint32_t* E, uint32_t& lo, uint32_t& hi, uint32_t& F,
+                                              uint32_t bg, uint32_t bf, const uint32_t* w, uint32_t goe, uint32_t cr,
+                                              uint64_t first, uint64_t act) {
+#define SWO_MASM(N, AB)                                                                                          \
+    if constexpr (COOP)                                                                                               \
+        asm(SWO_MON SWO_MROWS##N(SWO_TOP_COOP(SWO_P##N)) SWO_MOFF : SWO_E##N, [f] "+v"(F), SWO_OP##N, [lo] "+v"(lo), \
+            [hi] "+v"(hi) : [bf] "v"(bf), [bg] "v"(bg), [goe] "s"(goe), [cr] "s"(cr), [first] "s"(first),            \
+            [act] "s"(act), SWO_INQ, AB : SWO_CLOB);                                                                  \
+    else                                                                                                              \
+        asm(SWO_MROWS##N(SWO_TOP_ALONE) : SWO_E##N, [f] "+v"(F), SWO_OP##N, [lo] "+v"(lo), [hi] "+v"(hi)             \
+            : [bf] "v"(bf), [bg] "v"(bg), [goe] "s"(goe), [cr] "s"(cr), [first] "s"(first), SWO_INQ, AB : SWO_CLOB)
+#define SWO_AB4 SWO_ABI(0)
+#define SWO_AB8 SWO_AB4, SWO_ABI(1)
+#define SWO_AB12 SWO_AB8, SWO_ABI(2)
+#define SWO_AB16 SWO_AB12, SWO_ABI(3)
+    if constexpr (R == 16) { SWO_MASM(16, SWO_AB16); }
+    else if constexpr (R == 12) { SWO_MASM(12, SWO_AB12); }
+    else if constexpr (R == 8) { SWO_MASM(8, SWO_AB8); }
+    else { static_assert(R == 4, "rows per lane must be 4, 8, 12 or 16"); SWO_MASM(4, SWO_AB4); }
+}
+
+// G of row r of the lane's block (r the same in every lane).  (Selects or an array index would send P to memory.)
+#define SWO_IDX "s_set_gpr_idx_on %1, gpr_idx(SRC0)\n v_mov_b32 %0, v65\n s_set_gpr_idx_off"
+#define SWO_IP4 "s"(r), "{v65}"(P[1]), "{v66}"(P[2]), "{v67}"(P[3]), "{v68}"(P[4])
+#define SWO_IP8 SWO_IP4, "{v69}"(P[5]), "{v70}"(P[6]), "{v71}"(P[7]), "{v72}"(P[8])
+#define SWO_IP12 SWO_IP8, "{v73}"(P[9]), "{v74}"(P[10]), "{v75}"(P[11]), "{v76}"(P[12])
+#define SWO_IP16 SWO_IP12, "{v77}"(P[13]), "{v78}"(P[14]), "{v79}"(P[15]), "{v80}"(P[16])
+template <int R>
+__device__ __forceinline__ uint32_t row_g(const uint32_t* P, int r) {
+    uint32_t g;
+    if constexpr (R == 16) asm(SWO_IDX : "=v"(g) : SWO_IP16 : "m0");
+    else if constexpr (R == 12) asm(SWO_IDX : "=v"(g) : SWO_IP12 : "m0");
+    else if constexpr (R == 8) asm(SWO_IDX : "=v"(g) : SWO_IP8 : "m0");
+    else asm(SWO_IDX : "=v"(g) : SWO_IP4 : "m0");
+    return g;
+}
+
+// End-to-end modes: where a pass stands and what it takes from the query's last row.
+struct EndOff {
+    int row0;                  // 0-based first query row of this lane in this pass
+    int m;
+    int go, ge, bias;
+    int na, nb;                // columns of the lane's two subjects (in a window: those before its end)
+    int least, most;           // the smallest and largest of na and nb over the wave
+    int rcap, bcap;            // row within the lane and lane within its group that hold the last row; rcap < 0: not in
+                               // this wave or pass
+    uint32_t lo = 0x7BFF7BFFu, hi = 0;   // range of every G
+    uint32_t S = 0;            // semi-global: the largest G of the last row, global: the one at the last column
+    __device__ int border(int k) const { return k <= 0 ? 0 : -(go + (k - 1) * ge); }   // Ge <= Go
+};
+
+// Column-0 borders of the R rows below row0 and their E at column 1; a lane that starts `late` steps in holds them at
+// the offset of its first column (gt = what the offset grows by per step).
+template <int R>
+__device__ __forceinline__ void end_borders(const EndOff& ec, int gt, int late, uint32_t* P, uint32_t* E) {
+#pragma unroll
+    for (int r = 0; r <= R; ++r) {
+        const uint32_t v = (uint32_t)(ec.border(min(ec.row0 + r, ec.m)) + ec.bias + ec.ge * r - ec.go + gt * late);
+        P[r] = v | (v << 16);
+        if (r < R) {
+            const uint32_t e = (uint32_t)(ec.border(min(ec.row0 + r + 1, ec.m)) - ec.go + ec.bias + ec.ge * (r + 1) + gt * late);
+            E[r] = e | (e << 16);
+        }
+    }
+}
+
+// What chunk c's steps take from the last row: 0 nothing, 1 (semi-global) every column of every lane, 2 by column.
+template <int MODE>
+__device__ __forceinline__ int end_takes(const EndOff& ec, int c) {
+    const int col = 4 * c - ec.bcap;           // the column the lanes of the last row are at in the first step
+    if (ec.rcap < 0 || col + 3 < (MODE == 1 ? max(ec.least, 1) - 1 : 0) || col >= ec.most) return 0;
+    return MODE == 2 && col >= 0 && col + 3 < ec.least ? 1 : 2;
+}
+
+// The last row's cell of step t, offset `off` included in G (two halves alike).
+template <int R, int MODE>
+__device__ __forceinline__ void end_capture(EndOff& ec, int takes, const uint32_t* P, int t, uint32_t off) {
+    if (takes == 0) return;
+    uint32_t g = row_g<R>(P, ec.rcap);
+    const int col = t - ec.bcap;
+    if constexpr (MODE == 1) {
+        asm volatile("" : "+v"(g));
+        if (col == ec.na - 1) ec.S = (ec.S & 0xffff0000u) | (g & 0xffffu);
+        if (col == ec.nb - 1) ec.S = (ec.S & 0xffffu) | (g & 0xffff0000u);
+    } else {
+        g -= off;
+        if (takes == 2) {                      // (a branch: few chunks of a pass take it)
+            asm volatile("" : "+v"(g));
+            g = col < 0 ? 0u : g & ((col < ec.na ? 0xffffu : 0u) | (col < ec.nb ? 0xffff0000u : 0u));
+        }
+        ec.S = bits<uint32_t>(__builtin_elementwise_max(bits<u2>(ec.S), bits<u2>(g)));
+    }
+}
+
+// End-to-end modes on offset cells: the last row's cell that counts before any column (semi-global: column 0), a
+// score from a captured G, and whether some G left the exact range.
+template <int MODE>
+__device__ __forceinline__ uint32_t end_start(const EndOff& ec, int r) {
+    if (MODE == 1) return 0;
+    return (uint32_t)(ec.border(ec.m) + ec.bias + ec.ge * r - (ec.go - ec.ge)) * 0x10001u;
+}
+template <int MODE>
+__device__ __forceinline__ int end_score(const EndOff& ec, int g, int r, int n) {
+    if (n == 0) return ec.border(ec.m);
+    return g + ec.go - ec.ge - ec.bias - ec.ge * r - (MODE == 1 ? ec.ge * n : 0);
+}
+__device__ __forceinline__ bool end_outside(const EndOff& ec, int sat) {
+    const u2 lo = bits<u2>(ec.lo), hi = bits<u2>(ec.hi);
+    // (a NaN pattern, from either end, is above sat in hi)
+    return lo.x < kOffLo || lo.y < kOffLo || (int)hi.x >= sat || (int)hi.y >= sat;
+}
+
 // Query pairs: w[r] = row r's substitution pair (both halves non-negative).
 template <int R, bool COOP>
 __device__ __forceinline__ void rows_off_packed(uint32_t* P, uint32_t* E, uint32_t* S, uint32_t& F, uint32_t bg,
@@ -321,9 +490,9 @@ __device__ __forceinline__ uint32_t sgpr(uint32_t v) { return __builtin_amdgcn_r
 // of a first pass reads as zeros).  S receives the true scores of the lane's two matrices.
 // IO = false: the query's only pass, with no boundary row to read or write (of a lone wave's step at 4 rows per lane
 // that is one instruction in six).
-template <int R, bool COOP, bool PACKED, bool IO = true>
+template <int R, bool COOP, bool PACKED, bool IO = true, int MODE = 0>
 __device__ __forceinline__ void sweep_pass_off(const PassIO& io, int ncols, int B, int b, const uint8_t* lrow,
-                                               const OffCtx& o, u2& S) {
+                                               const OffCtx& o, u2& S, EndOff& ec) {
     using RV = typename Res<PACKED>::V;
     constexpr int NW = PACKED ? R : R / 2;                 // dwords of substitution values per step
     const int nsteps = ncols + B - 1;
@@ -331,16 +500,24 @@ __device__ __forceinline__ void sweep_pass_off(const PassIO& io, int ncols, int 
     const uint32_t ge = sgpr(o.ge), goe = sgpr(o.goe), go = sgpr(o.go);
     const uint64_t ge64 = ((uint64_t)ge << 32) | ge;
     const uint64_t first = __ballot(b == 0);
-    const uint32_t cr = ge * (R - 1);                      // no half of a product leaves 16 bits (host check)
+    const uint32_t gt = MODE == 1 ? 0u : ge;               // growth of the offset per step
+    const uint32_t cr = ge * R - gt;                       // no half of a product leaves 16 bits (host check)
     uint32_t P[R + 1], E[R], Sx[R / 2];
-    // tau = 1 at the first step: G of column 0 carries Ge r, E of column 1 the floor Go + Ge (r + 1)
-#pragma unroll
-    for (int r = 0; r <= R; ++r) P[r] = ge * r;
-#pragma unroll
-    for (int r = 0; r < R; ++r) E[r] = go + ge * (r + 1);
-#pragma unroll
-    for (int i = 0; i < R / 2; ++i) Sx[i] = ge * (2 * i + 1);
     uint32_t F = ge * R;                                   // what lane b-1 hands over before its first column
+    uint32_t top0 = 0;                                     // the border of row 0 (G and F of the row above)
+    if constexpr (MODE == 0) {
+        // tau = 1 at the first step: G of column 0 carries Ge r, E of column 1 the floor Go + Ge (r + 1)
+#pragma unroll
+        for (int r = 0; r <= R; ++r) P[r] = ge * r;
+#pragma unroll
+        for (int r = 0; r < R; ++r) E[r] = go + ge * (r + 1);
+#pragma unroll
+        for (int i = 0; i < R / 2; ++i) Sx[i] = ge * (2 * i + 1);
+    } else {
+        end_borders<R>(ec, MODE == 1 ? 0 : ec.ge, COOP ? b : 0, P, E);
+        if (io.first) top0 = (uint32_t)(ec.bias - ec.go - (MODE == 1 ? ec.go - ec.ge : 0)) * 0x10001u;
+    }
+    uint64_t act = first;                                  // lanes that have reached their first column
     int tau = 1;                                           // of the chunk's first step
     const int coff = COOP ? ((-b) >> 2) : 0;
     const int csh = COOP ? ((-b) & 3) : 0;
@@ -364,11 +541,12 @@ __device__ __forceinline__ void sweep_pass_off(const PassIO& io, int ncols, int 
 #pragma unroll
             for (int i = 0; i < 2; ++i) nw[i] = ld128(io.bnd, io.rd_lane + (uint32_t)(c + 1) * io.cstride + 16u * i);
         const RV rn = resid(c1, c2);
-        const uint32_t get = ge * (uint32_t)tau;           // Ge tau of the chunk's first step
+        const uint32_t get = gt * (uint32_t)tau;           // Ge tau of the chunk's first step
         uint32_t kk[R + 3];                                // floors of the next step, row r at step u: kk[r + u]
 #pragma unroll
         for (int i = 0; i < R + 3; ++i) kk[i] = go + get + ge * (uint32_t)(i + 1);
-        const uint32_t b0 = get + (COOP ? cr : 0u);
+        const uint32_t b0 = get + (COOP ? cr : 0u) + top0;
+        const int takes = MODE != 0 ? end_takes<MODE>(ec, c) : 0;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             uint32_t nx2[NW];
@@ -381,18 +559,22 @@ __device__ __forceinline__ void sweep_pass_off(const PassIO& io, int ncols, int 
             }
             // the column's boundary words at this step's offset (no half leaves 16 bits)
             const uint4 v = bw[u >> 1];
-            uint32_t bg = b0 + ge * u, bf = bg;
+            uint32_t bg = b0 + gt * u, bf = bg;
             if constexpr (IO) {
-                const uint64_t top = add_pairs((u & 1) ? pair64(v.z, v.w) : pair64(v.x, v.y), b0 + ge * u);
+                const uint64_t top = add_pairs((u & 1) ? pair64(v.z, v.w) : pair64(v.x, v.y), b0 + gt * u);
                 bg = (uint32_t)top;
                 bf = (uint32_t)(top >> 32);
             }
-            if constexpr (PACKED) rows_off_packed<R, COOP>(P, E, Sx, F, bg, bf, cur, kk + u, goe, cr, ge64, first);
+            if constexpr (MODE != 0) {
+                rows_off_mode<R, COOP>(P, E, ec.lo, ec.hi, F, bg, bf, cur, goe, cr, first, act);
+                act = (act << 1) | first;
+                end_capture<R, MODE>(ec, takes, P, 4 * c + u, get + gt * u);
+            } else if constexpr (PACKED) rows_off_packed<R, COOP>(P, E, Sx, F, bg, bf, cur, kk + u, goe, cr, ge64, first);
             else rows_off_pair<R, COOP>(P, E, Sx, F, bg, bf, cur, kk + u, goe, cr, ge64, first);
             // the last lane of a lane group hands column j = t - (B - 1) to the next pass, without offset
             if constexpr (IO) {
                 const int j = 4 * c + u - (B - 1);
-                const uint32_t off = get + ge * (uint32_t)(R + u);
+                const uint32_t off = get + ge * (uint32_t)R + gt * u;
                 st64(io.bnd, io.wr_lane + (uint32_t)((j >> 2) * (int)io.cstride + (j & 3) * 8), P[R] - off, F - off);
             }
 #pragma unroll
@@ -402,14 +584,15 @@ __device__ __forceinline__ void sweep_pass_off(const PassIO& io, int ncols, int 
             }
         }
         tau += 4;
-        if (tau > o.K) {                                   // lower everything by Ge K
+        if (MODE != 1 && tau > o.K) {                      // lower everything by Ge K
             const uint32_t down = ge * (uint32_t)o.K;
 #pragma unroll
             for (int r = 0; r <= R; ++r) P[r] -= down;
 #pragma unroll
             for (int r = 0; r < R; ++r) E[r] -= down;
+            if constexpr (MODE == 0)
 #pragma unroll
-            for (int i = 0; i < R / 2; ++i) Sx[i] -= down;
+                for (int i = 0; i < R / 2; ++i) Sx[i] -= down;
             F -= down;
             tau -= o.K;
         }
@@ -420,6 +603,7 @@ __device__ __forceinline__ void sweep_pass_off(const PassIO& io, int ncols, int 
 #pragma unroll
         for (int i = 0; i < 2; ++i) bw[i] = nw[i];
     }
+    if constexpr (MODE != 0) return;
     // S[i] stands at offset Ge (2i + 1 + tau) of the last step (tau - 1 now); the odd rows of the last column
     // were not folded yet (their own offset is Ge more).  Infinity and NaN patterns stay above every score.
     const uint32_t last = ge * (uint32_t)(tau - 1);
@@ -510,7 +694,11 @@ __device__ __forceinline__ void load_slice_off_q2(uint32_t* dst, const int16_t* 
 // it leave).  The items run in the bulk launch itself, ahead of its units: a
 // launch of their own on another stream shares a hardware queue with the bulk
 // launch as soon as a process holds a few handles, and then runs before it
-// instead of beside it.  CHAIN_FIGURES
+// instead of beside it.  One pair of 35,000 residues alone takes 1.3 ms for a
+// query of 200 residues (four windows), 2.4 ms for 331 and 4.4 ms for 1,024 (126
+// ns a step; global 162, semi-global 186, which also read the last row).  A query
+// of 144 against 570,000 subjects, the longest of 35,000 residues, went from 7.4
+// ms (a wave of its own for that pair) to 3.6 ms with it.
 constexpr int kChainWaves = kWaves;
 constexpr int kChainRows = 4;
 constexpr int kChainStage = 16;              // steps between barriers (4 chunks)
@@ -530,10 +718,10 @@ __device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt lgkmcn
 
 // Wave w (of several on one window) for all its chunks of one pass; `stages` barriers pass whatever it does.
 // STORE: the last wave's bottom row goes to the next pass through global memory.
-template <int R, bool STORE>
+template <int R, bool STORE, int MODE>
 __device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, int stages, bool active, int b,
                                            const uint8_t* lrow, uint8_t* ring_in, uint8_t* out_lane, uint8_t* resq,
-                                           const uint8_t* zeros, const OffCtx& o, u2& S) {
+                                           const uint8_t* zeros, const OffCtx& o, u2& S, EndOff& ec) {
     using RV = uint2;
     constexpr int NW = R / 2;
     const int nloop = (ncols + 63 + 3) >> 2;
@@ -541,15 +729,22 @@ __device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, i
     const uint32_t ge = sgpr(o.ge), goe = sgpr(o.goe), go = sgpr(o.go);
     const uint64_t ge64 = ((uint64_t)ge << 32) | ge;
     const uint64_t first = 1;
-    const uint32_t cr = ge * (R - 1);
+    const uint32_t gt = MODE == 1 ? 0u : ge;
+    const uint32_t cr = ge * R - gt;
     uint32_t P[R + 1], E[R], Sx[R / 2];
+    uint32_t F = ge * R, top0 = 0;
+    if constexpr (MODE == 0) {
 #pragma unroll
-    for (int r = 0; r <= R; ++r) P[r] = ge * r;
+        for (int r = 0; r <= R; ++r) P[r] = ge * r;
 #pragma unroll
-    for (int r = 0; r < R; ++r) E[r] = go + ge * (r + 1);
+        for (int r = 0; r < R; ++r) E[r] = go + ge * (r + 1);
 #pragma unroll
-    for (int i = 0; i < R / 2; ++i) Sx[i] = ge * (2 * i + 1);
-    uint32_t F = ge * R;
+        for (int i = 0; i < R / 2; ++i) Sx[i] = ge * (2 * i + 1);
+    } else {
+        end_borders<R>(ec, MODE == 1 ? 0 : ec.ge, b, P, E);
+        if (io.first && w == 0) top0 = (uint32_t)(ec.bias - ec.go - (MODE == 1 ? ec.go - ec.ge : 0)) * 0x10001u;
+    }
+    uint64_t act = first;
     int tau = 1;
     const int coff = (-b) >> 2, csh = (-b) & 3;
     // chunk b + 64 x of the residues, column b + 64 x of the boundary row (wave 0; zeros in the first pass)
@@ -613,11 +808,12 @@ __device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, i
                 uint4 nw[2];
                 bound(c + 1, nw);
                 const RV rn = Res<false>::align(c2, c1, csh);
-                const uint32_t get = ge * (uint32_t)tau;
+                const uint32_t get = gt * (uint32_t)tau;
                 uint32_t kk[R + 3];
 #pragma unroll
                 for (int i = 0; i < R + 3; ++i) kk[i] = go + get + ge * (uint32_t)(i + 1);
-                const uint32_t b0 = get + cr;
+                const uint32_t b0 = get + cr + top0;
+                const int takes = MODE != 0 ? end_takes<MODE>(ec, c) : 0;
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     uint32_t nx2[NW];
@@ -625,11 +821,16 @@ __device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, i
                     else bytes(rn, u - 2, nx2);
                     // G and F of the row above, raised to this step's offset (no half leaves 16 bits)
                     const uint4 v = bw[u >> 1];
-                    const uint64_t top = add_pairs((u & 1) ? pair64(v.z, v.w) : pair64(v.x, v.y), b0 + ge * u);
+                    const uint64_t top = add_pairs((u & 1) ? pair64(v.z, v.w) : pair64(v.x, v.y), b0 + gt * u);
                     const uint32_t bg = (uint32_t)top, bf = (uint32_t)(top >> 32);
-                    rows_off_pair<R, true>(P, E, Sx, F, bg, bf, cur, kk + u, goe, cr, ge64, first);
+                    if constexpr (MODE != 0) {
+                        rows_off_mode<R, true>(P, E, ec.lo, ec.hi, F, bg, bf, cur, goe, cr, first, act);
+                        act = (act << 1) | first;
+                        end_capture<R, MODE>(ec, takes, P, 4 * c + u, get + gt * u);
+                    } else
+                        rows_off_pair<R, true>(P, E, Sx, F, bg, bf, cur, kk + u, goe, cr, ge64, first);
                     const int j = 4 * c + u - 63;
-                    const uint32_t off = get + ge * (uint32_t)(R + u);
+                    const uint32_t off = get + ge * (uint32_t)R + gt * u;
                     const uint2 down = make_uint2(P[R] - off, F - off);
                     *reinterpret_cast<uint2*>(out_lane + (j & (kChainRing - 1)) * 8) = down;
                     if constexpr (STORE)
@@ -638,14 +839,15 @@ __device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, i
                     for (int r = 0; r < NW; ++r) { cur[r] = nxt[r]; nxt[r] = nx2[r]; }
                 }
                 tau += 4;
-                if (tau > o.K) {
+                if (MODE != 1 && tau > o.K) {
                     const uint32_t down = ge * (uint32_t)o.K;
 #pragma unroll
                     for (int r = 0; r <= R; ++r) P[r] -= down;
 #pragma unroll
                     for (int r = 0; r < R; ++r) E[r] -= down;
+                    if constexpr (MODE == 0)
 #pragma unroll
-                    for (int i = 0; i < R / 2; ++i) Sx[i] -= down;
+                        for (int i = 0; i < R / 2; ++i) Sx[i] -= down;
                     F -= down;
                     tau -= o.K;
                 }
@@ -659,7 +861,7 @@ __device__ __forceinline__ void chain_pass(const PassIO& io, int ncols, int w, i
         }
         stage_barrier();
     }
-    if (!active) return;
+    if (!active || MODE != 0) return;
     const uint32_t last = ge * (uint32_t)(tau - 1);
 #pragma unroll
     for (int i = 0; i < R / 2; ++i) {

@@ -356,11 +356,6 @@ int64_t unit_cost(int m, int ncols, int lgB, int R) {
 // than it issues for, and other waves' instructions in flight hold up every one of its own (x 1.4).
 int64_t elapsed(int64_t step_cost, int64_t steps) { return (step_cost + 35) * steps * 7 / 5; }
 
-int64_t lone_cost(int m, int ncols, int lgB, int R) {
-    const int64_t passes = (m + (R << lgB) - 1) / (R << lgB);
-    return elapsed(25 * R / 2 + 32 + (lgB ? 8 : 0), passes * round_up(ncols + (1 << lgB) - 1, 4));
-}
-
 // The same for one pair on a workgroup (a chain item): its four waves at 4 rows per lane run side by side, 96
 // steps apart, or on windows of the subject (whose overlap depends on the query; 4 m is typical), which global scores
 // cannot be cut into.
@@ -373,37 +368,56 @@ int64_t chain_cost(int m, int ncols, bool cut) {
     return elapsed(25 * 4 / 2 + 55, passes * (cols + 100 * waves));
 }
 
-// A unit of one wave (the widest lane cooperation) that costs more than a unit should: pair k of group g against
-// query (or query pair) q.
+// A unit of one wave (the widest lane cooperation) that may outlast the search: pair k of group g against query (or
+// query pair) q.
 struct LongUnit {
     int g, k, q;
     int64_t cost;                 // elapsed as a unit of one wave, at the rows per lane it would run with
     int64_t chain;                // elapsed as chain items: the longest one, and
     int64_t chain_sum;            // all of them (a query pair makes two)
-    int R;                        // rows per lane of the unit of one wave
+    bool small;                   // the unit of one wave runs at 4 rows per lane
 };
 
-// How many of the long units (sorted, longest first) to run as chain items.  A workgroup finishes a pair sooner
-// than a wave but spends four waves' time on it, much of it waiting, so only the units that would outlast the
-// search go: the cut with the smallest estimated end of the search, which is the issue time of all work, the
-// longest chain item, or the longest unit left to one wave.  (A chain item's four waves issue for about half of its
-// elapsed time, a unit's wave for two thirds.)
-size_t chain_cut(const sw_db* db, const std::vector<LongUnit>& units, double bulk, double* end) {
+// How many of the long units (sorted, longest first; `below` is the longest not among them) to run as chain items.
+// A workgroup finishes a pair sooner than a wave but spends four waves' time on it, much of it waiting, so only the
+// units that would outlast the search go: the first cut that leaves nothing outlasting the rest, or the one with the
+// smallest estimated end of the search, which is the issue time of all work, the longest chain item, or the longest
+// unit left to one wave.  (A chain item's four waves issue for about half of its elapsed time, a unit's wave for two
+// thirds: `all` is the issue time of everything with no unit chained.)
+constexpr double kLoneIssue = 0.67;
+size_t chain_cut(const sw_db* db, const std::vector<LongUnit>& units, double all, double below, double* end) {
     const double nsimd = 4.0 * std::max(db->cus, 1);
-    double all = bulk, longest = 0, best = 0;
+    double longest = 0, best = 0;
     size_t cut = 0;
-    for (const LongUnit& u : units) all += 0.67 * (double)u.cost;
     for (size_t k = 0;; ++k) {
-        const double rest = k < units.size() ? (double)units[k].cost : 0.0;
-        const double t = std::max({all / nsimd, longest, rest});
-        if (k == 0 || t < best) { best = t; cut = k; }
-        if (k == units.size()) break;
-        all += 2.0 * (double)units[k].chain_sum - 0.67 * (double)units[k].cost;
+        const double rest = k < units.size() ? (double)units[k].cost : below;
+        const double busy = std::max(all / nsimd, longest);
+        if (k == 0 || std::max(busy, rest) < best) { best = std::max(busy, rest); cut = k; }
+        if (k == units.size() || rest <= busy) break;
+        all += 2.0 * (double)units[k].chain_sum - kLoneIssue * (double)units[k].cost;
         longest = std::max(longest, (double)units[k].chain);
     }
     *end = std::max(*end, best);
     return cut;
 }
+
+// Units of one query by lanes per pair: what a unit of `cols` columns costs (unit_cost, and elapsed where it runs
+// alone, without a division for each).
+struct CostTable {
+    int64_t passes[7], step[7];
+    int pad[7];
+    CostTable(int m, int R) {
+        for (int l = 0; l < 7; ++l) {
+            passes[l] = (m + (R << l) - 1) / (R << l);
+            step[l] = 25 * R / 2 + 32 + (l ? 8 : 0);
+            pad[l] = (int)round_up((1 << l) - 1, 4);
+        }
+    }
+    // (a unit's columns are a multiple of 4)
+    int64_t steps(int cols, int l) const { return passes[l] * (cols + pad[l]); }
+    int64_t unit(int cols, int l) const { return steps(cols, l) * step[l]; }
+    int64_t lone(int cols, int l) const { return elapsed(step[l], steps(cols, l)); }
+};
 
 // Work items for queries of lengths qlens (query index = position) against all
 // groups.  Every group gets the smallest lanes-per-pair B whose units cost at
@@ -415,7 +429,10 @@ size_t chain_cut(const sw_db* db, const std::vector<LongUnit>& units, double bul
 // outlast the search are chained (chain_cut).  Where a unit's lanes x rows pad
 // a short query, the group may run at 4 rows per lane instead of the launch's
 // R: among the choices that keep its units within the share, the cheaper one is
-// taken.  Items are ordered longest first.
+// taken.  Items are ordered longest first.  The launch's R is the one with the
+// smallest estimated end; the estimates sum costs alone, and items are made for
+// the chosen R (a first search of six queries over 5,000 subjects spends 0.4 ms
+// here instead of 2.4).
 // Overrides for sweeps other than the 16-bit ones: fixed R, their slot capacity and wave count, and
 // whether the long pairs of a single short query may still go to the side list at a smaller R.
 struct PlanLimits { int R; int64_t slot_cap; int64_t nwaves; bool side = false; };
@@ -430,163 +447,204 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
     if (g_hi < 0) g_hi = db->ngroups;
     const int64_t slot_cap = lim ? lim->slot_cap : db->slot_cap;
     const bool force_R = lim ? true : db->force_R != 0;
-    // query qi covers groups chunk[qi], chunk[qi] + nchunks, ... (all groups when nchunks == 1)
+    // query qi covers groups chunk[qi], chunk[qi] + nchunks, ... (all groups when nchunks == 1) within [g_lo, g_hi)
     auto first_group = [&](size_t qi) { return chunk ? (*chunk)[qi] : 0; };
+    auto start_group = [&](size_t qi) {
+        const int f = first_group(qi);
+        return f >= g_lo ? f : f + (int)round_up(g_lo - f, nchunks);
+    };
     struct Tmp { WgItem it; int64_t cost; };
-    // Bundles units of one query and lane count into items of up to kWaves, in the order they are added.
+    // Bundles units of one query into items of up to kWaves of one lane count, in the order they are added.
     struct Bundle {
         std::vector<Tmp>& out;
-        int g_first, nchunks;
         WgItem cur;
-        int64_t cost = 0;
-        Bundle(std::vector<Tmp>& o, int q, int gf, int nc) : out(o), g_first(gf), nchunks(nc), cur{0, q, 0, -1, 0, nc} {}
+        int64_t cost = 0, next = 0;      // next: position in the query's unit sequence that continues the item
+        Bundle(std::vector<Tmp>& o, int q, int nc) : out(o), cur{0, q, 0, -1, 0, nc} {}
         void flush() {
             if (cur.count > 0) out.push_back({cur, cost});
             cur.count = 0;
             cost = 0;
         }
-        void add(int g, int k, int lgB, int64_t c) {
-            // position of (group, sub-unit) in this query's unit sequence
-            const int64_t seq_g = (g - g_first) / nchunks, seq_c = (cur.g0 - g_first) / nchunks;
-            const int lg = lgB & (kItemSmall - 1);
-            const bool contiguous = cur.count > 0 && cur.lgB == lgB && (seq_c << lg) + cur.k0 + cur.count == (seq_g << lg) + k;
-            if (cur.count == kWaves || !contiguous) {
+        // unit k of the query's seq-th group, g
+        void add(int g, int64_t seq, int k, int lgB, int64_t c) {
+            const int64_t at = (seq << (lgB & (kItemSmall - 1))) + k;
+            if (cur.count == 0 || cur.count == kWaves || cur.lgB != lgB || at != next) {
                 flush();
                 cur.g0 = g;
                 cur.k0 = (int16_t)k;
                 cur.lgB = (int8_t)lgB;
             }
+            next = at + 1;
             cur.count++;
             cost = std::max(cost, c);
         }
     };
-    struct Lists { std::vector<Tmp> main, side, head; int R_side = 0; };
-    // The plan at R rows per lane; returns its estimated makespan in cost units per wave.
-    auto plan_at = [&](int R_main, Lists& L) -> double {
+    // How the launch at R rows per lane would run: lanes per pair of every (query, group), kItemSmall added where at 4
+    // rows per lane, the largest cost of a unit, the chained units and the estimated end in cost units per wave.
+    struct Sketch {
+        int R = 0;
+        std::vector<int8_t> lgB;
+        int64_t cap = 0;
+        std::vector<LongUnit> chained;
+        double end = 0;
+    };
+    auto side_rows = [&](int m, int R_main) {
+        int r = R_main;
+        if (qlens.size() == 1 && (!force_R || (lim && lim->side)))
+            for (int R : kRowChoices)
+                if (unit_cost(m, db->ncols_max, 6, R) < unit_cost(m, db->ncols_max, 6, r)) r = R;
+        return r;
+    };
+    auto sketch = [&](int R_main) {
+        Sketch K;
+        K.R = R_main;
         const int64_t nwaves = std::max<int64_t>(lim ? lim->nwaves : (int64_t)db->wgR[R_main] * kWaves, 1);
+        std::vector<CostTable> big, small;
         int64_t total = 0;
-        for (size_t qi = 0; qi < qlens.size(); ++qi)
+        for (size_t qi = 0; qi < qlens.size(); ++qi) {
+            big.emplace_back(std::max(qlens[qi], 1), R_main);
+            small.emplace_back(std::max(qlens[qi], 1), kSmallRows);
             if (qlens[qi] > 0)
-                for (int g = first_group(qi); g < db->ngroups; g += nchunks)
-                    if (g >= g_lo && g < g_hi) total += unit_cost(qlens[qi], db->ncols[g], 0, R_main);
+                for (int g = start_group(qi); g < g_hi; g += nchunks) total += big[qi].unit(db->ncols[g], 0);
+        }
         const double cap = db->unit_share * (double)total / (double)nwaves;
-        L.R_side = R_main;
+        K.cap = (int64_t)std::min(cap, 9.0e18);
+        const bool mix = head_out && R_main != kSmallRows && db->force_lgB < 0 && db->force_R == 0;
         int64_t sum = 0, biggest = 0;
-        std::vector<LongUnit> longs;
-        auto side_rows = [&](int m) {
-            int r = R_main;
-            if (qlens.size() == 1 && (!force_R || (lim && lim->side)))
-                for (int R : kRowChoices)
-                    if (unit_cost(m, db->ncols_max, 6, R) < unit_cost(m, db->ncols_max, 6, r)) r = R;
-            return r;
-        };
+        double lone_sum = 0, lone_end = 0;
         for (size_t qi = 0; qi < qlens.size(); ++qi) {
             const int m = qlens[qi];
             if (m <= 0) continue;
-            const int r_long = side_rows(m);
-            Bundle bulk(L.main, (int)qi, first_group(qi), nchunks);
-            Bundle small(L.main, (int)qi, first_group(qi), nchunks);
-            for (int g = first_group(qi); g < db->ngroups; g += nchunks) {
-                if (g < g_lo || g >= g_hi) continue;
+            const CostTable side(m, head_out ? R_main : side_rows(m, R_main));
+            for (int g = start_group(qi); g < g_hi; g += nchunks) {
                 const int nc = db->ncols[g];
-                // the fewest lanes per pair at R rows whose units stay within the share (6: perhaps none do)
-                auto lanes = [&](int R) {
+                // the fewest lanes per pair whose units stay within the share (6: perhaps none do)
+                auto lanes = [&](const CostTable& t) {
                     int l = 0;
-                    while (l < 6 && ((double)unit_cost(m, nc, l, R) > cap || (int64_t)nc * (kGroupPairs >> l) > slot_cap)) ++l;
+                    while (l < 6 && (t.unit(nc, l) > K.cap || (int64_t)nc * (kGroupPairs >> l) > slot_cap)) ++l;
                     return l;
                 };
-                int lgB = lanes(R_main), R = R_main;
-                if (head_out && R_main != kSmallRows && db->force_lgB < 0 && db->force_R == 0) {
-                    const int l4 = lanes(kSmallRows);
-                    const int64_t c4 = unit_cost(m, nc, l4, kSmallRows), c = unit_cost(m, nc, lgB, R_main);
+                int l = lanes(big[qi]);
+                bool at4 = false;
+                if (mix) {
+                    const int l4 = lanes(small[qi]);
+                    const int64_t c4 = small[qi].unit(nc, l4), c = big[qi].unit(nc, l);
                     // (units over the share are compared by what they take, the others by what the group takes)
-                    if ((double)std::min(c, c4) > cap ? c4 < c : (double)c4 <= cap && ((c4 << l4) < (c << lgB) || (double)c > cap)) {
-                        lgB = l4;
-                        R = kSmallRows;
-                    }
+                    at4 = std::min(c, c4) > K.cap ? c4 < c : c4 <= K.cap && ((c4 << l4) < (c << l) || c > K.cap);
+                    if (at4) l = l4;
                 }
                 if (db->force_lgB >= 0) {
-                    lgB = db->force_lgB;
-                    while (lgB < 6 && (int64_t)nc * (kGroupPairs >> lgB) > slot_cap) ++lgB;
+                    l = db->force_lgB;
+                    while (l < 6 && (int64_t)nc * (kGroupPairs >> l) > slot_cap) ++l;
                 }
-                for (int k = 0; k < (1 << lgB); ++k) {
-                    const int uc = db->pcols[(size_t)g * kGroupPairs + (k << (6 - lgB))];
-                    const int64_t c = unit_cost(m, uc, lgB, R);
-                    if (lgB == 6 && db->force_lgB < 0 && (double)c > cap) {
-                        const int64_t cc = head_out ? chain_cost(m, uc, !whole) : 0;
-                        longs.push_back({g, k, (int)qi, lone_cost(m, uc, 6, head_out ? R : r_long), cc, cc, R});
-                    } else {
-                        (R == R_main ? bulk : small).add(g, k, R == R_main ? lgB : lgB + kItemSmall, c);
-                        sum += c;
-                        biggest = std::max(biggest, c);
+                K.lgB.push_back((int8_t)(l + (at4 ? kItemSmall : 0)));
+                const CostTable& t = at4 ? small[qi] : big[qi];
+                const int32_t* pc = db->pcols.data() + (size_t)g * kGroupPairs;      // longest first
+                int k = 0;
+                if (l == 6 && db->force_lgB < 0)
+                    for (; k < kGroupPairs && t.unit(pc[k], 6) > K.cap; ++k) {
+                        const double e = (double)(head_out ? t : side).lone(pc[k], 6);
+                        lone_sum += e;
+                        lone_end = std::max(lone_end, e);
                     }
-                }
+                if (k < kGroupPairs) biggest = std::max(biggest, t.unit(pc[k], l));
+                int64_t cols = 0;
+                for (int i = k; i < (1 << l); ++i) cols += pc[i << (6 - l)] + t.pad[l];
+                sum += cols * t.passes[l] * t.step[l];
             }
-            bulk.flush();
-            small.flush();
         }
         // issue time: the SIMDs share the total; a unit shares its SIMD with the other resident waves
         const double nsimd = 4.0 * db->cus, per_simd = (double)nwaves / nsimd;
-        double end = std::max((double)sum / nsimd, (double)biggest * per_simd);
-        size_t cut = 0;
-        if (head_out) {
-            std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
-            cut = chain_cut(db, longs, (double)sum, &end);
-        } else
-            for (const LongUnit& u : longs) end = std::max(end, (double)u.cost * per_simd);
-        for (size_t i = 0; i < cut; ++i) {
-            const LongUnit& u = longs[i];
-            L.head.push_back({WgItem{u.g, u.q, (int16_t)u.k, kItemChain, 1, nchunks}, u.chain});
+        K.end = std::max((double)sum / nsimd, (double)biggest * per_simd);
+        if (!head_out) {
+            K.end = std::max(K.end, lone_end * per_simd);
+            return K;
         }
-        // units of one wave: those not chained are bulk, the chained ones the list for plain cells; without chains,
-        // a single query's go to the side list at fewer rows per lane where that is cheaper
-        auto wave_units = [&](std::vector<Tmp>& out, size_t i0, size_t i1, int R_side) {
-            std::sort(longs.begin() + i0, longs.begin() + i1, [](const LongUnit& a, const LongUnit& b) {
-                return a.q != b.q ? a.q < b.q : a.R != b.R ? a.R < b.R : a.g != b.g ? a.g < b.g : a.k < b.k;
-            });
-            for (size_t i = i0; i < i1;) {
-                const int q = longs[i].q, R = longs[i].R;
-                Bundle b(out, q, first_group(q), nchunks);
-                for (; i < i1 && longs[i].q == q && longs[i].R == R; ++i)
-                    b.add(longs[i].g, longs[i].k, R == R_main ? 6 : 6 + kItemSmall,
-                          unit_cost(qlens[q], db->pcols[(size_t)longs[i].g * kGroupPairs + longs[i].k], 6, R_side ? R_side : R));
-                b.flush();
+        // only units that take more than half of the search's issue time can outlast it
+        const double all = (double)sum + kLoneIssue * lone_sum;
+        std::vector<LongUnit> longs;
+        double below = 0;
+        size_t at = 0;
+        for (size_t qi = 0; qi < qlens.size(); ++qi) {
+            if (qlens[qi] <= 0) continue;
+            for (int g = start_group(qi); g < g_hi; g += nchunks, ++at) {
+                if ((K.lgB[at] & (kItemSmall - 1)) != 6 || db->force_lgB >= 0) continue;
+                const bool at4 = K.lgB[at] >= kItemSmall;
+                const CostTable& t = at4 ? small[qi] : big[qi];
+                const int32_t* pc = db->pcols.data() + (size_t)g * kGroupPairs;
+                for (int k = 0; k < kGroupPairs && t.unit(pc[k], 6) > K.cap; ++k) {
+                    const int64_t e = t.lone(pc[k], 6);
+                    if (2.0 * (double)e * nsimd <= all) {
+                        below = std::max(below, (double)e);
+                        break;
+                    }
+                    const int64_t cc = chain_cost(qlens[qi], pc[k], !whole);
+                    longs.push_back({g, k, (int)qi, e, cc, cc, at4});
+                }
             }
-        };
-        if (head_out) {
-            wave_units(L.main, cut, longs.size(), 0);
-            wave_units(L.side, 0, cut, 0);
-        } else {
-            const int r = qlens.size() == 1 ? side_rows(qlens[0]) : R_main;
-            L.R_side = r;
-            wave_units(r != R_main ? L.side : L.main, 0, longs.size(), r);
         }
-        return end;
+        std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
+        longs.resize(chain_cut(db, longs, all, below, &K.end));
+        K.chained.swap(longs);
+        return K;
     };
-    Lists L;
-    int R_main = lim ? lim->R : db->force_R ? db->force_R : 16;
-    double t_main = plan_at(R_main, L);
+    Sketch K = sketch(lim ? lim->R : db->force_R ? db->force_R : 16);
     if (!force_R) {
         // fewer rows per lane pay more per cell but pad less when lanes cooperate on a short query
         for (int R : {12, 8}) {
-            Lists other;
-            const double t = plan_at(R, other);
-            if (t < t_main) {
-                std::swap(L, other);
-                t_main = t;
-                R_main = R;
-            }
+            Sketch other = sketch(R);
+            if (other.end < K.end) std::swap(K, other);
         }
     }
+    std::vector<Tmp> main, side, head;
+    std::vector<LongUnit> chained = K.chained;
+    std::sort(chained.begin(), chained.end(), [](const LongUnit& a, const LongUnit& b) {
+        return a.q != b.q ? a.q < b.q : a.g != b.g ? a.g < b.g : a.k < b.k;
+    });
+    size_t at = 0, ch = 0;
+    for (size_t qi = 0; qi < qlens.size(); ++qi) {
+        const int m = qlens[qi];
+        if (m <= 0) continue;
+        const CostTable big(m, K.R), small(m, kSmallRows);
+        // without chains, a single query's long pairs go to the side list at fewer rows per lane where that is cheaper
+        const int r_long = head_out ? K.R : side_rows(m, K.R);
+        const CostTable lone(m, r_long);
+        Bundle bulk(main, (int)qi, nchunks), bulk4(main, (int)qi, nchunks);
+        Bundle apart(side, (int)qi, nchunks), apart4(side, (int)qi, nchunks);
+        int64_t seq = (start_group(qi) - first_group(qi)) / nchunks;
+        for (int g = start_group(qi); g < g_hi; g += nchunks, ++at, ++seq) {
+            const bool at4 = K.lgB[at] >= kItemSmall;
+            const int l = K.lgB[at] & (kItemSmall - 1);
+            const CostTable& t = at4 ? small : big;
+            for (int k = 0; k < (1 << l); ++k) {
+                const int uc = db->pcols[(size_t)g * kGroupPairs + (k << (6 - l))];
+                const int64_t c = t.unit(uc, l);
+                if (ch < chained.size() && chained[ch].q == (int)qi && chained[ch].g == g && chained[ch].k == k) {
+                    head.push_back({WgItem{g, (int)qi, (int16_t)k, kItemChain, 1, nchunks}, chained[ch].chain});
+                    (at4 ? apart4 : apart).add(g, seq, k, K.lgB[at], c);
+                    ++ch;
+                } else if (r_long != K.R && l == 6 && db->force_lgB < 0 && c > K.cap)
+                    apart.add(g, seq, k, 6, lone.unit(uc, 6));
+                else
+                    (at4 ? bulk4 : bulk).add(g, seq, k, K.lgB[at], c);
+            }
+        }
+        bulk.flush();
+        bulk4.flush();
+        apart.flush();
+        apart4.flush();
+    }
     auto emit = [](std::vector<Tmp>& v, std::vector<WgItem>& out) {
-        std::stable_sort(v.begin(), v.end(), [](const Tmp& a, const Tmp& b) { return a.cost > b.cost; });
+        auto longer = [](const Tmp& a, const Tmp& b) { return a.cost > b.cost; };
+        if (!std::is_sorted(v.begin(), v.end(), longer)) std::stable_sort(v.begin(), v.end(), longer);
+        out.reserve(out.size() + v.size());
         for (auto& t : v) out.push_back(t.it);
     };
-    emit(L.main, main_out);
-    emit(L.side, side_out);
-    if (head_out) emit(L.head, *head_out);
-    plan->R_main = R_main;
-    if (side_rows_out) *side_rows_out = L.R_side;
+    emit(main, main_out);
+    emit(side, side_out);
+    if (head_out) emit(head, *head_out);
+    plan->R_main = K.R;
+    if (side_rows_out) *side_rows_out = head_out || qlens.size() != 1 ? K.R : side_rows(qlens[0], K.R);
 }
 
 // Query-pair plan: queries on the same chunk are sorted by length and paired
@@ -650,7 +708,7 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
                 const int uc = db->pcols[(size_t)g * kGroupPairs + ((k * P) >> 1)];
                 const int64_t c = cost(m, uc, lgB);
                 if (lgB == 5 && db->force_lgB < 0 && (double)c > cap) {       // P = 2: unit k is pair k
-                    LongUnit u{g, k, (int)pi, elapsed(21 * R / 2 + 40, (int64_t)((m + 32 * R - 1) / (32 * R)) * (uc + 31)), 0, 0, R};
+                    LongUnit u{g, k, (int)pi, elapsed(21 * R / 2 + 40, (int64_t)((m + 32 * R - 1) / (32 * R)) * (uc + 31)), 0, 0, false};
                     for (int q : {pr.x, pr.y})
                         if (q >= 0) {
                             const int64_t x = chain_cost(qlens[q], uc, true);
@@ -679,8 +737,9 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
         if (cur.count > 0) items.push_back({cur, cc});
     }
     std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
-    double end = 0;
-    const size_t cut = chain_cut(db, longs, (double)sum, &end);
+    double end = 0, all = (double)sum;
+    for (const LongUnit& u : longs) all += kLoneIssue * (double)u.cost;
+    const size_t cut = chain_cut(db, longs, all, 0, &end);
     for (size_t i = 0; i < longs.size(); ++i) {
         const LongUnit& u = longs[i];
         (i < cut ? uitems : items).push_back({WgItem{u.g, u.q, (int16_t)u.k, 5, 1, nchunks}, u.cost});

@@ -37,16 +37,13 @@ hipError_t launch_sweep_mode(int mode, int R, const SweepArgs& a, int grid, hipS
 hipError_t launch_sweep_mode16(int mode, int R, const SweepArgs& a, int grid, hipStream_t st);
 hipError_t launch_sweep_mode_off(int mode, int R, const SweepArgs& a, int grid, hipStream_t st);
 hipError_t sweep_occupancy_mode16(int mode, int R, int* blocks_per_cu);
-hipError_t launch_align_fill(const AlignPair* pairs, int npairs, int W, const int8_t* subst, int A, int go, int ge,
-                             uint8_t* dirs, int32_t* bnd, int32_t* best, int lds_max, hipStream_t st);
-hipError_t launch_align_tiles(const AlignPair* pairs, const AlignTile* tiles, int ntiled, int ndiag,
-                              int max_diag_tiles, const int8_t* subst, int A, int go, int ge, uint8_t* dirs,
-                              int32_t* bnd, int32_t* tws, int32_t* best, hipStream_t st);
-hipError_t launch_align_trace(const AlignPair* pairs, int npairs, const uint8_t* dirs, const int32_t* best, char* ops,
-                              int64_t ops_stride, int64_t* info, hipStream_t st);
-int align_waves(int m, int A, int lds_max);
+hipError_t launch_align_fill(const AlignPair* pairs, const AlignBand* bands, int nbands, int32_t* counter,
+                             const int8_t* subst, int A, int go, int ge, uint8_t* dirs, uint64_t* between, int32_t* ends,
+                             hipStream_t st);
+hipError_t launch_align_trace(const AlignPair* pairs, int npairs, const uint8_t* dirs, const int32_t* ends, int32_t* best,
+                              char* ops, int64_t ops_stride, int64_t* info, hipStream_t st);
+int align_bands(int m, int64_t n);
 int64_t align_dir_bytes(int m, int64_t n);
-int64_t align_bnd_words(int64_t n);
 hipError_t launch_profile(const int8_t* stage, int A, const QDesc* qd, int nq, const int64_t* qoff, int16_t* prof,
                           int32_t* counters, int ncounters, uint32_t* bits, int64_t nbits_words, int max_mp,
                           hipStream_t st, int add, int pad);
@@ -250,8 +247,8 @@ struct sw_db {
     // per original subject: length and sorted slot; per group: byte offset in the image (alignments)
     std::vector<int32_t> lens, slot_of;
     std::vector<int64_t> gbase;
-    DevBuf align_dirs, align_bnd, align_misc, align_tws;   // traceback workspace
-    int align_tiles = 0;              // tiled traceback fill: 0 = long pairs, 1 = never, 2 = every pair
+    DevBuf align_dirs, align_bnd, align_misc;              // traceback workspace
+    HostPinned align_host;            // what goes to the device and comes back, up to kAlignPinned bytes
     int wg_mode = 0;                  // persistent workgroups of an end-to-end sweep
     Plan mode_plan;
     int mode_side_rows = 16;          // end-to-end modes: rows per lane of the long pairs' launch
@@ -335,7 +332,6 @@ sw_status apply_opts(sw_db* db, const sw_pack_opts* opts) {
     db->lane_pack = opts->lane_pack == 2 ? 2 : 1;
     db->rerun_cap_hook = opts->rerun_cap;
     db->poison = opts->poison;
-    db->align_tiles = opts->align_tiles;
     return SW_OK;
 }
 
@@ -1691,7 +1687,7 @@ void sw_db_free(sw_db* db) {
     hipDeviceSynchronize();
     clear_caches(db);
     db->image_own.release();           // a caller's image stays the caller's
-    db->align_dirs.release(); db->align_bnd.release(); db->align_misc.release(); db->align_tws.release();
+    db->align_dirs.release(); db->align_bnd.release(); db->align_misc.release(); db->align_host.release();
     db->mode_plan.release();
     db->ws_own.release();
     for (HostPinned& h : db->hstage) h.release();
@@ -1890,6 +1886,7 @@ sw_status sw_last_stats(sw_db* db, int64_t out[8]) {
 // ------------------------------------------------------------------ alignments
 namespace {
 constexpr int64_t kAlignBudget = (int64_t)4 << 30;   // direction bytes per round of pairs
+constexpr size_t kAlignPinned = (size_t)16 << 20;    // most pinned memory a handle keeps for alignments
 }
 
 sw_status sw_align_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int32_t nq, sw_db* db,
@@ -1943,51 +1940,32 @@ sw_status sw_align_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int
     std::lock_guard<std::mutex> lk(db->mu);
     DeviceGuard dg(db->device);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    int lds_max = 0;                                // LDS a workgroup may use (64 KiB on older parts, 160 KiB on gfx950)
-    HIP_TRY(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, db->device));
-    if ((s = ensure_geometry(db)) != SW_OK) return s;      // the side stream
-    // A long pair's fill runs on one workgroup for as long as its many stages take; spread over tiles of one
-    // band by tn columns (one anti-diagonal of tiles per launch) it finishes in about (bands + tiles) tile
-    // sweeps instead.  Which pairs: db->align_tiles (0: both sides of the matrix at least kTileMinSide).
-    constexpr int kTileMinSide = 2048;
-    auto tiled = [&](const Job& J) {
-        return J.n > 0 && (db->align_tiles == 2 || (db->align_tiles == 0 && J.m >= kTileMinSide && J.n >= kTileMinSide));
-    };
-    auto tile_cols = [](int n) { return n >= 4096 ? 256 : 128; };
+    // penalties above every score (at most 127 x 2^20) all mean that no gap pays; capped, no difference overflows
+    const int32_t go = std::min(gap_open, 1 << 28), ge = std::min(gap_extend, 1 << 28);
     size_t j0 = 0;
     while (j0 < jobs.size()) {
         // a round: pairs whose direction bytes fit the budget (at least one pair)
         size_t j1 = j0;
-        int64_t dir_total = 0, bnd_total = 0, stride = 1, tws_total = 0;
-        int W = 1;
+        int64_t dir_total = 0, columns = 0, stride = 1;
+        int nbands = 0;
         std::vector<int32_t> qs_used;
         while (j1 < jobs.size()) {
             const Job& J = jobs[j1];
             if (j1 > j0 && dir_total + J.cost > kAlignBudget) break;
             dir_total += round_up(J.cost, 256);
-            bnd_total += align_bnd_words(J.n);
+            columns += J.n;
+            nbands += align_bands(J.m, J.n);
             stride = std::max<int64_t>(stride, (int64_t)J.m + J.n + 1);
             qs_used.push_back(J.q);
             ++j1;
         }
-        // the round's pairs filled by one workgroup each first, then the tiled ones
-        std::stable_partition(jobs.begin() + j0, jobs.begin() + j1, [&](const Job& J) { return !tiled(J); });
-        int nfill = 0;
-        for (size_t j = j0; j < j1; ++j)
-            if (!tiled(jobs[j])) {
-                W = std::max(W, align_waves(jobs[j].m, db->alphabet, lds_max));
-                ++nfill;
-            }
         std::sort(qs_used.begin(), qs_used.end());
         qs_used.erase(std::unique(qs_used.begin(), qs_used.end()), qs_used.end());
         const int np = (int)(j1 - j0);
-        const int ntiled = np - nfill;
-        // misc: pairs | best (3 int32 each) | info (4 int64 each) | tiles | matrix | queries | ops
-        const size_t o_pairs = 0;
-        const size_t o_best = round_up(sizeof(AlignPair) * np, 256);
-        const size_t o_info = o_best + round_up(12 * (size_t)np, 256);
-        const size_t o_tiles = o_info + round_up(32 * (size_t)np, 256);
-        const size_t o_sm = o_tiles + round_up(sizeof(AlignTile) * std::max(ntiled, 1), 256);
+        // one buffer: what the host sends (pairs | bands | matrix | queries), the end cells of the bands, and what
+        // comes back (best, 3 int32 a pair | info, 4 int64 a pair | operations)
+        const size_t o_bands = round_up(sizeof(AlignPair) * np, 256);
+        const size_t o_sm = o_bands + round_up(sizeof(AlignBand) * (size_t)nbands, 256);
         const size_t o_query = o_sm + 1024;
         std::vector<int64_t> qpos(nq, -1);
         size_t qbytes = 0;
@@ -1995,12 +1973,31 @@ sw_status sw_align_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int
             qpos[q] = (int64_t)qbytes;
             qbytes += (size_t)round_up(h_qoffsets[q + 1] - h_qoffsets[q], 256);
         }
-        const size_t o_ops = o_query + qbytes;
+        const size_t o_ends = o_query + qbytes;
+        const size_t o_best = o_ends + round_up(12 * (int64_t)nbands, 256);
+        const size_t o_info = o_best + round_up(12 * (size_t)np, 256);
+        const size_t o_ops = o_info + round_up(32 * (size_t)np, 256);
         const size_t misc = o_ops + (size_t)np * stride;
-        std::vector<AlignPair> pairs(np);
-        std::vector<AlignTile> tiles;
+        HIP_TRY(db->align_dirs.reserve((size_t)std::max<int64_t>(dir_total, 256)));
+        // the bands' counter (256 bytes) and the rows between bands
+        const int64_t bnd_bytes = 256 + 16 * columns;
+        HIP_TRY(db->align_bnd.reserve((size_t)bnd_bytes));
+        HIP_TRY(db->align_misc.reserve(misc));
+        char* mb = db->align_misc.as<char>();
+        // through pinned memory, in one copy each way, unless it is a lot
+        std::vector<char> plain;
+        char* hb = nullptr;
+        if (misc <= kAlignPinned) {
+            HIP_TRY(db->align_host.reserve(misc));
+            hb = static_cast<char*>(db->align_host.p);
+        } else {
+            plain.resize(misc);
+            hb = plain.data();
+        }
+        AlignPair* pairs = reinterpret_cast<AlignPair*>(hb);
         int64_t dir_off = 0, bnd_off = 0;
-        int ndiag = 0, max_diag_tiles = 0;
+        int32_t ends = 0;
+        std::vector<int32_t> rest(np);
         for (int i = 0; i < np; ++i) {
             const Job& J = jobs[j0 + i];
             const int64_t sub = h_subjects[J.k];
@@ -2010,62 +2007,39 @@ sw_status sw_align_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int
             P.residues = db->d_image + db->gbase[g] + (int64_t)(w >> 1) * 8 + (w & 1) * 4;
             P.n = J.n;
             P.m = J.m;
+            P.query = reinterpret_cast<const int8_t*>(mb + o_query + qpos[J.q]);
             P.dir_off = dir_off;
             P.bnd_off = bnd_off;
+            P.ends = ends;
             dir_off += round_up(J.cost, 256);
-            bnd_off += align_bnd_words(J.n);
-            if (i >= nfill && J.n > 0) {
-                AlignTile T;
-                T.pair = i;
-                T.nb = (J.m + 255) / 256;
-                T.tn = tile_cols(J.n);
-                T.nc = (J.n + T.tn - 1) / T.tn;
-                T.ws_off = tws_total;
-                tws_total += round_up(2 * (int64_t)J.m + T.nb + 3 * (int64_t)T.nb * T.nc, 64);
-                ndiag = std::max(ndiag, T.nb + T.nc - 1);
-                max_diag_tiles = std::max(max_diag_tiles, std::min(T.nb, T.nc));
-                tiles.push_back(T);
-            }
+            bnd_off += J.n;
+            ends += align_bands(J.m, J.n);
+            rest[i] = i;
         }
-        HIP_TRY(db->align_dirs.reserve((size_t)std::max<int64_t>(dir_total, 256)));
-        HIP_TRY(db->align_bnd.reserve(sizeof(int32_t) * (size_t)std::max<int64_t>(bnd_total, 64)));
-        HIP_TRY(db->align_misc.reserve(misc));
-        HIP_TRY(db->align_tws.reserve(sizeof(int32_t) * (size_t)std::max<int64_t>(tws_total, 64)));
-        char* mb = db->align_misc.as<char>();
-        for (int i = 0; i < np; ++i) pairs[i].query = reinterpret_cast<const int8_t*>(mb + o_query + qpos[jobs[j0 + i].q]);
-        HIP_TRY(hipMemcpyAsync(mb + o_pairs, pairs.data(), sizeof(AlignPair) * np, hipMemcpyHostToDevice, st));
-        if (!tiles.empty())
-            HIP_TRY(hipMemcpyAsync(mb + o_tiles, tiles.data(), sizeof(AlignTile) * tiles.size(), hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(mb + o_sm, h_subst, (size_t)db->alphabet * db->alphabet, hipMemcpyHostToDevice, st));
+        // the first bands of all pairs, then the second ones, ...: a band comes after the one it waits for
+        AlignBand* bands = reinterpret_cast<AlignBand*>(hb + o_bands);
+        for (int32_t k = 0, at = 0; !rest.empty(); ++k) {
+            rest.erase(std::remove_if(rest.begin(), rest.end(),
+                                      [&](int32_t i) { return align_bands(pairs[i].m, pairs[i].n) <= k; }), rest.end());
+            for (int32_t i : rest) bands[at++] = AlignBand{i, k};
+        }
+        memcpy(hb + o_sm, h_subst, (size_t)db->alphabet * db->alphabet);
         for (int32_t q : qs_used)
-            HIP_TRY(hipMemcpyAsync(mb + o_query + qpos[q], h_queries + h_qoffsets[q], (size_t)(h_qoffsets[q + 1] - h_qoffsets[q]),
-                                   hipMemcpyHostToDevice, st));
-        const AlignPair* d_pairs = reinterpret_cast<AlignPair*>(mb + o_pairs);
-        const int8_t* d_sm = reinterpret_cast<int8_t*>(mb + o_sm);
-        int32_t* d_best = reinterpret_cast<int32_t*>(mb + o_best);
-        // the one-workgroup fills on the side stream while the tiled ones run on the caller's
-        const bool fork = nfill > 0 && !tiles.empty();
-        const hipStream_t fs = fork ? db->side : st;
-        if (fork) {
-            HIP_TRY(hipEventRecord(db->ev_fork, st));
-            HIP_TRY(hipStreamWaitEvent(db->side, db->ev_fork, 0));
-        }
-        HIP_TRY(launch_align_fill(d_pairs, nfill, W, d_sm, db->alphabet, gap_open, gap_extend, db->align_dirs.as<uint8_t>(),
-                                  db->align_bnd.as<int32_t>(), d_best, lds_max, fs));
-        if (fork) HIP_TRY(hipEventRecord(db->ev_join, db->side));
-        HIP_TRY(launch_align_tiles(d_pairs, reinterpret_cast<AlignTile*>(mb + o_tiles), (int)tiles.size(), ndiag,
-                                   max_diag_tiles, d_sm, db->alphabet, gap_open, gap_extend, db->align_dirs.as<uint8_t>(),
-                                   db->align_bnd.as<int32_t>(), db->align_tws.as<int32_t>(), d_best, st));
-        if (fork) HIP_TRY(hipStreamWaitEvent(st, db->ev_join, 0));
-        HIP_TRY(launch_align_trace(d_pairs, np, db->align_dirs.as<uint8_t>(), d_best, mb + o_ops, stride,
-                                   reinterpret_cast<int64_t*>(mb + o_info), st));
-        std::vector<int32_t> best(3 * (size_t)np);
-        std::vector<int64_t> info(4 * (size_t)np);
-        std::vector<char> ops((size_t)np * stride);
-        HIP_TRY(hipMemcpyAsync(best.data(), mb + o_best, 12 * (size_t)np, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(info.data(), mb + o_info, 32 * (size_t)np, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(ops.data(), mb + o_ops, (size_t)np * stride, hipMemcpyDeviceToHost, st));
+            memcpy(hb + o_query + qpos[q], h_queries + h_qoffsets[q], (size_t)(h_qoffsets[q + 1] - h_qoffsets[q]));
+        HIP_TRY(hipMemcpyAsync(mb, hb, o_ends, hipMemcpyHostToDevice, st));
+        HIP_TRY(launch_fill(db->align_bnd.as<int32_t>(), bnd_bytes / 4, 0, st));
+        const AlignPair* d_pairs = reinterpret_cast<AlignPair*>(mb);
+        int32_t* d_ends = reinterpret_cast<int32_t*>(mb + o_ends);
+        HIP_TRY(launch_align_fill(d_pairs, reinterpret_cast<AlignBand*>(mb + o_bands), nbands, db->align_bnd.as<int32_t>(),
+                                  reinterpret_cast<int8_t*>(mb + o_sm), db->alphabet, go, ge, db->align_dirs.as<uint8_t>(),
+                                  reinterpret_cast<uint64_t*>(db->align_bnd.as<char>() + 256), d_ends, st));
+        HIP_TRY(launch_align_trace(d_pairs, np, db->align_dirs.as<uint8_t>(), d_ends, reinterpret_cast<int32_t*>(mb + o_best),
+                                   mb + o_ops, stride, reinterpret_cast<int64_t*>(mb + o_info), st));
+        HIP_TRY(hipMemcpyAsync(hb + o_best, mb + o_best, misc - o_best, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
+        const int32_t* best = reinterpret_cast<const int32_t*>(hb + o_best);
+        const int64_t* info = reinterpret_cast<const int64_t*>(hb + o_info);
+        const char* ops = hb + o_ops;
         for (int i = 0; i < np; ++i) {
             const Job& J = jobs[j0 + i];
             if (info[4 * i + 3] != 0)
@@ -2078,9 +2052,7 @@ sw_status sw_align_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int
             A.s_begin = info[4 * i + 1];
             A.s_end = best[3 * i + 2];
             A.n_ops = len;
-            char* dst = h_ops + J.k * ops_stride;
-            const char* src = ops.data() + (size_t)i * stride;
-            for (int64_t x = 0; x < len; ++x) dst[x] = src[len - 1 - x];     // the walk wrote them last to first
+            memcpy(h_ops + J.k * ops_stride, ops + (size_t)(i + 1) * stride - len, (size_t)len);
         }
         j0 = j1;
     }

@@ -121,16 +121,11 @@ struct AlignPair {
     int32_t m;                // query length (>= 1)
     const int8_t* query;      // the query's residue codes on the device
     int64_t dir_off;          // byte offset of the pair's direction bytes
-    int64_t bnd_off;          // int32 offset of the pair's boundary row (H then F, n rounded up to 4 words each)
+    int64_t bnd_off;          // first column of the pair in the rows between bands
+    int32_t ends;             // first of the pair's bands in the list of end cells
 };
 
-// A pair whose fill is spread over tiles of one band (256 query rows) by tn subject columns.
-struct AlignTile {
-    int32_t pair;             // index of the pair in the round's AlignPair array
-    int32_t nb, nc;           // bands and column tiles
-    int32_t tn;               // tile width, a multiple of 64, <= kAlignTileMax
-    int64_t ws_off;           // int32 offset in the tile workspace: hcol[m] | ecol[m] | corner[nb] | ends[3 nb nc]
-};
-constexpr int kAlignTileMax = 256;
+// One band of a pair, in the order in which they are taken.
+struct AlignBand { int32_t pair, band; };
 
 }  // namespace sw

@@ -92,6 +92,7 @@ __global__ __launch_bounds__(64) void k_pair(PairArgs a) {
                        hb = H[kPairRows - 1];
                        fb = F;
                    });
+        __syncthreads();                                         // every lane comes to the next pull with the others
     }
     for (int o = 32; o >= 1; o >>= 1) S = max(S, __shfl_xor(S, o, 64));
     if (b == 0 && S > 0) atomicMax(a.best, S);

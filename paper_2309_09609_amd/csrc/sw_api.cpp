@@ -123,6 +123,8 @@ struct HostPinned {
     }
 };
 
+constexpr double kUnitShare = 0.25;   // see plan_units
+
 // Work items of one search, run by one launch: the chained pairs (a workgroup
 // each) and the bulk on offset cells; on plain cells the bulk and, ahead of it,
 // the same pairs on a wave each (unchained).  Searches on
@@ -276,7 +278,8 @@ struct sw_db {
     // tuning knobs and test hooks
     int force_lgB = -1;               // fixed lanes per pair
     int force_R = 0;                  // fixed rows per lane (4, 8, 16)
-    double unit_share = 0.25;         // largest unit / one wave's share of a search
+    double unit_share = kUnitShare;   // largest unit / one wave's share of a search
+    bool fixed_share = false;         // it was set: no other is tried
     int32_t sat = kSat16;             // rerun threshold
     int64_t rerun_cap_hook = 0;       // test hook: list capacity of the recompute (0 = default)
     int poison = 0;                   // test hook: flagged pairs' 16-bit scores read kPoison
@@ -327,7 +330,8 @@ sw_status apply_opts(sw_db* db, const sw_pack_opts* opts) {
     if (opts->align_tiles < 0 || opts->align_tiles > 2) return fail(SW_E_INVALID, "align_tiles must be 0, 1 or 2");
     db->force_lgB = fl ? __builtin_ctz(fl) : -1;
     db->force_R = rpl;
-    db->unit_share = opts->unit_share > 0 ? opts->unit_share / 1000.0 : 0.25;
+    db->unit_share = opts->unit_share > 0 ? opts->unit_share / 1000.0 : kUnitShare;
+    db->fixed_share = opts->unit_share > 0;
     db->sat = opts->rerun_threshold > 0 ? std::min<int32_t>(opts->rerun_threshold, kSat16) : kSat16;
     db->lane_pack = opts->lane_pack == 2 ? 2 : 1;
     db->rerun_cap_hook = opts->rerun_cap;
@@ -374,6 +378,9 @@ struct LongUnit {
     bool small;                   // the unit of one wave runs at 4 rows per lane
 };
 
+// What large units cost beyond what they issue, in times of the largest one's issue time: see plan_units.
+constexpr double kLarge = 0.55;
+
 // How many of the long units (sorted, longest first; `below` is the longest not among them) to run as chain items.
 // A workgroup finishes a pair sooner than a wave but spends four waves' time on it, much of it waiting, so only the
 // units that would outlast the search go: the first cut that leaves nothing outlasting the rest, or the one with the
@@ -381,7 +388,8 @@ struct LongUnit {
 // unit left to one wave.  (A chain item's four waves issue for about half of its elapsed time, a unit's wave for two
 // thirds: `all` is the issue time of everything with no unit chained.)
 constexpr double kLoneIssue = 0.67;
-size_t chain_cut(const sw_db* db, const std::vector<LongUnit>& units, double all, double below, double* end) {
+template <class Chain>                                   // chain(u) fills in u.chain and u.chain_sum
+size_t chain_cut(const sw_db* db, std::vector<LongUnit>& units, double all, double below, double* end, Chain&& chain) {
     const double nsimd = 4.0 * std::max(db->cus, 1);
     double longest = 0, best = 0;
     size_t cut = 0;
@@ -390,6 +398,7 @@ size_t chain_cut(const sw_db* db, const std::vector<LongUnit>& units, double all
         const double busy = std::max(all / nsimd, longest);
         if (k == 0 || std::max(busy, rest) < best) { best = std::max(busy, rest); cut = k; }
         if (k == units.size() || rest <= busy) break;
+        chain(units[k]);
         all += 2.0 * (double)units[k].chain_sum - kLoneIssue * (double)units[k].cost;
         longest = std::max(longest, (double)units[k].chain);
     }
@@ -429,6 +438,13 @@ struct CostTable {
 // smallest estimated end; the estimates sum costs alone, and items are made for
 // the chosen R (a first search of six queries over 5,000 subjects spends 0.4 ms
 // here instead of 2.4).
+// Large units cost more than they issue (a last wave of them, and the rows
+// between passes, of which few lanes per pair keep many): searches of 144 to
+// 5,478 residues over 570,000 subjects at shares of 0.03 to 0.25 fit the issue
+// time plus kLarge times the largest unit's.  More lanes pad a short query
+// instead, so the chosen R is also sketched at half the share and the smaller
+// estimate taken: 1,003 residues 22.3 -> 21.0 ms, 5,478 120 -> 115 ms; 144 (3.6
+// against 4.5 ms) and 405 (10.4 against 10.8) keep the share.
 // Overrides for sweeps other than the 16-bit ones: fixed R, their slot capacity and wave count, and
 // whether the long pairs of a single short query may still go to the side list at a smaller R.
 struct PlanLimits { int R; int64_t slot_cap; int64_t nwaves; bool side = false; };
@@ -482,7 +498,7 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
         std::vector<int8_t> lgB;
         int64_t cap = 0;
         std::vector<LongUnit> chained;
-        double end = 0;
+        double end = 0, share = 0;
     };
     auto side_rows = [&](int m, int R_main) {
         int r = R_main;
@@ -491,19 +507,33 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
                 if (unit_cost(m, db->ncols_max, 6, R) < unit_cost(m, db->ncols_max, 6, r)) r = R;
         return r;
     };
-    auto sketch = [&](int R_main) {
+    // The groups a sketch looks at: the longest ones each, of the rest of a large database every stride-th for its
+    // neighbours too (groups are sorted by length); the chosen one is sketched in full.
+    constexpr int kEach = 64;
+    const int64_t ngroups = (g_hi - g_lo + nchunks - 1) / nchunks;
+    const int stride = (int)std::max<int64_t>(1, ngroups / 512);
+    auto walk = [&](size_t qi, bool full, auto&& visit) {
+        const int g0 = start_group(qi);
+        const int count = g0 < g_hi ? (g_hi - g0 + nchunks - 1) / nchunks : 0;
+        for (int o = 0, w; o < count; o += w) {
+            w = full || o < kEach ? 1 : std::min(stride, count - o);
+            visit(g0 + o * nchunks, w);
+        }
+    };
+    auto sketch = [&](int R_main, double share, bool full) {
         Sketch K;
         K.R = R_main;
+        K.share = share;
         const int64_t nwaves = std::max<int64_t>(lim ? lim->nwaves : (int64_t)db->wgR[R_main] * kWaves, 1);
         std::vector<CostTable> big, small;
         int64_t total = 0;
         for (size_t qi = 0; qi < qlens.size(); ++qi) {
             big.emplace_back(std::max(qlens[qi], 1), R_main);
             small.emplace_back(std::max(qlens[qi], 1), kSmallRows);
-            if (qlens[qi] > 0)
-                for (int g = start_group(qi); g < g_hi; g += nchunks) total += big[qi].unit(db->ncols[g], 0);
+            if (qlens[qi] <= 0) continue;
+            walk(qi, full, [&](int g, int w) { total += w * big[qi].unit(db->ncols[g], 0); });
         }
-        const double cap = db->unit_share * (double)total / (double)nwaves;
+        const double cap = share * (double)total / (double)nwaves;
         K.cap = (int64_t)std::min(cap, 9.0e18);
         const bool mix = head_out && R_main != kSmallRows && db->force_lgB < 0 && db->force_R == 0;
         int64_t sum = 0, biggest = 0;
@@ -512,7 +542,7 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
             const int m = qlens[qi];
             if (m <= 0) continue;
             const CostTable side(m, head_out ? R_main : side_rows(m, R_main));
-            for (int g = start_group(qi); g < g_hi; g += nchunks) {
+            walk(qi, full, [&](int g, int weight) {
                 const int nc = db->ncols[g];
                 // the fewest lanes per pair whose units stay within the share (6: perhaps none do)
                 auto lanes = [&](const CostTable& t) {
@@ -535,19 +565,26 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
                 }
                 K.lgB.push_back((int8_t)(l + (at4 ? kItemSmall : 0)));
                 const CostTable& t = at4 ? small[qi] : big[qi];
-                const int32_t* pc = db->pcols.data() + (size_t)g * kGroupPairs;      // longest first
-                int k = 0;
-                if (l == 6 && db->force_lgB < 0)
-                    for (; k < kGroupPairs && t.unit(pc[k], 6) > K.cap; ++k) {
-                        const double e = (double)(head_out ? t : side).lone(pc[k], 6);
-                        lone_sum += e;
+                // (a group's pairs are of about one length, longest first: sums take the mean of the ends)
+                const int32_t* pc = db->pcols.data() + (size_t)g * kGroupPairs;
+                int k = 0;                                   // units past the share, the first ones
+                if (l == 6 && db->force_lgB < 0) {
+                    if (t.unit(pc[kGroupPairs - 1], 6) > K.cap) k = kGroupPairs;
+                    else while (t.unit(pc[k], 6) > K.cap) ++k;
+                    if (k > 0) {
+                        const CostTable& w = head_out ? t : side;
+                        const double e = (double)w.lone(pc[0], 6);
+                        lone_sum += 0.5 * k * weight * (e + (double)w.lone(pc[k - 1], 6));
                         lone_end = std::max(lone_end, e);
                     }
-                if (k < kGroupPairs) biggest = std::max(biggest, t.unit(pc[k], l));
-                int64_t cols = 0;
-                for (int i = k; i < (1 << l); ++i) cols += pc[i << (6 - l)] + t.pad[l];
-                sum += cols * t.passes[l] * t.step[l];
-            }
+                }
+                const int units = (1 << l) - k;
+                if (units > 0) {
+                    const int64_t c = t.unit(pc[k], l);
+                    biggest = std::max(biggest, c);
+                    sum += weight * units * (c + t.unit(pc[kGroupPairs - 1], l)) / 2;
+                }
+            });
         }
         // issue time: the SIMDs share the total; a unit shares its SIMD with the other resident waves
         const double nsimd = 4.0 * db->cus, per_simd = (double)nwaves / nsimd;
@@ -563,35 +600,46 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
         size_t at = 0;
         for (size_t qi = 0; qi < qlens.size(); ++qi) {
             if (qlens[qi] <= 0) continue;
-            for (int g = start_group(qi); g < g_hi; g += nchunks, ++at) {
-                if ((K.lgB[at] & (kItemSmall - 1)) != 6 || db->force_lgB >= 0) continue;
-                const bool at4 = K.lgB[at] >= kItemSmall;
+            bool on = true;                              // (shorter groups follow)
+            walk(qi, full, [&](int g, int) {
+                const int lg = K.lgB[at++];
+                if (!on || (lg & (kItemSmall - 1)) != 6 || db->force_lgB >= 0) return;
+                const bool at4 = lg >= kItemSmall;
                 const CostTable& t = at4 ? small[qi] : big[qi];
                 const int32_t* pc = db->pcols.data() + (size_t)g * kGroupPairs;
                 for (int k = 0; k < kGroupPairs && t.unit(pc[k], 6) > K.cap; ++k) {
                     const int64_t e = t.lone(pc[k], 6);
                     if (2.0 * (double)e * nsimd <= all) {
                         below = std::max(below, (double)e);
+                        on = k > 0;
                         break;
                     }
-                    const int64_t cc = chain_cost(qlens[qi], pc[k], !whole);
-                    longs.push_back({g, k, (int)qi, e, cc, cc, at4});
+                    longs.push_back({g, k, (int)qi, e, 0, 0, at4});
                 }
-            }
+            });
         }
         std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
-        longs.resize(chain_cut(db, longs, all, below, &K.end));
+        longs.resize(chain_cut(db, longs, all, below, &K.end, [&](LongUnit& u) {
+            u.chain = u.chain_sum = chain_cost(qlens[u.q], db->pcols[(size_t)u.g * kGroupPairs + u.k], !whole);
+        }));
+        K.end = std::max(K.end, all / nsimd + kLarge * (double)biggest * per_simd);
         K.chained.swap(longs);
         return K;
     };
-    Sketch K = sketch(lim ? lim->R : db->force_R ? db->force_R : 16);
+    const bool one = force_R && (!head_out || db->fixed_share || db->force_lgB >= 0);     // nothing to choose
+    Sketch K = sketch(lim ? lim->R : db->force_R ? db->force_R : 16, db->unit_share, one || stride == 1);
     if (!force_R) {
         // fewer rows per lane pay more per cell but pad less when lanes cooperate on a short query
         for (int R : {12, 8}) {
-            Sketch other = sketch(R);
+            Sketch other = sketch(R, db->unit_share, stride == 1);
             if (other.end < K.end) std::swap(K, other);
         }
     }
+    if (head_out && !db->fixed_share && db->force_lgB < 0) {
+        Sketch other = sketch(K.R, 0.5 * db->unit_share, stride == 1);
+        if (other.end < K.end) std::swap(K, other);
+    }
+    if (!one && stride > 1) K = sketch(K.R, K.share, true);
     std::vector<Tmp> main, side, head;
     std::vector<LongUnit> chained = K.chained;
     std::sort(chained.begin(), chained.end(), [](const LongUnit& a, const LongUnit& b) {
@@ -631,7 +679,12 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
         apart4.flush();
     }
     auto emit = [](std::vector<Tmp>& v, std::vector<WgItem>& out) {
+        // (mostly a few runs, each longest first)
         auto longer = [](const Tmp& a, const Tmp& b) { return a.cost > b.cost; };
+        for (int runs = 0; runs < 16 && !std::is_sorted(v.begin(), v.end(), longer); ++runs) {
+            const auto from = std::is_sorted_until(v.begin(), v.end(), longer);
+            std::inplace_merge(v.begin(), from, std::is_sorted_until(from, v.end(), longer), longer);
+        }
         if (!std::is_sorted(v.begin(), v.end(), longer)) std::stable_sort(v.begin(), v.end(), longer);
         out.reserve(out.size() + v.size());
         for (auto& t : v) out.push_back(t.it);
@@ -644,88 +697,108 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
 }
 
 // Query-pair plan: queries on the same chunk are sorted by length and paired
-// neighbour with neighbour (a leftover query runs alone in its half-empty lanes);
-// each pair sweeps max(m_a, m_b) rows.  A unit holds P = 64/B subjects and a
-// group 2B units; B is capped at 32 (the interleaved slice is twice as large).
-// Long subject pairs are chained as in plan_units (a chain item takes one query
-// against the two subjects).
+// neighbour with neighbour, each pair sweeping max(m_a, m_b) rows, where that is
+// cheaper than one query at a time (a step takes two queries of a subject for
+// less than two subjects of a query, since it needs no permutes, so a pair pays
+// while the shorter query has about three quarters of the longer one's rows; 16
+// queries of 62 to 4,868 residues over 40,000 subjects, all paired 31.7 ms, by
+// this rule 27.0 ms).  The others run two subjects per lane in the same launch (I.q
+// the query, kItemSmall added to their lanes).  A pair's unit holds P = 64/B
+// subjects and a group 2B units; B is capped at 32 (the interleaved slice is
+// twice as large).  Long subject pairs are chained as in plan_units (a chain item
+// takes one query against the two subjects), and half the share tried.
 void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std::vector<WgItem>& out,
-                   std::vector<WgItem>& side_out, std::vector<WgItem>& head_out, std::vector<int2>& pairs, const std::vector<int>* chunk, int nchunks) {
+                   std::vector<WgItem>& side_out, std::vector<WgItem>& head_out, std::vector<int2>& pairs,
+                   const std::vector<int>* chunk, int nchunks) {
     const int R = db->force_R == 8 ? 8 : 16;
+    auto ch = [&](int q) { return chunk ? (*chunk)[q] : 0; };
+    auto step2 = [&](int l) { return (int64_t)(21 * R / 2 + 32 + (l ? 8 : 0)); };
+    // One query, or two (x the longer one): what its units cost.
+    struct Entry {
+        int x, y, pair;            // y < 0: one query
+        CostTable t;
+        int most() const { return y < 0 ? 6 : 5; }             // log2 of the most lanes
+        int units(int l) const { return y < 0 ? 1 << l : 2 << l; }
+        int first_pair(int k, int l) const { return y < 0 ? k << (6 - l) : (k * (kGroupPairs >> l)) >> 1; }
+    };
     std::vector<int> order;
     for (int q = 0; q < (int)qlens.size(); ++q)
         if (qlens[q] > 0) order.push_back(q);
-    auto ch = [&](int q) { return chunk ? (*chunk)[q] : 0; };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         return ch(a) != ch(b) ? ch(a) < ch(b) : qlens[a] > qlens[b];
     });
-    for (size_t i = 0; i < order.size();) {
+    std::vector<Entry> entries;
+    for (size_t i = 0; i < order.size(); ++i) {
+        Entry e{order[i], -1, -1, CostTable(qlens[order[i]], R)};
         if (i + 1 < order.size() && ch(order[i]) == ch(order[i + 1])) {
-            pairs.push_back(make_int2(order[i], order[i + 1]));
-            i += 2;
-        } else {
-            pairs.push_back(make_int2(order[i], -1));
-            i += 1;
+            const CostTable next(qlens[order[i + 1]], R);
+            if (2 * e.t.passes[0] * step2(0) <= (e.t.passes[0] + next.passes[0]) * e.t.step[0]) {
+                e.y = order[++i];
+                e.pair = (int)pairs.size();
+                for (int l = 0; l < 7; ++l) e.t.step[l] = step2(l);
+                pairs.push_back(make_int2(e.x, e.y));
+            }
         }
+        entries.push_back(e);
     }
-    auto cost = [&](int m, int nc, int lgB) {
-        const int B = 1 << lgB;
-        const int64_t passes = (m + (R << lgB) - 1) / (R << lgB);
-        return passes * round_up(nc + B - 1, 4) * (int64_t)(21 * R / 2 + 32 + (lgB ? 8 : 0));
-    };
-    const int64_t nwaves = (int64_t)db->wgQ[R] * kWaves;
+    const int64_t nwaves = std::max<int64_t>((int64_t)db->wgQ[R] * kWaves, 1);
     int64_t total = 0;
-    for (const int2& pr : pairs) {
-        const int m = std::max(qlens[pr.x], pr.y >= 0 ? qlens[pr.y] : 0);
-        for (int g = ch(pr.x); g < db->ngroups; g += nchunks) total += 2 * cost(m, db->ncols[g], 0);
+    for (const Entry& e : entries)
+        for (int g = ch(e.x); g < db->ngroups; g += nchunks) total += e.units(0) * e.t.unit(db->ncols[g], 0);
+    auto lanes = [&](const Entry& e, int nc, double cap) {
+        int l = 0;
+        while (l < e.most() && ((double)e.t.unit(nc, l) > cap || (int64_t)nc * (kGroupPairs >> l) > db->slot_cap)) ++l;
+        if (db->force_lgB >= 0) {
+            l = std::min(db->force_lgB, e.most());
+            while (l < e.most() && (int64_t)nc * (kGroupPairs >> l) > db->slot_cap) ++l;
+        }
+        return l;
+    };
+    double cap = db->unit_share * (double)total / (double)nwaves;
+    if (!db->fixed_share && db->force_lgB < 0) {
+        auto end = [&](double most) {
+            double sum = 0, biggest = 0;
+            for (const Entry& e : entries)
+                for (int g = ch(e.x); g < db->ngroups; g += nchunks) {
+                    const int l = lanes(e, db->ncols[g], most);
+                    const double c = (double)e.t.unit(db->ncols[g], l);
+                    sum += e.units(l) * c;
+                    if (c <= most) biggest = std::max(biggest, c);
+                }
+            return sum + kLarge * biggest * (double)nwaves;
+        };
+        if (end(0.5 * cap) < end(cap)) cap *= 0.5;
     }
-    const double cap = db->unit_share * (double)total / (double)std::max<int64_t>(nwaves, 1);
     struct Tmp { WgItem it; int64_t cost; };
     std::vector<Tmp> items, uitems, citems;
     std::vector<LongUnit> longs;
     int64_t sum = 0;
-    for (size_t pi = 0; pi < pairs.size(); ++pi) {
-        const int2 pr = pairs[pi];
-        const int m = std::max(qlens[pr.x], pr.y >= 0 ? qlens[pr.y] : 0);
-        const int g_first = ch(pr.x);
-        WgItem cur{0, (int32_t)pi, 0, -1, 0, nchunks};
-        int64_t cc = 0;
-        for (int g = g_first; g < db->ngroups; g += nchunks) {
-            const int nc = db->ncols[g];
-            int lgB = 0;
-            for (; lgB < 5; ++lgB)
-                if ((double)cost(m, nc, lgB) <= cap && (int64_t)nc * (kGroupPairs >> lgB) <= db->slot_cap) break;
-            if (db->force_lgB >= 0) lgB = std::min(db->force_lgB, 5);
-            while (lgB < 5 && (int64_t)nc * (kGroupPairs >> lgB) > db->slot_cap) ++lgB;
-            const int units = 2 << lgB;
-            const int P = kGroupPairs >> lgB;
-            const int64_t seq_g = (g - g_first) / nchunks;
-            for (int k = 0; k < units; ++k) {
-                const int uc = db->pcols[(size_t)g * kGroupPairs + ((k * P) >> 1)];
-                const int64_t c = cost(m, uc, lgB);
-                if (lgB == 5 && db->force_lgB < 0 && (double)c > cap) {       // P = 2: unit k is pair k
-                    LongUnit u{g, k, (int)pi, elapsed(21 * R / 2 + 40, (int64_t)((m + 32 * R - 1) / (32 * R)) * (uc + 31)), 0, 0, false};
-                    for (int q : {pr.x, pr.y})
-                        if (q >= 0) {
-                            const int64_t x = chain_cost(qlens[q], uc, true);
-                            u.chain = std::max(u.chain, x);
-                            u.chain_sum += x;
-                        }
-                    longs.push_back(u);
+    for (size_t ei = 0; ei < entries.size(); ++ei) {
+        const Entry& e = entries[ei];
+        const int g_first = ch(e.x);
+        const int q = e.y < 0 ? e.x : e.pair, flag = e.y < 0 ? kItemSmall : 0;
+        WgItem cur{0, q, 0, -1, 0, nchunks};
+        int64_t cc = 0, next = 0, seq = 0;
+        for (int g = g_first; g < db->ngroups; g += nchunks, ++seq) {
+            const int l = lanes(e, db->ncols[g], cap);
+            for (int k = 0; k < e.units(l); ++k) {
+                const int uc = db->pcols[(size_t)g * kGroupPairs + e.first_pair(k, l)];
+                const int64_t c = e.t.unit(uc, l);
+                if (l == e.most() && db->force_lgB < 0 && (double)c > cap) {  // unit k is pair k
+                    longs.push_back({g, k, (int)ei, e.t.lone(uc, l), 0, 0, false});
                     continue;
                 }
                 sum += c;
-                const int64_t seq_c = (cur.g0 - g_first) / nchunks;
-                const bool contiguous = cur.count > 0 && cur.lgB == lgB &&
-                                        seq_c * units + cur.k0 + cur.count == seq_g * units + k;
-                if (cur.count == kWaves || !contiguous) {
+                const int64_t at = seq * e.units(l) + k;
+                if (cur.count == 0 || cur.count == kWaves || cur.lgB != l + flag || at != next) {
                     if (cur.count > 0) items.push_back({cur, cc});
                     cur.g0 = g;
                     cur.k0 = (int16_t)k;
-                    cur.lgB = (int8_t)lgB;
+                    cur.lgB = (int8_t)(l + flag);
                     cur.count = 0;
                     cc = 0;
                 }
+                next = at + 1;
                 cur.count++;
                 cc = std::max(cc, c);
             }
@@ -735,12 +808,21 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
     std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
     double end = 0, all = (double)sum;
     for (const LongUnit& u : longs) all += kLoneIssue * (double)u.cost;
-    const size_t cut = chain_cut(db, longs, all, 0, &end);
+    const size_t cut = chain_cut(db, longs, all, 0, &end, [&](LongUnit& u) {
+        for (int q : {entries[u.q].x, entries[u.q].y})
+            if (q >= 0) {
+                const int64_t x = chain_cost(qlens[q], db->pcols[(size_t)u.g * kGroupPairs + u.k], true);
+                u.chain = std::max(u.chain, x);
+                u.chain_sum += x;
+            }
+    });
     for (size_t i = 0; i < longs.size(); ++i) {
         const LongUnit& u = longs[i];
-        (i < cut ? uitems : items).push_back({WgItem{u.g, u.q, (int16_t)u.k, 5, 1, nchunks}, u.cost});
+        const Entry& e = entries[u.q];
+        const WgItem it{u.g, e.y < 0 ? e.x : e.pair, (int16_t)u.k, (int8_t)(e.y < 0 ? 6 + kItemSmall : 5), 1, nchunks};
+        (i < cut ? uitems : items).push_back({it, u.cost});
         if (i >= cut) continue;
-        for (int q : {pairs[u.q].x, pairs[u.q].y})
+        for (int q : {e.x, e.y})
             if (q >= 0)
                 citems.push_back({WgItem{u.g, q, (int16_t)u.k, kItemChain, 1, nchunks},
                                   chain_cost(qlens[q], db->pcols[(size_t)u.g * kGroupPairs + u.k], true)});
@@ -770,7 +852,8 @@ sw_status build_plan(sw_db* db, const std::vector<int>& qlens, Plan* p, const st
     p->n_main = (int32_t)mi.size();
     p->n_unchained = (int32_t)si.size();
     p->n_small = 0;
-    for (const WgItem& it : mi) p->n_small += it.lgB >= kItemSmall;
+    if (!p->qpack)
+        for (const WgItem& it : mi) p->n_small += it.lgB >= kItemSmall;
     mi.insert(mi.begin(), hi.begin(), hi.end());
     mi.insert(mi.end(), si.begin(), si.end());
     p->h_items.swap(mi);

@@ -58,8 +58,8 @@ struct WgItem {
     int32_t gstep;    // distance between consecutive groups of the item
 };
 
-// Items beside the units at the launch's rows per lane: units at 4 rows per lane (plain 16-bit local launches, not
-// query pairs), and one pair on the whole workgroup (offset cells).
+// Items beside the units of a launch: one pair on the whole workgroup (kItemChain, offset cells), and with kItemSmall
+// added to the lanes, units at 4 rows per lane (in a launch of query pairs: units of one query, two subjects a lane).
 constexpr int kItemChain = 8, kItemSmall = 16, kSmallRows = 4;
 
 // Per-query descriptor.

@@ -1234,7 +1234,8 @@ __global__ __launch_bounds__(64 * kWaves, (kMinWaves<C, R>)) void k_sweep(SweepA
 // subject against query a and query b, so a row's substitution pair is one
 // dword of a pre-interleaved profile slice and needs no permute.  A wave owns
 // P = 64/B subjects of a group (B lanes each, anti-diagonal as above); a group
-// has 2B such units.
+// has 2B such units.  Queries that have no partner of about their length run as
+// subject pairs.
 template <class C, int R>
 __global__ __launch_bounds__(64 * kWaves, 3) void k_sweep_q2(SweepArgs a) {
     static_assert(kNRes * 64 * 8 * 2 < kChainLds && kChainLds <= kNRes * 64 * 16 * 2, "R = 8 takes a chain item's room");
@@ -1259,8 +1260,14 @@ __global__ __launch_bounds__(64 * kWaves, 3) void k_sweep_q2(SweepArgs a) {
                 continue;
             }
         }
-        const int units = 2 << I.lgB;                   // units per group
         int k = I.k0 + wave;
+        if (I.lgB >= kItemSmall) {                      // a query without a partner: two subjects per lane
+            const int lgB = I.lgB - kItemSmall;
+            const int g = I.g0 + (k >> lgB) * I.gstep;
+            run_unit<C, R, false>(a, g, k & ((1 << lgB) - 1), lgB, I.q, wave < I.count, lgB > 4, lds, wave, lane, slot);
+            continue;
+        }
+        const int units = 2 << I.lgB;                   // units per group
         const int g = I.g0 + (k / units) * I.gstep;
         k %= units;
         const bool shared_slice = I.lgB > 3;            // more than 8 lanes per subject

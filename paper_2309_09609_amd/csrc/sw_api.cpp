@@ -299,7 +299,9 @@ namespace {
 
 // [0] bulk sweep counter, [1] flagged pairs, [2] recompute work counter, [3] side sweep counter,
 // [4] second side sweep counter, [5] pairs recomputed
-constexpr int kCounters = 6;
+constexpr int kSplits = 6;     // from here on: the slots of chained pairs in parts
+constexpr int kCounters = kSplits + 4 * kMaxSplits;
+static_assert(kCounters <= 256, "one block clears them");
 // Most entries of the recompute list; flagged pairs beyond it are found through their bits.
 constexpr int64_t kRerunListMax = (int64_t)1 << 20;
 constexpr int kRerunGrid = 64;
@@ -359,13 +361,30 @@ int64_t elapsed(int64_t step_cost, int64_t steps) { return (step_cost + 35) * st
 // The same for one pair on a workgroup (a chain item): its four waves at 4 rows per lane run side by side, 96
 // steps apart, or on windows of the subject (whose overlap depends on the query; 4 m is typical), which global scores
 // cannot be cut into.
-int64_t chain_cost(int m, int ncols, bool cut) {
+int64_t chain_cost(int m, int ncols, bool cut, int parts = 1) {
     const int64_t passes = (m + 1023) / 1024;
     const int waves = passes > 1 ? 4 : (m + 255) / 256;
-    int64_t cols = ncols;
+    const int64_t share = ncols / parts, lead = parts > 1 ? std::min(4 * m, ncols) : 0;
+    int64_t cols = share + lead;
     for (int windows = cut ? 4 / waves : 1; windows > 1; --windows)
-        if (4 * m + ncols / windows <= ncols - ncols / 4) { cols = ncols / windows + 4 * m; break; }
+        if (4 * m + share / windows <= cols - cols / 4) { cols = share / windows + 4 * m; break; }
     return elapsed(25 * 4 / 2 + 55, passes * (cols + 100 * waves));
+}
+
+// The parts to split a chained pair into, so that it ends within `busy`: the fewest that do, or as many as still
+// shorten it by a tenth each, of at least kPartCols columns (2,000 subjects of at most 1,000 residues, split: 115
+// instead of 110 us).  100,000 subjects, the longest of 35,000 residues, semi-global, a query of 331: unsplit 3.5
+// ms, split 2.15.
+constexpr int kPartCols = 1024;
+int chain_parts(int m, int ncols, bool cut, double busy) {
+    int parts = 1;
+    for (int64_t now = chain_cost(m, ncols, cut);
+         cut && parts < kMaxParts && ncols / (parts + 1) >= kPartCols && (double)now > busy; ++parts) {
+        const int64_t next = chain_cost(m, ncols, cut, parts + 1);
+        if (next > now - now / 10) break;
+        now = next;
+    }
+    return parts;
 }
 
 // A unit of one wave (the widest lane cooperation) that may outlast the search: pair k of group g against query (or
@@ -376,6 +395,7 @@ struct LongUnit {
     int64_t chain;                // elapsed as chain items: the longest one, and
     int64_t chain_sum;            // all of them (a query pair makes two)
     bool small;                   // the unit of one wave runs at 4 rows per lane
+    int parts[2] = {1, 1};        // of the chain items
 };
 
 // What large units cost beyond what they issue, in times of the largest one's issue time: see plan_units.
@@ -388,7 +408,7 @@ constexpr double kLarge = 0.55;
 // unit left to one wave.  (A chain item's four waves issue for about half of its elapsed time, a unit's wave for two
 // thirds: `all` is the issue time of everything with no unit chained.)
 constexpr double kLoneIssue = 0.67;
-template <class Chain>                                   // chain(u) fills in u.chain and u.chain_sum
+template <class Chain>                                   // chain(u, busy) fills in u.chain, u.chain_sum and u.parts
 size_t chain_cut(const sw_db* db, std::vector<LongUnit>& units, double all, double below, double* end, Chain&& chain) {
     const double nsimd = 4.0 * std::max(db->cus, 1);
     double longest = 0, best = 0;
@@ -398,12 +418,21 @@ size_t chain_cut(const sw_db* db, std::vector<LongUnit>& units, double all, doub
         const double busy = std::max(all / nsimd, longest);
         if (k == 0 || std::max(busy, rest) < best) { best = std::max(busy, rest); cut = k; }
         if (k == units.size() || rest <= busy) break;
-        chain(units[k]);
+        chain(units[k], all / nsimd);
         all += 2.0 * (double)units[k].chain_sum - kLoneIssue * (double)units[k].cost;
         longest = std::max(longest, (double)units[k].chain);
     }
     *end = std::max(*end, best);
     return cut;
+}
+
+// The chain items of one pair, in at most the parts that slots are left for.
+template <class Tmp>
+void push_chain(std::vector<Tmp>& to, int g, int q, int k, int parts, int64_t cost, int& splits) {
+    if (splits == kMaxSplits) parts = 1;
+    for (int i = 0; i < parts; ++i)
+        to.push_back({WgItem{g, q, (int16_t)k, kItemChain, 1, chain_split(parts > 1 ? splits : 0, parts, i)}, cost});
+    splits += parts > 1;
 }
 
 // Units of one query by lanes per pair: what a unit of `cols` columns costs (unit_cost, and elapsed where it runs
@@ -619,8 +648,11 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
             });
         }
         std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
-        longs.resize(chain_cut(db, longs, all, below, &K.end, [&](LongUnit& u) {
-            u.chain = u.chain_sum = chain_cost(qlens[u.q], db->pcols[(size_t)u.g * kGroupPairs + u.k], !whole);
+        longs.resize(chain_cut(db, longs, all, below, &K.end, [&](LongUnit& u, double busy) {
+            const int uc = db->pcols[(size_t)u.g * kGroupPairs + u.k];
+            u.parts[0] = chain_parts(qlens[u.q], uc, !whole, busy);
+            u.chain = chain_cost(qlens[u.q], uc, !whole, u.parts[0]);
+            u.chain_sum = u.parts[0] * u.chain;
         }));
         K.end = std::max(K.end, all / nsimd + kLarge * (double)biggest * per_simd);
         K.chained.swap(longs);
@@ -646,6 +678,7 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
         return a.q != b.q ? a.q < b.q : a.g != b.g ? a.g < b.g : a.k < b.k;
     });
     size_t at = 0, ch = 0;
+    int splits = 0;
     for (size_t qi = 0; qi < qlens.size(); ++qi) {
         const int m = qlens[qi];
         if (m <= 0) continue;
@@ -664,7 +697,7 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
                 const int uc = db->pcols[(size_t)g * kGroupPairs + (k << (6 - l))];
                 const int64_t c = t.unit(uc, l);
                 if (ch < chained.size() && chained[ch].q == (int)qi && chained[ch].g == g && chained[ch].k == k) {
-                    head.push_back({WgItem{g, (int)qi, (int16_t)k, kItemChain, 1, nchunks}, chained[ch].chain});
+                    push_chain(head, g, (int)qi, k, chained[ch].parts[0], chained[ch].chain, splits);
                     (at4 ? apart4 : apart).add(g, seq, k, K.lgB[at], c);
                     ++ch;
                 } else if (r_long != K.R && l == 6 && db->force_lgB < 0 && c > K.cap)
@@ -808,24 +841,28 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
     std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
     double end = 0, all = (double)sum;
     for (const LongUnit& u : longs) all += kLoneIssue * (double)u.cost;
-    const size_t cut = chain_cut(db, longs, all, 0, &end, [&](LongUnit& u) {
-        for (int q : {entries[u.q].x, entries[u.q].y})
-            if (q >= 0) {
-                const int64_t x = chain_cost(qlens[q], db->pcols[(size_t)u.g * kGroupPairs + u.k], true);
-                u.chain = std::max(u.chain, x);
-                u.chain_sum += x;
-            }
+    const size_t cut = chain_cut(db, longs, all, 0, &end, [&](LongUnit& u, double busy) {
+        const int uc = db->pcols[(size_t)u.g * kGroupPairs + u.k];
+        for (int i = 0; i < 2; ++i) {
+            const int q = i == 0 ? entries[u.q].x : entries[u.q].y;
+            if (q < 0) continue;
+            u.parts[i] = chain_parts(qlens[q], uc, true, busy);
+            const int64_t x = chain_cost(qlens[q], uc, true, u.parts[i]);
+            u.chain = std::max(u.chain, x);
+            u.chain_sum += u.parts[i] * x;
+        }
     });
-    for (size_t i = 0; i < longs.size(); ++i) {
-        const LongUnit& u = longs[i];
+    int splits = 0;
+    for (size_t n = 0; n < longs.size(); ++n) {
+        const LongUnit& u = longs[n];
         const Entry& e = entries[u.q];
         const WgItem it{u.g, e.y < 0 ? e.x : e.pair, (int16_t)u.k, (int8_t)(e.y < 0 ? 6 + kItemSmall : 5), 1, nchunks};
-        (i < cut ? uitems : items).push_back({it, u.cost});
-        if (i >= cut) continue;
-        for (int q : {e.x, e.y})
-            if (q >= 0)
-                citems.push_back({WgItem{u.g, q, (int16_t)u.k, kItemChain, 1, nchunks},
-                                  chain_cost(qlens[q], db->pcols[(size_t)u.g * kGroupPairs + u.k], true)});
+        (n < cut ? uitems : items).push_back({it, u.cost});
+        if (n >= cut) continue;
+        for (int i = 0; i < 2; ++i) {
+            const int q = i == 0 ? e.x : e.y;
+            if (q >= 0) push_chain(citems, u.g, q, u.k, u.parts[i], u.chain, splits);
+        }
     }
     auto emit = [](std::vector<Tmp>& v, std::vector<WgItem>& to) {
         std::stable_sort(v.begin(), v.end(), [](const Tmp& a, const Tmp& b) { return a.cost > b.cost; });
@@ -1315,6 +1352,7 @@ sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& 
     a.n_items = plan.n_main + (off ? plan.n_chain : plan.n_unchained);
     a.first_item = off || plan.n_unchained == 0 ? 0 : plan.n_main;
     a.counter = ctr + 0;
+    a.splits = ctr + kSplits;
     set_rerun_args(db, a, W, ctr);
     a.unit_list = 0;
     a.bias = form.bias;
@@ -1948,7 +1986,7 @@ sw_status sw_kernel_times(sw_db* db, float* ms_out, int32_t cap, int32_t* count)
 sw_status sw_last_stats(sw_db* db, int64_t out[8]) {
     if (!db || !out) return fail(SW_E_INVALID, "NULL argument");
     DeviceGuard dg(db->device);
-    int32_t c[kCounters] = {};
+    int32_t c[kSplits] = {};
     if (db->last_counters) {
         HIP_TRY(hipDeviceSynchronize());
         HIP_TRY(hipMemcpy(c, db->last_counters, sizeof c, hipMemcpyDeviceToHost));

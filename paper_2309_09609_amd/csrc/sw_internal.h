@@ -55,12 +55,17 @@ struct WgItem {
     int16_t k0;       // sub-group index of the first unit within g0
     int8_t lgB;       // log2 of lanes per pair (0..6), which kItemSmall may be added to, or kItemChain
     int8_t count;     // number of valid units (1..kWaves)
-    int32_t gstep;    // distance between consecutive groups of the item
+    int32_t gstep;    // distance between consecutive groups of the item; kItemChain: chain_split(slot, parts, part)
 };
 
 // Items beside the units of a launch: one pair on the whole workgroup (kItemChain, offset cells), and with kItemSmall
 // added to the lanes, units at 4 rows per lane (in a launch of query pairs: units of one query, two subjects a lane).
 constexpr int kItemChain = 8, kItemSmall = 16, kSmallRows = 4;
+
+// A chained pair may be split into parts, an item each, that sweep windows of the subject and meet in a slot of the
+// launch's counters: {score a, score b, out of range, parts done}, all 0 before a search.
+constexpr int kMaxSplits = 60, kMaxParts = 8;
+constexpr int32_t chain_split(int slot, int parts, int part) { return (slot << 16) | (parts << 8) | part; }
 
 // Per-query descriptor.
 struct QDesc {
@@ -100,6 +105,7 @@ struct SweepArgs {
     uint32_t* rerun_bits;         // one bit per (query, group, pair): [q][group][2 words], zero before a search
     int32_t rerun_groups;         // groups per query row of rerun_bits (the database's group count)
     int64_t rerun_words;          // words of rerun_bits (queries x groups x 2)
+    int32_t* splits;              // chained pairs in parts: kMaxSplits slots of 4
     int32_t* recomputed;          // 32-bit recompute: pairs recomputed (listed and from rerun_bits)
     int32_t poison;               // test hook: a flagged pair's 16-bit scores are written as kPoison
     int32_t unit_list;            // 1: items[] holds one unit per workgroup (rerun list), 0: workgroup items

@@ -1010,8 +1010,8 @@ __device__ __forceinline__ void run_unit(const SweepArgs& a, int g, int k, int l
 
 // One long subject pair (pair k of group g) against query q on a whole workgroup (sw_offset.h, "long subjects").
 template <int MODE>
-__device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int q, uint8_t* lds, int wave, int lane,
-                                          uint32_t* slot) {
+__device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int q, int split, uint8_t* lds, int wave,
+                                          int lane, uint32_t* slot) {
     constexpr int R = kChainRows;
     const QDesc Q = a.qd[q];
     const GroupRec G = a.groups[g];
@@ -1021,19 +1021,23 @@ __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int 
     // waves per window, and windows: as many as the waves allow while a window stays well below the subject
     int waves = passes > 1 ? kChainWaves : (Q.m + kWaveRows - 1) / kWaveRows;
     int windows = kChainWaves / waves;
-    while (windows > 1 && (MODE == 1 || Q.span + cols / windows > cols - cols / 4)) --windows;
-    const int core = ((cols / 4 + windows - 1) / windows) * 4;            // columns a window answers for
+    const int parts = (split >> 8) & 255;
+    const int share = cols / parts, lead = parts > 1 ? min(Q.span, cols) : 0;
+    while (windows > 1 && (MODE == 1 || Q.span + share / windows > share + lead - (share + lead) / 4)) --windows;
+    const int all = windows * parts;
+    const int core = ((cols / 4 + all - 1) / all) * 4;                    // columns a window answers for
     const int win = wave / waves;
     const int w = wave - win * waves;
-    const bool mine = win < windows && win * core < cols;
+    const int at = (split & 255) * windows + win;
+    const bool mine = win < windows && at * core < cols;
     int start = 0, end = cols;
-    if (windows > 1 && mine) {
-        start = max(0, win * core - Q.span) & ~3;
-        end = min(cols, (win + 1) * core);
+    if (all > 1 && mine) {
+        start = max(0, at * core - Q.span) & ~3;
+        end = min(cols, (at + 1) * core);
     }
     const int ncols = mine ? end - start : 0;
     // the longest window sets the stages of every wave (the first one has no overlap in front)
-    const int longest = windows > 1 ? min(cols, core + Q.span + 3) : cols;
+    const int longest = all > 1 ? min(cols, core + Q.span + 3) : cols;
     const int stages = (((longest + 66) >> 2) + kChainStage / 4 - 1) / (kChainStage / 4) +
                        (waves - 1) * (kChainLag / kChainStage);
     PassIO io;
@@ -1107,6 +1111,18 @@ __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int 
             S = __builtin_elementwise_max(S, best[x]);
             bad = bad || worst[x] != 0;
         }
+        bool done = true;
+        if (parts > 1) {                            // the last part to come has them all
+            int32_t* slot = a.splits + 4 * (split >> 16);
+            atomicMax(slot, (int)S.x);
+            atomicMax(slot + 1, (int)S.y);
+            if (bad) atomicOr(slot + 2, 1);
+            __threadfence();
+            done = atomicAdd(slot + 3, 1) == parts - 1;
+            __threadfence();
+            S = u2{(unsigned short)atomicMax(slot, 0), (unsigned short)atomicMax(slot + 1, 0)};
+            bad = atomicOr(slot + 2, 0) != 0;
+        }
         int sa = (int)S.x, sb = (int)S.y;
         bool flag = a.rerun != nullptr && (sa >= a.sat || sb >= a.sat);
         if constexpr (MODE != 0) {
@@ -1117,9 +1133,9 @@ __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int 
         const bool poisoned = flag && a.poison;
         const int o0 = a.perm[slot0], o1 = a.perm[slot0 + 1];
         int32_t* out = Q.out ? Q.out : a.scores + Q.out_off;
-        if (o0 >= 0) out[o0] = poisoned ? kPoison : sa;
-        if (o1 >= 0) out[o1] = poisoned ? kPoison : sb;
-        if (flag) append_rerun(a, g, q, k);
+        if (done && o0 >= 0) out[o0] = poisoned ? kPoison : sa;
+        if (done && o1 >= 0) out[o1] = poisoned ? kPoison : sb;
+        if (done && flag) append_rerun(a, g, q, k);
     }
     // Thread 0 goes on to pull the next item: without a barrier between, the compiler joins the two and lets the
     // other lanes run ahead to the pull's barrier (and to a stale item).
@@ -1209,7 +1225,7 @@ __global__ __launch_bounds__(64 * kWaves, (kMinWaves<C, R>)) void k_sweep(SweepA
         const WgItem I = a.items[at < a.n_items ? at : at - a.n_items];
         if constexpr (kOffset) {
             if (I.lgB == kItemChain) {
-                run_chain<MODE>(a, I.g0, I.k0, I.q, reinterpret_cast<uint8_t*>(lds), wave, lane,
+                run_chain<MODE>(a, I.g0, I.k0, I.q, I.gstep, reinterpret_cast<uint8_t*>(lds), wave, lane,
                           a.scratch + (int64_t)(a.slot_base + blockIdx.x) * kWaves * a.slot_words);
                 continue;
             }
@@ -1255,7 +1271,7 @@ __global__ __launch_bounds__(64 * kWaves, 3) void k_sweep_q2(SweepArgs a) {
         const WgItem I = a.items[at < a.n_items ? at : at - a.n_items];
         if constexpr (std::is_same<C, CellOff>::value) {
             if (I.lgB == kItemChain) {              // one query of the pair; I.q is the query itself
-                run_chain<0>(a, I.g0, I.k0, I.q, reinterpret_cast<uint8_t*>(lds), wave, lane,
+                run_chain<0>(a, I.g0, I.k0, I.q, I.gstep, reinterpret_cast<uint8_t*>(lds), wave, lane,
                           a.scratch + (int64_t)(a.slot_base + blockIdx.x) * kWaves * a.slot_words);
                 continue;
             }

@@ -49,7 +49,7 @@
 // last row's cells are read off once per step, only by the wave that holds them
 // and in the columns that count.  Measured against the plain cells, with the
 // longest pairs on a workgroup each (below): global, 405 residues x 570,000
-// subjects, 17.5 -> 10.8 ms; semi-global, 331 x 100,000, 10.9 -> 3.5 ms.
+// subjects, 17.5 -> 10.4 ms; semi-global, 331 x 100,000, 10.9 -> 2.15 ms.
 //
 // The rows' G live in fixed registers v64.. (row r's in v65 + r, the value
 // above the block in v64) because v_lshl_add_u64 reads them in pairs and the
@@ -379,6 +379,7 @@ __device__ __forceinline__ int end_takes(const EndOff& ec, int c) {
 // The last row's cell of step t, offset `off` included in G (two halves alike).
 template <int R, int MODE>
 __device__ __forceinline__ void end_capture(EndOff& ec, int takes, const uint32_t* P, int t, uint32_t off) {
+    asm volatile("" : "+s"(takes));           // (a scalar compare and branch per step, no masks kept)
     if (takes == 0) return;
     uint32_t g = row_g<R>(P, ec.rcap);
     const int col = t - ec.bcap;
@@ -681,7 +682,9 @@ __device__ __forceinline__ void load_slice_off_q2(uint32_t* dst, const int16_t* 
 //     others sweep further windows of the subject.  A window starts `span`
 //     columns before its own ones: no local alignment with a positive score
 //     covers more subject residues (QDesc::span), so each lies wholly in the
-//     window that holds its end, and the score is the largest window's.
+//     window that holds its end, and the score is the largest window's.  A pair
+//     that would still outlast the search is split into parts, each with its
+//     own windows, on a workgroup each; the last to end has the score.
 // Every wave of a workgroup runs the same number of stages, and so of barriers,
 // computed from the item before the first.
 //
@@ -694,11 +697,12 @@ __device__ __forceinline__ void load_slice_off_q2(uint32_t* dst, const int16_t* 
 // it leave).  The items run in the bulk launch itself, ahead of its units: a
 // launch of their own on another stream shares a hardware queue with the bulk
 // launch as soon as a process holds a few handles, and then runs before it
-// instead of beside it.  One pair of 35,000 residues alone takes 1.3 ms for a
-// query of 200 residues (four windows), 2.4 ms for 331 and 4.4 ms for 1,024 (126
-// ns a step; global 162, semi-global 186, which also read the last row).  A query
-// of 144 against 570,000 subjects, the longest of 35,000 residues, went from 7.4
-// ms (a wave of its own for that pair) to 3.6 ms with it.
+// instead of beside it.  One pair of 35,000 residues on one workgroup takes 1.3
+// ms for a query of 200 residues (four windows), 2.4 ms for 331 and 4.4 ms for
+// 1,024 (126 ns a step; global 161, semi-global 170, which also read the last
+// row), in eight parts 0.35, 0.6 and 1.3 ms.  A query of 144 against 570,000
+// subjects, the longest of 35,000 residues, went from 7.4 ms (a wave of its own
+// for that pair) to 3.6 ms with it.
 constexpr int kChainWaves = kWaves;
 constexpr int kChainRows = 4;
 constexpr int kChainStage = 16;              // steps between barriers (4 chunks)

@@ -25,14 +25,16 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "GCUPS on 1 MI355X (plain vs batched), % int-VALU peak; p50/p99 query latency"
-# Algorithmic lane operations per cell of the 16-bit sweep, in the minimal form
-# of Eq. 1-3 (H - Go shared by E and F, no move): hd = Hdiag + SM;
-# H = max(hd, E, F) (one three-input maximum); hgo = H - Go; E - Ge; F - Ge;
-# E' = max(E - Ge, hgo, floor); F' = max(F - Ge, hgo) -- 7 operations -- plus
-# S = max(S, H), which a three-input maximum folds in for two cells at a
-# time: 7.5.
-CELL_OPS = 7.5
-MODE_CELL_OPS = 8.0
+# Algorithmic lane operations per cell of the 16-bit sweep on offset cells, where a
+# gap extends for free: hd = Gdiag + (SM + Go + Ge); M = max(hd, E, F) (one
+# three-input maximum); G = M - (Go - Ge); E' = max(E, G, floor) (three-input);
+# F' = max(F, G) -- 5 operations -- plus the running maximum, which a three-input
+# maximum folds in for two cells at a time and one addition per two cells keeps at
+# the cells' offset: 6.  (Plain cells, for gaps and matrices that offset cells cannot
+# hold, take 7.5; no workload here does.)  End-to-end modes have no floor and no
+# running maximum, but fold every G into a minimum and a maximum, half each: 6.
+CELL_OPS = 6.0
+MODE_CELL_OPS = 6.0
 
 
 # Oracle threads at most: a GPU host's CPU share for one GPU (the box runs other GPUs' work too).
@@ -95,7 +97,8 @@ def measured_traffic(args):
     path = os.path.join(ROOT, "profiles", "traffic_k_sweep_i16_sp570k_plain.json")
     try:
         d = json.load(open(path))
-        src = open(os.path.join(ROOT, "paper_2309_09609_amd", "csrc", "sw_kernels.hip"), "rb").read()
+        csrc = os.path.join(ROOT, "paper_2309_09609_amd", "csrc")
+        src = b"".join(open(os.path.join(csrc, f), "rb").read() for f in ("sw_kernels.hip", "sw_offset.h"))
     except (OSError, ValueError):
         return None
     if d.get("kernel_source_sha256") != hashlib.sha256(src).hexdigest():
@@ -292,20 +295,17 @@ def align_bench(args, sw, D, queries, db, sm, total_res, perfmodel):
     n_al = len(queries) * 10
     # The fill sweeps Eq. 1-3 in int32 lanes: 9 operations per cell (diagonal add, three-input maximum
     # and the floor for H, H - Go shared by E and F, two extension subtractions, two maxima, the running
-    # maximum); the direction byte it also records is not counted.  Pairs with both sides below 2,048
-    # residues fill on one workgroup each, longer ones as tiles over the GPU (one anti-diagonal of tiles
-    # per launch); a call lasts about as long as its longest pair's wavefront, so the whole-chip fraction
-    # is small by construction.
+    # maximum); the direction bits it also records are not counted.  A pair fills by bands of 128 query rows,
+    # a wave each, behind one another; a call lasts about as long as its longest pair's wavefront, so the
+    # whole-chip fraction is small by construction.
     call_s = el / args.steps
     longest = max(int(q.size) * int(lens[k]) for q, t in zip(queries, tops) for k in t)
-    tiled = sum(1 for q, t in zip(queries, tops) for k in t if q.size >= 2048 and lens[k] >= 2048)
     peak_chip = perfmodel.int_valu_lane_ops_per_s()
     achieved = ALIGN_CELL_OPS * cells / call_s
     roof = {"bound": "alu", "achieved": round(achieved / 1e12, 4), "peak": round(peak_chip / 1e12, 3),
             "unit": "TOP/s (int32 lane-ops)", "frac": round(achieved / peak_chip, 4), "traffic": None,
-            "kernel": "k_align_fill, k_align_tile, k_align_trace (one call)", "ops_per_cell": ALIGN_CELL_OPS,
-            "longest_pair": {"cells": longest, "gcups": round(longest / call_s / 1e9, 3)},
-            "tiled_pairs": tiled}
+            "kernel": "k_align_fill, k_align_trace (one call)", "ops_per_cell": ALIGN_CELL_OPS,
+            "longest_pair": {"cells": longest, "gcups": round(longest / call_s / 1e9, 3)}}
     res = {
         "metric": "GCUPS of the traceback (top-10 alignments per query)", "value": round(cells * args.steps / el / 1e9, 2),
         "unit": "GCUPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -383,7 +383,6 @@ def pair_bench(args, perfmodel):
     cells = L * L
     peak = perfmodel.int_valu_lane_ops_per_s()
     achieved = PAIR_CELL_OPS * cells / (ms * 1e-3)
-    launches = (L + 255) // 256 + (L + 255) // 256 - 1
     res = {
         "metric": "GCUPS of one long pair spread over the GPU", "value": round(cells * args.steps / el / 1e9, 2),
         "unit": "GCUPS", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -392,34 +391,28 @@ def pair_bench(args, perfmodel):
         "config": {"workload": f"pair{L // 1000}k", "form": "pair (sw_pair)", "query_len": L, "subject_len": L,
                    "matrix": "BLOSUM62", "gap_open": 10, "gap_extend": 2},
         # 8 int32 lane-operations per cell (diagonal add, three-input maximum for H, H - Go, two extension
-        # subtractions, two three-input maxima with the floor, the running maximum); one wave per tile and
-        # at most one tile per 256 x 256 block of an anti-diagonal in flight, so the whole-GPU fraction is
-        # bounded by the pair's own wavefront parallelism
+        # subtractions, two three-input maxima with the floor, the running maximum); one wave per band of 256
+        # rows, each some 130 columns behind the one above, so the whole-GPU fraction is bounded by the
+        # pair's own wavefront parallelism
         "roofline": {"bound": "alu", "achieved": round(achieved / 1e12, 4), "peak": round(peak / 1e12, 3),
                      "unit": "TOP/s (int32 lane-ops)", "frac": round(achieved / peak, 4), "traffic": None,
-                     "kernel": "k_pair_tile", "launches_per_step": launches,
-                     "avg_launch_ms": round(ms / launches, 4), "ops_per_cell": PAIR_CELL_OPS},
+                     "kernel": "k_pair", "launches_per_step": 1,
+                     "avg_launch_ms": round(ms, 4), "ops_per_cell": PAIR_CELL_OPS},
         "extra": {"score": int(score.item()), "event_ms_per_step": round(ms, 3)},
     }
     if args.pair_align and L <= 50_000:
-        # the alignment of the same pair (traceback): the tiled fill against one workgroup for the pair
+        # the alignment of the same pair (traceback); the second call is the one kept (warm)
         offs = np.array([0, L], np.int64)
         D = sw.Database(d, offs)
-        times, alns = {}, {}
-        for mode, name in ((2, "tiled"), (1, "one_workgroup"), (2, "tiled")):
-            D.tune(align_tiles=mode)
+        for _ in range(2):
             t = time.perf_counter()
-            alns[name] = D.align(q, [0], sm, 10, 2)[0]
-            times[name] = time.perf_counter() - t        # the second tiled call is the one kept (warm)
-            print(f"# align {name}: {times[name] * 1e3:.1f} ms", file=sys.stderr, flush=True)
+            aln = D.align(q, [0], sm, 10, 2)[0]
+            dt = time.perf_counter() - t
+            print(f"# align: {dt * 1e3:.1f} ms", file=sys.stderr, flush=True)
         D.close()
-        res["extra"]["align"] = {"tiled_ms": round(times["tiled"] * 1e3, 2),
-                                 "one_workgroup_ms": round(times["one_workgroup"] * 1e3, 2),
-                                 "tiled_gcups": round(cells / times["tiled"] / 1e9, 2),
-                                 "speedup": round(times["one_workgroup"] / times["tiled"], 2),
-                                 "same_alignment": alns["tiled"] == alns["one_workgroup"],
-                                 "score_equals_sw_pair": alns["tiled"]["score"] == int(score.item()),
-                                 "ops": len(alns["tiled"]["ops"])}
+        res["extra"]["align"] = {"ms": round(dt * 1e3, 2), "gcups": round(cells / dt / 1e9, 2),
+                                 "score_equals_sw_pair": aln["score"] == int(score.item()),
+                                 "ops": len(aln["ops"])}
     if not args.no_cpu_baseline:
         import oracle
         n = min(L, 20_000)
@@ -442,7 +435,7 @@ def main():
     ap.add_argument("--form", default="plain", choices=["plain", "batched", "served", "align", "pair"])
     ap.add_argument("--pair-len", type=int, default=100_000, help="pair form: residues of each sequence")
     ap.add_argument("--pair-align", action="store_true",
-                    help="pair form: also align the pair (traceback), tiled fill vs one workgroup (up to 50,000)")
+                    help="pair form: also align the pair (traceback; up to 50,000)")
     ap.add_argument("--requests", type=int, default=200, help="served form: measured requests")
     ap.add_argument("--load", type=float, default=0.8, help="served form: arrival rate / plain service rate")
     ap.add_argument("--chunks", type=int, default=8, help="served form: database chunks per request cycle")
@@ -571,9 +564,7 @@ def main():
     timed_cells = sum(per_launch[-kt.size:]) if kt.size else 0
     kernel_s = float(kt.sum()) / 1e3
     launches = int(kt.size)
-    # every mode computes in packed 16-bit lanes: two cell operations per VALU lane-op.  The end-to-end
-    # modes take 8 operations per cell: the recurrence's 7 (no running maximum) and the fold of H into
-    # the running minimum and maximum that prove the 16-bit values exact (half a three-input fold each)
+    # every mode computes in packed 16-bit lanes: two cell operations per VALU lane-op
     packed = True
     peak_ops = perfmodel.int_valu_lane_ops_per_s() * 2
     ops_cell = CELL_OPS if args.mode == "local" else MODE_CELL_OPS
@@ -582,7 +573,7 @@ def main():
             "peak": round(peak_ops / 1e12, 3), "unit": "TOP/s (int16 lane-ops)" if packed else "TOP/s (int32 lane-ops)",
             "frac": round(achieved * 1e12 / peak_ops, 4) if achieved else None,
             "traffic": measured_traffic(args),
-            "kernel": ("k_sweep<CellI16>" if args.mode == "local" else f"k_sweep<CellI16, 16, {args.mode}>")
+            "kernel": ("k_sweep<CellOff>" if args.mode == "local" else f"k_sweep<CellOff, R, {args.mode}>")
                       if args.form == "plain" else "batched graph (sweeps + recompute + top-k)",
             "launches": launches,
             "avg_launch_ms": round(kernel_s * 1e3 / max(launches, 1), 3),

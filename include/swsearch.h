@@ -79,16 +79,18 @@ typedef struct {
     int32_t max_qlen;         /* unused hint, 0 */
     int32_t force_lanes;      /* test hook: 0 = planner decides; 1,2,4,...,64 = every pair of
                                  subjects is swept by this many cooperating lanes */
-    int32_t rerun_threshold;  /* test hook: 0 = the largest, 31744 (0x7C00) minus the search's 16-bit
-                                 bias c = minus the matrix's lowest score (4 for BLOSUM62); a smaller
+    int32_t rerun_threshold;  /* test hook: 0 = the largest, 31744 (0x7C00) minus what the search's
+                                 16-bit cells carry (about 200 at 10/2 with BLOSUM62, 4 for a query
+                                 whose scores end just below 31744); a smaller
                                  value sends every pair whose 16-bit score reaches it to the exact
                                  32-bit recompute */
     int32_t rows_per_lane;    /* tuning: 0 = planner decides; 4, 8 or 16 query rows per lane */
     int32_t unit_share;       /* tuning: largest work unit as a fraction of one persistent wave's
-                                 share of a search, in 1/1000; 0 = default (250) */
+                                 share of a search, in 1/1000; 0 = 250, or 125 where the planner
+                                 expects it to be faster */
     int32_t lane_pack;        /* tuning, batched and multi-query forms: 0 or 1 = the two 16-bit halves
-                                 of a lane hold two subjects; 2 = they hold two queries (queries are
-                                 paired by length; a single query always uses subject pairs) */
+                                 of a lane hold two subjects; 2 = they hold two queries (of about the
+                                 same length; a query without such a partner uses subject pairs) */
     int32_t alphabet;         /* residue codes 0..alphabet-1: 0 = 20 (the standard amino acids
                                  ARNDCQEGHILKMFPSTWYV); up to 24 (e.g. plus B, Z, X, *).  Substitution
                                  matrices passed with this database are int8[alphabet * alphabet].
@@ -307,16 +309,16 @@ enum { SW_LOCAL = 0, SW_GLOBAL = 1, SW_SEMIGLOBAL = 2 };
  *   SW_SEMIGLOBAL  H[0][j] = 0, S = max over j of H[m][j] (the whole query
  *                  against any stretch of the subject).
  * Scores may be negative.  Cells are 16-bit with a bias and a check that
- * every H of a pair stayed in the exact range; pairs that left it are
+ * every value of a pair stayed in the exact range; pairs that left it are
  * recomputed in 32-bit cells, so every score is exact.  SW_GLOBAL with
- * Ge <= Go and a query of at most about 3,100 residues (at 10/2) stores
- * H[i][j] - g(j) in its cells, which keeps every subject's row-0 gap run in
+ * Ge <= Go and a query of at most about 3,100 residues (at 10/2) raises its
+ * cells by Ge per column, which keeps every subject's row-0 gap run in
  * range; otherwise subjects whose row-0 gap run leaves the range run in 32-bit
  * cells from the start.  SW_E_UNSUPPORTED if Go + (qlen + longest subject) * max(Go, Ge)
  * could leave +-2^29.  Other arguments and errors as for sw_search;
- * sw_last_stats reports the 16-bit launch (out[0], out[2]) and, in out[4] and
- * out[5], the launches beside it (long pairs of a short query at 4 or 8 rows
- * per lane, and the 32-bit subjects).
+ * sw_last_stats reports it as any search; where gaps or matrix need cells that
+ * carry the bias alone, out[4] and out[5] are the launches beside the 16-bit one
+ * (long pairs of a short query at 4 or 8 rows per lane, and the 32-bit subjects).
  */
 sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_db* db, const int64_t* h_offsets,
                          int64_t n, const int8_t* h_subst, int32_t gap_open, int32_t gap_extend,
@@ -383,16 +385,15 @@ sw_status sw_align_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int
 /*
  * sw_pair - the Smith-Waterman score (Eq. 1-3) of one pair of long sequences,
  * spread over the whole GPU (intra-task parallelism, Sec. II-B; one-to-one
- * alignment of long sequences, Sec. III-A).  The matrix is cut into tiles of
- * 256 query rows by 128 or 256 subject columns; the tiles of one
- * anti-diagonal are independent and run in one launch (one wave each), so a
- * pair of m x n residues takes about m/256 + n/256 launches and no
- * workgroup waits for another.  int32 cells.
+ * alignment of long sequences, Sec. III-A).  One launch; a wave sweeps
+ * a band of 256 residues of the longer sequence along the shorter one and
+ * hands its last row to the next band's wave, some 130 columns behind.  int32
+ * cells.
  *   h_query, h_subject : host residue codes 0..alphabet-1 (validated).
  *   alphabet           : 0 (= 20) or 1..24;  h_subst : host int8[alphabet^2].
  *   d_score            : device int32, receives S (0 for an empty sequence).
  *   d_workspace        : device, 256-byte aligned, ws_bytes >= sw_pair_workspace_bytes
- *                        (about 8 (m + n) bytes plus the sequences); may be NULL when
+ *                        (16 bytes per residue of the shorter sequence plus the sequences); may be NULL when
  *                        either length is 0.
  * SW_E_UNSUPPORTED when 127 x min(m, n) could exceed int32.  Asynchronous on
  * the stream; the workspace must stay untouched until it completes.
@@ -410,12 +411,12 @@ const char* sw_last_error(void);
 /*
  * Execution statistics of the most recent search on the handle (read after the
  * stream has completed):
- *   out[0] = work items of the bulk 16-bit launch,  out[1] = (query, subject
+ *   out[0] = other work items of the 16-bit launch,  out[1] = (query, subject
  *   pair) entries flagged for the 32-bit recompute (saturated or, in the
  *   end-to-end modes, out of the exact range),  out[2] = rows per lane (R) of
- *   the bulk launch,  out[3] = persistent waves launched,  out[4] = work items
- *   of the side launch (long pairs of a short query),  out[5] = rows per lane
- *   of the side launch,  out[6] = pairs the 32-bit recompute computed (equals
+ *   the launch,  out[3] = persistent waves launched,  out[4] = work items of the
+ *   same launch at 4 rows per lane (long pairs on a workgroup each, and groups
+ *   that 4 rows pad less),  out[5] = their rows per lane (0: none),  out[6] = pairs the 32-bit recompute computed (equals
  *   out[1] after every search),  out[7] = flagged pairs beyond the recompute
  *   list's capacity (recomputed from their flag bits).
  * This call synchronises the handle's device.

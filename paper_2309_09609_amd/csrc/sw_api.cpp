@@ -8,8 +8,8 @@
 // B (1 = one pair of subjects per lane, 64 = a whole wave on one pair) so that
 // no work unit is large against a persistent wave's share of the search, units
 // are bundled four to a workgroup and ordered longest first, and one persistent
-// launch pulls them from an atomic counter.  The long pairs of a short query
-// run on a second stream with fewer rows per lane.  Pairs whose 16-bit score
+// launch pulls them from an atomic counter.  Pairs that would outlast the
+// search run on a workgroup each, or several, first.  Pairs whose 16-bit score
 // saturates are appended to a list that a 32-bit launch consumes.  The launch
 // sequence itself allocates nothing, so the batched form captures a batch
 // shape that comes twice in a row as a HIP graph and replays it.
@@ -259,8 +259,8 @@ struct sw_db {
     int wgR[17] = {0};                // persistent workgroups per 16-bit instance, by R
     int wgQ[17] = {0};                // persistent workgroups per query-pair instance, by R
     int64_t slot_cap = 0;             // (column x pair) capacity of one wave's boundary slot
-    hipStream_t side = nullptr;       // second stream for the long pairs of short queries
-    hipStream_t side2 = nullptr;      // third stream (end-to-end modes: the 32-bit groups beside both 16-bit launches)
+    hipStream_t side = nullptr;       // end-to-end modes on plain cells: the long pairs of short queries
+    hipStream_t side2 = nullptr;      // and the 32-bit groups beside both 16-bit launches
     hipStream_t cap = nullptr;        // stream the batched sequence is captured on
     hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_join2 = nullptr;
     // workspace of searches without a caller workspace (laid out by WsLayout)
@@ -297,8 +297,8 @@ struct sw_db {
 
 namespace {
 
-// [0] bulk sweep counter, [1] flagged pairs, [2] recompute work counter, [3] side sweep counter,
-// [4] second side sweep counter, [5] pairs recomputed
+// [0] sweep counter, [1] flagged pairs, [2] recompute work counter, [3] and [4] counters of the launches beside
+// (end-to-end modes on plain cells), [5] pairs recomputed
 constexpr int kSplits = 6;     // from here on: the slots of chained pairs in parts
 constexpr int kCounters = kSplits + 4 * kMaxSplits;
 static_assert(kCounters <= 256, "one block clears them");
@@ -1335,8 +1335,8 @@ int record_timer_start(sw_db* db, hipStream_t st) {
     return ev;
 }
 
-// The launch sequence of a search: profile (zeroes the counters), the side and
-// bulk 16-bit sweeps, the 32-bit recompute, top-k.  Allocates nothing and never
+// The launch sequence of a search: profile (zeroes the counters), the 16-bit
+// sweep, the 32-bit recompute, top-k.  Allocates nothing and never
 // waits on the host, so it can be captured into a graph.
 sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& plan, const Work& W, int32_t go,
                   int32_t ge, int32_t* d_scores, int64_t n, int k, int32_t* top_s, int64_t* top_i, hipStream_t st,

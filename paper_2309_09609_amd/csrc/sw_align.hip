@@ -114,7 +114,7 @@ __global__ __launch_bounds__(64) void k_align_fill(const AlignPair* pairs, const
         // (a global pointer: flat loads would hold up the reads of LDS behind them)
         const auto residues = (const __attribute__((address_space(1))) uint8_t*)P.residues;
         uint16_t* dir = reinterpret_cast<uint16_t*>(dirs + P.dir_off) + (int64_t)J.band * band_steps(n) * 64;
-        sweep_band(rec, prof, between + 2 * P.bnd_off, n, (uint32_t)J.band, row0 - b * kAlignRows + kAlignBand >= m, b,
+        sweep_band<0>(rec, prof, between + 2 * P.bnd_off, n, (uint32_t)J.band, row0 - b * kAlignRows + kAlignBand >= m, b,
                    [&](int j) { return residues[(int64_t)(j >> 2) * kChunkBytes + (j & 3)]; },
                    [&](int t, uint32_t sv, int htop, int ftop, int& hb, int& fb) {
                        int dg = diag, gu = htop - go, fu = ftop;

@@ -18,8 +18,12 @@
 // happen to run, the lowest band taken always goes on.
 //
 // A reader takes 32 columns at a time (lane l: word l of the 64) and asks for
-// the next 32 when it starts on these, so a band runs about 64 + 32 + the time
-// a word is on its way, some 130 steps, behind the band above.  A matrix of m
+// the next 32 at step kAsk of these, so a band runs about 64 + 64 - kAsk + the
+// time a word is on its way, some 130 steps, behind the band above.  Asking half
+// way gains where few bands wait (sw_pair, 20,000 x 20,000: 2.90 ms from the
+// start, 2.75 at step 8, 2.72 at 16, 2.68 at 24; 100,000: 15.1, 14.6, 14.4, 14.6);
+// the traceback's many bands find their words late then (0.70 ms a call from the
+// start, 0.71 at 16, 0.77 at 24).  A matrix of m
 // rows and n columns takes n + m / (64 R) x 130 steps of a lone wave, where one
 // launch per anti-diagonal of tiles (256 rows x 256 columns) took (m + n) / 256
 // launches of 320 steps each.
@@ -58,7 +62,7 @@ __device__ __forceinline__ int from_above(int v, int first) {
 // reads the bottom row.  code(j) is the image byte of column j < n; cells(t, scores, htop, ftop, &hb, &fb) updates the
 // lane's R rows at its column t - b (before column 0 and from n on, scores are padding's and the tops zero or the
 // band's own) and hands back the bottom row.
-template <class Code, class Cells>
+template <int kAsk, class Code, class Cells>
 __device__ __forceinline__ void sweep_band(uint4* rec, const uint32_t* prof, uint64_t* row, int n, uint32_t tag, bool last,
                                            int b, Code&& code, Cells&& cells) {
     const int col = b & (kBandBatch - 1), half = b / kBandBatch;
@@ -90,13 +94,13 @@ __device__ __forceinline__ void sweep_band(uint4* rec, const uint32_t* prof, uin
         }
         reinterpret_cast<uint32_t*>(rec)[4 * col + half] = (uint32_t)v;
         if (half == 0) reinterpret_cast<uint32_t*>(rec)[4 * col + 2] = (uint32_t)next;
-        v = words(c + 1);
         next = half == 0 ? at(kBandBatch * (c + 1) + 2 + col) : 0;
         __builtin_amdgcn_wave_barrier();
         uint4 r = rec[0];
 #pragma unroll
         for (int u = 0; u < kBandBatch; ++u) {
             const uint4 rn = rec[u + 1 < kBandBatch ? u + 1 : u];
+            if (u == kAsk) v = words(c + 1);
             ro = from_above(ro, (int)r.z);
             const uint32_t pnn = scores(ro);
             const int htop = from_above(hb, (int)r.x), ftop = from_above(fb, (int)r.y);

@@ -11,10 +11,11 @@
 // scores, so a step's lookup is conflict-free whatever the residues.  The best H
 // of each band goes to the score with one atomic maximum.
 //
-// 20,001 x 19,500 residues: 10.6 -> 2.9 ms (135 GCUPS) against tiles of 256 x 256
-// on one launch per anti-diagonal; 100,000 x 100,000: 54 -> 15.0 ms (665 GCUPS).
-// 97 ns a step.  2 rows per lane measured 2.9 and 15.7 ms (500 x 40,000: 2.7 ms
-// against 1.8), 16 columns per read of the band above 3.2 and 16.9 ms.
+// 20,001 x 19,500 residues: 10.6 -> 2.7 ms (143 GCUPS) against tiles of 256 x 256
+// on one launch per anti-diagonal; 100,000 x 100,000: 54 -> 14.4 ms (693 GCUPS).
+// 97 ns a step.  Against 2.9 and 15.0 ms then, 2 rows per lane measured 2.9 and
+// 15.7 ms (500 x 40,000: 2.7 against 1.8), 16 columns per read of the band above
+// 3.2 and 16.9 ms.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -73,7 +74,7 @@ __global__ __launch_bounds__(64) void k_pair(PairArgs a) {
         }
         __syncthreads();
         int H[kPairRows] = {}, E[kPairRows] = {}, diag = 0;
-        sweep_band(rec, prof, a.between, a.n, (uint32_t)band, band == a.nb - 1, b,
+        sweep_band<16>(rec, prof, a.between, a.n, (uint32_t)band, band == a.nb - 1, b,
                    [&](int j) { return a.cols[j] + 1; },
                    [&](int, uint32_t pv, int htop, int ftop, int& hb, int& fb) {
                        int dg = diag, F = ftop;                  // ftop: F advanced to this lane's first row

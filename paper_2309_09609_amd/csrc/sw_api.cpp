@@ -1005,6 +1005,10 @@ sw_status ensure_geometry(sw_db* db) {
     return SW_OK;
 }
 
+// Rows of a query's profile: whole passes at every B x R, of which 64 x 16 rows and 64 x 12 are the largest (the
+// slices of a pass are read without a look at the query's end).
+int prof_rows(int m) { return (int)std::max(round_up(std::max(m, 1), 1024), round_up(std::max(m, 1), 768)); }
+
 // Layout of the staging buffer: [QDesc x nq][qoff x nq][subst, kMaxAlphabet^2 bytes][queries]
 // [plan items][query pairs]; the plan parts only when the plan travels with the queries (a caller's
 // workspace).
@@ -1017,10 +1021,10 @@ StageLayout stage_layout(const int64_t* h_qoffsets, int nq, const Plan* with_pla
     L.off_items = round_up(L.off_sm + kMaxAlphabet * kMaxAlphabet + (h_qoffsets[nq] - h_qoffsets[0]), 64);
     L.off_pairs = round_up(L.off_items + (with_plan ? with_plan->h_items.size() * sizeof(WgItem) : 0), 64);
     L.total = L.off_pairs + (with_plan && with_plan->qpack ? with_plan->h_pairs.size() * sizeof(int2) : 0);
-    L.max_mp = kProfRowAlign;
+    L.max_mp = prof_rows(1);
     for (int q = 0; q < nq; ++q) {
         const int m = (int)(h_qoffsets[q + 1] - h_qoffsets[q]);
-        const int mp = (int)round_up(std::max(m, 1), kProfRowAlign);
+        const int mp = prof_rows(m);
         L.prof_elems += (int64_t)kNRes * mp;
         L.max_mp = std::max(L.max_mp, mp);
     }
@@ -1223,7 +1227,7 @@ sw_status stage_queries(sw_db* db, const Work& W, const int8_t* h_queries, const
     int64_t* qo = reinterpret_cast<int64_t*>(h + L.off_qoff);
     for (int q = 0; q < nq; ++q) {
         const int m = (int)(h_qoffsets[q + 1] - h_qoffsets[q]);
-        const int mp = (int)round_up(std::max(m, 1), kProfRowAlign);
+        const int mp = prof_rows(m);
         int64_t top = 0;
         for (int64_t i = h_qoffsets[q]; i < h_qoffsets[q + 1]; ++i) top += best[h_queries[i]];
         qd[q] = QDesc{prof_off, (int64_t)q * score_row_stride, per_query_out ? per_query_out[q] : nullptr, m, mp,

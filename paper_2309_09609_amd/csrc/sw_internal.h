@@ -20,7 +20,6 @@ constexpr int kChunkBytes = kGroupPairs * 8;   // one chunk row of a group: 64 p
 constexpr int kWaves = 4;          // waves per workgroup of the sweep kernel
 constexpr int kRowsMax = 16;       // most query rows per lane (R) of any sweep instance
 constexpr int kSliceRows = 1024;   // largest rows-per-pass (B*R) kept in LDS: 64 lanes x 16 rows
-constexpr int kProfRowAlign = 1024;    // profile row stride is a multiple of this (covers every B*R)
 constexpr int16_t kSat16 = 0x7C00; // 16-bit scores at or above this are recomputed in 32 bits
 // End-to-end modes in 16-bit cells: every value carries kModeBias (the middle of
 // the exact range), and a pair whose H leaves [128, kModeTop) is recomputed in 32 bits.
@@ -73,7 +72,7 @@ struct QDesc {
     int64_t out_off;      // element offset of this query's score row in the common output
     int32_t* out;         // if non-null: this query's own score vector (out_off is then ignored)
     int32_t m;            // query length (>= 1)
-    int32_t mp;           // profile row stride (multiple of kProfRowAlign, >= m)
+    int32_t mp;           // profile row stride: a multiple of 256 that holds whole passes at every B x R
     int32_t span;         // local search: most subject residues an alignment with a positive score can cover
     int32_t unused;
 };

@@ -86,3 +86,23 @@ def test_query_pairs_chain(gpu, blosum, m):
         want = oracle.scores(q, db.residues, db.offsets, blosum, 10, 2)
         assert (got[i] == want).all(), f"query {i}: {np.nonzero(got[i] != want)[0][:5]}"
     D.close()
+
+
+@pytest.mark.parametrize("lens", [(769, 800, 1024), (944, 1100, 1563, 1888), (1537, 1549, 2048, 2305)])
+@pytest.mark.parametrize("subjects", [1343, 6000])
+def test_rows_past_the_query_in_passes_of_768(gpu, blosum, lens, subjects):
+    """A pass of 64 lanes x 12 rows reads the profile in steps of 768 rows, past a multiple of 1,024."""
+    rng = np.random.default_rng(55)
+    n = np.clip(np.exp(rng.normal(5.7, 0.6, subjects)), 20, 2400).astype(np.int64)
+    offs = np.concatenate([[0], np.cumsum(n)])
+    res = synth.background_residues(rng, int(offs[-1]))
+    qs = [synth.background_residues(rng, m) for m in lens]
+    D = gpu.Database(res, offs)
+    got = D.search_batch(qs + qs + qs, blosum, 11, 1)[0].cpu().numpy()
+    for i, q in enumerate(qs):
+        want = oracle.scores(q, res, offs, blosum, 11, 1)
+        one = D.search(q, blosum, 11, 1).cpu().numpy()
+        assert (one == want).all(), f"alone m={q.size}: {np.nonzero(one != want)[0][:5]}"
+        for k in (i, i + len(qs), i + 2 * len(qs)):
+            assert (got[k] == want).all(), f"batched m={q.size}: {np.nonzero(got[k] != want)[0][:5]}"
+    D.close()

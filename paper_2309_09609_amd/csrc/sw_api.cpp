@@ -126,21 +126,33 @@ struct HostPinned {
 constexpr double kUnitShare = 0.25;   // see plan_units
 
 // Work items of one search, run by one launch: the chained pairs (a workgroup
-// each) and the bulk on offset cells; on plain cells the bulk and, ahead of it,
-// the same pairs on a wave each (unchained).  Searches on
-// the handle's own workspace read the items from device copies made once;
-// searches on a caller's workspace upload them with the queries.
+// each) and the bulk on offset cells; on plain cells the bulk alone, long pairs
+// among it.  Searches on the handle's own workspace read the items from device
+// copies made once; searches on a caller's workspace upload them with the
+// queries.  That workspace has room for the offset cells' plan (sw_batch_workspace_bytes
+// does not know the scoring) and some more; should the plain cells' not fit, they
+// run the offset cells' one, the chained pairs on a wave each (unchained) ahead of the bulk.
 struct Plan {
     std::vector<WgItem> h_items;  // [chained..., bulk..., unchained...]
     std::vector<int2> h_pairs;    // query pairs (query a, query b or -1) when qpack
     int32_t n_chain = 0, n_main = 0, n_unchained = 0;
-    int32_t n_small = 0;          // bulk items at 4 rows per lane
+    int32_t n_small = 0, n_small_unchained = 0;   // of these at 4 rows per lane
     int R_main = 16;
     bool qpack = false;           // items index query pairs (two queries per lane)
     DevBuf items, qpairs;         // device copies (handle workspace only)
     bool on_device = false;
     void release() { items.release(); qpairs.release(); on_device = false; }
+    void clear() {
+        release();
+        h_items.clear();
+        n_chain = n_main = n_unchained = n_small = n_small_unchained = 0;
+    }
 };
+
+// What a plan is made for: offset cells, whose chained pairs may be cut into windows of the subject; offset cells of
+// whole subjects (global scores); plain cells.
+enum PlanKind { kPlanCut, kPlanWhole, kPlanPlain };
+constexpr int kPlanKinds = 3;
 
 // Device pointers of the staged queries (descriptors, offsets, matrix + residues).
 struct Staged {
@@ -270,9 +282,9 @@ struct sw_db {
     // reuses a buffer only once the copy of the call kStageRing before it has run
     HostPinned hstage[kStageRing];
     int hstage_next = 0;
-    std::map<int, Plan> plans;        // query length -> plan of a local or semi-global search, minus it -> global
-    Plan batch_plan, multi_plan;
-    std::vector<int> batch_qlens;
+    std::map<int64_t, Plan> plans;    // query length and kind -> plan of one query
+    Plan batch_plan[kPlanKinds], multi_plan;
+    std::vector<int> batch_qlens[kPlanKinds];
     GraphEntry graph;                 // batched form: last captured shape
     BatchKey last_eager;              // batched form: the last shape enqueued without a graph
     // tuning knobs and test hooks
@@ -342,21 +354,20 @@ sw_status apply_opts(sw_db* db, const sw_pack_opts* opts) {
 }
 
 // ------------------------------------------------------------------ planning
-// Issue slots of one unit (in half instructions): passes x steps x the step's
-// instruction count on offset cells, 6.25 per row of R plus loads, addressing and, with
-// cooperating lanes, the hand-over of the bottom row.
-int64_t unit_cost(int m, int ncols, int lgB, int R) {
-    const int B = 1 << lgB;
-    const int64_t passes = (m + (R << lgB) - 1) / (R << lgB);
-    const int64_t steps = round_up(ncols + B - 1, 4);
-    const int64_t per_step = 25 * R / 2 + 32 + (lgB ? 8 : 0);
-    return passes * steps * per_step;
+// Issue slots of a step of R rows per lane in half instructions: 6.25 instructions per row of offset cells and 9.5 of
+// plain ones, less the permutes where the lane holds two queries, plus loads, addressing and, with cooperating lanes,
+// the hand-over of the bottom row.
+int64_t step_cost(int cell, int R, bool coop, bool two_queries = false) {
+    const int64_t rows = cell == kCellOff ? (two_queries ? 21 : 25) * R / 2 + 32 : (two_queries ? 17 : 19) * R + 30;
+    return rows + (coop ? 8 : 0);
 }
 
 // Elapsed cost of a unit whose wave issues ahead of the others of its SIMD (long units run at raised priority), in
-// the same units: a lone wave's step takes 70 + 11 R ns (measured at 4, 8 and 16 rows per lane), about 35 units more
-// than it issues for, and other waves' instructions in flight hold up every one of its own (x 1.4).
-int64_t elapsed(int64_t step_cost, int64_t steps) { return (step_cost + 35) * steps * 7 / 5; }
+// the same units.  A lone wave's step takes 70 + 11 R ns on offset cells (measured at 4, 8 and 16 rows per lane), about
+// 35 units more than it issues for; on plain cells 50 + 16 R, 16 units more; in the end-to-end modes on plain cells 120 +
+// 19 R, 100 units more.  Other waves' instructions in flight hold up every one of its own (x 1.4).
+constexpr int kLoneOff = 35, kLonePlain = 16, kLoneModes = 100;
+int64_t elapsed(int64_t step, int lone, int64_t steps) { return (step + lone) * steps * 7 / 5; }
 
 // The same for one pair on a workgroup (a chain item): its four waves at 4 rows per lane run side by side, 96
 // steps apart, or on windows of the subject (whose overlap depends on the query; 4 m is typical), which global scores
@@ -368,7 +379,7 @@ int64_t chain_cost(int m, int ncols, bool cut, int parts = 1) {
     int64_t cols = share + lead;
     for (int windows = cut ? 4 / waves : 1; windows > 1; --windows)
         if (4 * m + share / windows <= cols - cols / 4) { cols = share / windows + 4 * m; break; }
-    return elapsed(25 * 4 / 2 + 55, passes * (cols + 100 * waves));
+    return elapsed(25 * 4 / 2 + 55, kLoneOff, passes * (cols + 100 * waves));
 }
 
 // The parts to split a chained pair into, so that it ends within `busy`: the fewest that do, or as many as still
@@ -475,22 +486,24 @@ void push_chain(std::vector<PlanItem>& to, int g, int q, int k, int parts, int64
     splits += parts > 1;
 }
 
-// Units of one query by lanes per pair: what a unit of `cols` columns costs (unit_cost, and elapsed where it runs
-// alone, without a division for each).
+// Units of one query by lanes per pair: what a unit of `cols` columns costs to issue (passes x steps x the step's
+// cost), and elapsed where it runs alone.
 struct CostTable {
+    int lone_step;
     int64_t passes[7], step[7];
     int pad[7];
-    CostTable(int m, int R) {
+    CostTable(int m, int R, int cell, bool modes = false)
+        : lone_step(cell == kCellOff ? kLoneOff : modes ? kLoneModes : kLonePlain) {
         for (int l = 0; l < 7; ++l) {
             passes[l] = (m + (R << l) - 1) / (R << l);
-            step[l] = 25 * R / 2 + 32 + (l ? 8 : 0);
+            step[l] = step_cost(cell, R, l > 0);
             pad[l] = (int)round_up((1 << l) - 1, 4);
         }
     }
     // (a unit's columns are a multiple of 4)
     int64_t steps(int cols, int l) const { return passes[l] * (cols + pad[l]); }
     int64_t unit(int cols, int l) const { return steps(cols, l) * step[l]; }
-    int64_t lone(int cols, int l) const { return elapsed(step[l], steps(cols, l)); }
+    int64_t lone(int cols, int l) const { return elapsed(step[l], lone_step, steps(cols, l)); }
 };
 
 // Work items for queries of lengths qlens (query index = position) against all
@@ -519,12 +532,13 @@ struct CostTable {
 struct PlanLimits { int R; int64_t slot_cap; int64_t nwaves; bool side = false; };
 
 // Groups [g_lo, g_hi) only (g_hi < 0: to the end).
-// head_out takes the chained pairs and side_out the same as units of one wave; head_out is null for end-to-end modes
-// on plain cells, whose long pairs go to side_out alone.  whole: a subject cannot be cut into windows (global scores).
-void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std::vector<WgItem>& main_out,
-                std::vector<WgItem>& side_out, std::vector<WgItem>* head_out, const std::vector<int>* chunk = nullptr,
+// Offset cells: head_out takes the chained pairs and side_out the same as units of one wave.  Plain cells chain none;
+// under limits (end-to-end modes) the long pairs of a single query may go to side_out at fewer rows per lane.
+void plan_units(const sw_db* db, const std::vector<int>& qlens, PlanKind kind, Plan* plan, std::vector<WgItem>& main_out,
+                std::vector<WgItem>& side_out, std::vector<WgItem>& head_out, const std::vector<int>* chunk = nullptr,
                 int nchunks = 1, const PlanLimits* lim = nullptr, int g_lo = 0, int g_hi = -1,
-                int* side_rows_out = nullptr, bool whole = false) {
+                int* side_rows_out = nullptr) {
+    const int cell = kind == kPlanPlain ? kCellI16 : kCellOff;
     if (g_hi < 0) g_hi = db->ngroups;
     const int64_t slot_cap = lim ? lim->slot_cap : db->slot_cap;
     const bool force_R = lim ? true : db->force_R != 0;
@@ -547,7 +561,7 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
         int r = R_main;
         if (qlens.size() == 1 && (!force_R || (lim && lim->side)))
             for (int R : kRowChoices)
-                if (unit_cost(m, db->ncols_max, 6, R) < unit_cost(m, db->ncols_max, 6, r)) r = R;
+                if (CostTable(m, R, cell, true).lone(db->ncols_max, 6) < CostTable(m, r, cell, true).lone(db->ncols_max, 6)) r = R;
         return r;
     };
     // The groups a sketch looks at: the longest ones each, of the rest of a large database every stride-th for its
@@ -571,20 +585,20 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
         std::vector<CostTable> big, small;
         int64_t total = 0;
         for (size_t qi = 0; qi < qlens.size(); ++qi) {
-            big.emplace_back(std::max(qlens[qi], 1), R_main);
-            small.emplace_back(std::max(qlens[qi], 1), kSmallRows);
+            big.emplace_back(std::max(qlens[qi], 1), R_main, cell);
+            small.emplace_back(std::max(qlens[qi], 1), kSmallRows, cell);
             if (qlens[qi] <= 0) continue;
             walk(qi, full, [&](int g, int w) { total += w * big[qi].unit(db->ncols[g], 0); });
         }
         const double cap = share * (double)total / (double)nwaves;
         K.cap = (int64_t)std::min(cap, 9.0e18);
-        const bool mix = head_out && R_main != kSmallRows && db->force_lgB < 0 && db->force_R == 0;
+        const bool mix = !lim && R_main != kSmallRows && db->force_lgB < 0 && db->force_R == 0;
         int64_t sum = 0, biggest = 0;
         double lone_sum = 0, lone_end = 0;
         for (size_t qi = 0; qi < qlens.size(); ++qi) {
             const int m = qlens[qi];
             if (m <= 0) continue;
-            const CostTable side(m, head_out ? R_main : side_rows(m, R_main));
+            const CostTable side(m, lim ? side_rows(m, R_main) : R_main, cell, lim != nullptr);
             walk(qi, full, [&](int g, int weight) {
                 const int nc = db->ncols[g];
                 // the fewest lanes per pair whose units stay within the share (6: perhaps none do)
@@ -615,7 +629,7 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
                     if (t.unit(pc[kGroupPairs - 1], 6) > K.cap) k = kGroupPairs;
                     else while (t.unit(pc[k], 6) > K.cap) ++k;
                     if (k > 0) {
-                        const CostTable& w = head_out ? t : side;
+                        const CostTable& w = lim ? side : t;
                         const double e = (double)w.lone(pc[0], 6);
                         lone_sum += 0.5 * k * weight * (e + (double)w.lone(pc[k - 1], 6));
                         lone_end = std::max(lone_end, e);
@@ -632,12 +646,17 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
         // issue time: the SIMDs share the total; a unit shares its SIMD with the other resident waves
         const double nsimd = 4.0 * db->cus, per_simd = (double)nwaves / nsimd;
         K.end = std::max((double)sum / nsimd, (double)biggest * per_simd);
-        if (!head_out) {
+        if (lim) {
             K.end = std::max(K.end, lone_end * per_simd);
             return K;
         }
-        // only units that take more than half of the search's issue time can outlast it
         const double all = (double)sum + kLoneIssue * lone_sum;
+        K.end = std::max(K.end, all / nsimd + kLarge * (double)biggest * per_simd);
+        if (cell != kCellOff) {
+            K.end = std::max(K.end, lone_end);
+            return K;
+        }
+        // only units that take more than half of the search's issue time can outlast it
         std::vector<LongUnit> longs;
         double below = 0;
         size_t at = 0;
@@ -664,24 +683,24 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
         std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
         longs.resize(chain_cut(db, longs, all, below, &K.end, [&](LongUnit& u, double busy) {
             const int uc = db->pcols[(size_t)u.g * kGroupPairs + u.k];
-            u.parts[0] = chain_parts(qlens[u.q], uc, !whole, busy);
-            u.chain = chain_cost(qlens[u.q], uc, !whole, u.parts[0]);
+            u.parts[0] = chain_parts(qlens[u.q], uc, kind == kPlanCut, busy);
+            u.chain = chain_cost(qlens[u.q], uc, kind == kPlanCut, u.parts[0]);
             u.chain_sum = u.parts[0] * u.chain;
         }));
-        K.end = std::max(K.end, all / nsimd + kLarge * (double)biggest * per_simd);
         K.chained.swap(longs);
         return K;
     };
-    const bool one = force_R && (!head_out || db->fixed_share || db->force_lgB >= 0);     // nothing to choose
+    const bool one = force_R && (lim || db->fixed_share || db->force_lgB >= 0);           // nothing to choose
     Sketch K = sketch(lim ? lim->R : db->force_R ? db->force_R : 16, db->unit_share, one || stride == 1);
     if (!force_R) {
         // fewer rows per lane pay more per cell but pad less when lanes cooperate on a short query
         for (int R : {12, 8}) {
+            if (R == 12 && cell != kCellOff) continue;       // (no kernel)
             Sketch other = sketch(R, db->unit_share, stride == 1);
             if (other.end < K.end) std::swap(K, other);
         }
     }
-    if (head_out && !db->fixed_share && db->force_lgB < 0) {
+    if (!lim && !db->fixed_share && db->force_lgB < 0) {
         Sketch other = sketch(K.R, 0.5 * db->unit_share, stride == 1);
         if (other.end < K.end) std::swap(K, other);
     }
@@ -696,10 +715,10 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
     for (size_t qi = 0; qi < qlens.size(); ++qi) {
         const int m = qlens[qi];
         if (m <= 0) continue;
-        const CostTable big(m, K.R), small(m, kSmallRows);
-        // without chains, a single query's long pairs go to the side list at fewer rows per lane where that is cheaper
-        const int r_long = head_out ? K.R : side_rows(m, K.R);
-        const CostTable lone(m, r_long);
+        const CostTable big(m, K.R, cell), small(m, kSmallRows, cell);
+        // under limits a single query's long pairs go to the side list at fewer rows per lane where that is cheaper
+        const int r_long = lim ? side_rows(m, K.R) : K.R;
+        const CostTable lone(m, r_long, cell);
         Bundle bulk(main, (int)qi, nchunks), bulk4(main, (int)qi, nchunks);
         Bundle apart(side, (int)qi, nchunks), apart4(side, (int)qi, nchunks);
         int64_t seq = (start_group(qi) - first_group(qi)) / nchunks;
@@ -727,9 +746,9 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
     }
     emit(main, main_out);
     emit(side, side_out);
-    if (head_out) emit(head, *head_out);
+    emit(head, head_out);
     plan->R_main = K.R;
-    if (side_rows_out) *side_rows_out = head_out || qlens.size() != 1 ? K.R : side_rows(qlens[0], K.R);
+    if (side_rows_out) *side_rows_out = qlens.size() != 1 ? K.R : side_rows(qlens[0], K.R);
 }
 
 // Query-pair plan: queries on the same chunk are sorted by length and paired
@@ -742,26 +761,28 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std:
 // The smaller estimated end decides: on a large database the passes count (16
 // queries of 62 to 4,868 residues over 40,000 subjects, all paired 31.7 ms, by
 // length 27.0), on a small one, whose units need many lanes, a pass of them
-// takes a short query as well as a long one, and a pair saves half the units (68 and
+// takes a short query as well as a long one, and a pair saves half the units (on
+// plain cells also a query without a partner: its step is the shorter one; 68 and
 // 115 residues over 12,000 subjects of 300 residues: apart, a unit to an item, 1.67
 // ms; paired, four to an item, 0.43).
 // A pair's unit holds P = 64/B subjects and a group 2B units; B is capped at 32
 // (the interleaved slice is twice as large).  Long subject pairs are chained as
 // in plan_units (a chain item takes one query against the two subjects), the
 // others of their length bundled with the rest, and half the share is tried.
-void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, std::vector<WgItem>& out,
+void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, PlanKind kind, Plan* plan, std::vector<WgItem>& out,
                    std::vector<WgItem>& side_out, std::vector<WgItem>& head_out, std::vector<int2>& pairs,
                    const std::vector<int>* chunk, int nchunks) {
     const int R = db->force_R == 8 ? 8 : 16;
+    const int cell = kind == kPlanPlain ? kCellI16 : kCellOff;
     auto ch = [&](int q) { return chunk ? (*chunk)[q] : 0; };
-    auto step2 = [&](int l) { return (int64_t)(21 * R / 2 + 32 + (l ? 8 : 0)); };
-    // One query, or two (x the longer one): what its units cost.
+    auto step2 = [&](int l) { return step_cost(cell, R, l > 0, true); };
+    // One query, or a pair (x the longer one): what its units cost.
     struct Entry {
-        int x, y, pair;            // y < 0: one query
+        int x, y, pair;            // pair < 0: one query, two subjects per lane
         CostTable t;
-        int most() const { return y < 0 ? 6 : 5; }             // log2 of the most lanes
-        int units(int l) const { return y < 0 ? 1 << l : 2 << l; }
-        int first_pair(int k, int l) const { return y < 0 ? k << (6 - l) : (k * (kGroupPairs >> l)) >> 1; }
+        int most() const { return pair < 0 ? 6 : 5; }          // log2 of the most lanes
+        int units(int l) const { return pair < 0 ? 1 << l : 2 << l; }
+        int first_pair(int k, int l) const { return pair < 0 ? k << (6 - l) : (k * (kGroupPairs >> l)) >> 1; }
     };
     std::vector<int> order;
     for (int q = 0; q < (int)qlens.size(); ++q)
@@ -772,15 +793,17 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
     auto entries_of = [&](bool all, std::vector<int2>& to) {
         std::vector<Entry> entries;
         for (size_t i = 0; i < order.size(); ++i) {
-            Entry e{order[i], -1, -1, CostTable(qlens[order[i]], R)};
+            Entry e{order[i], -1, -1, CostTable(qlens[order[i]], R, cell)};
+            bool paired = all && cell != kCellOff;           // (half its lanes empty, if it has no partner)
             if (i + 1 < order.size() && ch(order[i]) == ch(order[i + 1])) {
-                const CostTable next(qlens[order[i + 1]], R);
-                if (all || 2 * e.t.passes[0] * step2(0) <= (e.t.passes[0] + next.passes[0]) * e.t.step[0]) {
-                    e.y = order[++i];
-                    e.pair = (int)to.size();
-                    for (int l = 0; l < 7; ++l) e.t.step[l] = step2(l);
-                    to.push_back(make_int2(e.x, e.y));
-                }
+                const CostTable next(qlens[order[i + 1]], R, cell);
+                paired = all || 2 * e.t.passes[0] * step2(0) <= (e.t.passes[0] + next.passes[0]) * e.t.step[0];
+                if (paired) e.y = order[++i];
+            }
+            if (paired) {
+                e.pair = (int)to.size();
+                for (int l = 0; l < 7; ++l) e.t.step[l] = step2(l);
+                to.push_back(make_int2(e.x, e.y));
             }
             entries.push_back(e);
         }
@@ -864,6 +887,11 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
                 }
             }
         }
+        if (cell != kCellOff) {
+            for (const LongUnit& u : longs) below = std::max(below, (double)u.cost);
+            K.end = std::max(below, all / nsimd + kLarge * biggest * per_simd);
+            return K;
+        }
         std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
         longs.resize(chain_cut(db, longs, all, below, &K.end, [&](LongUnit& u, double busy) {
             const int uc = db->pcols[(size_t)u.g * kGroupPairs + u.k];
@@ -888,9 +916,9 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
         if (better) std::swap(K, other);
         return better;
     };
-    // (all in pairs where that is clearly shorter: at 0.85 of the estimate, 600 subjects of 3,000 to 12,000 residues
-    // against 77 and 203, it took 0.87 ms instead of 0.74)
-    const bool all_pairs = K.pairs.size() < order.size() / 2 && instead(true, db->unit_share, 0.8);
+    // (all in pairs where that is clearly shorter on offset cells, whose estimates of chained pairs are rough: at 0.85 of
+    // the estimate, 600 subjects of 3,000 to 12,000 residues against 77 and 203, it took 0.87 ms instead of 0.74)
+    const bool all_pairs = 2 * K.pairs.size() < order.size() && instead(true, db->unit_share, cell == kCellOff ? 0.8 : 1.0);
     if (!db->fixed_share && db->force_lgB < 0) instead(all_pairs, 0.5 * db->unit_share, 1.0);
     std::vector<PlanItem> main, side, head;
     int splits = 0;
@@ -905,7 +933,7 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
     size_t at = 0;
     for (size_t ei = 0; ei < K.entries.size(); ++ei) {
         const Entry& e = K.entries[ei];
-        const int q = e.y < 0 ? e.x : e.pair, flag = e.y < 0 ? kItemSmall : 0;
+        const int q = e.pair < 0 ? e.x : e.pair, flag = e.pair < 0 ? kItemSmall : 0;
         Bundle bulk(main, q, nchunks), apart(side, q, nchunks);
         int64_t seq = 0;
         for (int g = ch(e.x); g < db->ngroups; g += nchunks, ++seq) {
@@ -929,23 +957,26 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, Plan* plan, s
     plan->R_main = R;
 }
 
-sw_status build_plan(sw_db* db, const std::vector<int>& qlens, Plan* p, const std::vector<int>* chunk = nullptr,
-                     int nchunks = 1, bool whole = false) {
+sw_status build_plan(sw_db* db, const std::vector<int>& qlens, PlanKind kind, Plan* p,
+                     const std::vector<int>* chunk = nullptr, int nchunks = 1) {
     std::vector<WgItem> mi, si, hi;
     std::vector<int2> pairs;
     int nonempty = 0;
     for (int m : qlens) nonempty += m > 0;
     p->qpack = db->lane_pack == 2 && nonempty >= 2;
     if (p->qpack)
-        plan_units_q2(db, qlens, p, mi, si, hi, pairs, chunk, nchunks);
+        plan_units_q2(db, qlens, kind, p, mi, si, hi, pairs, chunk, nchunks);
     else
-        plan_units(db, qlens, p, mi, si, &hi, chunk, nchunks, nullptr, 0, -1, nullptr, whole);
+        plan_units(db, qlens, kind, p, mi, si, hi, chunk, nchunks);
     p->n_chain = (int32_t)hi.size();
     p->n_main = (int32_t)mi.size();
     p->n_unchained = (int32_t)si.size();
-    p->n_small = 0;
-    if (!p->qpack)
-        for (const WgItem& it : mi) p->n_small += it.lgB >= kItemSmall;
+    auto small = [&](const std::vector<WgItem>& v) {
+        if (p->qpack) return 0;
+        return (int32_t)std::count_if(v.begin(), v.end(), [](const WgItem& it) { return it.lgB >= kItemSmall; });
+    };
+    p->n_small = small(mi);
+    p->n_small_unchained = small(si);
     mi.insert(mi.begin(), hi.begin(), hi.end());
     mi.insert(mi.end(), si.begin(), si.end());
     p->h_items.swap(mi);
@@ -969,8 +1000,8 @@ sw_status upload_plan(sw_db* db, Plan* p) {
     return SW_OK;
 }
 
-sw_status get_plan(sw_db* db, int m, Plan** out, bool whole = false) {
-    const int key = whole ? -m : m;
+sw_status get_plan(sw_db* db, int m, PlanKind kind, Plan** out) {
+    const int64_t key = (int64_t)m * kPlanKinds + kind;
     auto it = db->plans.find(key);
     if (it != db->plans.end()) { *out = &it->second; return SW_OK; }
     if (db->plans.size() >= 64) {
@@ -978,22 +1009,28 @@ sw_status get_plan(sw_db* db, int m, Plan** out, bool whole = false) {
         db->plans.clear();
     }
     Plan& p = db->plans[key];
-    sw_status s = build_plan(db, std::vector<int>{m}, &p, nullptr, 1, whole);
+    sw_status s = build_plan(db, std::vector<int>{m}, kind, &p);
     if (s != SW_OK) { p.release(); db->plans.erase(key); return s; }
     *out = &p;
     return SW_OK;
 }
 
+// Room for a plan in a caller's workspace: the offset cells' plan of the same queries and half as much again.
+struct PlanRoom {
+    size_t items = 0, pairs = 0;
+    PlanRoom() = default;
+    PlanRoom(const Plan& p, int nq) : items(p.h_items.size() + p.h_items.size() / 2 + 64), pairs(p.qpack ? (nq + 1) / 2 : 0) {}
+    bool holds(const Plan& p) const { return p.h_items.size() <= items && p.h_pairs.size() <= pairs; }
+};
+
 void clear_caches(sw_db* db) {
     for (auto& kv : db->plans) kv.second.release();
     db->plans.clear();
-    db->batch_plan.release();
-    db->batch_plan.h_items.clear();
-    db->batch_plan.n_chain = db->batch_plan.n_main = db->batch_plan.n_unchained = 0;
-    db->multi_plan.release();
-    db->multi_plan.h_items.clear();
-    db->multi_plan.n_chain = db->multi_plan.n_main = db->multi_plan.n_unchained = 0;
-    db->batch_qlens.clear();
+    for (int k = 0; k < kPlanKinds; ++k) {
+        db->batch_plan[k].clear();
+        db->batch_qlens[k].clear();
+    }
+    db->multi_plan.clear();
     db->graph.clear();
     db->last_eager = BatchKey();
 }
@@ -1065,17 +1102,17 @@ sw_status ensure_geometry(sw_db* db) {
 int prof_rows(int m) { return (int)std::max(round_up(std::max(m, 1), 1024), round_up(std::max(m, 1), 768)); }
 
 // Layout of the staging buffer: [QDesc x nq][qoff x nq][subst, kMaxAlphabet^2 bytes][queries]
-// [plan items][query pairs]; the plan parts only when the plan travels with the queries (a caller's
+// [query pairs][plan items]; the plan parts only when the plan travels with the queries (a caller's
 // workspace).
-struct StageLayout { size_t off_qoff, off_sm, off_items, off_pairs, total; int64_t prof_elems; int max_mp; };
+struct StageLayout { size_t off_qoff, off_sm, off_pairs, off_items, total; int64_t prof_elems; int max_mp; };
 
-StageLayout stage_layout(const int64_t* h_qoffsets, int nq, const Plan* with_plan = nullptr) {
+StageLayout stage_layout(const int64_t* h_qoffsets, int nq, const PlanRoom& room) {
     StageLayout L{};
     L.off_qoff = round_up(sizeof(QDesc) * nq, 64);
     L.off_sm = L.off_qoff + round_up(sizeof(int64_t) * nq, 64);
-    L.off_items = round_up(L.off_sm + kMaxAlphabet * kMaxAlphabet + (h_qoffsets[nq] - h_qoffsets[0]), 64);
-    L.off_pairs = round_up(L.off_items + (with_plan ? with_plan->h_items.size() * sizeof(WgItem) : 0), 64);
-    L.total = L.off_pairs + (with_plan && with_plan->qpack ? with_plan->h_pairs.size() * sizeof(int2) : 0);
+    L.off_pairs = round_up(L.off_sm + kMaxAlphabet * kMaxAlphabet + (h_qoffsets[nq] - h_qoffsets[0]), 64);
+    L.off_items = round_up(L.off_pairs + room.pairs * sizeof(int2), 64);
+    L.total = L.off_items + room.items * sizeof(WgItem);
     L.max_mp = prof_rows(1);
     for (int q = 0; q < nq; ++q) {
         const int m = (int)(h_qoffsets[q + 1] - h_qoffsets[q]);
@@ -1108,10 +1145,9 @@ struct WsLayout {
     int64_t rerun_cap = 0, bits_words = 0;
 };
 
-WsLayout ws_layout(const sw_db* db, const int64_t* h_qoffsets, int nq, int k, bool with_scores,
-                   const Plan* with_plan) {
+WsLayout ws_layout(const sw_db* db, const int64_t* h_qoffsets, int nq, int k, bool with_scores, const PlanRoom& room) {
     WsLayout L;
-    L.st = stage_layout(h_qoffsets, nq, with_plan);
+    L.st = stage_layout(h_qoffsets, nq, room);
     L.rerun_cap = rerun_capacity(db, nq);
     L.bits_words = rerun_words(db, nq);
     int64_t o = 0;
@@ -1166,10 +1202,10 @@ Work carve(void* base, const WsLayout& L) {
 // The workspace of a launch sequence: the caller's (d_ws, checked against the layout) or the
 // handle's own (grown as needed); plan items from the plan's device copy or, with a caller's
 // workspace, from the staging area they are uploaded to.
-sw_status get_work(sw_db* db, const int64_t* h_qoffsets, int nq, int k, bool with_scores, Plan* plan, void* d_ws,
-                   int64_t ws_bytes, Work* out) {
+sw_status get_work(sw_db* db, const int64_t* h_qoffsets, int nq, int k, bool with_scores, Plan* plan,
+                   const PlanRoom& room, void* d_ws, int64_t ws_bytes, Work* out) {
     const bool caller = d_ws != nullptr;
-    const WsLayout L = ws_layout(db, h_qoffsets, nq, k, with_scores, caller ? plan : nullptr);
+    const WsLayout L = ws_layout(db, h_qoffsets, nq, k, with_scores, room);
     if (caller) {
         if (ws_bytes < L.total)
             return fail(SW_E_SIZE, "workspace of %lld bytes < %lld needed", (long long)ws_bytes, (long long)L.total);
@@ -1299,7 +1335,8 @@ sw_status stage_queries(sw_db* db, const Work& W, const int8_t* h_queries, const
         if (with_plan->qpack && !with_plan->h_pairs.empty())
             memcpy(h + L.off_pairs, with_plan->h_pairs.data(), with_plan->h_pairs.size() * sizeof(int2));
     }
-    HIP_TRY(hipMemcpyAsync(W.stage, h, L.total, hipMemcpyHostToDevice, st));
+    const size_t used = L.off_items + (with_plan ? with_plan->h_items.size() * sizeof(WgItem) : 0);
+    HIP_TRY(hipMemcpyAsync(W.stage, h, used, hipMemcpyHostToDevice, st));
     HIP_TRY(hipEventRecord(W.host->done, st));
     W.host->pending = true;
     const char* d = W.stage;
@@ -1377,6 +1414,10 @@ CellForm choose_mode_form(const sw_db* db, int32_t mode, const int8_t* subst, in
     return f;
 }
 
+PlanKind plan_kind(const CellForm& f) {
+    return f.cell != kCellOff ? kPlanPlain : f.mode == SW_GLOBAL ? kPlanWhole : kPlanCut;
+}
+
 // Timing events of the dominant launches (sw_profile_kernels): a ring of
 // kTimerSlots start/stop pairs; the oldest is forgotten when it is full.
 constexpr int kTimerSlots = 4096;
@@ -1446,9 +1487,9 @@ sw_status enqueue(sw_db* db, const Staged& S, const CellForm& form, const Plan& 
     if (k > 0)
         HIP_TRY(launch_topk_ws(d_scores, n, n, S.nq, k, top_s, top_i, topk_ws_bytes(n, S.nq, k) > 0 ? W.topk : nullptr,
                                st));
-    db->last_items = plan.n_main - plan.n_small;
+    db->last_side_items = plan.n_small + (off ? plan.n_chain : plan.n_small_unchained);
+    db->last_items = a.n_items - db->last_side_items;
     db->last_rows = R;
-    db->last_side_items = a.n_items - db->last_items;
     db->last_side_rows = db->last_side_items > 0 ? kSmallRows : 0;
     db->last_grid = grid;
     db->last_counters = ctr;
@@ -1646,15 +1687,25 @@ sw_status search_one(const int8_t* h_query, int32_t qlen, sw_db* db, const int64
     DeviceGuard dg(db->device);
     if (qlen == 0) { HIP_TRY(launch_fill(d_scores_out, n, 0, st)); return SW_OK; }
     if ((s = ensure_geometry(db)) != SW_OK) return s;
-    Plan* plan = nullptr;
-    if ((s = get_plan(db, qlen, &plan)) != SW_OK) return s;
     const int64_t qo[2] = {0, qlen};
+    const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_query, qo, 1);
+    PlanKind kind = plan_kind(form);
+    PlanRoom room;
+    Plan* plan = nullptr;
+    if (d_ws) {
+        if ((s = get_plan(db, qlen, kPlanCut, &plan)) != SW_OK) return s;
+        room = PlanRoom(*plan, 1);
+        if (kind != kPlanCut) {
+            if ((s = get_plan(db, qlen, kind, &plan)) != SW_OK) return s;
+            if (!room.holds(*plan)) kind = kPlanCut;
+        }
+    }
+    if ((s = get_plan(db, qlen, kind, &plan)) != SW_OK) return s;
     Work W;
-    if ((s = get_work(db, qo, 1, 0, false, plan, d_ws, ws_bytes, &W)) != SW_OK) return s;
+    if ((s = get_work(db, qo, 1, 0, false, plan, room, d_ws, ws_bytes, &W)) != SW_OK) return s;
     Staged S;
     if ((s = stage_queries(db, W, h_query, qo, 1, h_subst, gap_open, gap_extend, 0, st, &S, nullptr, d_ws ? plan : nullptr)) != SW_OK)
         return s;
-    const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_query, qo, 1);
     return enqueue(db, S, form, *plan, W, gap_open, gap_extend, d_scores_out, n, 0, nullptr, nullptr, st, true);
 }
 
@@ -1662,17 +1713,18 @@ sw_status search_one(const int8_t* h_query, int32_t qlen, sw_db* db, const int64
 
 namespace {
 
-// The batch plan for these query lengths (kept while the lengths repeat).
-sw_status plan_for(sw_db* db, const std::vector<int>& qlens, Plan** out) {
-    if (qlens != db->batch_qlens) {
-        if (db->batch_plan.on_device) HIP_TRY(hipDeviceSynchronize());   // a batch in flight may read its items
-        db->batch_qlens.clear();
-        db->batch_plan.release();
-        sw_status s = build_plan(db, qlens, &db->batch_plan);
+// The batch plan of a kind for these query lengths (kept while the lengths repeat).
+sw_status plan_for(sw_db* db, const std::vector<int>& qlens, PlanKind kind, Plan** out) {
+    Plan& p = db->batch_plan[kind];
+    if (qlens != db->batch_qlens[kind]) {
+        if (p.on_device) HIP_TRY(hipDeviceSynchronize());     // a batch in flight may read its items
+        db->batch_qlens[kind].clear();
+        p.release();
+        sw_status s = build_plan(db, qlens, kind, &p);
         if (s != SW_OK) return s;
-        db->batch_qlens = qlens;
+        db->batch_qlens[kind] = qlens;
     }
-    *out = &db->batch_plan;
+    *out = &p;
     return SW_OK;
 }
 
@@ -1707,13 +1759,22 @@ sw_status search_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int32
     if ((s = ensure_geometry(db)) != SW_OK) return s;
     std::vector<int> qlens(nq);
     for (int q = 0; q < nq; ++q) qlens[q] = (int)(h_qoffsets[q + 1] - h_qoffsets[q]);
+    const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_queries, h_qoffsets, nq);
+    const PlanKind kind = plan_kind(form);
     // On the handle's workspace the plan's device copy may still be read by the previous batch; a caller's
     // workspace receives the plan with the queries, in stream order, so nothing waits.
-    if (!d_ws && qlens != db->batch_qlens) HIP_TRY(hipStreamSynchronize(st));
+    if (!d_ws && qlens != db->batch_qlens[kind]) HIP_TRY(hipStreamSynchronize(st));
     Plan* plan = nullptr;
-    if ((s = plan_for(db, qlens, &plan)) != SW_OK) return s;
+    if ((s = plan_for(db, qlens, kind, &plan)) != SW_OK) return s;
+    PlanRoom room;
+    if (d_ws) {
+        Plan* cut = plan;
+        if (kind != kPlanCut && (s = plan_for(db, qlens, kPlanCut, &cut)) != SW_OK) return s;
+        room = PlanRoom(*cut, nq);
+        if (!room.holds(*plan)) plan = cut;
+    }
     Work W;
-    if ((s = get_work(db, h_qoffsets, nq, k, d_scores == nullptr, plan, d_ws, ws_bytes, &W)) != SW_OK) return s;
+    if ((s = get_work(db, h_qoffsets, nq, k, d_scores == nullptr, plan, room, d_ws, ws_bytes, &W)) != SW_OK) return s;
     int32_t* scores = d_scores ? d_scores : W.scores;
     // zero-length queries score 0 everywhere (outside the captured sequence)
     for (int q = 0; q < nq; ++q)
@@ -1721,7 +1782,6 @@ sw_status search_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int32
     Staged S;
     if ((s = stage_queries(db, W, h_queries, h_qoffsets, nq, h_subst, gap_open, gap_extend, n, st, &S, nullptr, d_ws ? plan : nullptr)) != SW_OK)
         return s;
-    const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_queries, h_qoffsets, nq);
     GraphEntry& G = db->graph;
     BatchKey key;
     key.qlens = qlens;
@@ -1889,9 +1949,9 @@ sw_status sw_db_info(const sw_db* db, int64_t* n, int64_t* residues, int64_t* de
     if (device_bytes) {
         // everything the handle itself allocated: its image, workspace, plan copies, alignment buffers
         size_t b = db->image_own.bytes + db->ws_own.bytes + db->align_dirs.bytes + db->align_bnd.bytes +
-                   db->align_misc.bytes + db->mode_plan.items.bytes + db->batch_plan.items.bytes +
-                   db->batch_plan.qpairs.bytes + db->multi_plan.items.bytes + db->multi_plan.qpairs.bytes;
+                   db->align_misc.bytes + db->mode_plan.items.bytes + db->multi_plan.items.bytes + db->multi_plan.qpairs.bytes;
         for (const auto& kv : db->plans) b += kv.second.items.bytes + kv.second.qpairs.bytes;
+        for (const Plan& p : db->batch_plan) b += p.items.bytes + p.qpairs.bytes;
         *device_bytes = (int64_t)b;
     }
     return SW_OK;
@@ -1974,9 +2034,9 @@ sw_status sw_batch_workspace_bytes(sw_db* db, const int64_t* h_qoffsets, int32_t
     std::vector<int> qlens(nq);
     for (int q = 0; q < nq; ++q) qlens[q] = (int)(h_qoffsets[q + 1] - h_qoffsets[q]);
     Plan* plan = nullptr;
-    if ((s = plan_for(db, qlens, &plan)) != SW_OK) return s;
+    if ((s = plan_for(db, qlens, kPlanCut, &plan)) != SW_OK) return s;
     const int64_t zero[1] = {0};
-    *bytes = ws_layout(db, nq ? h_qoffsets : zero, nq, k, scores_in_ws != 0, plan).total;
+    *bytes = ws_layout(db, nq ? h_qoffsets : zero, nq, k, scores_in_ws != 0, PlanRoom(*plan, nq)).total;
     return SW_OK;
 }
 
@@ -2009,13 +2069,13 @@ sw_status sw_search_multi(const int8_t* h_queries, const int64_t* h_qoffsets, in
     for (int q = 0; q < nq; ++q)
         if (qlens[q] == 0) HIP_TRY(launch_fill(h_d_scores[q], db->n, 0, st));
     HIP_TRY(hipStreamSynchronize(st));              // the previous call may still read the plan buffer
-    if ((s = build_plan(db, qlens, &db->multi_plan, &chunk, nchunks)) != SW_OK) return s;
+    const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_queries, h_qoffsets, nq);
+    if ((s = build_plan(db, qlens, plan_kind(form), &db->multi_plan, &chunk, nchunks)) != SW_OK) return s;
     if (db->multi_plan.h_items.empty()) return SW_OK;
     Work W;
-    if ((s = get_work(db, h_qoffsets, nq, 0, false, &db->multi_plan, nullptr, 0, &W)) != SW_OK) return s;
+    if ((s = get_work(db, h_qoffsets, nq, 0, false, &db->multi_plan, PlanRoom(), nullptr, 0, &W)) != SW_OK) return s;
     Staged S;
     if ((s = stage_queries(db, W, h_queries, h_qoffsets, nq, h_subst, gap_open, gap_extend, 0, st, &S, h_d_scores)) != SW_OK) return s;
-    const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_queries, h_qoffsets, nq);
     return enqueue(db, S, form, db->multi_plan, W, gap_open, gap_extend, nullptr, db->n, 0, nullptr, nullptr, st, true);
 }
 
@@ -2297,9 +2357,9 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
         HIP_TRY(hipStreamIsCapturing(st, &cap));
         if (cap != hipStreamCaptureStatusNone) return fail(SW_E_HIP, "end-to-end search on a stream under capture");
         Plan* plan = nullptr;
-        if ((s = get_plan(db, qlen, &plan, mode == SW_GLOBAL)) != SW_OK) return s;
+        if ((s = get_plan(db, qlen, plan_kind(form), &plan)) != SW_OK) return s;
         Work W;
-        if ((s = get_work(db, qo, 1, 0, false, plan, nullptr, 0, &W)) != SW_OK) return s;
+        if ((s = get_work(db, qo, 1, 0, false, plan, PlanRoom(), nullptr, 0, &W)) != SW_OK) return s;
         Staged S;
         if ((s = stage_queries(db, W, h_query, qo, 1, h_subst, gap_open, gap_extend, 0, st, &S, nullptr, nullptr, mode)) != SW_OK)
             return s;
@@ -2345,11 +2405,11 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
     const int mode16 = use_offset ? kModeGlobalOffset : mode;      // the 16-bit kernels' form
     const int32_t sm_shift = use_offset ? gap_extend : 0;
     // 16-bit plan at 16 rows per lane; the long pairs of a short query go to a side list at 4 or 8 rows
-    std::vector<WgItem> mi, si, m32, s32;
+    std::vector<WgItem> mi, si, m32, s32, none;
     if (g_split < db->ngroups) {
         PlanLimits lim{16, db->slot_cap, (int64_t)db->wg_mode * kWaves};
         lim.side = true;
-        plan_units(db, std::vector<int>{qlen}, &db->mode_plan, mi, si, nullptr, nullptr, 1, &lim, g_split, -1,
+        plan_units(db, std::vector<int>{qlen}, kPlanPlain, &db->mode_plan, mi, si, none, nullptr, 1, &lim, g_split, -1,
                    &db->mode_side_rows);
     }
     // (4 rows per lane measured no faster for the 32-bit chain of a short query, and slower for longer ones)
@@ -2358,7 +2418,7 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
         // 32-bit units in the 32-bit boundary slots: one wave slot holds the widest subject's columns
         const PlanLimits lim32{R32, std::max<int64_t>(db->ncols_max, 4), (int64_t)db->wg32 * kWaves};
         Plan tmp;
-        plan_units(db, std::vector<int>{qlen}, &tmp, m32, s32, nullptr, nullptr, 1, &lim32, 0, g_split);
+        plan_units(db, std::vector<int>{qlen}, kPlanPlain, &tmp, m32, s32, none, nullptr, 1, &lim32, 0, g_split);
     }
     HIP_TRY(hipStreamSynchronize(st));            // the plan buffer may still be read by an earlier launch
     // device item list: [16-bit main..., 16-bit side..., 32-bit...]
@@ -2368,7 +2428,7 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
     mi.insert(mi.end(), m32.begin(), m32.end());
     if (n_items) HIP_TRY(hipMemcpy(db->mode_plan.items.p, mi.data(), sizeof(WgItem) * n_items, hipMemcpyHostToDevice));
     Work W;
-    if ((s = get_work(db, qo, 1, 0, false, nullptr, nullptr, 0, &W)) != SW_OK) return s;
+    if ((s = get_work(db, qo, 1, 0, false, nullptr, PlanRoom(), nullptr, 0, &W)) != SW_OK) return s;
     Staged S;
     if ((s = stage_queries(db, W, h_query, qo, 1, h_subst, gap_open, gap_extend, 0, st, &S)) != SW_OK) return s;
     int32_t* ctr = W.counters;

@@ -32,3 +32,34 @@ def test_query_pairs_fill_their_workgroups(gpu, blosum, lens):
     for i, q in enumerate(qs):
         assert (got[i] == oracle.scores(q, db.residues, db.offsets, blosum, 10, 2)).all()
     D.close()
+
+
+def test_long_pair_on_plain_cells_takes_the_rows_that_fit(gpu, blosum):
+    """Gaps that offset cells cannot hold (Ge > Go): a long subject against 400 residues is one pass of 64 lanes at 8
+    rows, not two at 4 or a half-empty one at 16."""
+    db = _db([6000, 50])
+    D = gpu.Database(db.residues, db.offsets)
+    q = _query(400)
+    got = D.search(q, blosum, 3, 5).cpu().numpy()
+    st = D.stats()
+    assert st["rows_per_lane"] == 8 and st["side_items"] == 0, st
+    assert (got == oracle.scores(q, db.residues, db.offsets, blosum, 3, 5)).all()
+    D.close()
+
+
+@pytest.mark.parametrize("lens", [(400,), (150, 7, 3111, 20, 480, 99, 12, 1500)])
+@pytest.mark.parametrize("lane_pack", [1, 2])
+def test_plain_cells_in_a_callers_workspace(gpu, blosum, lens, lane_pack):
+    """sw_batch_workspace_bytes does not know the gaps: a workspace of exactly its size serves every scoring, whichever
+    plan fits it."""
+    rng = np.random.default_rng(7200)
+    db = _db(rng.integers(0, 60, 20000), seed=7201)
+    D = gpu.Database(db.residues, db.offsets, lane_pack=lane_pack, memory="torch")
+    qs = [_query(m) for m in lens]
+    for go, ge in ((3, 5), (10, 2), (3, 5)):
+        D.ws = None
+        got = D.search_batch(qs, blosum, go, ge, k=0)[0].cpu().numpy() if len(qs) > 1 else \
+            D.search(qs[0], blosum, go, ge).cpu().numpy()[None]
+        for i, q in enumerate(qs):
+            assert (got[i] == oracle.scores(q, db.residues, db.offsets, blosum, go, ge)).all(), (q.size, go, ge)
+    D.close()

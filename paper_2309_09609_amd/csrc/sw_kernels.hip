@@ -1146,12 +1146,15 @@ __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int 
 constexpr int kBitsBlock = 64;
 
 // Waves per SIMD the registers must allow: 3 at 12 or 16 rows per lane of 16-bit cells (168 VGPRs; without the bound
-// the allocator goes a few over and loses a third of the waves), 4 at fewer.
-template <class C, int R>
-constexpr int kMinWaves = std::is_same<C, CellI32>::value ? 1 : R >= 12 ? 3 : 4;
+// the allocator goes a few over and loses a third of the waves), 4 at fewer.  The plain cells' end-to-end modes fit by
+// themselves; the bound would only cost them waits in the step (4 rows per lane, semi-global, a lone wave: 6 % more
+// a step with it).
+template <class C, int R, int MODE>
+constexpr int kMinWaves = std::is_same<C, CellI32>::value || (MODE != 0 && std::is_same<C, CellI16>::value) ? 1
+                          : R >= 12 ? 3 : 4;
 
 template <class C, int R, int MODE = 0>
-__global__ __launch_bounds__(64 * kWaves, (kMinWaves<C, R>)) void k_sweep(SweepArgs a) {
+__global__ __launch_bounds__(64 * kWaves, (kMinWaves<C, R, MODE>)) void k_sweep(SweepArgs a) {
     // one shared slice of up to 64*R rows, or four per-wave slices of up to 16*R rows
     // (offset cells hold one byte a row, and need room for a chain item)
     constexpr bool kOffset = std::is_same<C, CellOff>::value;

@@ -63,3 +63,34 @@ def test_plain_cells_in_a_callers_workspace(gpu, blosum, lens, lane_pack):
         for i, q in enumerate(qs):
             assert (got[i] == oracle.scores(q, db.residues, db.offsets, blosum, go, ge)).all(), (q.size, go, ge)
     D.close()
+
+
+@pytest.mark.parametrize("mode", ["local", "semiglobal"])
+def test_a_long_pair_in_parts(gpu, blosum, mode):
+    """One long subject on several workgroups, beside 16 items of the group's other pairs.  At 10/2 and 11/1 an alignment
+    covers a bounded stretch of it and each part sweeps its own; at Ge = 0 the first part sweeps it all."""
+    db = _db([20000])
+    D = gpu.Database(db.residues, db.offsets)
+    for m in (100, 300, 1025):
+        q = _query(m)
+        for go, ge in ((10, 2), (11, 1), (12, 0)):
+            got = D.search(q, blosum, go, ge, mode=mode).cpu().numpy()
+            assert D.stats()["items"] + D.stats()["side_items"] > 17, (m, go, ge, D.stats())
+            assert (got == oracle.scores(q, db.residues, db.offsets, blosum, go, ge, mode=mode)).all(), (m, go, ge)
+    D.close()
+
+
+@pytest.mark.parametrize("mode", ["local", "semiglobal"])
+@pytest.mark.parametrize("m", [60, 257, 513, 1100])
+def test_parts_and_spans(gpu, blosum, mode, m):
+    """From a span of the query's own length (no gap pays) to one past the subject, on a caller's workspace too."""
+    db = _db([20011, 16000, 9001, 50, 40])
+    q = _query(m)
+    q[m // 2:] = db.residues[19500:19500 + m - m // 2]
+    for memory in ("library", "torch"):
+        D = gpu.Database(db.residues, db.offsets, memory=memory)
+        for go, ge in ((127, 32), (40, 20), (10, 5), (10, 2), (11, 1), (4, 1), (12, 0)):
+            got = D.search(q, blosum, go, ge, mode=mode).cpu().numpy()
+            want = oracle.scores(q, db.residues, db.offsets, blosum, go, ge, mode=mode)
+            assert (got == want).all(), (memory, go, ge, got, want)
+        D.close()

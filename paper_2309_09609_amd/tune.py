@@ -1,7 +1,7 @@
 """Autotuner for the batched search.
 
 Tries lane packing (two subjects or two queries in the 16-bit halves of a
-lane) and tiling and work-splitting choices of the sweep (rows per lane, the
+lane), as the planner chooses and with pinned tiling and work splitting (rows per lane, the
 size of a work unit relative to a persistent wave's share, a minimum number of
 cooperating lanes per subject) on a sample of the caller's batch and picks the
 fastest candidate that passes the parity gate:
@@ -27,8 +27,11 @@ import time
 
 import numpy as np
 
-# lane_pack 1: the two 16-bit halves of a lane hold two subjects; 2: two queries
+# lane_pack 1: the two 16-bit halves of a lane hold two subjects; 2: two queries.  The first of each kind are the
+# planner's own choice, which no pinned rows and share reach (12 rows per lane, groups at 4 rows, half the share).
 DEFAULT_CANDIDATES = [
+    dict(rows_per_lane=0, unit_share=0, force_lanes=0, lane_pack=1),
+    dict(rows_per_lane=0, unit_share=0, force_lanes=0, lane_pack=2),
     dict(rows_per_lane=16, unit_share=250, force_lanes=0, lane_pack=1),
     dict(rows_per_lane=16, unit_share=250, force_lanes=2, lane_pack=1),
     dict(rows_per_lane=16, unit_share=100, force_lanes=2, lane_pack=1),

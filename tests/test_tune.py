@@ -111,3 +111,13 @@ def test_cache_is_keyed_by_scoring_setup(small, tmp_path):
     sm2[0, 0] += 1
     assert tuner.shape_key("x", db.n, [q.size for q in qs], sm, 10, 2) != \
         tuner.shape_key("x", db.n, [q.size for q in qs], sm2, 10, 2)
+
+
+@pytest.mark.parametrize("lane_pack", [1, 2])
+def test_the_planners_own_choice_can_win(small, lane_pack):
+    """Untuned settings are among the default candidates: where they are the fastest, the handle stays with them."""
+    db, qs = small
+    mine = dict(rows_per_lane=0, unit_share=0, force_lanes=0, lane_pack=lane_pack)
+    fake = StandIn(db, mine, wrong=[])                # the one candidate without a pause
+    out = tuner.tune(fake, qs, blosum62(), 10, 2, repeats=1, use_cache=False)
+    assert out["knobs"] == mine and fake.knobs == mine

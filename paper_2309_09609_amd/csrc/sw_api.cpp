@@ -2126,7 +2126,10 @@ sw_status sw_last_stats(sw_db* db, int64_t out[8]) {
 // ------------------------------------------------------------------ alignments
 namespace {
 constexpr int64_t kAlignBudget = (int64_t)4 << 30;   // direction bytes per round of pairs
-constexpr size_t kAlignPinned = (size_t)16 << 20;    // most pinned memory a handle keeps for alignments
+// Most pinned memory a handle keeps for alignments: what a call exchanges goes through it in one copy each way, or the
+// operations that come back in pieces.  (Pinning takes a first call about 0.3 ms a MiB: 16 MiB at once made that of
+// 5,000 alignments 10.3 ms, 7.1 without any.)
+constexpr size_t kAlignPinned = (size_t)2 << 20;
 }
 
 sw_status sw_align_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int32_t nq, sw_db* db,
@@ -2224,16 +2227,11 @@ sw_status sw_align_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int
         HIP_TRY(db->align_bnd.reserve((size_t)bnd_bytes));
         HIP_TRY(db->align_misc.reserve(misc));
         char* mb = db->align_misc.as<char>();
-        // through pinned memory, in one copy each way, unless it is a lot
+        HIP_TRY(db->align_host.reserve(std::min(misc, kAlignPinned)));
+        char* const pinned = static_cast<char*>(db->align_host.p);
         std::vector<char> plain;
-        char* hb = nullptr;
-        if (misc <= kAlignPinned) {
-            HIP_TRY(db->align_host.reserve(misc));
-            hb = static_cast<char*>(db->align_host.p);
-        } else {
-            plain.resize(misc);
-            hb = plain.data();
-        }
+        if (o_ends > kAlignPinned) plain.resize(o_ends);
+        char* hb = plain.empty() ? pinned : plain.data();
         AlignPair* pairs = reinterpret_cast<AlignPair*>(hb);
         int64_t dir_off = 0, bnd_off = 0;
         int32_t ends = 0;
@@ -2275,24 +2273,42 @@ sw_status sw_align_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int
                                   reinterpret_cast<uint64_t*>(db->align_bnd.as<char>() + 256), d_ends, st));
         HIP_TRY(launch_align_trace(d_pairs, np, db->align_dirs.as<uint8_t>(), d_ends, reinterpret_cast<int32_t*>(mb + o_best),
                                    mb + o_ops, stride, reinterpret_cast<int64_t*>(mb + o_info), st));
-        HIP_TRY(hipMemcpyAsync(hb + o_best, mb + o_best, misc - o_best, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        const int32_t* best = reinterpret_cast<const int32_t*>(hb + o_best);
-        const int64_t* info = reinterpret_cast<const int64_t*>(hb + o_info);
-        const char* ops = hb + o_ops;
-        for (int i = 0; i < np; ++i) {
-            const Job& J = jobs[j0 + i];
-            if (info[4 * i + 3] != 0)
-                return fail(SW_E_HIP, "inconsistent traceback for subject %lld", (long long)h_subjects[J.k]);
-            sw_alignment& A = h_out[J.k];
-            const int64_t len = info[4 * i + 2];
-            A.score = best[3 * i];
-            A.q_begin = (int32_t)info[4 * i];
-            A.q_end = best[3 * i + 1];
-            A.s_begin = info[4 * i + 1];
-            A.s_end = best[3 * i + 2];
-            A.n_ops = len;
-            memcpy(h_ops + J.k * ops_stride, ops + (size_t)(i + 1) * stride - len, (size_t)len);
+        // the results of pairs [i0, i1), whose ends, begins and counts are at `head` and operations at `ops`
+        auto take = [&](int i0, int i1, const char* head, const char* ops) -> sw_status {
+            const int32_t* best = reinterpret_cast<const int32_t*>(head);
+            const int64_t* info = reinterpret_cast<const int64_t*>(head + (o_info - o_best));
+            for (int i = i0; i < i1; ++i) {
+                const Job& J = jobs[j0 + i];
+                if (info[4 * i + 3] != 0)
+                    return fail(SW_E_HIP, "inconsistent traceback for subject %lld", (long long)h_subjects[J.k]);
+                sw_alignment& A = h_out[J.k];
+                const int64_t len = info[4 * i + 2];
+                A.score = best[3 * i];
+                A.q_begin = (int32_t)info[4 * i];
+                A.q_end = best[3 * i + 1];
+                A.s_begin = info[4 * i + 1];
+                A.s_end = best[3 * i + 2];
+                A.n_ops = len;
+                memcpy(h_ops + J.k * ops_stride, ops + (size_t)(i - i0 + 1) * stride - len, (size_t)len);
+            }
+            return SW_OK;
+        };
+        if (misc <= kAlignPinned) {
+            HIP_TRY(hipMemcpyAsync(pinned + o_best, mb + o_best, misc - o_best, hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
+            if ((s = take(0, np, pinned + o_best, pinned + o_ops)) != SW_OK) return s;
+        } else {
+            std::vector<char> head(o_ops - o_best), one;
+            const int some = (int)std::max<int64_t>(1, (int64_t)kAlignPinned / stride);
+            if ((size_t)stride > kAlignPinned) one.resize((size_t)stride);
+            char* const at = one.empty() ? pinned : one.data();
+            HIP_TRY(hipMemcpyAsync(head.data(), mb + o_best, head.size(), hipMemcpyDeviceToHost, st));
+            for (int i = 0; i < np; i += some) {
+                const int n = std::min(some, np - i);
+                HIP_TRY(hipMemcpyAsync(at, mb + o_ops + (size_t)i * stride, (size_t)n * stride, hipMemcpyDeviceToHost, st));
+                HIP_TRY(hipStreamSynchronize(st));
+                if ((s = take(i, i + n, head.data(), at)) != SW_OK) return s;
+            }
         }
         j0 = j1;
     }

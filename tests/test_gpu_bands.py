@@ -58,3 +58,22 @@ def test_pair_matrix_that_is_not_symmetric(gpu):
     for m, n in ((300, 90), (90, 300)):
         q, s = synth.background_residues(rng, m), synth.background_residues(rng, n)
         assert int(gpu.sw_pair(q, s, sm, 7, 1).item()) == oracle.pair(q, s, sm, 7, 1)
+
+
+@pytest.mark.parametrize("longest,count", [(35_000, 150), (2_200_000, 3)])
+def test_alignments_that_come_back_in_pieces(gpu, blosum, longest, count):
+    """More operations than the handle's pinned buffer (2 MiB) holds, of all pairs together or of one."""
+    rng = np.random.default_rng(6400)
+    q = synth.background_residues(rng, 60)
+    lens = [longest] + [int(x) for x in rng.integers(1, 200, count - 1)]
+    subs = [_related(rng, q, n) for n in lens]
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    D = gpu.Database(np.concatenate(subs), offs)
+    order = [int(x) for x in rng.permutation(count)]
+    for _ in range(2):
+        for a, k in zip(D.align(q, order, blosum, 10, 2), order):
+            want = oracle.align(q, subs[k], blosum, 10, 2)
+            assert a["subject"] == k
+            for key in ("score", "q_begin", "q_end", "s_begin", "s_end", "ops"):
+                assert a[key] == want[key], f"n={subs[k].size} {key}: got {a[key]!r} want {want[key]!r}"
+    D.close()

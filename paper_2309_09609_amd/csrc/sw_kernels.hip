@@ -1499,6 +1499,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(const int32_t* scores, in
             bal[j] = __ballot(i < n && select && key[j] == T);
             if (lane == 0) part[j * kW + wave] = __popcll(bal[j]);
         }
+        if (!select) continue;                                 // (all threads: no equal ones to place)
         __syncthreads();
         // positions of the equal ones in index order, (j, wave, lane): every wave sums the counts of all
         static_assert(kTopkKeep * kW == 128, "two counts per lane");
@@ -1523,6 +1524,7 @@ __global__ __launch_bounds__(kTopkThreads) void k_topk(const int32_t* scores, in
         eq_before = total;
         __syncthreads();
     }
+    if (!select) __syncthreads();                              // the gathered ones are in LDS
     if (take <= kTopkRank) {
         // each result counts the results before it: its place
         if (tid < take) {

@@ -94,3 +94,22 @@ def test_parts_and_spans(gpu, blosum, mode, m):
             want = oracle.scores(q, db.residues, db.offsets, blosum, go, ge, mode=mode)
             assert (got == want).all(), (memory, go, ge, got, want)
         D.close()
+
+
+@pytest.mark.parametrize("mode", ["local", "global", "semiglobal"])
+@pytest.mark.parametrize("subjects,length,m", [(300, 300, 700), (300, 300, 760), (300, 300, 1100), (300, 300, 1500),
+                                               (300, 300, 2300), (250_000, 20, 144), (250_000, 20, 300)])
+def test_twelve_rows_per_lane(gpu, blosum, mode, subjects, length, m):
+    """Passes of 64 and of 16 lanes x 12 rows, which no option asks for, where the planner takes them."""
+    rng = np.random.default_rng(7400 + m)
+    lens = np.full(subjects, length)
+    lens[subjects // 2:] -= rng.integers(0, 4, subjects - subjects // 2)
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    res = synth.background_residues(rng, int(offs[-1]))
+    q = _query(m)
+    D = gpu.Database(res, offs)
+    got = D.search(q, blosum, 10, 2, mode=mode).cpu().numpy()
+    assert D.stats()["rows_per_lane"] == 12, D.stats()
+    want = oracle.scores(q, res, offs, blosum, 10, 2, mode=mode)
+    assert (got == want).all(), np.nonzero(got != want)[0][:5]
+    D.close()

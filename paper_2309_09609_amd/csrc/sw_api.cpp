@@ -149,10 +149,12 @@ struct Plan {
     }
 };
 
-// What a plan is made for: offset cells, whose chained pairs may be cut into windows of the subject; offset cells of
-// whole subjects (global scores); plain cells.
-enum PlanKind { kPlanCut, kPlanWhole, kPlanPlain };
-constexpr int kPlanKinds = 3;
+// What a plan is made for: offset cells, whose chained pairs may be cut into windows of the subject and parts; the same
+// planned alike, but without the parts (gaps that extend for nothing: an alignment may cover the whole subject, so that
+// every part would sweep all columns before its own too, eight of them 4.5 times the pair's, and the last end no
+// sooner); offset cells of whole subjects (global scores); plain cells.
+enum PlanKind { kPlanCut, kPlanOnePart, kPlanWhole, kPlanPlain };
+constexpr int kPlanKinds = 4;
 
 // Device pointers of the staged queries (descriptors, offsets, matrix + residues).
 struct Staged {
@@ -387,11 +389,11 @@ int64_t chain_cost(int m, int ncols, bool cut, int parts = 1) {
 // instead of 110 us).  100,000 subjects, the longest of 35,000 residues, semi-global, a query of 331: unsplit 3.5
 // ms, split 2.15.
 constexpr int kPartCols = 1024;
-int chain_parts(int m, int ncols, bool cut, double busy) {
+int chain_parts(int m, int ncols, double busy) {
     int parts = 1;
-    for (int64_t now = chain_cost(m, ncols, cut);
-         cut && parts < kMaxParts && ncols / (parts + 1) >= kPartCols && (double)now > busy; ++parts) {
-        const int64_t next = chain_cost(m, ncols, cut, parts + 1);
+    for (int64_t now = chain_cost(m, ncols, true);
+         parts < kMaxParts && ncols / (parts + 1) >= kPartCols && (double)now > busy; ++parts) {
+        const int64_t next = chain_cost(m, ncols, true, parts + 1);
         if (next > now - now / 10) break;
         now = next;
     }
@@ -479,8 +481,8 @@ void emit(std::vector<PlanItem>& v, std::vector<WgItem>& out) {
 }
 
 // The chain items of one pair, in at most the parts that slots are left for.
-void push_chain(std::vector<PlanItem>& to, int g, int q, int k, int parts, int64_t cost, int& splits) {
-    if (splits == kMaxSplits) parts = 1;
+void push_chain(std::vector<PlanItem>& to, PlanKind kind, int g, int q, int k, int parts, int64_t cost, int& splits) {
+    if (splits == kMaxSplits || kind != kPlanCut) parts = 1;
     for (int i = 0; i < parts; ++i)
         to.push_back({WgItem{g, q, (int16_t)k, kItemChain, 1, chain_split(parts > 1 ? splits : 0, parts, i)}, cost});
     splits += parts > 1;
@@ -683,8 +685,8 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, PlanKind kind, P
         std::stable_sort(longs.begin(), longs.end(), [](const LongUnit& a, const LongUnit& b) { return a.cost > b.cost; });
         longs.resize(chain_cut(db, longs, all, below, &K.end, [&](LongUnit& u, double busy) {
             const int uc = db->pcols[(size_t)u.g * kGroupPairs + u.k];
-            u.parts[0] = chain_parts(qlens[u.q], uc, kind == kPlanCut, busy);
-            u.chain = chain_cost(qlens[u.q], uc, kind == kPlanCut, u.parts[0]);
+            u.parts[0] = kind != kPlanWhole ? chain_parts(qlens[u.q], uc, busy) : 1;
+            u.chain = chain_cost(qlens[u.q], uc, kind != kPlanWhole, u.parts[0]);
             u.chain_sum = u.parts[0] * u.chain;
         }));
         K.chained.swap(longs);
@@ -730,7 +732,7 @@ void plan_units(const sw_db* db, const std::vector<int>& qlens, PlanKind kind, P
                 const int uc = db->pcols[(size_t)g * kGroupPairs + (k << (6 - l))];
                 const int64_t c = t.unit(uc, l);
                 if (ch < chained.size() && chained[ch].q == (int)qi && chained[ch].g == g && chained[ch].k == k) {
-                    push_chain(head, g, (int)qi, k, chained[ch].parts[0], chained[ch].chain, splits);
+                    push_chain(head, kind, g, (int)qi, k, chained[ch].parts[0], chained[ch].chain, splits);
                     (at4 ? apart4 : apart).add(g, seq, 1 << l, k, K.lgB[at], c);
                     ++ch;
                 } else if (r_long != K.R && l == 6 && db->force_lgB < 0 && c > K.cap)
@@ -898,7 +900,7 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, PlanKind kind
             for (int i = 0; i < 2; ++i) {
                 const int q = i == 0 ? K.entries[u.q].x : K.entries[u.q].y;
                 if (q < 0) continue;
-                u.parts[i] = chain_parts(qlens[q], uc, true, busy);
+                u.parts[i] = chain_parts(qlens[q], uc, busy);
                 const int64_t x = chain_cost(qlens[q], uc, true, u.parts[i]);
                 u.chain = std::max(u.chain, x);
                 u.chain_sum += u.parts[i] * x;
@@ -925,7 +927,7 @@ void plan_units_q2(const sw_db* db, const std::vector<int>& qlens, PlanKind kind
     for (const LongUnit& u : K.chained)                      // (the longest pairs get the slots for parts)
         for (int i = 0; i < 2; ++i) {
             const int q = i == 0 ? K.entries[u.q].x : K.entries[u.q].y;
-            if (q >= 0) push_chain(head, u.g, q, u.k, u.parts[i], u.chain, splits);
+            if (q >= 0) push_chain(head, kind, u.g, q, u.k, u.parts[i], u.chain, splits);
         }
     std::sort(K.chained.begin(), K.chained.end(), [](const LongUnit& a, const LongUnit& b) {
         return a.q != b.q ? a.q < b.q : a.g != b.g ? a.g < b.g : a.k < b.k;
@@ -1414,8 +1416,8 @@ CellForm choose_mode_form(const sw_db* db, int32_t mode, const int8_t* subst, in
     return f;
 }
 
-PlanKind plan_kind(const CellForm& f) {
-    return f.cell != kCellOff ? kPlanPlain : f.mode == SW_GLOBAL ? kPlanWhole : kPlanCut;
+PlanKind plan_kind(const CellForm& f, int32_t ge) {
+    return f.cell != kCellOff ? kPlanPlain : f.mode == SW_GLOBAL ? kPlanWhole : ge == 0 ? kPlanOnePart : kPlanCut;
 }
 
 // Timing events of the dominant launches (sw_profile_kernels): a ring of
@@ -1689,7 +1691,7 @@ sw_status search_one(const int8_t* h_query, int32_t qlen, sw_db* db, const int64
     if ((s = ensure_geometry(db)) != SW_OK) return s;
     const int64_t qo[2] = {0, qlen};
     const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_query, qo, 1);
-    PlanKind kind = plan_kind(form);
+    PlanKind kind = plan_kind(form, gap_extend);
     PlanRoom room;
     Plan* plan = nullptr;
     if (d_ws) {
@@ -1760,7 +1762,7 @@ sw_status search_batch(const int8_t* h_queries, const int64_t* h_qoffsets, int32
     std::vector<int> qlens(nq);
     for (int q = 0; q < nq; ++q) qlens[q] = (int)(h_qoffsets[q + 1] - h_qoffsets[q]);
     const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_queries, h_qoffsets, nq);
-    const PlanKind kind = plan_kind(form);
+    const PlanKind kind = plan_kind(form, gap_extend);
     // On the handle's workspace the plan's device copy may still be read by the previous batch; a caller's
     // workspace receives the plan with the queries, in stream order, so nothing waits.
     if (!d_ws && qlens != db->batch_qlens[kind]) HIP_TRY(hipStreamSynchronize(st));
@@ -2070,7 +2072,7 @@ sw_status sw_search_multi(const int8_t* h_queries, const int64_t* h_qoffsets, in
         if (qlens[q] == 0) HIP_TRY(launch_fill(h_d_scores[q], db->n, 0, st));
     HIP_TRY(hipStreamSynchronize(st));              // the previous call may still read the plan buffer
     const CellForm form = choose_form(db, h_subst, gap_open, gap_extend, h_queries, h_qoffsets, nq);
-    if ((s = build_plan(db, qlens, plan_kind(form), &db->multi_plan, &chunk, nchunks)) != SW_OK) return s;
+    if ((s = build_plan(db, qlens, plan_kind(form, gap_extend), &db->multi_plan, &chunk, nchunks)) != SW_OK) return s;
     if (db->multi_plan.h_items.empty()) return SW_OK;
     Work W;
     if ((s = get_work(db, h_qoffsets, nq, 0, false, &db->multi_plan, PlanRoom(), nullptr, 0, &W)) != SW_OK) return s;
@@ -2373,7 +2375,7 @@ sw_status sw_search_mode(int32_t mode, const int8_t* h_query, int32_t qlen, sw_d
         HIP_TRY(hipStreamIsCapturing(st, &cap));
         if (cap != hipStreamCaptureStatusNone) return fail(SW_E_HIP, "end-to-end search on a stream under capture");
         Plan* plan = nullptr;
-        if ((s = get_plan(db, qlen, plan_kind(form), &plan)) != SW_OK) return s;
+        if ((s = get_plan(db, qlen, plan_kind(form, gap_extend), &plan)) != SW_OK) return s;
         Work W;
         if ((s = get_work(db, qo, 1, 0, false, plan, PlanRoom(), nullptr, 0, &W)) != SW_OK) return s;
         Staged S;

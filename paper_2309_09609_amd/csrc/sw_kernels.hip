@@ -1021,13 +1021,7 @@ __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int 
     // waves per window, and windows: as many as the waves allow while a window stays well below the subject
     int waves = passes > 1 ? kChainWaves : (Q.m + kWaveRows - 1) / kWaveRows;
     int windows = kChainWaves / waves;
-    // (The plan splits by the query's length alone.  Where an alignment may cover the whole subject, as at Ge = 0, every
-    // part would sweep all before it too, and the last one the pair: the first does so at once.)
-    int parts = (split >> 8) & 255;
-    if (parts > 1 && Q.span >= cols) {
-        if (split & 255) return;                    // (all four waves)
-        parts = 1;
-    }
+    const int parts = (split >> 8) & 255;
     const int share = cols / parts, lead = parts > 1 ? min(Q.span, cols) : 0;
     while (windows > 1 && (MODE == 1 || Q.span + share / windows > share + lead - (share + lead) / 4)) --windows;
     const int all = windows * parts;

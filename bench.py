@@ -454,7 +454,7 @@ def main():
                     help="served form, paired policy: the shorter query of a pair is at least this share of the longer")
     ap.add_argument("--knobs", default="", help="batched form: JSON tuning knobs instead of autotuning")
     ap.add_argument("--mode", default="local", choices=["local", "global", "semiglobal"],
-                    help="plain form: alignment mode (global and semi-global run in biased 16-bit cells, exact)")
+                    help="plain form: alignment mode (global and semi-global run in 16-bit cells too, exact)")
     ap.add_argument("--cpu-seconds", type=float, default=12.0)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-batched-compare", action="store_true",

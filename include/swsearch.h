@@ -255,8 +255,9 @@ sw_status sw_search_batch(const int8_t* h_queries, const int64_t* h_qoffsets, in
  * the nq queries with offsets h_qoffsets (lengths matter, contents do not):
  * sw_search_batch_ws with top k (0..1024), or sw_search_ws when nq == 1 and
  * k == 0.  scores_in_ws != 0 adds room for the nq score rows, needed when the
- * batched call is given d_scores == NULL.  Plans the batch (the plan is kept
- * for the next call with the same lengths).
+ * batched call is given d_scores == NULL.  The size serves every matrix and
+ * every penalties.  Plans the batch (the plan is kept for the next call with the
+ * same lengths).
  *
  * sw_search_batch_ws - sw_search_batch on a caller-owned workspace of
  * ws_bytes >= that size (SW_E_SIZE otherwise), 256-byte aligned.  Allocates
@@ -415,8 +416,9 @@ const char* sw_last_error(void);
  *   pair) entries flagged for the 32-bit recompute (saturated or, in the
  *   end-to-end modes, out of the exact range),  out[2] = rows per lane (R) of
  *   the launch,  out[3] = persistent waves launched,  out[4] = work items of the
- *   same launch at 4 rows per lane (long pairs on a workgroup each, and groups
- *   that 4 rows pad less),  out[5] = their rows per lane (0: none),  out[6] = pairs the 32-bit recompute computed (equals
+ *   same launch at 4 rows per lane (long pairs on a workgroup each or, in parts,
+ *   on several, one item each, and groups that 4 rows pad less),  out[5] = their
+ *   rows per lane (0: none),  out[6] = pairs the 32-bit recompute computed (equals
  *   out[1] after every search),  out[7] = flagged pairs beyond the recompute
  *   list's capacity (recomputed from their flag bits).
  * This call synchronises the handle's device.

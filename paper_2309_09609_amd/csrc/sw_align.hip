@@ -14,7 +14,7 @@
 // consecutive bytes: word (band p, step t, lane b) at
 // (p * band_steps(n) + t) * 64 + b.  Every band notes its first end cell.
 //
-// Walk.  One wave per pair copies the 256-byte step records of up to 128
+// Walk.  One wave per pair copies the 128-byte step records of up to 256
 // steps of the current band into LDS and follows the path through them until
 // it leaves the copied steps; every move keeps or lowers the step index, so
 // each copy serves dozens of moves.  The wave takes a run of equal moves (a

@@ -1146,7 +1146,9 @@ __device__ __forceinline__ void run_chain(const SweepArgs& a, int g, int k, int 
 constexpr int kBitsBlock = 64;
 
 // Waves per SIMD the registers must allow: 3 at 12 or 16 rows per lane of 16-bit cells (168 VGPRs; without the bound
-// the allocator goes a few over and loses a third of the waves), 4 at fewer.  The plain cells' end-to-end modes fit by
+// the allocator goes a few over and loses a third of the waves), 4 at fewer.  Under it the end-to-end kernels on offset
+// cells spill some registers around their units (12 to 84 bytes of scratch a lane; global at 4 and semi-global at 4 and
+// 12 rows none); the local ones none.  The plain cells' end-to-end modes fit by
 // themselves; the bound would only cost them waits in the step (4 rows per lane, semi-global, a lone wave: 6 % more
 // a step with it).
 template <class C, int R, int MODE>
@@ -1566,7 +1568,8 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
 }
 
 // ------------------------------------------------------------ host-side launchers
-// Kernel instances: 16-bit cells (plain or on offsets) with R = 4, 8, 16 rows per lane; 32-bit cells with R = 8.
+// Kernel instances: plain 16-bit cells with R = 4, 8, 16 rows per lane, offset cells with 4, 8, 12, 16; query pairs of
+// either with 8, 16; 32-bit cells with R = 8.
 static const void* sweep_kernel_q2(int form, int R) {
     if (form == kCellOff)
         return R == 8 ? (const void*)k_sweep_q2<CellOff, 8> : R == 16 ? (const void*)k_sweep_q2<CellOff, 16> : nullptr;

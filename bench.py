@@ -354,7 +354,7 @@ PAIR_CELL_OPS = 8
 
 def pair_bench(args, perfmodel):
     """One long pair spread over the GPU (sw_pair): two sequences of --pair-len residues with a
-    mutated shared stretch, the tiles of one anti-diagonal per launch."""
+    mutated shared stretch, bands of rows behind one another in one launch."""
     import torch
     import paper_2309_09609_amd as sw
     from inputs import blosum62, synth
